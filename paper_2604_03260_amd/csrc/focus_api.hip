@@ -41,6 +41,39 @@ bool contiguous_tensors(const focus_params* p)
     return true;
 }
 
+// Share of wasted matrix work in the window spans of class tiles (see make_layout).
+double window_waste(const focus::Layout& L, double none)
+{
+    const double w = (double)L.window, spread = (double)L.NC * L.BQ;
+    const double local_share = w / (0.5 * L.n * (1.0 - none) + w);
+    return local_share * spread / (w + spread);
+}
+
+// Masked layout (one class in position order, memberships tested per pair) instead of tiles of one class each?
+// The masked kernel visits every key tile of the causal prefix; class tiles skip what cannot be allowed, but a class
+// leaves its last query tile partly empty, meets every key class in at least one tile, and pays more per tile at the
+// edges.  Counted in visits of a 128-row tile to a 64-key tile, with uniform memberships; the constants (half a
+// tile lost per key class met, a work-group's fixed cost of 12 visits, a masked visit at 0.9 of a class visit) are
+// fitted to 147 measured pairs, K = 4 .. 32, top 1 .. 3, 512 .. 131072 tokens, 12 .. 128 heads, d = 64 and 128:
+// the choice is never more than 1 % slower than the other one on them.  Both sides, at 32/8 heads of 128 (us):
+//   K=4 top-2:  class 216 / masked 153 at 4096 tokens, 1994 / 1994 at 16384, 6666 / 7792 at 32768;
+//   K=8 top-1:  190 / 150 at 4096, 366 / 506 at 8192;    K=8 top-3: 11630 / 8020 at 32768;
+//   K=16 top-2: 1831 / 152 at 4096, 4923 / 7432 at 32768;   K=16 top-3 (3 x 15/5 heads of 80, 5003 tokens, with the bucketing): 12580 / 410.
+bool prefer_masked(const focus::Layout& L, double none, bool two_pass)
+{
+    const double n = L.n, w = L.window, NC = L.NC, KT = focus::KT, BQ = focus::BQ_VECTOR;
+    const double half = L.causal ? 0.5 : 1.0;                // share of the keys a row sees, on average
+    const double share = 1.0 - none;                         // share of the key classes that meet a query class
+    const double per = n / NC, lost = 0.5, fixed = 12.0, masked_visit = 0.9;
+    const double tiles = NC * std::ceil(n / (NC * BQ));
+    double visits = tiles * (NC * share * (per * half / KT + lost) + fixed);
+    if (two_pass)
+        visits += std::ceil(n / BQ) * ((w + BQ) / KT + fixed);
+    else
+        visits += tiles * NC * none * (std::min(per, (w + std::min(n, NC * BQ)) / NC) * 2.0 * half / KT + lost);
+    return visits > std::ceil(n / BQ) * (n * half / KT + 1.0 + fixed) * masked_visit;
+}
+
 // Validates the params and derives the workspace layout and the head map.
 // soft: the layout of the soft-gated attention (one class in position order whatever K, topk and the window are).
 // local: the position-ordered second layout that a two-pass problem embeds in its workspace.
@@ -114,6 +147,37 @@ focus_status make_layout(const focus_params* p, focus::Layout* L, focus::HeadMap
             L->NC = best_nc;
         }
     }
+    // 16-bit types at long n: 256-row tiles (8 wavefronts share every K/V tile: half the L2->LDS traffic per FLOP,
+    // which is what bounds the kernel once a KV head's K/V no longer sits in L2/MALL)
+    L->dp = (p->d <= 64) ? 64 : (p->d <= 128) ? 128 : 256;
+    const bool can256 = p->dtype != FOCUS_F32 && p->d <= 128 && !L->coarse && !soft;   // shapes with an 8-wavefront kernel
+    L->BQ = (can256 && p->n >= LONG_N) ? 256 : BQ_VECTOR;
+    // Two passes (see attn_launch) where the rows of a class tile spread over so many positions that the window
+    // spans of the classes without a common group, rectangles of key tiles around a diagonal band, would be mostly
+    // masked: estimated share of wasted matrix work = (window pairs among all pairs) x spread / (window + spread)
+    // with uniform memberships; from 4 % on, and only where the second set of launches is small change (n >= 16384).
+    // FOCUS_TWO_PASS (tests, measurements): "1" two passes where the kernels allow them, "0" one pass over class
+    // tiles; otherwise the estimates choose among those two and the masked layout.
+    if (!soft && !local && !L->dense) {
+        const int classes_of = L->coarse ? L->S : p->K;      // P(two sets of topk groups, or of as many super-groups, do not meet)
+        double none = 1.0;
+        for (int i = 0; i < p->topk; ++i) none *= std::max(0.0, (double)(classes_of - p->topk - i) / (double)(classes_of - i));
+        const char* env = getenv("FOCUS_TWO_PASS");
+        const int force = (env && (env[0] == '0' || env[0] == '1')) ? env[0] - '0' : -1;
+        const bool can_two = !L->coarse && p->causal && p->dtype != FOCUS_F32;
+        L->two_pass = can_two && (force >= 0 ? force == 1 : p->n >= 16384 && window_waste(*L, none) >= 0.04);
+        if (force != 0 && !(force == 1 && can_two) && prefer_masked(*L, none, L->two_pass != 0)) {
+            L->masked = 1;
+            L->two_pass = 0;
+            L->coarse = 1;
+            L->S = 1;
+            L->NC = 1;
+            L->BQ = BQ_VECTOR;
+        }
+    }
+    // With two passes the spread of a tile's rows no longer costs masked work, so the 256-row tiles (every K/V tile
+    // fetched feeds twice the rows) pay from 131072 tokens on already (measured: cfg4a 61.8 -> 60.0 ms, cfg4b 177 -> 174 ms)
+    if ((L->two_pass || local) && can256 && p->n >= LONG_N_TWO_PASS) L->BQ = 256;
     // strides: all zero = contiguous [B,H,n,d]; else positive, rows 16-byte aligned, inside int64
     {
         const int64_t* src[3] = {p->q_strides, p->kv_strides, p->o_strides};
@@ -138,27 +202,6 @@ focus_status make_layout(const focus_params* p, focus::Layout* L, focus::HeadMap
         }
     }
     L->nblk = (p->n + SB - 1) / SB;
-    // bf16 at long n: 256-row tiles (8 wavefronts share every K/V tile: half the L2->LDS traffic per FLOP,
-    // which is what bounds the kernel once a KV head's K/V no longer sits in L2/MALL)
-    L->dp = (p->d <= 64) ? 64 : (p->d <= 128) ? 128 : 256;
-    const bool can256 = p->dtype != FOCUS_F32 && p->d <= 128 && !L->coarse && !soft;   // shapes with an 8-wavefront kernel
-    L->BQ = (can256 && p->n >= LONG_N) ? 256 : BQ_VECTOR;
-    // Two passes (see attn_launch) where the rows of a class tile spread over so many positions that the window
-    // spans of the classes without a common group, rectangles of key tiles around a diagonal band, would be mostly
-    // masked: estimated share of wasted matrix work = (window pairs among all pairs) x spread / (window + spread)
-    // with uniform memberships; from 4 % on, and only where the second set of launches is small change (n >= 16384).
-    if (!soft && !local && !L->dense && !L->coarse && p->causal && p->dtype != FOCUS_F32) {
-        double none = 1.0;                                   // C(K-k, k) / C(K, k): P(two topk-subsets of K do not meet)
-        for (int i = 0; i < p->topk; ++i) none *= (double)(p->K - p->topk - i) / (double)(p->K - i);
-        const double w = (double)L->window, spread = (double)L->NC * L->BQ;
-        const double local_share = w / (0.5 * p->n * (1.0 - none) + w);
-        const char* force = getenv("FOCUS_TWO_PASS");        // "0" / "1": override of the estimate (tests, measurements)
-        const bool est = p->n >= 16384 && local_share * spread / (w + spread) >= 0.04;
-        L->two_pass = (force && (force[0] == '0' || force[0] == '1')) ? (force[0] == '1') : est;
-    }
-    // With two passes the spread of a tile's rows no longer costs masked work, so the 256-row tiles (every K/V tile
-    // fetched feeds twice the rows) pay from 131072 tokens on already (measured: cfg4a 61.8 -> 60.0 ms, cfg4b 177 -> 174 ms)
-    if ((L->two_pass || local) && can256 && p->n >= LONG_N_TWO_PASS) L->BQ = 256;
     // class-major launch order only where the heads' K and V are far beyond the caches (see plan_heads_kernel)
     L->class_major = (L->BQ == 256 && p->n >= LONG_N) ? 1 : 0;
     L->NT = (p->n + L->BQ - 1) / L->BQ + L->NC;
@@ -195,6 +238,7 @@ focus_status make_layout(const focus_params* p, focus::Layout* L, focus::HeadMap
     L->off_qperm = take(BHq * L->NQP * 4);
     L->off_kpos = take(BHk * L->NKP * 4);
     L->off_kmsk = L->coarse ? take(BHk * L->NKP * 4) : off;
+    L->off_kbits = (L->masked && p->dtype != FOCUS_F32) ? take(BHk * (L->NKP / KT) * 4 * L->K * 4) : off;
     L->off_jobs = take(BHq * L->NT * 4);
     L->off_gk = (soft && p->dtype != FOCUS_F32) ? take((size_t)p->B * L->NKP * 128) : off;
     if (L->two_pass) {

@@ -80,6 +80,7 @@ template <> struct Half<true> {
     static __device__ inline float dot2(V2 a, V2 b, float c) { return __builtin_amdgcn_fdot2(a, b, c, false); }
 };
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef short s16x2 __attribute__((ext_vector_type(2)));
 
 constexpr int NTHR = 256;
 
@@ -144,6 +145,10 @@ __global__ __launch_bounds__(NTHR) void gather_vt_kernel(Layout L, const uint16_
 }
 
 // ---------------------------------------------------------------- attention
+// How a launch decides a pair outside the window.  PM_EXACT: by class (a key class shares a group with the rows' class
+// or it does not).  PM_COARSE, PM_MASKED: by the two membership masks, see the kernel's comment.
+constexpr int PM_EXACT = 0, PM_COARSE = 1, PM_MASKED = 2;
+constexpr int KBITS_MAX = 4 * 32;    // words of membership bits per key tile at K = 32: [unit][half-wave][group]
 constexpr int GROW = 128;     // bytes of a key's soft assignment in LDS: bf16 high parts of 32 groups, then the low parts
 
 // LDS rows of the K and V^T tiles are 16 bytes longer than their data: with pitches of 272 / 528 / 144 bytes
@@ -159,13 +164,15 @@ template <int D> struct TileGeom {
     static_assert(K_LDS % 1024 == 0 && V_LDS % 1024 == 0, "stages are filled in 1-KB wave loads");
 };
 
-template <int D, bool COARSE, bool SOFT>
+template <int D, int PM, bool SOFT>
 struct Smem {
     TilePlan plan;
     __attribute__((aligned(16))) int kpos[3][KT];
     __attribute__((aligned(16))) char k[2][TileGeom<D>::K_LDS];    // [stage][key][KROW] 16-bit elements
     __attribute__((aligned(16))) char vt[2][TileGeom<D>::V_LDS];   // [stage][d][VROW] 16-bit elements
-    __attribute__((aligned(16))) unsigned kmsk[COARSE ? 3 * KT : 4];   // membership masks of the keys (coarse classes)
+    __attribute__((aligned(16))) unsigned kmsk[PM == PM_COARSE ? 3 * KT : 4];      // membership masks of the keys (coarse classes)
+    __attribute__((aligned(16))) unsigned kbits[PM == PM_MASKED ? 3 * KBITS_MAX : 4];   // membership bits of the keys (masked)
+    unsigned upto[PM == PM_MASKED ? 30 : 1];                       // scores at or below a key offset (masked, see the loop)
     __attribute__((aligned(16))) char gk[SOFT ? 2 * KT * GROW : 16];   // [stage][key][GROW] soft assignments of the keys
 };
 
@@ -224,6 +231,11 @@ __device__ inline void pin_operands(V8 (&a)[N])
 // take 128 registers, so that shape runs one wavefront per SIMD with the full register file.
 // COARSE: membership classes are sets of super-groups; a key class that shares one with the rows' class
 // may or may not share a real group, so its pairs are tested against the two membership masks.
+// MASKED: one class in position order; a pair outside the window counts when the two membership masks meet.  The
+// assign pass leaves, per 32 keys, half-wave and group, a word whose bits say which of the 16 keys of a lane's scores
+// are in the group, so that a lane ORs the words of its row's topk groups once per 32 keys and then clears pairs of
+// 16-bit probabilities with three packed instructions (shift, arithmetic shift, and) instead of three per score.
+// Tiles inside every row's window need no test, tiles on the diagonal or across the window's edge test positions too.
 // SOFT: Sec. 2 Eq. 2, the attention of training: one class in position order, every causal pair computed; the
 // score of a pair outside the window is multiplied by sigmoid(lambda * g_i . g_j).  The affinities come off the
 // matrix cores next to the scores: G^T = g_K g_Q^T with both sides split into bf16 high and low parts (three
@@ -232,7 +244,7 @@ __device__ inline void pin_operands(V8 (&a)[N])
 // NOREF: the softmax without a reference (head of this file).  Every launch runs the kernel twice: the NOREF
 // instantiation first, whose work-groups check their bound, leave a flag (1 = done here, 0 = not mine) and do
 // the tile or return; then the other instantiation, whose work-groups return at once where the flag says done.
-template <int D, int KS, int DB, int MFMA_WAVES, bool SOFTCAP, bool PAIRS, bool F16, bool COARSE, bool SOFT, bool NOREF>
+template <int D, int KS, int DB, int MFMA_WAVES, bool SOFTCAP, bool PAIRS, bool F16, int PM, bool SOFT, bool NOREF>
 __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT) ? 1 : 8 / MFMA_WAVES) void attn_mfma_kernel(
     Layout L, HeadMap hm, int default_map, const uint16_t* __restrict__ q, const float* __restrict__ g,
     char* ws_rw, uint16_t* __restrict__ out, float* __restrict__ lse,
@@ -243,7 +255,8 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT) ? 1 : 8 / MFMA_
     typedef typename HT::T elem_t;
     typedef typename HT::V8 V8;
     typedef typename HT::V2 V2;
-    __shared__ Smem<D, COARSE, SOFT> S;
+    constexpr bool COARSE = PM == PM_COARSE, MASKED = PM == PM_MASKED;
+    __shared__ Smem<D, PM, SOFT> S;
     static_assert(KS * 16 <= D && DB * 32 <= D, "the products stay inside the copied rows");
     // With 512-byte key rows the operands of a whole phase would not fit the vector registers next to
     // Q, so that shape fetches and multiplies them in two halves (HV = 2); the others in one go.
@@ -291,7 +304,7 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT) ? 1 : 8 / MFMA_
     const int rloc = wave * 32 + n32;
     const bool rvalid = rloc < S.plan.nvalid;
     const int* qperm = (const int*)(ws + L.off_qperm) + (size_t)bhq * L.NQP;
-    const int qpos = rvalid ? qperm[S.plan.row0 + rloc] : -1;
+    const int qpos = !rvalid ? -1 : L.NC == 1 ? S.plan.row0 + rloc : qperm[S.plan.row0 + rloc];
     const int i_lo = S.plan.i_lo;
     const int total = S.plan.total;
     const int w = L.window;
@@ -301,7 +314,7 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT) ? 1 : 8 / MFMA_
     //   non-causal:  shares a group: qadj = qpos + 2^30, wlim = 2^31 (any real key; pads sit at INT_MAX);
     //                otherwise |qpos - kp| < w: qadj = qpos + w - 1, wlim = 2w - 1.
     unsigned mq_row = 0u;
-    if constexpr (COARSE) mq_row = rvalid ? ((const unsigned*)(ws + L.off_mq))[(size_t)bhq * L.n + qpos] : 0u;
+    if constexpr (COARSE || MASKED) mq_row = rvalid ? ((const unsigned*)(ws + L.off_mq))[(size_t)bhq * L.n + qpos] : 0u;
     // pair_set 3 (causal): a key of a class that shares a group counts when it lies at or below qpos - w; rows whose
     // window reaches position 0 have no such key (and -1 keeps the pads, at INT_MAX, out without wrapping around)
     const int qadj_inter = L.pair_set == 3 ? max(qpos - w, -1) : L.causal ? qpos : qpos + (1 << 30);
@@ -387,6 +400,7 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT) ? 1 : 8 / MFMA_
         for (int r = 0; r < 16; ++r) o[db][r] = 0.f;
     float m_ref = NOREF ? 0.f : -INFINITY, l_run = 0.f;
     int npairs = 0;
+    unsigned mword = 0u;                // masked: the pairs of the current unit that count
 
     const float sl2 = L.scale * LOG2E;
     const float cap_l2 = L.softcap * LOG2E;
@@ -425,7 +439,22 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT) ? 1 : 8 / MFMA_
     const unsigned ka_lane = lds_k0 + n32 * KROW + hh * 16;
     const unsigned va_lane = lds_v0 + n32 * VROW + hh * 16;
     const unsigned lds_km0 = lds_addr_of(&S.kmsk[0]);
+    const unsigned lds_kb0 = lds_addr_of(&S.kbits[0]);
     const unsigned lds_g0 = lds_addr_of(&S.gk[0]);
+    // masked: where this lane's half-wave finds the words of its row's first two groups; the groups after those
+    const int kb_words = 4 * L.K;                        // words of membership bits per key tile
+    const char* kb_base = ws + L.off_kbits + (size_t)bhk * (L.NKP / KT) * (kb_words * 4);
+    unsigned mq_rest = 0u;
+    int kb_g0 = 0, kb_g1 = 0;
+    if constexpr (MASKED) {
+        mq_rest = mq_row;
+        kb_g0 = mq_rest ? __builtin_ctz(mq_rest) : 0;
+        mq_rest &= mq_rest - 1u;
+        kb_g1 = mq_rest ? __builtin_ctz(mq_rest) : kb_g0;
+        mq_rest &= mq_rest - 1u;                         // (0 - 1 keeps 0: a row without groups, past the tile's end)
+        kb_g0 += hh * L.K;
+        kb_g1 += hh * L.K;
+    }
 
 #define F4_DMA_K(TILE, STAGE)                                                                        \
     do {                                                                                             \
@@ -448,6 +477,10 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT) ? 1 : 8 / MFMA_
     } while (0)
 #define F4_DMA_KPOS(TILE, BUF)                                                                       \
     do {                                                                                             \
+        if constexpr (MASKED) {          /* positions are slots; the membership bits travel in their place */ \
+            if (wave == 0 && lane < L.K)                                                             \
+                lds_dma16(kb_base + (size_t)(TILE) * (kb_words * 4), (unsigned)lane * 16, lds_kb0 + (BUF) * (KBITS_MAX * 4)); \
+        } else                                                                                       \
         if (wave == 0 && lane < KT / 4) {                                                            \
             lds_dma16(kpos_base + (size_t)(TILE) * (KT * 4), (unsigned)lane * 16, lds_kp0 + (BUF) * (KT * 4)); \
             if constexpr (COARSE)                                                                    \
@@ -503,7 +536,32 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT) ? 1 : 8 / MFMA_
     // bits 0..29 tile index, bit 30 "class shares a group" flag, bit 31 "no mask needed" flag.
     // LDS is touched only when the walk enters a new class; past the end the last tile repeats.
     int w_c = -1, w_t = 0, w_end = 0, w_int_beg = 0, w_int_end = 0, w_flag = 0, w_last = 0;
+    // masked: [fa, fb) and [fc, ...) hold only keys outside every row's window (and causal): membership decides alone
+    int m_fb = 0, m_fc = 0x3fffffff;
+    if constexpr (MASKED) {
+        const int i_hi = S.plan.i_hi;
+        if (L.pair_set == 1) {
+            if (L.causal) m_fb = (i_lo + 1) / KT; else m_fc = 0;
+        } else if (L.pair_set == 0) {
+            m_fb = max(0, i_lo - w + 1) / KT;
+            if (!L.causal) m_fc = (i_hi + w + KT - 1) / KT;
+        }
+        w_t = __builtin_amdgcn_readfirstlane(S.plan.t0[0]);
+        w_end = w_t + total;
+        w_int_beg = __builtin_amdgcn_readfirstlane(S.plan.ibeg[0]);
+        w_int_end = __builtin_amdgcn_readfirstlane(S.plan.iend[0]);
+        m_fb = __builtin_amdgcn_readfirstlane(m_fb);
+        m_fc = __builtin_amdgcn_readfirstlane(m_fc);
+    }
     auto next_tile = [&]() -> unsigned {
+        if constexpr (MASKED) {
+            if (w_t < w_end) {
+                w_last = w_t | ((w_t < m_fb || w_t >= m_fc) ? (1 << 30) : 0) |
+                         ((w_t >= w_int_beg && w_t < w_int_end) ? (int)0x80000000u : 0);
+                ++w_t;
+            }
+            return (unsigned)w_last;
+        }
         if (w_t >= w_end) {
             int c = w_c + 1;
             while (c < L.NC && S.plan.cum[c + 1] == S.plan.cum[c]) ++c;
@@ -524,6 +582,14 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT) ? 1 : 8 / MFMA_
     };
     constexpr unsigned TILE_MASK = 0x3fffffffu;
 
+    if constexpr (MASKED) {              // (read after the prologue's barrier)
+        if (tid < 30) {
+            unsigned word = 0u;
+            for (int r = 0; r < 16; ++r)
+                if (8 * (r / 4) + r % 4 < tid) word |= 1u << (r / 2 + (r & 1) * 16);
+            S.upto[tid] = word;
+        }
+    }
     // ---- prologue: K(0), V(0) -> stage 0; K(1) -> stage 1; kpos(0), kpos(1); zero V stage 1
     unsigned pk0, pk1, pk2;                                  // packed tiles t, t+1, t+2
     {
@@ -615,6 +681,38 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT) ? 1 : 8 / MFMA_
         }                                                                                                \
     }                                                                                                    \
     if (SOFT) {                          /* masked above */                                              \
+    } else if constexpr (MASKED) {                                                                       \
+        /* the membership word of this lane's 16 keys: bit p of the low (high) half is score 2p (2p + 1) */ \
+        mword = 0xffffffffu;                                                                             \
+        if (!interior) {                                                                                 \
+            const unsigned* kb_ = &S.kbits[(KPB) * KBITS_MAX + (U) * 2 * L.K];                           \
+            unsigned sh_ = kb_[kb_g0] | kb_[kb_g1];                                                      \
+            if (L.topk > 2) {                                                                            \
+                unsigned m_ = mq_rest;                                                                   \
+                for (int i_ = 2; i_ < L.topk; ++i_) {                                                    \
+                    sh_ |= kb_[hh * L.K + (m_ ? __builtin_ctz(m_) : 0)] & (m_ ? 0xffffffffu : 0u);       \
+                    m_ &= m_ - 1u;                                                                       \
+                }                                                                                        \
+            }                                                                                            \
+            sh_ = mq_row ? sh_ : 0u;                                                                     \
+            if (!shares_) {              /* the diagonal or the window's edge: positions decide too */    \
+                /* upto[x + 1]: the scores whose key lies at or below offset x of the lane's first key (32 and 28 apart) */ \
+                const int kp0_ = (int)(pk0 & TILE_MASK) * KT + (U) * 32 + 4 * hh;                        \
+                const unsigned in_ = sh_;                                                                \
+                const unsigned hi_ = S.upto[min(max(qadj_local - kp0_, -1), 28) + 1];                    \
+                const unsigned lo_ = S.upto[min(max(qpos - w - kp0_, -1), 28) + 1];                      \
+                const unsigned real_ = S.upto[min(max(L.n - 1 - kp0_, -1), 28) + 1];                     \
+                const unsigned cz_ = L.causal ? hi_ : real_;                                             \
+                const unsigned loc_ = hi_ & real_ & ~lo_;                                                \
+                sh_ = L.pair_set == 0 ? (loc_ | (in_ & cz_)) : L.pair_set == 1 ? (in_ & cz_) : (loc_ & ~in_); \
+            }                                                                                            \
+            mword = sh_;                                                                                 \
+            if constexpr (!NOREF) {      /* the running maximum is over the pairs that count */           \
+                _Pragma("unroll") for (int r = 0; r < 16; ++r)                                           \
+                    SIN[r] = (mword & (1u << (r / 2 + (r & 1) * 16))) ? SIN[r] : -INFINITY;              \
+            }                                                                                            \
+        }                                                                                                \
+        if constexpr (PAIRS) npairs += __popc(mword) >> (interior ? 1 : 0);                              \
     } else if (!interior) {                                                                              \
         _Pragma("unroll") for (int r4 = 0; r4 < 4; ++r4) {                                               \
             const int4 kp4_ = *(const int4*)(&S.kpos[KPB][(U) * 32 + 8 * r4 + 4 * hh]);                  \
@@ -672,6 +770,10 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT) ? 1 : 8 / MFMA_
             pr_[0] = (elem_t)((FOCUS_ABLATE & 2) ? a0_ : __builtin_amdgcn_exp2f(a0_));                   \
             pr_[1] = (elem_t)((FOCUS_ABLATE & 2) ? a1_ : __builtin_amdgcn_exp2f(a1_));                   \
             /* the row sum adds the ROUNDED probabilities, the same numbers the PV product uses */      \
+            if constexpr (MASKED && NOREF) {   /* clear the probabilities of the pairs that do not count */ \
+                const s16x2 keep_ = (__builtin_bit_cast(s16x2, mword) << (short)(15 - r / 2)) >> (short)15; \
+                pr_ = __builtin_bit_cast(V2, (unsigned)(__builtin_bit_cast(unsigned, pr_) & __builtin_bit_cast(unsigned, keep_))); \
+            }                                                                                            \
             psum_ = HT::dot2(pr_, ones2, psum_);                                                         \
             POUT[r / 8][r % 8] = pr_[0];                                                                 \
             POUT[r / 8][r % 8 + 1] = pr_[1];                                                             \
@@ -846,32 +948,32 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT) ? 1 : 8 / MFMA_
     }
 }
 
-template <int D, int KS, int DB, int WAVES, bool SOFTCAP, bool PAIRS, bool F16, bool COARSE, bool SOFT = false>
+template <int D, int KS, int DB, int WAVES, bool SOFTCAP, bool PAIRS, bool F16, int PM, bool SOFT = false>
 hipError_t launch_one(const Layout& L, const HeadMap& hm, int default_map, const void* q, char* ws, void* out,
                       float* lse, int32_t* row_pairs, hipStream_t st, const float* g = nullptr)
 {
     const unsigned grid = (unsigned)((size_t)L.NT * L.B * L.Hq);
     if constexpr (!SOFT)
-        hipLaunchKernelGGL((attn_mfma_kernel<D, KS, DB, WAVES, SOFTCAP, PAIRS, F16, COARSE, SOFT, true>), dim3(grid),
+        hipLaunchKernelGGL((attn_mfma_kernel<D, KS, DB, WAVES, SOFTCAP, PAIRS, F16, PM, SOFT, true>), dim3(grid),
                            dim3(64 * WAVES), 0, st, L, hm, default_map, (const uint16_t*)q, g, ws, (uint16_t*)out, lse,
                            row_pairs);
-    hipLaunchKernelGGL((attn_mfma_kernel<D, KS, DB, WAVES, SOFTCAP, PAIRS, F16, COARSE, SOFT, false>), dim3(grid),
+    hipLaunchKernelGGL((attn_mfma_kernel<D, KS, DB, WAVES, SOFTCAP, PAIRS, F16, PM, SOFT, false>), dim3(grid),
                        dim3(64 * WAVES), 0, st, L, hm, default_map, (const uint16_t*)q, g, ws, (uint16_t*)out, lse,
                        row_pairs);
     return hipGetLastError();
 }
 
-template <int D, int KS, int DB, int WAVES, bool F16, bool COARSE>
+template <int D, int KS, int DB, int WAVES, bool F16, int PM>
 hipError_t launch_w(const Layout& L, const HeadMap& hm, int default_map, const void* q, char* ws, void* out,
                     float* lse, int32_t* row_pairs, hipStream_t st)
 {
     const bool sc = L.softcap > 0.f, pairs = row_pairs != nullptr;
     if (sc) {
-        return pairs ? launch_one<D, KS, DB, WAVES, true, true, F16, COARSE>(L, hm, default_map, q, ws, out, lse, row_pairs, st)
-                     : launch_one<D, KS, DB, WAVES, true, false, F16, COARSE>(L, hm, default_map, q, ws, out, lse, row_pairs, st);
+        return pairs ? launch_one<D, KS, DB, WAVES, true, true, F16, PM>(L, hm, default_map, q, ws, out, lse, row_pairs, st)
+                     : launch_one<D, KS, DB, WAVES, true, false, F16, PM>(L, hm, default_map, q, ws, out, lse, row_pairs, st);
     }
-    return pairs ? launch_one<D, KS, DB, WAVES, false, true, F16, COARSE>(L, hm, default_map, q, ws, out, lse, row_pairs, st)
-                 : launch_one<D, KS, DB, WAVES, false, false, F16, COARSE>(L, hm, default_map, q, ws, out, lse, row_pairs, st);
+    return pairs ? launch_one<D, KS, DB, WAVES, false, true, F16, PM>(L, hm, default_map, q, ws, out, lse, row_pairs, st)
+                 : launch_one<D, KS, DB, WAVES, false, false, F16, PM>(L, hm, default_map, q, ws, out, lse, row_pairs, st);
 }
 
 template <int D, int KS, int DB>
@@ -886,21 +988,24 @@ hipError_t launch_d(const Layout& L, const HeadMap& hm, int default_map, const v
         // 512-byte key rows plus the gate's accumulators and operands do not fit the register file
         if constexpr (D == 256) return hipErrorInvalidValue;
         else
-        return f16 ? launch_one<D, KS, DB, 4, false, false, true, false, true>(L, hm, default_map, q, ws, out, lse, nullptr, st, g)
-                   : launch_one<D, KS, DB, 4, false, false, false, false, true>(L, hm, default_map, q, ws, out, lse, nullptr, st, g);
+        return f16 ? launch_one<D, KS, DB, 4, false, false, true, PM_EXACT, true>(L, hm, default_map, q, ws, out, lse, nullptr, st, g)
+                   : launch_one<D, KS, DB, 4, false, false, false, PM_EXACT, true>(L, hm, default_map, q, ws, out, lse, nullptr, st, g);
     }
     // the query tile size fixed by focus_assign selects the work-group shape: 4 or 8 wavefronts
     if constexpr (D != 256) {
         if (L.BQ == 256)
-            return f16 ? launch_w<D, KS, DB, 8, true, false>(L, hm, default_map, q, ws, out, lse, row_pairs, st)
-                       : launch_w<D, KS, DB, 8, false, false>(L, hm, default_map, q, ws, out, lse, row_pairs, st);
+            return f16 ? launch_w<D, KS, DB, 8, true, PM_EXACT>(L, hm, default_map, q, ws, out, lse, row_pairs, st)
+                       : launch_w<D, KS, DB, 8, false, PM_EXACT>(L, hm, default_map, q, ws, out, lse, row_pairs, st);
     }
     if (L.BQ != 128) return hipErrorInvalidValue;
+    if (L.masked)                        // one class, membership tested per pair
+        return f16 ? launch_w<D, KS, DB, 4, true, PM_MASKED>(L, hm, default_map, q, ws, out, lse, row_pairs, st)
+                   : launch_w<D, KS, DB, 4, false, PM_MASKED>(L, hm, default_map, q, ws, out, lse, row_pairs, st);
     if (L.coarse)                        // coarse classes always use 128-row tiles
-        return f16 ? launch_w<D, KS, DB, 4, true, true>(L, hm, default_map, q, ws, out, lse, row_pairs, st)
-                   : launch_w<D, KS, DB, 4, false, true>(L, hm, default_map, q, ws, out, lse, row_pairs, st);
-    return f16 ? launch_w<D, KS, DB, 4, true, false>(L, hm, default_map, q, ws, out, lse, row_pairs, st)
-               : launch_w<D, KS, DB, 4, false, false>(L, hm, default_map, q, ws, out, lse, row_pairs, st);
+        return f16 ? launch_w<D, KS, DB, 4, true, PM_COARSE>(L, hm, default_map, q, ws, out, lse, row_pairs, st)
+                   : launch_w<D, KS, DB, 4, false, PM_COARSE>(L, hm, default_map, q, ws, out, lse, row_pairs, st);
+    return f16 ? launch_w<D, KS, DB, 4, true, PM_EXACT>(L, hm, default_map, q, ws, out, lse, row_pairs, st)
+               : launch_w<D, KS, DB, 4, false, PM_EXACT>(L, hm, default_map, q, ws, out, lse, row_pairs, st);
 }
 
 }  // namespace

@@ -64,6 +64,9 @@ struct Layout {
     float gate_slope;          // sigmoid(lambda * g_i . g_j); gate_slope = -lambda * log2(e).  One class, position order.
     int coarse;                // C(K,topk) exceeds MAX_CLASSES: classes are sets of S super-groups (group g folds
     int S;                     // onto g % S), a superset test; the kernels then test the real masks per pair
+    int masked;                // one class in position order, every pair outside the window tested against the two
+                               // membership masks (coarse with S = 1): short sequences, where classes would leave
+                               // tiles mostly empty (see prefer_masked in focus_api.hip)
     int pair_set;              // which pairs a launch attends: 0 the whole mask, 1 only pairs that share a group
                                // (set A of App. D), 2 only window pairs that share none (set B), 3 pairs that share
                                // a group and lie outside the window (second pass of a two-pass launch)
@@ -98,6 +101,8 @@ struct Layout {
     size_t off_qperm;                  // [B,Hq,NQP] positions in class order, -1 in pads (the scatter kernel writes both)
     size_t off_kpos;                   // [B,Hkv,NKP] positions in class order, KPOS_PAD in pads
     size_t off_kmsk;                   // [B,Hkv,NKP] membership masks in class order, 0 in pads (coarse classes only)
+    size_t off_kbits;                  // [B,Hkv,NKP/KT][2 units of 32 keys][2 half-waves][K] membership of the keys by group
+                                       // (masked, 16-bit types), one bit per key: see scatter_kernel
     size_t off_jobs;                   // [B,Hq,NT] (class << 24 | tile) heaviest first, -1 unused
     size_t off_gk;                     // [B,NKP,2,32] bf16: the soft assignment of every key position as bf16 high and
                                        // low parts, groups padded to 32, chunks swizzled per key (soft gate, 16-bit types)

@@ -26,6 +26,42 @@ struct TilePlan {
     int cls, tile, row0, nvalid, i_lo, i_hi, total;
 };
 
+// One class in position order (dense, local, soft-gated and masked layouts): a row's slot is its position, and the
+// whole plan follows from the tile's first and last position, without a single load (the walk through the class
+// tables below is a chain of four dependent loads and a histogram, several microseconds before the first product).
+__device__ inline bool plan_linear_tile(const Layout& L, int job, TilePlan& P)
+{
+    const int nt = (L.n + L.BQ - 1) / L.BQ;
+    if (job >= nt) return false;
+    if (threadIdx.x == 0) {
+        const int t = nt - 1 - job;                         // longest causal prefix first, as in the job list
+        const int i_lo = t * L.BQ, nvalid = min(L.BQ, L.n - i_lo), i_hi = i_lo + nvalid - 1, w = L.window;
+        const int x_hi = L.causal ? i_hi + 1 : L.n;         // keys past x_hi - 1 are allowed for no row
+        int a = 0, b = (x_hi + KT - 1) / KT;
+        if (L.dense && !L.local_only && L.pair_set == 2) {
+            b = 0;                                          // any two memberships meet: no pair is local only
+        } else if (L.local_only || L.pair_set == 2) {
+            a = max(0, i_lo - w + 1) / KT;
+            b = (min(x_hi, i_hi + w) + KT - 1) / KT;       // (causal: x_hi <= i_hi + w)
+        }
+        // [ibeg, iend): no test per pair.  All keys real, causal for every row and, where the window decides, inside
+        // every row's window.
+        const int safe_end = L.causal ? i_lo + 1 : (L.dense && !L.local_only) ? L.n : min(L.n, i_lo + w);
+        const bool by_window = L.local_only || L.masked;
+        const int ib = by_window ? max(a, (max(i_hi - w + 1, 0) + KT - 1) / KT) : a;
+        const int ie = max(ib, min(b, safe_end / KT));
+        P.cls = 0; P.tile = t; P.row0 = i_lo; P.nvalid = nvalid; P.i_lo = i_lo; P.i_hi = i_hi; P.total = b - a;
+        P.t0[0] = a;
+        P.cum[0] = 0;
+        P.cum[1] = b - a;
+        P.inter[0] = L.local_only ? 0 : 1;
+        P.ibeg[0] = (L.masked && L.pair_set != 0) ? a : ib;
+        P.iend[0] = (L.masked && L.pair_set != 0) ? a : ie;
+    }
+    __syncthreads();
+    return true;
+}
+
 // All threads of the work-group call this (blockDim.x >= 64).  Returns false when
 // the job slot is unused.
 __device__ inline bool plan_query_tile(const Layout& L, const char* __restrict__ ws, int bhq, int bhk, int job,
@@ -33,6 +69,7 @@ __device__ inline bool plan_query_tile(const Layout& L, const char* __restrict__
 {
     const int tid = threadIdx.x, nthr = blockDim.x;
     const int NC = L.NC;
+    if (NC == 1) return plan_linear_tile(L, job, P);
     const int jv = ((const int*)(ws + L.off_jobs))[(size_t)bhq * L.NT + job];
     if (jv == -1) return false;                             // class ids reach 255: the word is unsigned but for -1
     const int c = (int)((unsigned)jv >> 24), t = jv & 0xffffff;

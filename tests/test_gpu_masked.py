@@ -1,0 +1,71 @@
+"""The masked layout (one class in position order, memberships tested per pair), which short sequences take, at the
+sizes where its tiles and words end; and the class-tile kernels, which the size estimate keeps for longer sequences,
+on the small shapes where every row can be checked."""
+import pytest
+import torch
+
+from paper_2604_03260_amd import focus, workloads
+from tests import harness
+from tests import test_gpu_instantiations as inst
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(wl, inp=None):
+    inp = inp if inp is not None else workloads.make_inputs(wl, "cuda")
+    res = harness.run_gpu(wl, inp)
+    mq, mk = harness.check_assign(wl, inp, res)
+    harness.check_attn(wl, inp, res, mq, mk)
+    harness.check_pair_totals(wl, res, mq, mk)
+    return res
+
+
+# n around the 32-key units, 64-key tiles, 128-row tiles and 256-position sort blocks; windows of one key, inside a
+# unit, across units and tiles, nearly everything; one, two and more groups per token (the word loop past two groups)
+@pytest.mark.parametrize("n", [2, 31, 33, 64, 65, 127, 129, 257, 300])
+@pytest.mark.parametrize("w,K,topk,causal,dtype,d,softcap", [
+    (1, 4, 1, True, "bf16", 64, 0.0), (29, 8, 2, True, "bf16", 128, 0.0), (70, 8, 4, False, "f16", 80, 0.0),
+    (1, 16, 2, False, "bf16", 64, 0.0), (250, 32, 5, True, "bf16", 96, 30.0), (64, 32, 2, True, "bf16", 256, 0.0),
+    (33, 8, 1, True, "f32", 64, 0.0)])
+def test_masked_tile_edges(n, w, K, topk, causal, dtype, d, softcap):
+    if w >= n:
+        w = max(1, n - 1)
+    _check(workloads.Workload("m", 300 + n, 1, 4, 2, n, d, dtype, K, topk, w, causal=causal, softcap=softcap, mixture=3))
+
+
+def test_masked_rows_with_large_norms_take_the_running_reference():
+    """Key norms past the bound of the form without a reference: disallowed keys with the largest logits must not
+    move the row's reference (their probabilities would drown the allowed ones)."""
+    wl = workloads.Workload("m", 331, 1, 2, 1, 400, 64, "bf16", 4, 1, 16)
+    inp = workloads.make_inputs(wl, "cuda")
+    inp["q"] *= 8.0
+    inp["k"] *= 8.0
+    p = harness.params_of(wl)
+    ws = focus.alloc_workspace(p)
+    outs = []
+    for vector in (False, True):
+        out, lse = torch.empty_like(inp["q"]), torch.empty((1, 2, 400), dtype=torch.float32, device="cuda")
+        focus.focus_assign(p, inp["q"], inp["k"], inp["centroids"], ws)
+        focus.focus_attn_fwd(p, inp["q"], inp["k"], inp["v"], ws, out, lse, vector=vector)
+        outs.append((out.float(), lse))
+    # logits reach a few hundred: one bf16 ulp of the output (2^-8 relative, values up to 4) and fp32 logits
+    assert (outs[0][0] - outs[1][0]).abs().max() <= 2e-2
+    assert ((outs[0][1] - outs[1][1]).abs() / outs[1][1].abs().clamp(min=1.0)).max() <= 1e-4
+
+
+@pytest.mark.parametrize("d,softcap,pairs,dtype,coarse,noref", inst.CASES4)
+def test_class_tiles_all_rows(d, softcap, pairs, dtype, coarse, noref, monkeypatch):
+    """The same shapes as one pass over class-ordered tiles (exact and coarse classes)."""
+    monkeypatch.setenv("FOCUS_TWO_PASS", "0")
+    inst.test_four_wavefront_instantiations_all_rows(d, softcap, pairs, dtype, coarse, noref)
+
+
+@pytest.mark.parametrize("n,K,topk,w", [(777, 4, 2, 32), (1500, 32, 2, 40), (700, 16, 3, 16), (2000, 12, 3, 30)])
+def test_class_tiles_against_the_masked_layout(n, K, topk, w, monkeypatch):
+    """Both layouts of one problem: equal memberships, pair counts and (to rounding) outputs."""
+    wl = workloads.Workload("m", 340, 1, 4, 2, n, 128, "bf16", K, topk, w, mixture=4)
+    inp = workloads.make_inputs(wl, "cuda")
+    masked = _check(wl, inp)
+    monkeypatch.setenv("FOCUS_TWO_PASS", "0")
+    classes = _check(wl, inp)
+    assert torch.equal(masked["row_pairs"], classes["row_pairs"])
