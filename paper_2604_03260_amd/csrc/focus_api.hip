@@ -238,7 +238,7 @@ focus_status make_layout(const focus_params* p, focus::Layout* L, focus::HeadMap
     L->off_qperm = take(BHq * L->NQP * 4);
     L->off_kpos = take(BHk * L->NKP * 4);
     L->off_kmsk = L->coarse ? take(BHk * L->NKP * 4) : off;
-    L->off_kbits = (L->masked && p->dtype != FOCUS_F32) ? take(BHk * (L->NKP / KT) * 4 * L->K * 4) : off;
+    L->off_kbits = (L->masked && p->dtype != FOCUS_F32) ? take(BHk * (L->NKP / KT) * 4 * (L->K + 1) * 4) : off;
     L->off_jobs = take(BHq * L->NT * 4);
     L->off_gk = (soft && p->dtype != FOCUS_F32) ? take((size_t)p->B * L->NKP * 128) : off;
     if (L->two_pass) {

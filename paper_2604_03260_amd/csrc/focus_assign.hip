@@ -486,15 +486,9 @@ __global__ __launch_bounds__(SB) void scatter_kernel(Layout L, int which, const 
         const unsigned long long has = __ballot(valid && ((mask >> g) & 1u));
         if (lane == 0) s_wg[wave][g] = __popcll(has);
         if (put_bits && lane < 4 && (blk * 4 + wave) * KT < L.NKP) {
-            // masked layout: slot = position, this wavefront holds one key tile of 64.  Lane (unit, half-wave) packs
-            // the 16 keys 8*r4 + 4*hh + e that the attention lanes of that half-wave hold as scores r = 4*r4 + e:
-            // key of score 2p in bit p, of score 2p + 1 in bit 16 + p.
-            const unsigned x = (unsigned)(has >> (32 * (lane >> 1))) >> (4 * (lane & 1));
-            unsigned word = 0;
-#pragma unroll
-            for (int r = 0; r < 16; ++r)
-                word |= ((x >> (8 * (r / 4) + r % 4)) & 1u) << (r / 2 + (r & 1) * 16);
-            ((uint32_t*)(ws + L.off_kbits))[((size_t)bh * (L.NKP / KT) + blk * 4 + wave) * (4 * K) + lane * K + g] = word;
+            // masked layout: slot = position, this wavefront holds one key tile of 64
+            ((uint32_t*)(ws + L.off_kbits))[(((size_t)bh * (L.NKP / KT) + blk * 4 + wave) * 4 + lane) * (K + 1) + g] =
+                pack_unit_bits((uint32_t)(has >> (32 * (lane >> 1))), lane & 1);
         }
     }
     __syncthreads();

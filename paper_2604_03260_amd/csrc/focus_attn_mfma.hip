@@ -107,22 +107,38 @@ constexpr float CAP_CUBIC_Z = 0.15f;        // ... and to z^3 (the z^5 term is t
 __host__ __device__ constexpr int slot_to_key16(int p16) { return 8 * ((p16 % 8) / 4) + 4 * (p16 / 8) + (p16 % 8) % 4; }
 
 // ---------------------------------------------------------------- gathers into class order
+// any of the eight 16-bit values infinite or NaN
+__device__ inline bool nonfinite8(const uint4& u, bool f16)
+{
+    const uint32_t w[4] = {u.x, u.y, u.z, u.w}, m = f16 ? 0x7c00u : 0x7f80u;
+    bool bad = false;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) bad = bad || (w[e] & m) == m || ((w[e] >> 16) & m) == m;
+    return bad;
+}
+
 template <int D>
 __global__ __launch_bounds__(NTHR) void gather_vt_kernel(Layout L, const uint16_t* __restrict__ v, char* __restrict__ ws)
 {
     constexpr int CPR = D / 8;
     constexpr int RS = D + 2;                        // padded LDS row stride in elements
     __shared__ uint16_t s_v[KT * RS];
+    __shared__ unsigned s_bad[KT / 32];
     const int cin = L.d / 8;
     const int tile = blockIdx.x, bhk = blockIdx.y, tid = threadIdx.x;
     const int* kpos = (const int*)(ws + L.off_kpos) + (size_t)bhk * L.NKP + (size_t)tile * KT;
     const uint4* src = (const uint4*)v + ((size_t)(bhk / L.Hkv) * L.ks[0] + (size_t)(bhk % L.Hkv) * L.ks[1]) / 8;
     const size_t pitch = (size_t)L.ks[2] / 8;
+    if (tid < KT / 32) s_bad[tid] = 0u;
+    __syncthreads();
     for (int id = tid; id < KT * CPR; id += NTHR) {
         const int row = id / CPR, ch = id % CPR;
         const int kp = kpos[row];
         uint4 val = make_uint4(0, 0, 0, 0);
         if (kp != KPOS_PAD && ch < cin) val = src[(size_t)kp * pitch + ch];
+        // Masked layout: every key of the causal prefix is visited, with a zero probability where it is not allowed,
+        // and 0 * inf would spoil rows that do not attend it.  Such V rows go in as zeros and are marked.
+        if (L.masked && nonfinite8(val, L.dtype == 2)) atomicOr(&s_bad[row >> 5], 1u << (row & 31));
         uint32_t* d32 = (uint32_t*)(s_v + row * RS + ch * 8);   // RS even -> 4-byte aligned
         d32[0] = val.x; d32[1] = val.y; d32[2] = val.z; d32[3] = val.w;
     }
@@ -135,20 +151,23 @@ __global__ __launch_bounds__(NTHR) void gather_vt_kernel(Layout L, const uint16_
         for (int j = 0; j < 8; ++j) {
             const int p = c * 8 + j;
             const int key = (p / 16) * 16 + slot_to_key16(p % 16);
-            e[j] = s_v[key * RS + drow];
+            e[j] = ((s_bad[key >> 5] >> (key & 31)) & 1u) ? (uint16_t)0 : s_v[key * RS + drow];
         }
         uint4 val;
         val.x = e[0] | ((uint32_t)e[1] << 16); val.y = e[2] | ((uint32_t)e[3] << 16);
         val.z = e[4] | ((uint32_t)e[5] << 16); val.w = e[6] | ((uint32_t)e[7] << 16);
         dst[id] = val;
     }
+    if (L.masked && tid < 4)
+        ((uint32_t*)(ws + L.off_kbits))[(((size_t)bhk * (L.NKP / KT) + tile) * 4 + tid) * (L.K + 1) + L.K] =
+            pack_unit_bits(s_bad[tid >> 1], tid & 1);
 }
 
 // ---------------------------------------------------------------- attention
 // How a launch decides a pair outside the window.  PM_EXACT: by class (a key class shares a group with the rows' class
 // or it does not).  PM_COARSE, PM_MASKED: by the two membership masks, see the kernel's comment.
 constexpr int PM_EXACT = 0, PM_COARSE = 1, PM_MASKED = 2;
-constexpr int KBITS_MAX = 4 * 32;    // words of membership bits per key tile at K = 32: [unit][half-wave][group]
+constexpr int KBITS_MAX = 4 * 33;    // words of bits per key tile at K = 32: [unit][half-wave][group, V row not finite]
 constexpr int GROW = 128;     // bytes of a key's soft assignment in LDS: bf16 high parts of 32 groups, then the low parts
 
 // LDS rows of the K and V^T tiles are 16 bytes longer than their data: with pitches of 272 / 528 / 144 bytes
@@ -442,7 +461,8 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT) ? 1 : 8 / MFMA_
     const unsigned lds_kb0 = lds_addr_of(&S.kbits[0]);
     const unsigned lds_g0 = lds_addr_of(&S.gk[0]);
     // masked: where this lane's half-wave finds the words of its row's first two groups; the groups after those
-    const int kb_words = 4 * L.K;                        // words of membership bits per key tile
+    const int kb_row = L.K + 1, kb_words = 4 * kb_row;   // words per half-wave of a unit, per key tile
+    unsigned vbad = 0u;                                  // the row attends a key whose V row is not finite
     const char* kb_base = ws + L.off_kbits + (size_t)bhk * (L.NKP / KT) * (kb_words * 4);
     unsigned mq_rest = 0u;
     int kb_g0 = 0, kb_g1 = 0;
@@ -452,8 +472,8 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT) ? 1 : 8 / MFMA_
         mq_rest &= mq_rest - 1u;
         kb_g1 = mq_rest ? __builtin_ctz(mq_rest) : kb_g0;
         mq_rest &= mq_rest - 1u;                         // (0 - 1 keeps 0: a row without groups, past the tile's end)
-        kb_g0 += hh * L.K;
-        kb_g1 += hh * L.K;
+        kb_g0 += hh * kb_row;
+        kb_g1 += hh * kb_row;
     }
 
 #define F4_DMA_K(TILE, STAGE)                                                                        \
@@ -478,7 +498,7 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT) ? 1 : 8 / MFMA_
 #define F4_DMA_KPOS(TILE, BUF)                                                                       \
     do {                                                                                             \
         if constexpr (MASKED) {          /* positions are slots; the membership bits travel in their place */ \
-            if (wave == 0 && lane < L.K)                                                             \
+            if (wave == 0 && lane < kb_row)                                                          \
                 lds_dma16(kb_base + (size_t)(TILE) * (kb_words * 4), (unsigned)lane * 16, lds_kb0 + (BUF) * (KBITS_MAX * 4)); \
         } else                                                                                       \
         if (wave == 0 && lane < KT / 4) {                                                            \
@@ -683,14 +703,14 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT) ? 1 : 8 / MFMA_
     if (SOFT) {                          /* masked above */                                              \
     } else if constexpr (MASKED) {                                                                       \
         /* the membership word of this lane's 16 keys: bit p of the low (high) half is score 2p (2p + 1) */ \
+        const unsigned* kb_ = &S.kbits[(KPB) * KBITS_MAX + (U) * 2 * kb_row];                            \
         mword = 0xffffffffu;                                                                             \
         if (!interior) {                                                                                 \
-            const unsigned* kb_ = &S.kbits[(KPB) * KBITS_MAX + (U) * 2 * L.K];                           \
             unsigned sh_ = kb_[kb_g0] | kb_[kb_g1];                                                      \
             if (L.topk > 2) {                                                                            \
                 unsigned m_ = mq_rest;                                                                   \
                 for (int i_ = 2; i_ < L.topk; ++i_) {                                                    \
-                    sh_ |= kb_[hh * L.K + (m_ ? __builtin_ctz(m_) : 0)] & (m_ ? 0xffffffffu : 0u);       \
+                    sh_ |= kb_[hh * kb_row + (m_ ? __builtin_ctz(m_) : 0)] & (m_ ? 0xffffffffu : 0u);       \
                     m_ &= m_ - 1u;                                                                       \
                 }                                                                                        \
             }                                                                                            \
@@ -712,6 +732,7 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT) ? 1 : 8 / MFMA_
                     SIN[r] = (mword & (1u << (r / 2 + (r & 1) * 16))) ? SIN[r] : -INFINITY;              \
             }                                                                                            \
         }                                                                                                \
+        vbad |= mword & kb_[hh * kb_row + L.K];                                                          \
         if constexpr (PAIRS) npairs += __popc(mword) >> (interior ? 1 : 0);                              \
     } else if (!interior) {                                                                              \
         _Pragma("unroll") for (int r4 = 0; r4 < 4; ++r4) {                                               \
@@ -897,8 +918,11 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT) ? 1 : 8 / MFMA_
     // ---- epilogue
     const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
     if constexpr (PAIRS) npairs += __shfl_xor(npairs, 32, 64);
+    if constexpr (MASKED) vbad |= (unsigned)__shfl_xor((int)vbad, 32, 64);
     if (!rvalid) return;
     float inv = (l_tot > 0.f) ? 1.f / l_tot : 0.f;            // an empty row (restricted pair set): out = 0, lse = -inf
+    // (masked: V rows that are not finite were staged as zeros, so that rows which do not attend them stay right)
+    if (MASKED && vbad != 0u) inv = __uint_as_float(0x7fc00000u);
     uint16_t* orow = out + (size_t)b * L.os[0] + (size_t)h * L.os[1] + (size_t)qpos * L.os[2];
     // Second pass of a two-pass launch: this row's result over the pairs inside the window is in out / lse
     // (16-bit, natural log).  out = (e^{l1} o1 + e^{l2} o2) / (e^{l1} + e^{l2}), App. D's merge, in log2 units.

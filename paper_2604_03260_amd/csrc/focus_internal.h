@@ -101,8 +101,8 @@ struct Layout {
     size_t off_qperm;                  // [B,Hq,NQP] positions in class order, -1 in pads (the scatter kernel writes both)
     size_t off_kpos;                   // [B,Hkv,NKP] positions in class order, KPOS_PAD in pads
     size_t off_kmsk;                   // [B,Hkv,NKP] membership masks in class order, 0 in pads (coarse classes only)
-    size_t off_kbits;                  // [B,Hkv,NKP/KT][2 units of 32 keys][2 half-waves][K] membership of the keys by group
-                                       // (masked, 16-bit types), one bit per key: see scatter_kernel
+    size_t off_kbits;                  // [B,Hkv,NKP/KT][2 units of 32 keys][2 half-waves][K + 1] one bit per key (masked,
+                                       // 16-bit types; pack_unit_bits): membership by group, then "its V row is not finite" 
     size_t off_jobs;                   // [B,Hq,NT] (class << 24 | tile) heaviest first, -1 unused
     size_t off_gk;                     // [B,NKP,2,32] bf16: the soft assignment of every key position as bf16 high and
                                        // low parts, groups padded to 32, chunks swizzled per key (soft gate, 16-bit types)
@@ -117,6 +117,15 @@ struct Layout {
     size_t off_vt;                     // [B,Hkv,NKP/KT,dp,KT] values, transposed per key tile (16-bit types)
     size_t total;
 };
+
+// The bits of one half-wave of a 32-key unit (x: bit j = key j) in the order its attention lanes hold their scores:
+// score r belongs to key 8*(r/4) + 4*half + r%4; score 2p in bit p, score 2p + 1 in bit 16 + p.
+__host__ __device__ inline uint32_t pack_unit_bits(uint32_t x, int half)
+{
+    uint32_t word = 0;
+    for (int r = 0; r < 16; ++r) word |= ((x >> (8 * (r / 4) + 4 * half + r % 4)) & 1u) << (r / 2 + (r & 1) * 16);
+    return word;
+}
 
 // colex rank of the k-subset `m` among all k-subsets (device + host)
 __host__ __device__ inline uint32_t binom_u32(int a, int b)

@@ -1,6 +1,7 @@
 """The masked layout (one class in position order, memberships tested per pair), which short sequences take, at the
 sizes where its tiles and words end; and the class-tile kernels, which the size estimate keeps for longer sequences,
 on the small shapes where every row can be checked."""
+import numpy as np
 import pytest
 import torch
 
@@ -69,3 +70,26 @@ def test_class_tiles_against_the_masked_layout(n, K, topk, w, monkeypatch):
     monkeypatch.setenv("FOCUS_TWO_PASS", "0")
     classes = _check(wl, inp)
     assert torch.equal(masked["row_pairs"], classes["row_pairs"])
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("f16", 80)])
+def test_spoiled_values_reach_only_the_rows_that_attend_them(dtype, d):
+    """V rows with NaN or infinities: the masked tiles visit every key of the causal prefix, with probability zero
+    where the pair is not allowed, and 0 * inf must not spoil those rows."""
+    wl = workloads.Workload("m", 350, 1, 4, 2, 700, d, dtype, 8, 1, 40, mixture=3)
+    inp = workloads.make_inputs(wl, "cuda")
+    bad_keys = (3, 100, 333, 500)
+    for j, x in zip(bad_keys, (float("nan"), float("inf"), -float("inf"), float("inf"))):
+        inp["v"][0, 0, j, (7 * j) % d] = x
+    res = harness.run_gpu(wl, inp)
+    mq, mk = harness.check_assign(wl, inp, res)
+    rows, attending = [], []
+    for h in range(wl.Hq):
+        for i in range(wl.n):
+            hit = h < 2 and any(j <= i and (i - j < wl.window or (int(mq[0, h, i]) & int(mk[0, 0, j]))) for j in bad_keys)
+            (attending if hit else rows).append((0, h, i))
+    assert len(rows) > 1000 and len(attending) > 100
+    inp["v"] = torch.nan_to_num(inp["v"], nan=0.0, posinf=0.0, neginf=0.0)         # (for the oracle)
+    harness.check_attn(wl, inp, res, mq, mk, rows=np.array(rows, dtype=np.int32))
+    at = torch.tensor(attending, device="cuda")
+    assert not torch.isfinite(res["out"][at[:, 0], at[:, 1], at[:, 2]].float()).all(dim=-1).any()
