@@ -228,6 +228,8 @@ hipError_t launch_assign(const Layout& L, const HeadMap& hm, const void* q, cons
 hipError_t launch_attn_simple(const Layout& L, const HeadMap& hm, const void* q, const void* k,
                               const void* v, const float* g, char* ws, void* out, float* lse, int32_t* row_pairs,
                               hipStream_t st);
+hipError_t launch_attn_f32(const Layout& L, const HeadMap& hm, const void* q, const void* k, const void* v, char* ws,
+                           void* out, float* lse, int32_t* row_pairs, hipStream_t st);
 hipError_t launch_soft_gather_g(const Layout& L, const float* g, char* ws, hipStream_t st);
 hipError_t launch_attn_merge(size_t rows, int d, int dtype, const void* oa, const float* la, const void* ob,
                              const float* lb, void* out, float* lse, hipStream_t st);

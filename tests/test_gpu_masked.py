@@ -72,7 +72,7 @@ def test_class_tiles_against_the_masked_layout(n, K, topk, w, monkeypatch):
     assert torch.equal(masked["row_pairs"], classes["row_pairs"])
 
 
-@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("f16", 80)])
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("f16", 80), ("f32", 64), ("f32", 256)])
 def test_spoiled_values_reach_only_the_rows_that_attend_them(dtype, d):
     """V rows with NaN or infinities: the masked tiles visit every key of the causal prefix, with probability zero
     where the pair is not allowed, and 0 * inf must not spoil those rows."""
@@ -93,3 +93,15 @@ def test_spoiled_values_reach_only_the_rows_that_attend_them(dtype, d):
     harness.check_attn(wl, inp, res, mq, mk, rows=np.array(rows, dtype=np.int32))
     at = torch.tensor(attending, device="cuda")
     assert not torch.isfinite(res["out"][at[:, 0], at[:, 1], at[:, 2]].float()).all(dim=-1).any()
+
+
+# the fp32 kernel at the edges of its 32-row quarters, 32-key units and the round-robin of its four wavefronts, in
+# class tiles and in the masked layout (test_masked_tile_edges), every head dim
+@pytest.mark.parametrize("n", [1, 32, 33, 95, 129, 400])
+@pytest.mark.parametrize("d,K,topk,w,causal,softcap,tiles", [
+    (64, 4, 2, 17, True, 0.0, "0"), (80, 8, 3, 40, True, 0.0, None), (96, 16, 3, 25, False, 5.0, "0"),
+    (128, 4, 1, 64, True, 0.0, "0"), (256, 8, 2, 33, False, 0.0, None), (128, 2, 2, 500, True, 0.0, None)])
+def test_f32_kernel_edges(n, d, K, topk, w, causal, softcap, tiles, monkeypatch):
+    if tiles:
+        monkeypatch.setenv("FOCUS_TWO_PASS", tiles)
+    _check(workloads.Workload("m", 360 + n, 2, 4, 2, n, d, "f32", K, topk, w, causal=causal, softcap=softcap, mixture=2))
