@@ -295,16 +295,19 @@ focus_status make_route_layout(const focus_route_params* rp, focus::RouteLayout*
     memset(R, 0, sizeof(*R));
     R->B = rp->B; R->n = rp->n; R->dm = rp->d_model; R->dg = rp->d_g; R->K = rp->K; R->topk = rp->topk;
     R->dtype = rp->dtype; R->iters = rp->sinkhorn_iters; R->tau = rp->tau;
-    R->nproj = (rp->n + 63) / 64;
+    const int tb = focus::route_tokens_per_group(rp->B, rp->n, rp->d_g);
+    R->nproj = (rp->n + tb - 1) / tb;
     R->nsink = std::min(256, (rp->n + 255) / 256);
     R->sink_tokens = (rp->n + R->nsink - 1) / R->nsink;
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off = align256(off + bytes); return o; };
-    R->off_w64 = take((size_t)rp->d_model * rp->d_g * 8);
-    R->off_c64 = take((size_t)rp->K * rp->d_g * 8);
+    // (the size is part of the contract: focus_route_noalloc refuses what exceeds its buffer.  These first two blocks
+    // held fp64 copies of W_g and C that the projection no longer needs)
+    take((size_t)rp->d_model * rp->d_g * 8);
+    take((size_t)rp->K * rp->d_g * 8);
     R->off_S = take((size_t)rp->B * rp->n * rp->K * 8);
-    R->off_maxpart = take((size_t)rp->B * R->nproj * 8);
-    R->off_smax = take((size_t)rp->B * 8);
+    R->off_maxpart = take((size_t)rp->B * ((rp->n + 63) / 64) * 8);
+    take((size_t)rp->B * 8);
     R->off_colpart = take((size_t)2 * rp->B * R->nsink * 32 * 8);
     R->total = off;
     return FOCUS_OK;

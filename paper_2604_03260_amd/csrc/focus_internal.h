@@ -167,20 +167,21 @@ __host__ __device__ inline int class_of_mask(uint32_t mask, int dense, int coars
     return cls;
 }
 
+// Tokens per work-group of the router's projection: 8 wavefronts of 16 tokens where that still gives every compute unit
+// a work-group (they share the staged W_g), 4 otherwise and where d_g > 16 (the scores would not fit 64 KB of LDS).
+inline int route_tokens_per_group(int B, int n, int dg) { return (dg <= 16 && (long long)B * ((n + 127) / 128) >= 256) ? 128 : 64; }
+
 // Shapes and workspace offsets of the router (focus_route).
 struct RouteLayout {
     int B, n, dm, dg, K, topk;
     int dtype;                 // of the hidden states: 0 fp32, 1 bf16
     int iters;                 // Sinkhorn rounds, 0 = none
     double tau;
-    int nproj;                 // work-groups of the projection per sequence = ceil(n / 64)
+    int nproj;                 // work-groups of the projection per sequence = ceil(n / route_tokens_per_group)
     int nsink;                 // work-groups of a Sinkhorn pass per sequence (<= 256)
     int sink_tokens;           // tokens per Sinkhorn work-group
-    size_t off_w64;            // W_g as fp64 [dm][dg]
-    size_t off_c64;            // C as fp64 [K][dg]
     size_t off_S;              // [B][n][K] fp64: scores, then exp((S - max)/tau) in place
     size_t off_maxpart;        // [B][nproj] fp64
-    size_t off_smax;           // [B] fp64
     size_t off_colpart;        // [2][B][nsink][KP] fp64 column partial sums, ping-pong between passes
     size_t total;
 };

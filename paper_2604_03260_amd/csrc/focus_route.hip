@@ -10,13 +10,8 @@
 // and, without Sinkhorn, the membership are reproducible bit for bit.
 //
 // Kernels:
-//   to_f64            W_g and C as fp64 tables (wave-uniform operands come from scalar loads);
-//   route_project     one wavefront = 64 tokens (one per lane) x JW router outputs; hidden rows are
-//                     streamed once through LDS in 64-component chunks (coalesced 16-byte loads, register
-//                     prefetch of the next chunk, double-buffered LDS, one barrier per chunk); writes S,
+//   route_project     a wavefront = 16 tokens x all router outputs on v_mfma_f64_16x16x4 (see the kernel); writes S,
 //                     the work-group's largest score, and the masks directly when no Sinkhorn is asked;
-//   route_max         largest score of each sequence (the shift that keeps exp finite; the first
-//                     column step divides it out again);
 //   sinkhorn_pass     Sinkhorn as diagonal scaling: Q = diag(u) E diag(v) with E = exp((S - max)/tau).
 //                     A round is  v_g = 1 / sum_i u_i E[i,g],  u_i = 1 / sum_g E[i,g] v_g,  so one pass
 //                     over E per round: every work-group first folds the previous pass's per-block
@@ -59,16 +54,6 @@ namespace {
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int RT = 64;                       // tokens per work-group of the projection (one per lane)
-constexpr int RC = 64;                       // hidden components per LDS stage (staging only: the sum runs on across stages)
-
-__global__ void to_f64_kernel(const float* __restrict__ src, double* __restrict__ dst, size_t count)
-{
-    size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const size_t step = (size_t)gridDim.x * blockDim.x;
-    for (; i < count; i += step) dst[i] = (double)src[i];
-}
-
 __device__ inline double wave_max(double x)
 {
 #pragma unroll
@@ -101,109 +86,158 @@ __device__ inline uint32_t topk_mask(const double (&s)[KP], int K, int topk)
 }
 
 // ---------------------------------------------------------------- projection + scores
-template <typename T, int JW, int NW>
+// z = W_g^T h on the fp64 matrix cores.  v_mfma_f64_16x16x4 adds its four products to the accumulator one by one in
+// index order, each with one rounding (a fused multiply-add; checked on 512000 results against the scalar chain, and
+// by the bit-exact router tests), so one instruction is four steps of the same sum as before for 16 tokens x 16 outputs.
+// The vector form of this kernel (a lane per token, W_g through scalar loads) reached 17 % of the fp64 rate at 32768
+// tokens, held by the issue of fp64 instructions (one per 16 cycles and wavefront) and by the scalar loads; a matrix
+// instruction keeps the fp64 units busy for 64 cycles by itself.  32768 x 4096 bf16, d_g = 16: 306 -> 117 us
+// (37 TFLOP/s, what one dependent chain per wavefront and two wavefronts per SIMD reach with registers alone; the sum of
+// a token is one chain); 1024 tokens 275 -> 78 us, 131072 tokens 521 -> 411 us, d_g = 64 x 2048: 306 -> 177 us.
+//
+// A work-group is NW wavefronts of 16 tokens.  Hidden rows and W_g (fp32) pass through LDS in chunks of 128 bytes per
+// row, two buffers, one barrier per chunk, the next four chunks' loads in flight meanwhile.  The A operand of step i is
+// component 4*i + l/16 of token l%16: rows are stored with the components of one l/16 side by side, so a lane reads
+// its whole chunk with two 16-byte loads.  Accumulator register r of lane l is token 4*r + l/16, output l%16.
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
+constexpr int A_ROW = 128 + 16;              // LDS pitch of a staged row: 4 interleaved parts of 32 bytes, padded
+
+template <typename T, int DG, int NW>
 __global__ __launch_bounds__(64 * NW) void route_project_kernel(RouteLayout R, const T* __restrict__ hidden,
-                                                                 const double* __restrict__ w64,
-                                                                 const double* __restrict__ c64,
+                                                                 const float* __restrict__ wg,
+                                                                 const float* __restrict__ cent,
                                                                  char* __restrict__ ws,
                                                                  uint32_t* __restrict__ masks,
                                                                  double* __restrict__ soft)
 {
-    constexpr int DG = JW * NW;
-    constexpr int NTHR = 64 * NW;
-    constexpr int ROW_BYTES = RC * (int)sizeof(T);
-    constexpr int ROW_STRIDE = ROW_BYTES + 16;
-    constexpr int CPR = ROW_BYTES / 16;                  // 16-byte pieces per staged row
-    constexpr int LPT = RT * CPR / NTHR;                 // pieces per thread
-    constexpr int EPC = 16 / (int)sizeof(T);
-    // dynamic LDS: two staging buffers during the projection, then z [RT][DG+1] and S [RT][K|1] in their place
+    constexpr int NTHR = 64 * NW, TB = 16 * NW;
+    constexpr int RC = 128 / (int)sizeof(T);             // components per chunk
+    constexpr int CB = (DG + 15) / 16;                   // blocks of 16 outputs
+    constexpr int WP = CB * 16 + (CB > 1 ? 16 : 0);      // LDS pitch of a row of W_g in floats: the four rows of a step on different banks
+    constexpr int PF = 4;                                // chunks in flight: one takes 0.85 us of products, a load 1 to 2
+    constexpr int WPT = (RC * DG + NTHR - 1) / NTHR;     // floats of W_g per thread and chunk
+    // dynamic LDS: two buffers of hidden rows and of W_g during the projection, then z [TB][DG+1] and S [TB][K|1]
     extern __shared__ __align__(16) char s_dyn[];
     __shared__ double s_wmax[NW];
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int b = blockIdx.y;
-    const int tok0 = blockIdx.x * RT;
+    const int tok0 = blockIdx.x * TB;
     const int n = R.n, dm = R.dm, K = R.K;
-    const int rows = min(RT, n - tok0);
+    const int rows = min(TB, n - tok0);
     const int row_bytes = dm * (int)sizeof(T);
     const char* gbase = (const char*)hidden + ((size_t)b * n + tok0) * row_bytes;
     const int nchunk = (dm + RC - 1) / RC;
+    char* s_a = s_dyn;
+    float* s_w = (float*)(s_dyn + 2 * TB * A_ROW);
+    for (int e = tid; e < 2 * RC * WP; e += NTHR) s_w[e] = 0.f;      // outputs past d_g (4, 8) stay zero
+    __syncthreads();
 
-    u32x4 st[LPT];
-#define FOCUS_ROUTE_LOAD(CH)                                                                          \
-    do {                                                                                              \
-        _Pragma("unroll") for (int i = 0; i < LPT; ++i) {                                             \
-            const int pid_ = tid + i * NTHR;                                                          \
-            const int r_ = pid_ / CPR, cc_ = pid_ % CPR;                                              \
-            const int byte_ = (CH) * ROW_BYTES + cc_ * 16;                                            \
-            const u32x4 z_ = {0u, 0u, 0u, 0u};                                                        \
-            st[i] = (r_ < rows && byte_ < row_bytes) ? *(const u32x4*)(gbase + (size_t)r_ * row_bytes + byte_) : z_; \
-        }                                                                                             \
-    } while (0)
-
-    double acc[JW];
+    u32x4 sta[PF][2];
+    float swa[PF][WPT];
+    auto load_chunk = [&](int ch, u32x4 (&st)[2], float (&sw)[WPT]) {
 #pragma unroll
-    for (int j = 0; j < JW; ++j) acc[j] = 0.0;
-
-    FOCUS_ROUTE_LOAD(0);
-    for (int ch = 0; ch < nchunk; ++ch) {
-        char* buf = s_dyn + (ch & 1) * (RT * ROW_STRIDE);
-#pragma unroll
-        for (int i = 0; i < LPT; ++i) {
-            const int pid = tid + i * NTHR;
-            *(u32x4*)(buf + (pid / CPR) * ROW_STRIDE + (pid % CPR) * 16) = st[i];
+        for (int i = 0; i < 2; ++i) {                    // this wavefront's 16 rows, 8 pieces of 16 bytes each
+            const int pid = i * 64 + lane, row = wave * 16 + pid / 8, byte = ch * 128 + pid % 8 * 16;
+            const u32x4 z = {0u, 0u, 0u, 0u};
+            st[i] = (row < rows && byte < row_bytes) ? *(const u32x4*)(gbase + (size_t)row * row_bytes + byte) : z;
         }
-        __syncthreads();               // also orders this write after every wave's reads two chunks ago
-        if (ch + 1 < nchunk) FOCUS_ROUTE_LOAD(ch + 1);
-        const int tbase = ch * RC;
-        const int tcount = min(RC, dm - tbase);          // dm is a multiple of 8: whole pieces only
-#pragma unroll 1
-        for (int cc = 0; cc * EPC < tcount; ++cc) {
-            const u32x4 val = *(const u32x4*)(buf + lane * ROW_STRIDE + cc * 16);
-            double xv[EPC];
+#pragma unroll
+        for (int i = 0; i < WPT; ++i) {
+            const int e = i * NTHR + tid;
+            sw[i] = (e < RC * DG && ch * RC + e / DG < dm) ? wg[(size_t)ch * RC * DG + e] : 0.f;
+        }
+    };
+    f64x4 acc[CB];
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) acc[cb] = f64x4{0.0, 0.0, 0.0, 0.0};
+
+#pragma unroll
+    for (int p = 0; p < PF; ++p)
+        if (p < nchunk) load_chunk(p, sta[p], swa[p]);
+    for (int ch0 = 0; ch0 < nchunk; ch0 += PF) {
+#pragma unroll
+    for (int p = 0; p < PF; ++p) {
+        const int ch = ch0 + p;
+        if (ch >= nchunk) break;                         // uniform over the work-group
+        u32x4 (&st)[2] = sta[p];
+        float (&sw)[WPT] = swa[p];
+        char* abuf = s_a + (ch & 1) * (TB * A_ROW);
+        float* wbuf = s_w + (ch & 1) * (RC * WP);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int pid = i * 64 + lane;
+            uint32_t* dst = (uint32_t*)(abuf + (wave * 16 + pid / 8) * A_ROW) + pid % 8;
+            const u32x4 v = st[i];
+            if constexpr (sizeof(T) == 4) {              // components 4c .. 4c+3: step c of the four parts
+                dst[0] = v[0]; dst[8] = v[1]; dst[16] = v[2]; dst[24] = v[3];
+            } else {                                     // components 8c .. 8c+7: steps 2c and 2c + 1
+                dst[0] = (v[0] & 0xffffu) | (v[2] << 16);
+                dst[8] = (v[0] >> 16) | (v[2] & 0xffff0000u);
+                dst[16] = (v[1] & 0xffffu) | (v[3] << 16);
+                dst[24] = (v[1] >> 16) | (v[3] & 0xffff0000u);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < WPT; ++i) {
+            const int e = i * NTHR + tid;
+            if (e < RC * DG) wbuf[(e / DG) * WP + e % DG] = sw[i];
+        }
+        __syncthreads();               // also orders these writes after every wave's reads two chunks ago
+        if (ch + PF < nchunk) load_chunk(ch + PF, st, sw);
+        const u32x4* ar = (const u32x4*)(abuf + (wave * 16 + (lane & 15)) * A_ROW + (lane >> 4) * 32);
+        const u32x4 a0 = ar[0], a1 = ar[1];
+        const float* wr = wbuf + (lane >> 4) * WP + (lane & 15);
+        const int steps = min(RC, dm - ch * RC) / 4;     // dm is a multiple of 8
+        auto step = [&](int i) {
+            double a;
             if constexpr (sizeof(T) == 4) {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) xv[e] = (double)__uint_as_float(val[e]);
-            } else if constexpr (std::is_same<T, f16_bits>::value) {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    xv[2 * e] = (double)f16_bits_to_f32((uint16_t)(val[e] & 0xffffu));
-                    xv[2 * e + 1] = (double)f16_bits_to_f32((uint16_t)(val[e] >> 16));
-                }
+                a = (double)__uint_as_float(i < 4 ? a0[i % 4] : a1[i % 4]);
             } else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    xv[2 * e] = (double)__uint_as_float(val[e] << 16);
-                    xv[2 * e + 1] = (double)__uint_as_float(val[e] & 0xffff0000u);
-                }
+                const uint32_t w2 = (i < 8) ? a0[(i / 2) % 4] : a1[(i / 2) % 4];
+                if constexpr (std::is_same<T, f16_bits>::value)
+                    a = (double)f16_bits_to_f32((uint16_t)(i % 2 ? w2 >> 16 : w2 & 0xffffu));
+                else
+                    a = (double)__uint_as_float(i % 2 ? w2 & 0xffff0000u : w2 << 16);
             }
 #pragma unroll
-            for (int e = 0; e < EPC; ++e) {
-                const double* wr = w64 + (size_t)(tbase + cc * EPC + e) * DG + wave * JW;   // wave-uniform
+            for (int cb = 0; cb < CB; ++cb)
+                acc[cb] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, (double)wr[i * 4 * WP + cb * 16], acc[cb], 0, 0, 0);
+        };
+        // a full chunk without a branch per step: all its operands can be read ahead of the products
+        if (steps == RC / 4) {
 #pragma unroll
-                for (int j = 0; j < JW; ++j) acc[j] = fma(xv[e], wr[j], acc[j]);
-            }
+            for (int i = 0; i < RC / 4; ++i) step(i);
+        } else {
+#pragma unroll
+            for (int i = 0; i < RC / 4; ++i)
+                if (i < steps) step(i);
         }
     }
-#undef FOCUS_ROUTE_LOAD
+    }
 
-    // z of the 64 tokens -> LDS, then S[i,g] = sum_j z_j C[g][j] in index order (products rounded, then added)
+    // z of the tokens -> LDS, then S[i,g] = sum_j z_j C[g][j] in index order (products rounded, then added)
     __syncthreads();                                     // the staging buffers are free
     double* s_z = (double*)s_dyn;
-    double* s_s = s_z + RT * (DG + 1);
+    double* s_s = s_z + TB * (DG + 1);
     const int KS = K | 1;
 #pragma unroll
-    for (int j = 0; j < JW; ++j) s_z[lane * (DG + 1) + wave * JW + j] = acc[j];
+    for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            if (DG % 16 == 0 || (lane & 15) < DG)
+                s_z[(wave * 16 + 4 * r + (lane >> 4)) * (DG + 1) + cb * 16 + (lane & 15)] = acc[cb][r];
     __syncthreads();
     double mymax = -INFINITY;
-    for (int g = wave; g < K; g += NW) {
-        const double* cr = c64 + (size_t)g * DG;                                            // wave-uniform
+    const int tok = tid % TB;
+    for (int g = tid / TB; g < K; g += NTHR / TB) {
         double s = 0.0;
 #pragma unroll 4
-        for (int j = 0; j < DG; ++j) s = __dadd_rn(s, __dmul_rn(s_z[lane * (DG + 1) + j], cr[j]));
-        s_s[lane * KS + g] = s;
-        if (lane < rows) mymax = fmax(mymax, s);
+        for (int j = 0; j < DG; ++j) s = __dadd_rn(s, __dmul_rn(s_z[tok * (DG + 1) + j], (double)cent[(size_t)g * DG + j]));
+        s_s[tok * KS + g] = s;
+        if (tok < rows) mymax = fmax(mymax, s);
     }
     mymax = wave_max(mymax);
     if (lane == 0) s_wmax[wave] = mymax;
@@ -214,7 +248,7 @@ __global__ __launch_bounds__(64 * NW) void route_project_kernel(RouteLayout R, c
         ((double*)(ws + R.off_maxpart))[(size_t)b * R.nproj + blockIdx.x] = m;
     }
     if (tid < rows) {
-        const size_t tok = (size_t)b * n + tok0 + tid;
+        const size_t tg = (size_t)b * n + tok0 + tid;
         double* mine = s_s + tid * KS;
         if (R.iters == 0) {
             for (int g = 0; g < K; ++g) mine[g] = mine[g] / R.tau;
@@ -229,31 +263,18 @@ __global__ __launch_bounds__(64 * NW) void route_project_kernel(RouteLayout R, c
                 if (beaten < R.topk) m |= (1u << g);
             }
             if (__popc(m) != R.topk) m = (R.topk == 32) ? 0xffffffffu : ((1u << R.topk) - 1u);   // NaN scores
-            masks[tok] = m;
-            if (soft) for (int g = 0; g < K; ++g) soft[tok * K + g] = mine[g];
+            masks[tg] = m;
+            if (soft) for (int g = 0; g < K; ++g) soft[tg * K + g] = mine[g];
         } else {
-            double* Srow = (double*)(ws + R.off_S) + tok * K;
+            double* Srow = (double*)(ws + R.off_S) + tg * K;
             for (int g = 0; g < K; ++g) Srow[g] = mine[g];
         }
     }
 }
 
-// largest score of each sequence
-__global__ __launch_bounds__(256) void route_max_kernel(RouteLayout R, char* __restrict__ ws)
-{
-    __shared__ double s_w[4];
-    const int tid = threadIdx.x, b = blockIdx.x;
-    const double* mp = (const double*)(ws + R.off_maxpart) + (size_t)b * R.nproj;
-    double m = -INFINITY;
-    for (int i = tid; i < R.nproj; i += 256) m = fmax(m, mp[i]);
-    m = wave_max(m);
-    if ((tid & 63) == 0) s_w[tid >> 6] = m;
-    __syncthreads();
-    if (tid == 0) ((double*)(ws + R.off_smax))[b] = fmax(fmax(s_w[0], s_w[1]), fmax(s_w[2], s_w[3]));
-}
-
 // ---------------------------------------------------------------- Sinkhorn passes
-// pass 0: E = exp((S - max)/tau) in place, column partial sums of E.
+// pass 0: the largest score of the sequence (the shift that keeps exp finite; the first column step divides it out
+// again), E = exp((S - max)/tau) in place, column partial sums of E.
 // pass t = 1..N: v from the partial sums of pass t-1, u per row, partial sums of u E (or, on pass N, the outputs).
 template <int KP>
 __global__ __launch_bounds__(256) void sinkhorn_pass_kernel(RouteLayout R, int pass, char* __restrict__ ws,
@@ -278,7 +299,18 @@ __global__ __launch_bounds__(256) void sinkhorn_pass_kernel(RouteLayout R, int p
         }
         __syncthreads();
     }
-    const double smax = ((const double*)(ws + R.off_smax))[b];
+    // pass 0: the largest score of the sequence from the projection's work-groups, folded by every work-group
+    double smax = 0.0;
+    if (pass == 0) {
+        __shared__ double s_m[4];
+        const double* mp = (const double*)(ws + R.off_maxpart) + (size_t)b * R.nproj;
+        double m = -INFINITY;
+        for (int i = tid; i < R.nproj; i += 256) m = fmax(m, mp[i]);
+        m = wave_max(m);
+        if (lane == 0) s_m[wave] = m;
+        __syncthreads();
+        smax = fmax(fmax(s_m[0], s_m[1]), fmax(s_m[2], s_m[3]));
+    }
     double v[KP], cs[KP];
 #pragma unroll
     for (int g = 0; g < KP; ++g) {
@@ -333,30 +365,24 @@ __global__ __launch_bounds__(256) void sinkhorn_pass_kernel(RouteLayout R, int p
 }
 
 template <typename T>
-hipError_t launch_project(const RouteLayout& R, const void* hidden, char* ws, uint32_t* masks, double* soft,
-                          hipStream_t st)
+hipError_t launch_project(const RouteLayout& R, const void* hidden, const float* wg, const float* cent, char* ws,
+                          uint32_t* masks, double* soft, hipStream_t st)
 {
-    const double* w64 = (const double*)(ws + R.off_w64);
-    const double* c64 = (const double*)(ws + R.off_c64);
+    const int nw = route_tokens_per_group(R.B, R.n, R.dg) / 16;
     dim3 grid(R.nproj, R.B);
-    const size_t stage = 2 * (size_t)RT * (RC * sizeof(T) + 16);
-    const size_t tail = (size_t)RT * (R.dg + 1 + (R.K | 1)) * sizeof(double);
-    const size_t lds = stage > tail ? stage : tail;
-#define FOCUS_PROJ(JW, NW)                                                                                   \
-    hipLaunchKernelGGL((route_project_kernel<T, JW, NW>), grid, dim3(64 * NW), lds, st, R, (const T*)hidden, w64, \
-                       c64, ws, masks, soft)
-    // JW router outputs per wavefront: more of them amortise the fp64 conversion of every hidden value,
-    // fewer give more wavefronts.  A wavefront issues one fp64 instruction about every 16 cycles, a SIMD
-    // one every 4: the fp64 rate needs 4 or more wavefronts per SIMD, so the split follows the token count
-    // (measured at d_model 4096..8192, d_g 16: 8 x 2 wins from 2048 groups of 64 tokens on, 4 x 4 below,
-    // 16 x 1 nowhere).
-    const long groups = (long)R.nproj * R.B;
+    const int cb = (R.dg + 15) / 16, rc = 128 / (int)sizeof(T);
+    const size_t stage = 2 * ((size_t)nw * 16 * A_ROW + (size_t)rc * (cb * 16 + (cb > 1 ? 16 : 0)) * 4);
+    const size_t tail = (size_t)nw * 16 * (R.dg + 1 + (R.K | 1)) * sizeof(double);
+    const size_t lds = stage > tail ? stage : tail;      // at most 51 KB (8 wavefronts, d_g <= 16) or 51 KB (4, d_g = 64)
+#define FOCUS_PROJ(DG, NW)                                                                                   \
+    hipLaunchKernelGGL((route_project_kernel<T, DG, NW>), grid, dim3(64 * NW), lds, st, R, (const T*)hidden, wg, \
+                       cent, ws, masks, soft)
     switch (R.dg) {
-        case 4: FOCUS_PROJ(4, 1); break;
-        case 8: FOCUS_PROJ(4, 2); break;
-        case 16: if (groups >= 2048) FOCUS_PROJ(8, 2); else FOCUS_PROJ(4, 4); break;
-        case 32: FOCUS_PROJ(8, 4); break;
-        default: FOCUS_PROJ(16, 4); break;
+        case 4: if (nw == 8) FOCUS_PROJ(4, 8); else FOCUS_PROJ(4, 4); break;
+        case 8: if (nw == 8) FOCUS_PROJ(8, 8); else FOCUS_PROJ(8, 4); break;
+        case 16: if (nw == 8) FOCUS_PROJ(16, 8); else FOCUS_PROJ(16, 4); break;
+        case 32: FOCUS_PROJ(32, 4); break;
+        default: FOCUS_PROJ(64, 4); break;
     }
 #undef FOCUS_PROJ
     return hipGetLastError();
@@ -368,16 +394,11 @@ hipError_t launch_route(const RouteLayout& R, const void* hidden, const float* w
                         uint32_t* masks, double* soft, hipStream_t st)
 {
     hipError_t e;
-    const size_t nw = (size_t)R.dm * R.dg, nc = (size_t)R.K * R.dg;
-    hipLaunchKernelGGL(to_f64_kernel, dim3((unsigned)min((size_t)1024, (nw + 255) / 256)), dim3(256), 0, st, wg,
-                       (double*)(ws + R.off_w64), nw);
-    hipLaunchKernelGGL(to_f64_kernel, dim3(1), dim3(256), 0, st, cent, (double*)(ws + R.off_c64), nc);
-    if (R.dtype == 0) e = launch_project<float>(R, hidden, ws, masks, soft, st);
-    else if (R.dtype == 2) e = launch_project<f16_bits>(R, hidden, ws, masks, soft, st);
-    else e = launch_project<uint16_t>(R, hidden, ws, masks, soft, st);
+    if (R.dtype == 0) e = launch_project<float>(R, hidden, wg, cent, ws, masks, soft, st);
+    else if (R.dtype == 2) e = launch_project<f16_bits>(R, hidden, wg, cent, ws, masks, soft, st);
+    else e = launch_project<uint16_t>(R, hidden, wg, cent, ws, masks, soft, st);
     if (e != hipSuccess) return e;
     if (R.iters == 0) return hipSuccess;
-    hipLaunchKernelGGL(route_max_kernel, dim3(R.B), dim3(256), 0, st, R, ws);
     dim3 grid(R.nsink, R.B);
     for (int pass = 0; pass <= R.iters; ++pass) {
         if (R.K <= 4) hipLaunchKernelGGL((sinkhorn_pass_kernel<4>), grid, dim3(256), 0, st, R, pass, ws, masks, soft);
