@@ -113,81 +113,239 @@ __global__ void decode_zero_kernel(int* __restrict__ p, int count)
 }
 
 // ---------------------------------------------------------------- prefill of the cache state
-// membership of the cached keys 0 .. n_ctx-1: one thread per key, fp64 scores in index order;
-// KMAX = K rounded up, so that the scores stay in registers
-template <typename T, int KMAX>
+// Membership of the cached keys 0 .. n_ctx-1: fp64 scores summed in index order on v_mfma_f64_16x16x4, which adds its
+// four products to the accumulator one by one with one rounding each (see focus_route.hip).  A wavefront scores 64 keys
+// as four tiles of 16 that share the B operand (centroids, staged once per work-group as fp32); key rows are staged
+// 128 bytes at a time, coalesced, in the wavefront's own LDS, components 4*i + p of a row side by side for each p.
+// The thread-per-key form before it read every row with 16-byte loads 256 bytes apart and widened a centroid value per
+// product: 8 x 131072 keys of 128, K = 8: 290 -> 150 us; 8 x 32768, K = 4: 49 -> 33 us; 96 x 4096 of 64: 60 -> 29 us.
+// KM = K rounded up to 4, 8, 16 or 32; the products run on 16 or 32 columns.
+typedef double dec_f64x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t dec_rows4;
+constexpr int DEC_A_ROW = 128 + 16;               // LDS pitch of a staged row: four interleaved parts of 32 bytes, padded
+
+template <typename T, int KM>
 __global__ __launch_bounds__(256) void decode_prefill_score_kernel(DecodeLayout L, int n_ctx, const T* __restrict__ kc,
                                                                    const float* __restrict__ cents, char* __restrict__ st)
 {
-    const int j = blockIdx.x * 256 + threadIdx.x;
+    constexpr int RC = 128 / (int)sizeof(T);      // components per staged chunk
+    constexpr int CB = KM <= 16 ? 1 : 2;          // blocks of 16 columns
+    constexpr int WP = CB * 16 + (CB > 1 ? 16 : 0);
+    constexpr int SP = KM + 1;                    // doubles per key when the scores meet in LDS
+    constexpr int TG = (16 * 4 * SP * 8 <= 64 * DEC_A_ROW) ? 4 : 2;   // tiles whose scores fit the wavefront's staging space
+    static_assert(16 * TG * SP * 8 <= 64 * DEC_A_ROW, "scores stay inside the staging space");
+    __shared__ __align__(16) char s_a[4][64 * DEC_A_ROW];
+    extern __shared__ float s_c[];                // centroids [d][WP], zero past K
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int bhk = blockIdx.y, hk = bhk % L.Hkv;
-    if (j >= n_ctx) return;
-    const int K = L.K;
-    const T* row = kc + ((size_t)bhk * L.n + j) * L.d;
-    const float* c = cents + (size_t)hk * K * L.d;        // wave-uniform: scalar loads
-    double s[KMAX];
+    const int K = L.K, d = L.d;
+    for (int e = tid; e < d * WP; e += 256) {
+        const int t = e / WP, g = e % WP;
+        s_c[e] = g < K ? cents[((size_t)hk * K + g) * d + t] : 0.f;
+    }
+    __syncthreads();
+    const int j0 = (blockIdx.x * 4 + wave) * 64;  // first key of this wavefront
+    if (j0 >= n_ctx) return;                      // (no barrier after this point)
+    const int rows = min(64, n_ctx - j0);
+    const int row_bytes = d * (int)sizeof(T);
+    const char* gbase = (const char*)(kc + ((size_t)bhk * L.n + j0) * d);
+    const int nchunk = (d + RC - 1) / RC;
+    char* abuf = s_a[wave];
+    dec_rows4 stg[8];
+    auto load_chunk = [&](int ch) {
 #pragma unroll
-    for (int g = 0; g < KMAX; ++g) s[g] = 0.0;
-    for (int t0 = 0; t0 < L.d; t0 += 8) {            // 16-byte (bf16) or 32-byte (fp32) pieces of the row, index order kept
-        float xv[8];
-        dec_load8(row + t0, xv);
+        for (int i = 0; i < 8; ++i) {
+            const int row = i * 8 + lane / 8, byte = ch * 128 + lane % 8 * 16;
+            const dec_rows4 z = {0u, 0u, 0u, 0u};
+            stg[i] = (row < rows && byte < row_bytes) ? *(const dec_rows4*)(gbase + (size_t)row * row_bytes + byte) : z;
+        }
+    };
+    dec_f64x4 acc[4][CB];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const double x = (double)xv[e];
+    for (int t = 0; t < 4; ++t)
 #pragma unroll
-            for (int g = 0; g < KMAX; ++g)
-                if (g < K) s[g] = fma(x, (double)c[(size_t)g * L.d + t0 + e], s[g]);
+        for (int cb = 0; cb < CB; ++cb) acc[t][cb] = dec_f64x4{0.0, 0.0, 0.0, 0.0};
+    load_chunk(0);
+    for (int ch = 0; ch < nchunk; ++ch) {
+        // a wavefront's LDS accesses run in order: no barrier, only the compiler must keep the order
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            uint32_t* dst = (uint32_t*)(abuf + (i * 8 + lane / 8) * DEC_A_ROW) + lane % 8;
+            const dec_rows4 v = stg[i];
+            if constexpr (sizeof(T) == 4) {
+                dst[0] = v[0]; dst[8] = v[1]; dst[16] = v[2]; dst[24] = v[3];
+            } else {
+                dst[0] = (v[0] & 0xffffu) | (v[2] << 16);
+                dst[8] = (v[0] >> 16) | (v[2] & 0xffff0000u);
+                dst[16] = (v[1] & 0xffffu) | (v[3] << 16);
+                dst[24] = (v[1] >> 16) | (v[3] & 0xffff0000u);
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        if (ch + 1 < nchunk) load_chunk(ch + 1);
+        dec_rows4 ar[4][2];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const dec_rows4* p = (const dec_rows4*)(abuf + (t * 16 + (lane & 15)) * DEC_A_ROW + (lane >> 4) * 32);
+            ar[t][0] = p[0];
+            ar[t][1] = p[1];
+        }
+        const float* wr = s_c + (ch * RC + (lane >> 4)) * WP + (lane & 15);
+        const int steps = min(RC, d - ch * RC) / 4;
+        auto step = [&](int i) {
+            double bv[CB];
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb) bv[cb] = (double)wr[i * 4 * WP + cb * 16];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                double a;
+                if constexpr (sizeof(T) == 4) {
+                    a = (double)__uint_as_float(ar[t][(i / 4) % 2][i % 4]);
+                } else {
+                    const uint32_t w2 = ar[t][(i / 8) % 2][(i / 2) % 4];
+                    if constexpr (std::is_same<T, f16_bits>::value)
+                        a = (double)f16_bits_to_f32((uint16_t)(i % 2 ? w2 >> 16 : w2 & 0xffffu));
+                    else
+                        a = (double)__uint_as_float(i % 2 ? w2 & 0xffff0000u : w2 << 16);
+                }
+#pragma unroll
+                for (int cb = 0; cb < CB; ++cb) acc[t][cb] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, bv[cb], acc[t][cb], 0, 0, 0);
+            }
+        };
+        if (steps == RC / 4) {
+#pragma unroll
+            for (int i = 0; i < RC / 4; ++i) step(i);
+        } else {                                  // the last chunk of 80 or 96 components
+#pragma unroll
+            for (int i = 0; i < RC / 4; ++i)
+                if (i < steps) step(i);
         }
     }
-    uint32_t m = 0;
+    // accumulator register r of lane l: key 4*r + l/16 of the tile, group l%16
+    double* s_s = (double*)abuf;
 #pragma unroll
-    for (int g = 0; g < KMAX; ++g) {
-        int beaten = 0;
+    for (int t0 = 0; t0 < 4; t0 += TG) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
 #pragma unroll
-        for (int o = 0; o < KMAX; ++o) beaten += (o < K && o != g && (s[o] > s[g] || (s[o] == s[g] && o < g))) ? 1 : 0;
-        if (g < K && beaten < L.topk) m |= (1u << g);
+        for (int t = 0; t < TG; ++t)
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (cb * 16 + (lane & 15) < KM)
+                        s_s[(t * 16 + 4 * r + (lane >> 4)) * SP + cb * 16 + (lane & 15)] = acc[t0 + t][cb][r];
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        const int row = t0 * 16 + lane;
+        if (lane < TG * 16 && row < rows) {
+            // rank counting from LDS (unrolled over registers, 16 and 32 groups spill)
+            const double* mine = s_s + lane * SP;
+            uint32_t m = 0;
+            for (int g = 0; g < K; ++g) {
+                const double sg = mine[g];
+                int beaten = 0;
+#pragma unroll 4
+                for (int o = 0; o < K; ++o) {
+                    const double so = mine[o];
+                    beaten += (o != g && (so > sg || (so == sg && o < g))) ? 1 : 0;
+                }
+                if (beaten < L.topk) m |= (1u << g);
+            }
+            if (__popc(m) != L.topk) m = (L.topk == 32) ? 0xffffffffu : ((1u << L.topk) - 1u);   // NaN scores
+            ((uint32_t*)(st + L.off_mk))[(size_t)bhk * L.n + j0 + row] = m;
+        }
     }
-    if (__popc(m) != L.topk) m = (L.topk == 32) ? 0xffffffffu : ((1u << L.topk) - 1u);   // NaN scores
-    ((uint32_t*)(st + L.off_mk))[(size_t)bhk * L.n + j] = m;
 }
 
-// position list of one group of one (batch, KV head): ordered compaction, 256 positions per round
-__global__ __launch_bounds__(256) void decode_prefill_lists_kernel(DecodeLayout L, int n_ctx, char* __restrict__ st)
+// Position lists of up to KM groups of one (batch, KV head), one chunk of the context per work-group: it counts the masks of
+// the chunks before its own (they sit in L2; a few thousand per thread at most), then compacts its chunk in position
+// order, 1024 positions per round.  One work-group per group over the whole context walked it 256 positions at a time
+// with three barriers each: 8 heads, K = 8, 131072 positions 356 -> 40 us; K = 4, 32768 positions 78 -> 10 us.
+constexpr int DEC_LIST_THREADS = 1024;
+template <int KM>
+__global__ __launch_bounds__(DEC_LIST_THREADS) void decode_prefill_lists_kernel(DecodeLayout L, int n_ctx, int chunk, char* __restrict__ st)
 {
-    __shared__ int s_w[4];
-    __shared__ int s_base;
+    constexpr int NWV = DEC_LIST_THREADS / 64;
+    __shared__ int s_w[NWV][KM];                  // entries of a wavefront in this round, then where they begin
+    __shared__ int s_base[KM], s_run[KM];         // entries before this chunk, before this round
+    __shared__ int s_wp[KM];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int g = blockIdx.x, bhk = blockIdx.y;
+    const int bhk = blockIdx.y, g0 = blockIdx.z * KM;             // groups g0 .. g0 + K - 1
+    const int K = min(KM, L.K - g0);
+    const int beg = blockIdx.x * chunk, end = min(n_ctx, beg + chunk);
     const uint32_t* mk = (const uint32_t*)(st + L.off_mk) + (size_t)bhk * L.n;
-    int* list = (int*)(st + L.off_lists) + ((size_t)bhk * L.K + g) * L.n;
-    if (tid == 0) s_base = 0;
+    int* lists = (int*)(st + L.off_lists) + ((size_t)bhk * L.K + g0) * L.n;
+    if (tid < KM) { s_base[tid] = 0; s_wp[tid] = 0; }
     __syncthreads();
-    // entries below the window of the next step (position n_ctx): positions < n_ctx - window + 1
-    const int lo_next = n_ctx - L.window + 1;
-    int below = 0;
-    for (int j0 = 0; j0 < n_ctx; j0 += 256) {
-        const int j = j0 + tid;
-        const bool mine = j < n_ctx && ((mk[j] >> g) & 1u);
-        below += (mine && j < lo_next) ? 1 : 0;
-        const unsigned long long bal = __ballot(mine);
-        const unsigned long long lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-        if (lane == 0) s_w[wave] = __popcll(bal);
-        __syncthreads();
-        int before = s_base;
-        for (int w2 = 0; w2 < wave; ++w2) before += s_w[w2];
-        if (mine) list[before + __popcll(bal & lt)] = j;
-        __syncthreads();
-        if (tid == 0) s_base += s_w[0] + s_w[1] + s_w[2] + s_w[3];
-        __syncthreads();
-    }
-    if (tid == 0) ((int*)(st + L.off_counts))[(size_t)bhk * L.K + g] = s_base;
-    // block-wide sum of `below` -> the group's window pointer
-    __syncthreads();
+    // entries of every group before this chunk
+    {
+        int c[KM];
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) below += __shfl_xor(below, off, 64);
-    if (lane == 0) s_w[wave] = below;
+        for (int g = 0; g < KM; ++g) c[g] = 0;
+        for (int j = tid; j < beg; j += DEC_LIST_THREADS * 4) {
+            uint32_t m[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) m[i] = (j + i * DEC_LIST_THREADS < beg) ? mk[j + i * DEC_LIST_THREADS] >> g0 : 0u;
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int g = 0; g < KM; ++g) c[g] += (int)((m[i] >> g) & 1u);
+        }
+#pragma unroll
+        for (int g = 0; g < KM; ++g) {
+#pragma unroll
+            for (int off = 32; off >= 1; off >>= 1) c[g] += __shfl_xor(c[g], off, 64);
+            if (lane == 0 && c[g]) atomicAdd(&s_base[g], c[g]);
+        }
+    }
     __syncthreads();
-    if (tid == 0) ((int*)(st + L.off_wp))[(size_t)bhk * L.K + g] = s_w[0] + s_w[1] + s_w[2] + s_w[3];
+    // entries below the window of the next step (position n_ctx): positions < lo_next
+    const int lo_next = min(n_ctx, max(0, n_ctx - L.window + 1));
+    const unsigned long long lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+    if (tid < K) s_run[tid] = s_base[tid];
+    for (int j0 = beg; j0 < end; j0 += DEC_LIST_THREADS) {
+        const int j = j0 + tid;
+        const uint32_t m = j < end ? mk[j] >> g0 : 0u;
+        for (int g = 0; g < K; ++g) {
+            const unsigned long long has = __ballot((m >> g) & 1u);
+            const unsigned long long low = __ballot(((m >> g) & 1u) && j < lo_next);
+            if (lane == 0) {
+                s_w[wave][g] = __popcll(has);
+                if (low) atomicAdd(&s_wp[g], __popcll(low));
+            }
+        }
+        __syncthreads();
+        if (tid < K) {                            // first list entry of every wavefront in this round
+            int run = s_run[tid];
+            for (int w2 = 0; w2 < NWV; ++w2) {
+                const int x = s_w[w2][tid];
+                s_w[w2][tid] = run;
+                run += x;
+            }
+            s_run[tid] = run;
+        }
+        __syncthreads();
+        for (int g = 0; g < K; ++g) {
+            const unsigned long long has = __ballot((m >> g) & 1u);
+            if ((m >> g) & 1u) lists[(size_t)g * L.n + s_w[wave][g] + __popcll(has & lt)] = j;
+        }
+        // (a wavefront reads only its own row of s_w above and is the one that rewrites it in the next round)
+    }
+    __syncthreads();
+    const bool last = end == n_ctx;
+    if (tid < K) {
+        if (last) {
+            ((int*)(st + L.off_counts))[(size_t)bhk * L.K + g0 + tid] = s_run[tid];
+        }
+        // the chunk that holds position lo_next (the last one when lo_next is the end) knows the window pointer
+        if ((lo_next >= beg && lo_next < end) || (last && lo_next == n_ctx))
+            ((int*)(st + L.off_wp))[(size_t)bhk * L.K + g0 + tid] = s_base[tid] + s_wp[tid];
+    }
 }
 
 // ---------------------------------------------------------------- step 1: route and append
@@ -1191,24 +1349,29 @@ hipError_t launch_decode_prefill(const DecodeLayout& L, int n_ctx, const void* k
     hipLaunchKernelGGL(decode_zero_kernel, dim3((ncount + 255) / 256), dim3(256), 0, s, (int*)(st + L.off_counts), ncount);
     if (n_ctx == 0) return hipGetLastError();
     dim3 g1((n_ctx + 255) / 256, L.B * L.Hkv);
+    const int km = L.K <= 4 ? 4 : L.K <= 8 ? 8 : L.K <= 16 ? 16 : 32;
     if (token_masks) {
         hipLaunchKernelGGL(decode_prefill_masks_kernel, g1, dim3(256), 0, s, L, n_ctx, token_masks, st);
-        hipLaunchKernelGGL(decode_prefill_lists_kernel, dim3(L.K, L.B * L.Hkv), dim3(256), 0, s, L, n_ctx, st);
-        return hipGetLastError();
-    }
-#define FOCUS_DEC_SCORE(T_, KM_) hipLaunchKernelGGL((decode_prefill_score_kernel<T_, KM_>), g1, dim3(256), 0, s, L, n_ctx, (const T_*)kc, cents, st)
-    if (L.dtype == 0) {
-        if (L.K <= 4) FOCUS_DEC_SCORE(float, 4); else if (L.K <= 8) FOCUS_DEC_SCORE(float, 8);
-        else if (L.K <= 16) FOCUS_DEC_SCORE(float, 16); else FOCUS_DEC_SCORE(float, 32);
-    } else if (L.dtype == 2) {
-        if (L.K <= 4) FOCUS_DEC_SCORE(f16_bits, 4); else if (L.K <= 8) FOCUS_DEC_SCORE(f16_bits, 8);
-        else if (L.K <= 16) FOCUS_DEC_SCORE(f16_bits, 16); else FOCUS_DEC_SCORE(f16_bits, 32);
     } else {
-        if (L.K <= 4) FOCUS_DEC_SCORE(uint16_t, 4); else if (L.K <= 8) FOCUS_DEC_SCORE(uint16_t, 8);
-        else if (L.K <= 16) FOCUS_DEC_SCORE(uint16_t, 16); else FOCUS_DEC_SCORE(uint16_t, 32);
-    }
+        const size_t lds = (size_t)L.d * (km <= 16 ? 16 : 48) * 4;       // centroids; with the staging space below 86 KB
+#define FOCUS_DEC_SCORE(T_, KM_) hipLaunchKernelGGL((decode_prefill_score_kernel<T_, KM_>), g1, dim3(256), lds, s, L, n_ctx, (const T_*)kc, cents, st)
+#define FOCUS_DEC_SCORE_T(T_)                                                                                             \
+    { if (km == 4) FOCUS_DEC_SCORE(T_, 4); else if (km == 8) FOCUS_DEC_SCORE(T_, 8);                                      \
+      else if (km == 16) FOCUS_DEC_SCORE(T_, 16); else FOCUS_DEC_SCORE(T_, 32); }
+        if (L.dtype == 0) FOCUS_DEC_SCORE_T(float)
+        else if (L.dtype == 2) FOCUS_DEC_SCORE_T(f16_bits)
+        else FOCUS_DEC_SCORE_T(uint16_t)
+#undef FOCUS_DEC_SCORE_T
 #undef FOCUS_DEC_SCORE
-    hipLaunchKernelGGL(decode_prefill_lists_kernel, dim3(L.K, L.B * L.Hkv), dim3(256), 0, s, L, n_ctx, st);
+    }
+    // chunks of whole rounds, about one work-group per compute unit (twice as many count twice as many masks before their
+    // own), none shorter than two rounds
+    const long long want = ((long long)n_ctx * L.B * L.Hkv + 255) / 256;
+    const int chunk = (int)std::max<long long>(2 * DEC_LIST_THREADS, (want + DEC_LIST_THREADS - 1) / DEC_LIST_THREADS * DEC_LIST_THREADS);
+    const int gs = L.K <= 4 ? 4 : 8;                     // groups per work-group
+    dim3 g2((n_ctx + chunk - 1) / chunk, L.B * L.Hkv, (L.K + gs - 1) / gs);
+    if (gs == 4) hipLaunchKernelGGL(decode_prefill_lists_kernel<4>, g2, dim3(DEC_LIST_THREADS), 0, s, L, n_ctx, chunk, st);
+    else hipLaunchKernelGGL(decode_prefill_lists_kernel<8>, g2, dim3(DEC_LIST_THREADS), 0, s, L, n_ctx, chunk, st);
     return hipGetLastError();
 }
 
