@@ -71,3 +71,33 @@ def test_prefill_from_token_masks_is_exact():
     focus.focus_decode_prefill_tokens(p, n_ctx, torch.from_numpy(masks.view(np.int32)).cuda(), state)
     torch.cuda.synchronize()
     _check_state(focus.focus_decode_state_views(p, state), masks[:, None, :], n_ctx)
+
+
+@pytest.mark.parametrize("d,dtype,K,topk", [(64, "bf16", 4, 2), (80, "f16", 8, 1), (96, "bf16", 8, 2), (128, "f16", 4, 2)])
+def test_step_with_rows_of_the_next_round_in_flight(d, dtype, K, topk):
+    """Launches of 400 to 544 work-groups of 512-entry chunks keep the next round's rows in flight: a ragged last chunk,
+    scan and list walks, against attention in float64 over the state's own memberships."""
+    B, Hq, Hkv, n = 1, 16, 8, 27000 + d
+    dt = {"bf16": torch.bfloat16, "f16": torch.float16}[dtype]
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d)
+    rand = lambda *s: torch.randn(s, generator=g, device="cuda").to(dt)
+    kc, vc = rand(B, Hkv, n, d), rand(B, Hkv, n, d)
+    c = torch.randn((Hkv, K, d), generator=g, device="cuda")
+    p = focus.make_params(B, Hq, Hkv, n, d, K, topk, 700, dtype=dtype)
+    state = focus.alloc_decode_state(p)
+    focus.focus_decode_prefill(p, n - 1, kc, c, state)
+    q, k, v = rand(B, Hq, d), rand(B, Hkv, d), rand(B, Hkv, d)
+    out, lse = torch.empty_like(q), torch.empty((B, Hq), dtype=torch.float32, device="cuda")
+    focus.focus_decode_step(p, n - 1, q, k, v, c, kc, vc, state, out, lse)
+    torch.cuda.synchronize()
+    views = focus.focus_decode_state_views(p, state)
+    for h in range(Hq):
+        x = (kc[0, h // 2].double() @ q[0, h].double()) / d ** 0.5
+        row = (views["mk"][0, h // 2] & views["mq"][0, h]) != 0
+        row[n - 700:] = True
+        x = x.masked_fill(~row, -float("inf"))
+        ref = torch.softmax(x, 0) @ vc[0, h // 2].double()
+        # an average of thousands of rows: the tolerances of the 16-bit types scaled to its size (outputs near 0.02)
+        assert (out[0, h].double() - ref).abs().max() <= harness.TOL[dtype]["out_max"] * 0.05
+        assert (lse[0, h].double() - torch.logsumexp(x, 0)).abs() <= harness.TOL[dtype]["lse"]
