@@ -23,6 +23,7 @@
 // Memberships given per token (focus_assign_tokens) take token_classes in place
 // of score_topk.
 #include "focus_internal.h"
+#include "focus_score.h"
 #include <hip/hip_bf16.h>
 #include <algorithm>
 #include <type_traits>
@@ -399,6 +400,47 @@ __global__ __launch_bounds__(SB) void score_topk_kernel(Layout L, HeadMap hm, co
 #undef FOCUS_SCORE_LOAD
 }
 
+// ---------------------------------------------------------------- scores of a masked layout
+// Memberships and group histograms of one sort block on the fp64 matrix cores (focus_score.h), for layouts without
+// classes: no fp64 centroid table, so no launch before it.  The products run on 16 columns whatever K is: faster than the
+// vector form above 8 groups (3 x 20 heads x 5003 tokens of 80, K = 16: 65 -> 44 us) and where the launch is a
+// matter of latency; with 4 groups and thousands of sort blocks the vector form wins (96 x 2 heads x 4096 of 64: 30 us).
+template <typename T, int KM>
+__global__ __launch_bounds__(SB) void score_linear_kernel(Layout L, HeadMap hm, const T* __restrict__ xq, const T* __restrict__ xk,
+                                                          const float* __restrict__ cents, char* __restrict__ ws)
+{
+    __shared__ __align__(16) char s_a[4][SCORE_LDS];
+    __shared__ int s_h[4][32];
+    extern __shared__ float s_c[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int blk = blockIdx.x, K = L.K, n = L.n;
+    const int is_query = side_of_row(L, -1, blockIdx.y);
+    const int bh = row_in_side(L, -1, blockIdx.y);
+    const int H = is_query ? L.Hq : L.Hkv, h = bh % H, hk = is_query ? hm.kv[h] : h;
+    const long long* xs = is_query ? L.qs : L.ks;
+    score_stage_centroids<KM>(cents + (size_t)hk * K * L.d, s_c, K, L.d);
+    // (the scatter launch after this one raises these)
+    if (!is_query && blk == 0 && tid < KN2_SLOTS) ((unsigned*)(ws + L.off_kn2))[(size_t)bh * KN2_SLOTS + tid] = 0u;
+    __syncthreads();
+    const int j0 = blk * SB + wave * 64, rows = min(64, n - j0);
+    uint32_t m = 0;
+    if (rows > 0) {
+        const T* x = (is_query ? xq : xk) + (size_t)(bh / H) * xs[0] + (size_t)h * xs[1] + (size_t)j0 * xs[2];
+        m = score_rows_topk<T, KM>((const char*)x, (size_t)xs[2] * sizeof(T), rows, L.d, s_c, s_a[wave], K, L.topk);
+        if (lane < rows) ((uint32_t*)(ws + (is_query ? L.off_mq : L.off_mk)))[(size_t)bh * n + j0 + lane] = m;
+    }
+    for (int g = 0; g < K; ++g) {
+        const unsigned long long has = __ballot((m >> g) & 1u);
+        if (lane == 0) s_h[wave][g] = __popcll(has);
+    }
+    __syncthreads();
+    if (tid < K)
+        ((int*)(ws + (is_query ? L.off_qbg : L.off_kbg)))[((size_t)bh * (L.nblk + 1) + blk) * K + tid] =
+            s_h[0][tid] + s_h[1][tid] + s_h[2][tid] + s_h[3][tid];
+    if (tid == 0) ((int*)(ws + (is_query ? L.off_qbc : L.off_kbc)))[(size_t)bh * (L.nblk + 1) + blk] = min(SB, n - blk * SB);
+}
+
 // ---------------------------------------------------------------- start of an assign pass
 // The largest-key-norm slots to zero and, when centroids are given, their fp64 table: one small launch.
 __global__ __launch_bounds__(256) void assign_init_kernel(unsigned* __restrict__ zeros, size_t nzeros,
@@ -444,9 +486,14 @@ __device__ inline float chunk_norm2(const uint4& val, bool f16)
 // The copy also leaves the largest squared key norm of the (batch, KV head) in the workspace (off_kn2: KN2_SLOTS
 // partial maxima per head, cleared by assign_init): a non-negative float orders like its bit pattern, so one
 // atomicMax on the bits per work-group does it, and a NaN or infinite norm ends up above every finite one.
+// LINEAR (masked layouts): one class, slot = position.  OWN_SCAN: no scan launch ran; the work-group adds up the group
+// histograms of the row's sort blocks itself (a few thousand integers at most), and sort block 0 writes the row's counts.
+template <bool LINEAR, bool OWN_SCAN>
 __global__ __launch_bounds__(SB) void scatter_kernel(Layout L, int which, const uint16_t* __restrict__ k, char* __restrict__ ws)
 {
-    __shared__ int s_wc[4][MAX_CLASSES];
+    static_assert(LINEAR || !OWN_SCAN, "class offsets come from the scan launch");
+    __shared__ int s_wc[LINEAR ? 1 : 4][LINEAR ? 1 : MAX_CLASSES];
+    __shared__ int s_lo[32], s_tot[32];           // first entry of this block in every group's list; list lengths (OWN_SCAN)
     __shared__ int s_wg[4][32];
     __shared__ int s_dest[SB];
     __shared__ unsigned s_n2[SB / 64];
@@ -463,21 +510,40 @@ __global__ __launch_bounds__(SB) void scatter_kernel(Layout L, int which, const 
     const uint8_t* clsarr = (const uint8_t*)(ws + (is_query ? L.off_qcls : L.off_kcls));
     const size_t cls_stride = is_query ? (size_t)n : (size_t)L.nblk * SB;
     const uint32_t mask = valid ? masks[(size_t)bh * n + pos] : 0u;
-    const int cls = valid ? (int)clsarr[(size_t)bh * cls_stride + pos] : -1;
+    const int cls = !valid ? -1 : LINEAR ? 0 : (int)clsarr[(size_t)bh * cls_stride + pos];
 
-    for (int e = tid; e < 4 * MAX_CLASSES; e += SB) (&s_wc[0][0])[e] = 0;
+    if constexpr (!LINEAR) {
+        for (int e = tid; e < 4 * MAX_CLASSES; e += SB) (&s_wc[0][0])[e] = 0;
+    }
+    const int* bg_row = (const int*)(ws + (is_query ? L.off_qbg : L.off_kbg)) + (size_t)bh * (L.nblk + 1) * K;
+    if constexpr (OWN_SCAN) {
+        for (int g = wave; g < K; g += 4) {       // a wavefront per group: entries before this block, and in all
+            int before = 0, all = 0;
+            for (int b2 = lane; b2 < L.nblk; b2 += 64) {
+                const int x = bg_row[(size_t)b2 * K + g];
+                before += b2 < blk ? x : 0;
+                all += x;
+            }
+#pragma unroll
+            for (int off = 32; off >= 1; off >>= 1) {
+                before += __shfl_xor(before, off, 64);
+                all += __shfl_xor(all, off, 64);
+            }
+            if (lane == 0) { s_lo[g] = before; s_tot[g] = all; }
+        }
+    }
     __syncthreads();
 
     const unsigned long long lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
     // stable rank among the tokens of the same class inside this wavefront
     int rank_c = 0;
-    unsigned long long todo = __ballot(valid);
+    unsigned long long todo = LINEAR ? 0ull : __ballot(valid);
     while (todo) {
         const int leader = __ffsll((long long)todo) - 1;
         const int c0 = __shfl(cls, leader, 64);
         const unsigned long long same = __ballot(valid && cls == c0);
         if (valid && cls == c0) rank_c = __popcll(same & lt);
-        if (lane == leader) s_wc[wave][c0] = __popcll(same);
+        if (lane == leader) s_wc[LINEAR ? 0 : wave][LINEAR ? 0 : c0] = __popcll(same);
         todo &= ~same;
     }
     // per-wavefront totals of every group bit
@@ -492,16 +558,38 @@ __global__ __launch_bounds__(SB) void scatter_kernel(Layout L, int which, const 
         }
     }
     __syncthreads();
+    if (tid < K) {
+        if constexpr (OWN_SCAN) {
+            int go = 0;                           // groups lie back to back in the list
+            for (int g = 0; g < tid; ++g) go += s_tot[g];
+            if (blk == 0) {
+                ((int*)(ws + (is_query ? L.off_qgc : L.off_kgc)))[(size_t)bh * K + tid] = s_tot[tid];
+                ((int*)(ws + (is_query ? L.off_qgo : L.off_kgo)))[(size_t)bh * (K + 1) + tid] = go;
+                if (tid == K - 1) ((int*)(ws + (is_query ? L.off_qgo : L.off_kgo)))[(size_t)bh * (K + 1) + K] = go + s_tot[tid];
+            }
+            s_wg[3][tid] = go + s_lo[tid] + s_wg[0][tid] + s_wg[1][tid] + s_wg[2][tid];
+        } else {
+            const int* go = (const int*)(ws + (is_query ? L.off_qgo : L.off_kgo)) + (size_t)bh * (K + 1);
+            s_wg[3][tid] = go[tid] + bg_row[(size_t)blk * K + tid] + s_wg[0][tid] + s_wg[1][tid] + s_wg[2][tid];
+        }
+        // s_wg[w]: first list entry of wavefront w
+        s_wg[2][tid] = s_wg[3][tid] - s_wg[2][tid];
+        s_wg[1][tid] = s_wg[2][tid] - s_wg[1][tid];
+        s_wg[0][tid] = s_wg[1][tid] - s_wg[0][tid];
+    }
+    __syncthreads();
 
     const int* bc = (const int*)(ws + (is_query ? L.off_qbc : L.off_kbc)) + ((size_t)bh * (L.nblk + 1) + blk) * NC;
-    const int* bg = (const int*)(ws + (is_query ? L.off_qbg : L.off_kbg)) + ((size_t)bh * (L.nblk + 1) + blk) * K;
     const int* co = (const int*)(ws + (is_query ? L.off_qco : L.off_kco)) + (size_t)bh * (NC + 1);
-    const int* go = (const int*)(ws + (is_query ? L.off_qgo : L.off_kgo)) + (size_t)bh * (K + 1);
     int dest = -1;
     if (valid) {
-        int before = 0;
-        for (int w = 0; w < wave; ++w) before += s_wc[w][cls];
-        dest = co[cls] + bc[cls] + before + rank_c;
+        if constexpr (LINEAR) {
+            dest = pos;
+        } else {
+            int before = 0;
+            for (int w = 0; w < wave; ++w) before += s_wc[w][cls];
+            dest = co[cls] + bc[cls] + before + rank_c;
+        }
         if (is_query) {
             ((int*)(ws + L.off_qperm))[(size_t)bh * L.NQP + dest] = pos;
         } else {
@@ -514,11 +602,7 @@ __global__ __launch_bounds__(SB) void scatter_kernel(Layout L, int which, const 
     for (int g = 0; g < K; ++g) {
         const bool mine = valid && ((mask >> g) & 1u);
         const unsigned long long has = __ballot(mine);
-        if (mine) {
-            int bw = 0;
-            for (int w = 0; w < wave; ++w) bw += s_wg[w][g];
-            lists[go[g] + bg[g] + bw + __popcll(has & lt)] = pos;
-        }
+        if (mine) lists[s_wg[wave][g] + __popcll(has & lt)] = pos;
     }
 
     // ---- pads of the class-ordered arrays: the work-group of sort block b fills those of the classes b, b + nblk, ...
@@ -528,9 +612,10 @@ __global__ __launch_bounds__(SB) void scatter_kernel(Layout L, int which, const 
     const bool copy_k = !is_query && k != nullptr;
     const int CPR = L.dp / 8;                        // 16-byte chunks per row of the key copy (8, 16 or 32)
     uint4* kc = (uint4*)(ws + L.off_kc) + (size_t)bh * L.NKP * CPR;
-    for (int c = blk; c <= NC; c += L.nblk) {
-        const int p0 = c < NC ? co[c] + cnt[c] : co[NC];
-        const int p1 = c < NC ? co[c + 1] : plen;
+    for (int c = LINEAR ? L.nblk - 1 - blk : blk; c <= NC; c += L.nblk) {      // (LINEAR: NC = 1, left to the last sort blocks)
+        const int end0 = LINEAR ? min(plen, (n + KT - 1) / KT * KT) : 0;
+        const int p0 = LINEAR ? (c == 0 ? n : end0) : c < NC ? co[c] + cnt[c] : co[NC];
+        const int p1 = LINEAR ? (c == 0 ? end0 : plen) : c < NC ? co[c + 1] : plen;
         for (int p = p0 + tid; p < p1; p += SB) {
             if (is_query) {
                 ((int*)(ws + L.off_qperm))[(size_t)bh * L.NQP + p] = -1;
@@ -692,6 +777,10 @@ void launch_assign_init(const Layout& L, const float* centroids, char* ws, hipSt
                        centroids, (double*)(ws + L.off_cent64), L.Hkv, L.K, L.d, dcent, kmax);
 }
 
+// Masked layouts need no class tables and no job list: where a row's group histograms are few, the scatter launch adds
+// them up itself and the scan launch (10 us of latency, one work-group per row) is left out.
+bool own_scan(const Layout& L) { return L.masked && (long long)L.nblk * L.K <= 4096; }
+
 // from class ids, block prefixes and the per-row plan to the class-ordered arrays, group lists and key copy
 hipError_t launch_scatter(const Layout& L, const void* k, char* ws, hipStream_t st)
 {
@@ -701,7 +790,9 @@ hipError_t launch_scatter(const Layout& L, const void* k, char* ws, hipStream_t 
     const bool both = L.B * (L.Hq + L.Hkv) <= MAX_GRID_ROWS;
     for (int which = both ? -1 : 1; which >= -1; --which) {
         const int rows = which < 0 ? L.B * (L.Hq + L.Hkv) : which ? L.B * L.Hq : L.B * L.Hkv;
-        hipLaunchKernelGGL(scatter_kernel, dim3(L.nblk, rows), dim3(SB), 0, st, L, which, kcopy, ws);
+        if (own_scan(L)) hipLaunchKernelGGL((scatter_kernel<true, true>), dim3(L.nblk, rows), dim3(SB), 0, st, L, which, kcopy, ws);
+        else if (L.masked) hipLaunchKernelGGL((scatter_kernel<true, false>), dim3(L.nblk, rows), dim3(SB), 0, st, L, which, kcopy, ws);
+        else hipLaunchKernelGGL((scatter_kernel<false, false>), dim3(L.nblk, rows), dim3(SB), 0, st, L, which, kcopy, ws);
         if (which <= 0) break;
     }
     return hipGetLastError();
@@ -713,12 +804,31 @@ hipError_t launch_assign(const Layout& L, const HeadMap& hm, const void* q, cons
                          const float* centroids, char* ws, hipStream_t st)
 {
     hipError_t e;
+    const long long sort_blocks = (long long)L.B * (L.Hq + L.Hkv) * L.nblk;
+    if (L.masked && L.B * (L.Hq + L.Hkv) <= MAX_GRID_ROWS && (L.K > 8 || sort_blocks <= 512)) {
+        const int km = L.K <= 4 ? 4 : L.K <= 8 ? 8 : L.K <= 16 ? 16 : 32;
+        const dim3 grid(L.nblk, L.B * (L.Hq + L.Hkv));
+        const size_t lds = (size_t)L.d * score_wp(km) * 4;           // with the staging space below 87 KB
+#define FOCUS_SCORE_L(T_, KM_) hipLaunchKernelGGL((score_linear_kernel<T_, KM_>), grid, dim3(SB), lds, st, L, hm, (const T_*)q, (const T_*)k, centroids, ws)
+#define FOCUS_SCORE_LT(T_)                                                                                               \
+    { if (km == 4) FOCUS_SCORE_L(T_, 4); else if (km == 8) FOCUS_SCORE_L(T_, 8);                                          \
+      else if (km == 16) FOCUS_SCORE_L(T_, 16); else FOCUS_SCORE_L(T_, 32); }
+        if (L.dtype == 0) FOCUS_SCORE_LT(float)
+        else if (L.dtype == 2) FOCUS_SCORE_LT(f16_bits)
+        else FOCUS_SCORE_LT(uint16_t)
+#undef FOCUS_SCORE_LT
+#undef FOCUS_SCORE_L
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        if (!own_scan(L)) hipLaunchKernelGGL(scan_plan_kernel, dim3(L.B * (L.Hq + L.Hkv)), dim3(SCAN_THREADS), 0, st, L, ws);
+        return launch_scatter(L, k, ws, st);
+    }
     launch_assign_init(L, centroids, ws, st);
     if (L.dtype == 0) e = launch_score<float>(L, hm, q, k, ws, st);
     else if (L.dtype == 2) e = launch_score<f16_bits>(L, hm, q, k, ws, st);
     else e = launch_score<uint16_t>(L, hm, q, k, ws, st);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(scan_plan_kernel, dim3(L.B * (L.Hq + L.Hkv)), dim3(SCAN_THREADS), 0, st, L, ws);
+    if (!own_scan(L)) hipLaunchKernelGGL(scan_plan_kernel, dim3(L.B * (L.Hq + L.Hkv)), dim3(SCAN_THREADS), 0, st, L, ws);
     return launch_scatter(L, k, ws, st);
 }
 
@@ -728,7 +838,7 @@ hipError_t launch_assign_tokens(const Layout& L, const uint32_t* token_masks, co
     launch_assign_init(L, nullptr, ws, st);
     if (invalid_count) hipLaunchKernelGGL(fill_i32_kernel, dim3(1), dim3(64), 0, st, invalid_count, (size_t)1, 0);
     hipLaunchKernelGGL(token_classes_kernel, dim3(L.nblk, L.B), dim3(SB), 0, st, L, token_masks, ws, invalid_count);
-    hipLaunchKernelGGL(scan_plan_kernel, dim3(L.B * (L.Hq + L.Hkv)), dim3(SCAN_THREADS), 0, st, L, ws);
+    if (!own_scan(L)) hipLaunchKernelGGL(scan_plan_kernel, dim3(L.B * (L.Hq + L.Hkv)), dim3(SCAN_THREADS), 0, st, L, ws);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     return launch_scatter(L, k, ws, st);

@@ -20,6 +20,7 @@
 //      products on the matrix cores;
 //   3. merges the chunks' partial (o, max, sum) by their log-sum-exp weights (App. D "Merge", n-ary).
 #include "focus_internal.h"
+#include "focus_score.h"
 #include <algorithm>
 #include <type_traits>
 
@@ -113,153 +114,25 @@ __global__ void decode_zero_kernel(int* __restrict__ p, int count)
 }
 
 // ---------------------------------------------------------------- prefill of the cache state
-// Membership of the cached keys 0 .. n_ctx-1: fp64 scores summed in index order on v_mfma_f64_16x16x4, which adds its
-// four products to the accumulator one by one with one rounding each (see focus_route.hip).  A wavefront scores 64 keys
-// as four tiles of 16 that share the B operand (centroids, staged once per work-group as fp32); key rows are staged
-// 128 bytes at a time, coalesced, in the wavefront's own LDS, components 4*i + p of a row side by side for each p.
-// The thread-per-key form before it read every row with 16-byte loads 256 bytes apart and widened a centroid value per
-// product: 8 x 131072 keys of 128, K = 8: 290 -> 150 us; 8 x 32768, K = 4: 49 -> 33 us; 96 x 4096 of 64: 60 -> 29 us.
-// KM = K rounded up to 4, 8, 16 or 32; the products run on 16 or 32 columns.
-typedef double dec_f64x4 __attribute__((ext_vector_type(4)));
-typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t dec_rows4;
-constexpr int DEC_A_ROW = 128 + 16;               // LDS pitch of a staged row: four interleaved parts of 32 bytes, padded
-
+// Membership of the cached keys 0 .. n_ctx-1, 64 of them per wavefront (focus_score.h).  The thread-per-key form before it
+// read every row with 16-byte loads a row apart and widened a centroid value per product: 8 x 131072 keys of 128, K = 8:
+// 290 -> 150 us; 8 x 32768, K = 4: 49 -> 33 us; 96 x 4096 of 64: 60 -> 29 us.
 template <typename T, int KM>
 __global__ __launch_bounds__(256) void decode_prefill_score_kernel(DecodeLayout L, int n_ctx, const T* __restrict__ kc,
                                                                    const float* __restrict__ cents, char* __restrict__ st)
 {
-    constexpr int RC = 128 / (int)sizeof(T);      // components per staged chunk
-    constexpr int CB = KM <= 16 ? 1 : 2;          // blocks of 16 columns
-    constexpr int WP = CB * 16 + (CB > 1 ? 16 : 0);
-    constexpr int SP = KM + 1;                    // doubles per key when the scores meet in LDS
-    constexpr int TG = (16 * 4 * SP * 8 <= 64 * DEC_A_ROW) ? 4 : 2;   // tiles whose scores fit the wavefront's staging space
-    static_assert(16 * TG * SP * 8 <= 64 * DEC_A_ROW, "scores stay inside the staging space");
-    __shared__ __align__(16) char s_a[4][64 * DEC_A_ROW];
-    extern __shared__ float s_c[];                // centroids [d][WP], zero past K
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    __shared__ __align__(16) char s_a[4][SCORE_LDS];
+    extern __shared__ float s_c[];                // centroids [d][WP]
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int bhk = blockIdx.y, hk = bhk % L.Hkv;
-    const int K = L.K, d = L.d;
-    for (int e = tid; e < d * WP; e += 256) {
-        const int t = e / WP, g = e % WP;
-        s_c[e] = g < K ? cents[((size_t)hk * K + g) * d + t] : 0.f;
-    }
+    score_stage_centroids<KM>(cents + (size_t)hk * L.K * L.d, s_c, L.K, L.d);
     __syncthreads();
     const int j0 = (blockIdx.x * 4 + wave) * 64;  // first key of this wavefront
     if (j0 >= n_ctx) return;                      // (no barrier after this point)
-    const int rows = min(64, n_ctx - j0);
-    const int row_bytes = d * (int)sizeof(T);
-    const char* gbase = (const char*)(kc + ((size_t)bhk * L.n + j0) * d);
-    const int nchunk = (d + RC - 1) / RC;
-    char* abuf = s_a[wave];
-    dec_rows4 stg[8];
-    auto load_chunk = [&](int ch) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int row = i * 8 + lane / 8, byte = ch * 128 + lane % 8 * 16;
-            const dec_rows4 z = {0u, 0u, 0u, 0u};
-            stg[i] = (row < rows && byte < row_bytes) ? *(const dec_rows4*)(gbase + (size_t)row * row_bytes + byte) : z;
-        }
-    };
-    dec_f64x4 acc[4][CB];
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-#pragma unroll
-        for (int cb = 0; cb < CB; ++cb) acc[t][cb] = dec_f64x4{0.0, 0.0, 0.0, 0.0};
-    load_chunk(0);
-    for (int ch = 0; ch < nchunk; ++ch) {
-        // a wavefront's LDS accesses run in order: no barrier, only the compiler must keep the order
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            uint32_t* dst = (uint32_t*)(abuf + (i * 8 + lane / 8) * DEC_A_ROW) + lane % 8;
-            const dec_rows4 v = stg[i];
-            if constexpr (sizeof(T) == 4) {
-                dst[0] = v[0]; dst[8] = v[1]; dst[16] = v[2]; dst[24] = v[3];
-            } else {
-                dst[0] = (v[0] & 0xffffu) | (v[2] << 16);
-                dst[8] = (v[0] >> 16) | (v[2] & 0xffff0000u);
-                dst[16] = (v[1] & 0xffffu) | (v[3] << 16);
-                dst[24] = (v[1] >> 16) | (v[3] & 0xffff0000u);
-            }
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        if (ch + 1 < nchunk) load_chunk(ch + 1);
-        dec_rows4 ar[4][2];
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            const dec_rows4* p = (const dec_rows4*)(abuf + (t * 16 + (lane & 15)) * DEC_A_ROW + (lane >> 4) * 32);
-            ar[t][0] = p[0];
-            ar[t][1] = p[1];
-        }
-        const float* wr = s_c + (ch * RC + (lane >> 4)) * WP + (lane & 15);
-        const int steps = min(RC, d - ch * RC) / 4;
-        auto step = [&](int i) {
-            double bv[CB];
-#pragma unroll
-            for (int cb = 0; cb < CB; ++cb) bv[cb] = (double)wr[i * 4 * WP + cb * 16];
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                double a;
-                if constexpr (sizeof(T) == 4) {
-                    a = (double)__uint_as_float(ar[t][(i / 4) % 2][i % 4]);
-                } else {
-                    const uint32_t w2 = ar[t][(i / 8) % 2][(i / 2) % 4];
-                    if constexpr (std::is_same<T, f16_bits>::value)
-                        a = (double)f16_bits_to_f32((uint16_t)(i % 2 ? w2 >> 16 : w2 & 0xffffu));
-                    else
-                        a = (double)__uint_as_float(i % 2 ? w2 & 0xffff0000u : w2 << 16);
-                }
-#pragma unroll
-                for (int cb = 0; cb < CB; ++cb) acc[t][cb] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, bv[cb], acc[t][cb], 0, 0, 0);
-            }
-        };
-        if (steps == RC / 4) {
-#pragma unroll
-            for (int i = 0; i < RC / 4; ++i) step(i);
-        } else {                                  // the last chunk of 80 or 96 components
-#pragma unroll
-            for (int i = 0; i < RC / 4; ++i)
-                if (i < steps) step(i);
-        }
-    }
-    // accumulator register r of lane l: key 4*r + l/16 of the tile, group l%16
-    double* s_s = (double*)abuf;
-#pragma unroll
-    for (int t0 = 0; t0 < 4; t0 += TG) {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-#pragma unroll
-        for (int t = 0; t < TG; ++t)
-#pragma unroll
-            for (int cb = 0; cb < CB; ++cb)
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    if (cb * 16 + (lane & 15) < KM)
-                        s_s[(t * 16 + 4 * r + (lane >> 4)) * SP + cb * 16 + (lane & 15)] = acc[t0 + t][cb][r];
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        const int row = t0 * 16 + lane;
-        if (lane < TG * 16 && row < rows) {
-            // rank counting from LDS (unrolled over registers, 16 and 32 groups spill)
-            const double* mine = s_s + lane * SP;
-            uint32_t m = 0;
-            for (int g = 0; g < K; ++g) {
-                const double sg = mine[g];
-                int beaten = 0;
-#pragma unroll 4
-                for (int o = 0; o < K; ++o) {
-                    const double so = mine[o];
-                    beaten += (o != g && (so > sg || (so == sg && o < g))) ? 1 : 0;
-                }
-                if (beaten < L.topk) m |= (1u << g);
-            }
-            if (__popc(m) != L.topk) m = (L.topk == 32) ? 0xffffffffu : ((1u << L.topk) - 1u);   // NaN scores
-            ((uint32_t*)(st + L.off_mk))[(size_t)bhk * L.n + j0 + row] = m;
-        }
-    }
+    const uint32_t m = score_rows_topk<T, KM>((const char*)(kc + ((size_t)bhk * L.n + j0) * L.d), (size_t)L.d * sizeof(T),
+                                              min(64, n_ctx - j0), L.d, s_c, s_a[wave], L.K, L.topk);
+    if (j0 + lane < n_ctx) ((uint32_t*)(st + L.off_mk))[(size_t)bhk * L.n + j0 + lane] = m;
 }
 
 // Position lists of up to KM groups of one (batch, KV head), one chunk of the context per work-group: it counts the masks of
@@ -1381,7 +1254,7 @@ hipError_t launch_decode_prefill(const DecodeLayout& L, int n_ctx, const void* k
     if (token_masks) {
         hipLaunchKernelGGL(decode_prefill_masks_kernel, g1, dim3(256), 0, s, L, n_ctx, token_masks, st);
     } else {
-        const size_t lds = (size_t)L.d * (km <= 16 ? 16 : 48) * 4;       // centroids; with the staging space below 86 KB
+        const size_t lds = (size_t)L.d * score_wp(km) * 4;               // centroids; with the staging space below 86 KB
 #define FOCUS_DEC_SCORE(T_, KM_) hipLaunchKernelGGL((decode_prefill_score_kernel<T_, KM_>), g1, dim3(256), lds, s, L, n_ctx, (const T_*)kc, cents, st)
 #define FOCUS_DEC_SCORE_T(T_)                                                                                             \
     { if (km == 4) FOCUS_DEC_SCORE(T_, 4); else if (km == 8) FOCUS_DEC_SCORE(T_, 8);                                      \
