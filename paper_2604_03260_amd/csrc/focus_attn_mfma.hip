@@ -168,7 +168,10 @@ __global__ __launch_bounds__(NTHR) void gather_vt_kernel(Layout L, const uint16_
 // or it does not).  PM_COARSE, PM_MASKED: by the two membership masks, see the kernel's comment.
 constexpr int PM_EXACT = 0, PM_COARSE = 1, PM_MASKED = 2;
 constexpr int KBITS_MAX = 4 * 33;    // words of bits per key tile at K = 32: [unit][half-wave][group, V row not finite]
-constexpr int GROW = 128;     // bytes of a key's soft assignment in LDS: bf16 high parts of 32 groups, then the low parts
+// Bytes of a key's soft assignment: bf16 high parts of 16 or 32 groups, then the low parts, in 16-byte chunks swizzled so
+// that the 16 keys a read group covers fall on different banks.
+__host__ __device__ constexpr int grow_bytes(int kg) { return 64 * kg; }
+__host__ __device__ constexpr int grow_swizzle(int kg, int chunk, int key) { return kg == 1 ? chunk ^ ((key >> 2) & 3) : chunk ^ (key & 7); }
 
 // LDS rows of the K and V^T tiles are 16 bytes longer than their data: with pitches of 272 / 528 / 144 bytes
 // the 16 lanes of a ds_read_b128 group (16 consecutive rows, the same chunk) fall on 16 different bank
@@ -183,16 +186,16 @@ template <int D> struct TileGeom {
     static_assert(K_LDS % 1024 == 0 && V_LDS % 1024 == 0, "stages are filled in 1-KB wave loads");
 };
 
-template <int D, int PM, bool SOFT>
+template <int D, int PM, int SOFT>
 struct Smem {
-    TilePlan plan;
+    TilePlanT<(PM == PM_MASKED || SOFT) ? 1 : MAX_CLASSES> plan;      // one class where the layout is in position order
     __attribute__((aligned(16))) int kpos[3][KT];
     __attribute__((aligned(16))) char k[2][TileGeom<D>::K_LDS];    // [stage][key][KROW] 16-bit elements
     __attribute__((aligned(16))) char vt[2][TileGeom<D>::V_LDS];   // [stage][d][VROW] 16-bit elements
     __attribute__((aligned(16))) unsigned kmsk[PM == PM_COARSE ? 3 * KT : 4];      // membership masks of the keys (coarse classes)
     __attribute__((aligned(16))) unsigned kbits[PM == PM_MASKED ? 3 * KBITS_MAX : 4];   // membership bits of the keys (masked)
     unsigned upto[PM == PM_MASKED ? 30 : 1];                       // scores at or below a key offset (masked, see the loop)
-    __attribute__((aligned(16))) char gk[SOFT ? 2 * KT * GROW : 16];   // [stage][key][GROW] soft assignments of the keys
+    __attribute__((aligned(16))) char gk[SOFT ? 2 * KT * grow_bytes(SOFT) : 16];   // [stage][key][grow_bytes] soft assignments of the keys
 };
 
 // max of the two half-waves (lane l and lane l^32 hold the same query row)
@@ -259,12 +262,17 @@ __device__ inline void pin_operands(V8 (&a)[N])
 // score of a pair outside the window is multiplied by sigmoid(lambda * g_i . g_j).  The affinities come off the
 // matrix cores next to the scores: G^T = g_K g_Q^T with both sides split into bf16 high and low parts (three
 // products per 16 groups), the query side pre-multiplied by -lambda*log2(e) so that the gate is 1/(1 + 2^G).
-// Runs one wavefront per SIMD (two more accumulators and the operands of G do not fit 256 registers).
+// SOFT = 1 (K <= 16): one k-step of G, 64 bytes of soft assignment per key, the plan reduced to its one class and, at 128
+// components, operands in two halves (HV = 2): 242 registers and 81 KB of LDS, two wavefronts per SIMD.  The three
+// transcendentals per pair (768 cycles per 32 keys, against 608 of products) and the products then overlap: 8192 tokens,
+// 32/8 heads of 128: 1201 -> 773 us.  SOFT = 2 (K up to 32): one wavefront per SIMD, as both were.  The softmax keeps
+// its running reference: without one it was 761 us, but the largest probability of a row is then no longer exactly
+// one, and the result 4 % further from 64 bits.
 // NOREF: the softmax without a reference (head of this file).  Every launch runs the kernel twice: the NOREF
 // instantiation first, whose work-groups check their bound, leave a flag (1 = done here, 0 = not mine) and do
 // the tile or return; then the other instantiation, whose work-groups return at once where the flag says done.
-template <int D, int KS, int DB, int MFMA_WAVES, bool SOFTCAP, bool PAIRS, bool F16, int PM, bool SOFT, bool NOREF>
-__global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT) ? 1 : 8 / MFMA_WAVES) void attn_mfma_kernel(
+template <int D, int KS, int DB, int MFMA_WAVES, bool SOFTCAP, bool PAIRS, bool F16, int PM, int SOFT, bool NOREF>
+__global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT == 2) ? 1 : 8 / MFMA_WAVES) void attn_mfma_kernel(
     Layout L, HeadMap hm, int default_map, const uint16_t* __restrict__ q, const float* __restrict__ g,
     char* ws_rw, uint16_t* __restrict__ out, float* __restrict__ lse,
     int32_t* __restrict__ row_pairs)
@@ -279,7 +287,9 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT) ? 1 : 8 / MFMA_
     static_assert(KS * 16 <= D && DB * 32 <= D, "the products stay inside the copied rows");
     // With 512-byte key rows the operands of a whole phase would not fit the vector registers next to
     // Q, so that shape fetches and multiplies them in two halves (HV = 2); the others in one go.
-    constexpr int HV = (D == 256) ? 2 : 1;
+    constexpr int KG = SOFT == 1 ? 1 : 2;        // soft gate: k-steps of 16 groups
+    constexpr int GROW = grow_bytes(KG);
+    constexpr int HV = (D == 256 || (SOFT == 1 && D == 128 && KS == 8)) ? 2 : 1;
     constexpr int KSH = KS / HV;        // Q K^T MFMAs per half
     constexpr int DBH = DB / HV;        // O^T row blocks per half
     constexpr int NPVH = DBH * 2;       // P V MFMAs per half
@@ -292,14 +302,14 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT) ? 1 : 8 / MFMA_
     constexpr int NVI = (NVB + MFMA_WAVES - 1) / MFMA_WAVES;
     constexpr int ATHR = 64 * MFMA_WAVES;                // threads of the work-group
 
-    static_assert(!(SOFT && NOREF), "the soft gate keeps the running reference");
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    static_assert(!(SOFT && NOREF), "the soft gate keeps the running reference");
     const int n32 = lane & 31, hh = lane >> 5;
     int* nrflag = (int*)(ws_rw + L.off_nrflag) + blockIdx.x;
     if constexpr (NOREF) {
         if (tid == 0) *nrflag = 1;                 // unless the bound check below says otherwise
-    } else if constexpr (!SOFT) {
+    } else if constexpr (SOFT == 0) {
         if (*(volatile int*)nrflag != 0) return;   // the no-reference launch before this one did the tile
     }
 
@@ -318,7 +328,11 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT) ? 1 : 8 / MFMA_
     }
     const int bhq = b * L.Hq + h;
     const int bhk = b * L.Hkv + hm.kv[h];
-    if (!plan_query_tile(L, ws, bhq, bhk, job, S.plan)) return;
+    if constexpr (MASKED || SOFT != 0) {
+        if (!plan_linear_tile(L, job, S.plan)) return;
+    } else {
+        if (!plan_query_tile(L, ws, bhq, bhk, job, S.plan)) return;
+    }
 
     const int rloc = wave * 32 + n32;
     const bool rvalid = rloc < S.plan.nvalid;
@@ -396,12 +410,12 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT) ? 1 : 8 / MFMA_
     }
 
     // soft gate: this row's assignment times -lambda*log2(e), as bf16 high and low parts in B-operand order
-    bf16x8 gqh[2], gql[2];
-    const bool kg2 = L.K > 16;          // a second k-step of 16 groups
+    bf16x8 gqh[KG], gql[KG];
+    const bool kg2 = KG == 2 && L.K > 16;        // the second one is there at all
     if constexpr (SOFT) {
         const float* grow = g + ((size_t)b * L.n + (rvalid ? qpos : 0)) * L.K;
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks)
+        for (int ks = 0; ks < KG; ++ks)
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 const int c = ks * 16 + hh * 8 + e;
@@ -529,9 +543,9 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT) ? 1 : 8 / MFMA_
     // soft gate: high parts of the two k-steps, then the low parts, of the 32 keys of unit U
 #define F4_READ_G(KST, U)                                                                            \
     if constexpr (SOFT) {                                                                            \
-        _Pragma("unroll") for (int c = 0; c < 4; ++c) {                                              \
+        _Pragma("unroll") for (int c = 0; c < 2 * KG; ++c) {                                            \
             const int row_ = (U) * 32 + n32;                                                         \
-            ag[c] = lds_read16_async<bf16x8>(lds_g0 + (KST) * (KT * GROW) + row_ * GROW + ((((c >> 1) * 4 + (c & 1) * 2 + hh) ^ (row_ & 7)) * 16)); \
+            ag[c] = lds_read16_async<bf16x8>(lds_g0 + (KST) * (KT * GROW) + row_ * GROW + grow_swizzle(KG, (c / KG) * 2 * KG + (c % KG) * 2 + hh, row_) * 16);  \
         }                                                                                            \
     }
 #define F4_WAIT_OPERANDS()                                                                           \
@@ -544,11 +558,11 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT) ? 1 : 8 / MFMA_
         _Pragma("unroll") for (int r = 0; r < 16; ++r) GOUT[r] = 0.f;                                \
         GOUT = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ag[0], gqh[0], GOUT, 0, 0, 0);                \
         GOUT = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ag[0], gql[0], GOUT, 0, 0, 0);                \
-        GOUT = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ag[2], gqh[0], GOUT, 0, 0, 0);                \
-        if (kg2) {                                                                                   \
-            GOUT = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ag[1], gqh[1], GOUT, 0, 0, 0);            \
-            GOUT = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ag[1], gql[1], GOUT, 0, 0, 0);            \
-            GOUT = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ag[3], gqh[1], GOUT, 0, 0, 0);            \
+        GOUT = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ag[KG], gqh[0], GOUT, 0, 0, 0);                \
+        if constexpr (KG == 2) if (kg2) {                                                            \
+            GOUT = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ag[1], gqh[KG - 1], GOUT, 0, 0, 0);            \
+            GOUT = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ag[1], gql[KG - 1], GOUT, 0, 0, 0);            \
+            GOUT = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ag[2 * KG - 1], gqh[KG - 1], GOUT, 0, 0, 0);            \
         }                                                                                            \
     }
 
@@ -633,7 +647,7 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT) ? 1 : 8 / MFMA_
     ones2[0] = (elem_t)1.0f;
     ones2[1] = (elem_t)1.0f;
     V8 ak[KSH], av[NPVH];
-    bf16x8 ag[4];
+    bf16x8 ag[2 * KG];
     f32x16 g0acc, g1acc;
 #pragma unroll
     for (int r = 0; r < 16; ++r) { s0[r] = 0.f; s1[r] = 0.f; g0acc[r] = 0.f; g1acc[r] = 0.f; }
@@ -972,12 +986,12 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT) ? 1 : 8 / MFMA_
     }
 }
 
-template <int D, int KS, int DB, int WAVES, bool SOFTCAP, bool PAIRS, bool F16, int PM, bool SOFT = false>
+template <int D, int KS, int DB, int WAVES, bool SOFTCAP, bool PAIRS, bool F16, int PM, int SOFT = 0>
 hipError_t launch_one(const Layout& L, const HeadMap& hm, int default_map, const void* q, char* ws, void* out,
                       float* lse, int32_t* row_pairs, hipStream_t st, const float* g = nullptr)
 {
     const unsigned grid = (unsigned)((size_t)L.NT * L.B * L.Hq);
-    if constexpr (!SOFT)
+    if constexpr (SOFT == 0)
         hipLaunchKernelGGL((attn_mfma_kernel<D, KS, DB, WAVES, SOFTCAP, PAIRS, F16, PM, SOFT, true>), dim3(grid),
                            dim3(64 * WAVES), 0, st, L, hm, default_map, (const uint16_t*)q, g, ws, (uint16_t*)out, lse,
                            row_pairs);
@@ -1012,8 +1026,12 @@ hipError_t launch_d(const Layout& L, const HeadMap& hm, int default_map, const v
         // 512-byte key rows plus the gate's accumulators and operands do not fit the register file
         if constexpr (D == 256) return hipErrorInvalidValue;
         else
-        return f16 ? launch_one<D, KS, DB, 4, false, false, true, PM_EXACT, true>(L, hm, default_map, q, ws, out, lse, nullptr, st, g)
-                   : launch_one<D, KS, DB, 4, false, false, false, PM_EXACT, true>(L, hm, default_map, q, ws, out, lse, nullptr, st, g);
+        if (L.K <= 16)
+            return f16 ? launch_one<D, KS, DB, 4, false, false, true, PM_EXACT, 1>(L, hm, default_map, q, ws, out, lse, nullptr, st, g)
+                       : launch_one<D, KS, DB, 4, false, false, false, PM_EXACT, 1>(L, hm, default_map, q, ws, out, lse, nullptr, st, g);
+        else
+            return f16 ? launch_one<D, KS, DB, 4, false, false, true, PM_EXACT, 2>(L, hm, default_map, q, ws, out, lse, nullptr, st, g)
+                       : launch_one<D, KS, DB, 4, false, false, false, PM_EXACT, 2>(L, hm, default_map, q, ws, out, lse, nullptr, st, g);
     }
     // the query tile size fixed by focus_assign selects the work-group shape: 4 or 8 wavefronts
     if constexpr (D != 256) {
@@ -1037,12 +1055,13 @@ hipError_t launch_d(const Layout& L, const HeadMap& hm, int default_map, const v
 // the soft assignments of the key positions as the matrix cores read them (see Layout::off_gk)
 __global__ __launch_bounds__(256) void soft_gather_g_kernel(Layout L, const float* __restrict__ g, char* __restrict__ ws)
 {
-    const size_t total = (size_t)L.B * L.NKP * 8;         // 16-byte chunks: 4 of high parts, 4 of low parts per key
+    const int kg = L.K <= 16 ? 1 : 2, nch = 4 * kg;       // 16-byte chunks per key: half of them high parts, half low parts
+    const size_t total = (size_t)L.B * L.NKP * nch;
     for (size_t id = (size_t)blockIdx.x * blockDim.x + threadIdx.x; id < total; id += (size_t)gridDim.x * blockDim.x) {
-        const int c8 = (int)(id % 8);
-        const size_t slot = (id / 8) % L.NKP;             // one class in position order: slot = position, pads after n
-        const size_t b = id / 8 / L.NKP;
-        const int part = c8 / 4, e0 = (c8 % 4) * 8;
+        const int c8 = (int)(id % nch);
+        const size_t slot = (id / nch) % L.NKP;           // one class in position order: slot = position, pads after n
+        const size_t b = id / nch / L.NKP;
+        const int part = c8 / (2 * kg), e0 = (c8 % (2 * kg)) * 8;
         uint16_t h[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
@@ -1055,8 +1074,7 @@ __global__ __launch_bounds__(256) void soft_gather_g_kernel(Layout L, const floa
         uint4 u;
         u.x = h[0] | ((uint32_t)h[1] << 16); u.y = h[2] | ((uint32_t)h[3] << 16);
         u.z = h[4] | ((uint32_t)h[5] << 16); u.w = h[6] | ((uint32_t)h[7] << 16);
-        // chunks swizzled inside a key's 128 bytes so that 8 consecutive keys spread over the LDS banks
-        *(uint4*)(ws + L.off_gk + (b * L.NKP + slot) * GROW + (size_t)((c8 ^ (int)(slot & 7)) * 16)) = u;
+        *(uint4*)(ws + L.off_gk + (b * L.NKP + slot) * grow_bytes(kg) + (size_t)(grow_swizzle(kg, c8, (int)(slot & 63)) * 16)) = u;
     }
 }
 

@@ -104,8 +104,8 @@ struct Layout {
     size_t off_kbits;                  // [B,Hkv,NKP/KT][2 units of 32 keys][2 half-waves][K + 1] one bit per key (masked,
                                        // 16-bit types; pack_unit_bits): membership by group, then "its V row is not finite" 
     size_t off_jobs;                   // [B,Hq,NT] (class << 24 | tile) heaviest first, -1 unused
-    size_t off_gk;                     // [B,NKP,2,32] bf16: the soft assignment of every key position as bf16 high and
-                                       // low parts, groups padded to 32, chunks swizzled per key (soft gate, 16-bit types)
+    size_t off_gk;                     // [B,NKP,2,16 or 32] bf16: the soft assignment of every key position as bf16 high and
+                                       // low parts, groups padded to 16 or 32, chunks swizzled per key (soft gate, 16-bit types)
     size_t off_kn2;                    // [B,Hkv,KN2_SLOTS] bit patterns of partial maxima of the squared key norms of the
                                        // head (16-bit types; cleared by assign_init, raised by the scatter kernel's key
                                        // copy, the attention kernel takes the largest)

@@ -15,21 +15,24 @@
 
 namespace focus {
 
-struct TilePlan {
-    int t0[MAX_CLASSES];       // first key tile (global tile index inside the head)
-    int cum[MAX_CLASSES + 1];  // running number of tiles over the classes
-    uint8_t inter[MAX_CLASSES];
-    int ibeg[MAX_CLASSES];     // tiles [ibeg, iend) of the class need no per-element causal/window test
-    int iend[MAX_CLASSES];
-    int cnt_hi[MAX_CLASSES];   // keys of every class in the part of a sort block below the upper bound
-    int cnt_lo[MAX_CLASSES];   // ... and below the lower bound of the window span
+template <int MC>              // classes the plan has room for
+struct TilePlanT {
+    int t0[MC];                // first key tile (global tile index inside the head)
+    int cum[MC + 1];           // running number of tiles over the classes
+    uint8_t inter[MC];
+    int ibeg[MC];              // tiles [ibeg, iend) of the class need no per-element causal/window test
+    int iend[MC];
+    int cnt_hi[MC];            // keys of every class in the part of a sort block below the upper bound
+    int cnt_lo[MC];            // ... and below the lower bound of the window span
     int cls, tile, row0, nvalid, i_lo, i_hi, total;
 };
+typedef TilePlanT<MAX_CLASSES> TilePlan;
 
 // One class in position order (dense, local, soft-gated and masked layouts): a row's slot is its position, and the
 // whole plan follows from the tile's first and last position, without a single load (the walk through the class
 // tables below is a chain of four dependent loads and a histogram, several microseconds before the first product).
-__device__ inline bool plan_linear_tile(const Layout& L, int job, TilePlan& P)
+template <int MC>
+__device__ inline bool plan_linear_tile(const Layout& L, int job, TilePlanT<MC>& P)
 {
     const int nt = (L.n + L.BQ - 1) / L.BQ;
     if (job >= nt) return false;
