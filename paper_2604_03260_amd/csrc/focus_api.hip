@@ -450,7 +450,9 @@ focus_status attn_launch(const focus_params* p, int pair_set, const void* q, con
             L.merge_prev = 1;
             e = focus::launch_attn_mfma(L, hm, q, k, v, nullptr, (char*)workspace, out, lse1, row_pairs, (hipStream_t)stream);
         }
-    } else if (L.dtype != FOCUS_F32 && !force_vector)
+    } else if (L.dtype != FOCUS_F32 && !force_vector && focus::short_attention(L))
+        e = focus::launch_attn_short(L, hm, q, k, v, (char*)workspace, out, lse, row_pairs, (hipStream_t)stream);
+    else if (L.dtype != FOCUS_F32 && !force_vector)
         e = focus::launch_attn_mfma(L, hm, q, k, v, nullptr, (char*)workspace, out, lse, row_pairs, (hipStream_t)stream);
     // fp32: the matrix-core kernel, unless its work-groups (a quarter of a tile each) exceed one launch's grid
     else if (!force_vector && (size_t)L.NT * 4 * L.B * L.Hq <= 0x7fffffffull)

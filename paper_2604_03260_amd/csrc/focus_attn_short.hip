@@ -1,0 +1,329 @@
+// Attention forward for short 16-bit problems in position order (one class: masked and dense layouts), up to 128
+// components: the structure of the fp32 kernel (focus_attn_f32.hip) with 16-bit products.
+//
+// A work-group owns 32 query rows; its eight wavefronts walk the 32-key units of the causal prefix round-robin with a
+// running softmax each, operands straight from the caches, and merge once.  The tiled kernel (focus_attn_mfma.hip) needs
+// V staged by a launch before it and a second launch for rows that need a softmax reference, and walks up to n/64 tiles
+// one after the other in work-groups that are too few to fill the chip: at 512 tokens all of it is latency.
+// Here a chain is n/256 units and there is one launch.  V is read row-major with 2-byte loads, which is why the tiled
+// kernel wins as soon as throughput counts (see short_attention below).
+#include "focus_internal.h"
+#include "focus_tileplan.h"
+
+namespace focus {
+
+namespace {
+
+typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
+typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
+typedef __attribute__((__vector_size__(8 * sizeof(_Float16)))) _Float16 f16x8;
+typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
+template <bool F16> struct Half16;
+template <> struct Half16<false> {
+    typedef __bf16 T;
+    typedef bf16x8 V8;
+    static constexpr uint32_t EXP = 0x7f80u;
+    static __device__ inline f32x16 mfma(V8 a, V8 b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0); }
+};
+template <> struct Half16<true> {
+    typedef _Float16 T;
+    typedef f16x8 V8;
+    static constexpr uint32_t EXP = 0x7c00u;
+    static __device__ inline f32x16 mfma(V8 a, V8 b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0); }
+};
+template <typename T> __device__ inline uint32_t bits16(T x)
+{
+    uint16_t b;
+    __builtin_memcpy(&b, &x, 2);
+    return b;
+}
+constexpr float LOG2E = 1.4426950408889634f, LN2 = 0.6931471805599453f;
+
+// max of the two half-waves (lane l and lane l^32 hold the same query row)
+__device__ inline float both_halves_max(float x)
+{
+    const unsigned xi = __float_as_uint(x);
+    auto r = __builtin_amdgcn_permlane32_swap(xi, xi, false, false);
+    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+
+template <int D, bool F16>
+__global__ __launch_bounds__(512, 2) void attn_short_kernel(Layout L, HeadMap hm, int default_map, const uint16_t* __restrict__ q,
+                                                            const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
+                                                            const char* __restrict__ ws, uint16_t* __restrict__ out,
+                                                            float* __restrict__ lse, int32_t* __restrict__ row_pairs)
+{
+    typedef Half16<F16> HT;
+    typedef typename HT::T elem_t;
+    typedef typename HT::V8 V8;
+    constexpr int NW = 8;
+    constexpr int KS = D / 16;                    // products of one S^T unit
+    constexpr int DB = (D + 31) / 32;             // 32-component blocks of O^T
+    __shared__ TilePlanT<1> P;
+    __shared__ float s_o[NW / 2][DB * 16][64];         // partial results on their way between the wavefronts
+    __shared__ float s_m[NW / 2][64], s_l[NW / 2][64];
+    __shared__ int s_np[NW / 2][64];                   // pair count, bit 31: the row attends a non-finite value
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n32 = lane & 31, hh = lane >> 5;
+    const int BH = L.B * L.Hq;
+    const int quarter = 3 - (int)(blockIdx.x / BH) % 4, job = (int)(blockIdx.x / BH) / 4;
+    const int x = blockIdx.x % BH;
+    int b, h;
+    if (default_map) {                            // the query heads of a KV head share blockIdx % 8: one XCD, one L2
+        const int BHk = L.B * L.Hkv, G = L.Hq / L.Hkv;
+        b = (x % BHk) / L.Hkv;
+        h = (x % BHk % L.Hkv) * G + x / BHk;
+    } else {
+        b = x / L.Hq;
+        h = x % L.Hq;
+    }
+    const int bhq = b * L.Hq + h;
+    const int bhk = b * L.Hkv + hm.kv[h];
+    if (!plan_linear_tile(L, job, P)) return;
+    if (quarter * 32 >= P.nvalid) return;
+
+    const int rloc = quarter * 32 + n32;
+    const bool rvalid = rloc < P.nvalid;
+    const int qpos = rvalid ? P.row0 + rloc : -1;
+    const uint32_t mq_row = rvalid ? ((const uint32_t*)(ws + L.off_mq))[(size_t)bhq * L.n + qpos] : 0u;
+    const uint32_t* kmsk = (const uint32_t*)(ws + L.off_kmsk) + (size_t)bhk * L.NKP;     // masked only
+    const size_t koff = (size_t)b * L.ks[0] + (size_t)hm.kv[h] * L.ks[1];
+    // rows by a 24-bit multiply and a 32-bit offset (the launch checks that they fit)
+    const char* kbase = (const char*)(k + koff + hh * 8);
+    const char* vbase = (const char*)(v + koff + n32);
+    const unsigned pitch_bytes = (unsigned)L.ks[2] * 2u;
+    const int w = L.window;
+    const float scale = L.scale, cap = L.softcap;
+    const float sl2 = cap > 0.f ? LOG2E : scale * LOG2E;     // logits (scores without a cap) to log2 units
+
+    V8 qf[KS];
+    {
+        const uint16_t* qrow = q + (size_t)b * L.qs[0] + (size_t)h * L.qs[1] + (size_t)max(qpos, 0) * L.qs[2] + hh * 8;
+#pragma unroll
+        for (int c = 0; c < KS; ++c) qf[c] = *(const V8*)(qrow + 16 * c);
+    }
+    f32x16 o[DB];
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[db][r] = 0.f;
+    float m = -INFINITY, l = 0.f;
+    int npairs = 0;
+    bool spoiled = false;
+
+    for (int u = wave; u < 2 * P.total; u += NW) {
+        const int tile = P.t0[0] + (u >> 1), slot0 = tile * KT + (u & 1) * 32;
+        const bool interior = tile >= P.ibeg[0] && tile < P.iend[0];
+        // which pairs of the unit count, bit r = score r: key slot0 + 8*(r/4) + 4*hh + r%4
+        unsigned ok = 0xffffu;
+        if (!interior) {
+            ok = 0u;
+#pragma unroll
+            for (int r4 = 0; r4 < 4; ++r4) {
+                uint4 km4 = make_uint4(0u, 0u, 0u, 0u);
+                if (L.masked) km4 = *(const uint4*)(kmsk + slot0 + 8 * r4 + 4 * hh);
+                const uint32_t km[4] = {km4.x, km4.y, km4.z, km4.w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int kj = slot0 + 8 * r4 + 4 * hh + e, dlt = qpos - kj;
+                    const bool share = !L.masked || (mq_row & km[e]) != 0u;
+                    const bool loc = L.causal ? (dlt >= 0 && dlt < w) : (dlt < w && -dlt < w);
+                    const bool cz = L.causal ? dlt >= 0 : true;
+                    bool in = cz && (share || loc);
+                    if (L.masked && L.pair_set != 0) in = (L.pair_set == 1) ? (cz && share) : (loc && !share);
+                    ok |= (kj < L.n && in) ? 1u << (4 * r4 + e) : 0u;
+                }
+            }
+        }
+        if (!rvalid) ok = 0u;
+        if (!__any(ok != 0u)) continue;                                  // nothing here for any of the 32 rows
+        const bool all_ok = !__any(rvalid && ok != 0xffffu);
+
+        // keys, and the values with them: those arrive while the scores are computed
+        V8 kf[KS];
+        {
+            const char* kr = kbase + __umul24((unsigned)min(slot0 + n32, L.n - 1), pitch_bytes);
+#pragma unroll
+            for (int c = 0; c < KS; ++c) kf[c] = *(const V8*)(kr + 32 * c);
+        }
+        // values of this half-wave's 16 keys, component 32*db + l%32, two keys to a register
+        uint32_t vv[8][DB];
+#pragma unroll
+        for (int r2 = 0; r2 < 8; ++r2) {
+            const int k0 = slot0 + 8 * (r2 / 2) + 4 * hh + 2 * (r2 % 2);
+            const char* p0 = vbase + __umul24((unsigned)min(k0, L.n - 1), pitch_bytes);
+            const char* p1 = vbase + __umul24((unsigned)min(k0 + 1, L.n - 1), pitch_bytes);
+#pragma unroll
+            for (int db = 0; db < DB; ++db) {
+                const bool there = D % 32 == 0 || db * 32 + n32 < D;
+                const uint32_t lo = there ? *(const uint16_t*)(p0 + 64 * db) : 0u, hi = there ? *(const uint16_t*)(p1 + 64 * db) : 0u;
+                vv[r2][db] = lo | (hi << 16);
+            }
+        }
+        f32x16 s;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) s[r] = 0.f;
+#pragma unroll
+        for (int c = 0; c < KS; ++c) s = HT::mfma(kf[c], qf[c], s);
+        // softmax step in log2 units: p = 2^(s * sl2 - m), one rounding in the exponent (a row's m cancels)
+        if (cap > 0.f) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) s[r] = cap * tanhf(s[r] * scale / cap);
+        }
+        float mx = -INFINITY;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            s[r] = (ok >> r) & 1u ? s[r] : -INFINITY;
+            mx = fmaxf(mx, s[r]);
+        }
+        const float m_new = fmaxf(m, both_halves_max(mx) * sl2);
+        if (__any(m_new > m)) {
+            const float alpha = (m == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m - m_new);
+            m = m_new;
+            l *= alpha;
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
+        }
+        const float m_use = (m == -INFINITY) ? 0.f : m;
+        // probabilities rounded to the storage type; the row sum adds the rounded ones, the numbers the product uses
+        uint32_t pw[8];
+#pragma unroll
+        for (int r2 = 0; r2 < 8; ++r2) {
+            const elem_t p0 = (elem_t)__builtin_amdgcn_exp2f(fmaf(s[2 * r2], sl2, -m_use));       // masked: 2^-inf = 0
+            const elem_t p1 = (elem_t)__builtin_amdgcn_exp2f(fmaf(s[2 * r2 + 1], sl2, -m_use));
+            l += (float)p0 + (float)p1;
+            pw[r2] = bits16(p0) | (bits16(p1) << 16);
+        }
+        // A value that is not finite would reach the rows that do not attend it through 0 * inf: where the unit is not
+        // attended as a whole it is taken out, and the rows that do attend its key end as NaN.
+        if (!all_ok) {
+            bool any_bad = false;
+#pragma unroll
+            for (int r2 = 0; r2 < 8; ++r2)
+#pragma unroll
+                for (int db = 0; db < DB; ++db)
+                    any_bad = any_bad | ((vv[r2][db] & HT::EXP) == HT::EXP) | (((vv[r2][db] >> 16) & HT::EXP) == HT::EXP);
+            if (__any(any_bad)) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    bool bad = false;
+#pragma unroll
+                    for (int db = 0; db < DB; ++db) {
+                        const bool nf = ((vv[r / 2][db] >> (16 * (r % 2))) & HT::EXP) == HT::EXP;
+                        bad = bad || nf;
+                        vv[r / 2][db] = nf ? vv[r / 2][db] & (r % 2 ? 0xffffu : 0xffff0000u) : vv[r / 2][db];
+                    }
+                    const unsigned long long bal = __ballot(bad);
+                    if ((unsigned)(hh ? bal >> 32 : bal) != 0u && ((ok >> r) & 1u)) spoiled = true;
+                }
+            }
+        }
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {                                    // 16 keys each
+            const u32x4 pt = {pw[4 * t], pw[4 * t + 1], pw[4 * t + 2], pw[4 * t + 3]};
+            const V8 pb = __builtin_bit_cast(V8, pt);
+#pragma unroll
+            for (int db = 0; db < DB; ++db) {
+                const u32x4 vt = {vv[4 * t][db], vv[4 * t + 1][db], vv[4 * t + 2][db], vv[4 * t + 3][db]};
+                o[db] = HT::mfma(__builtin_bit_cast(V8, vt), pb, o[db]);
+            }
+        }
+        npairs += __popc(ok);
+    }
+    l += __shfl_xor(l, 32, 64);
+    npairs += __shfl_xor(npairs, 32, 64);
+    int tag = npairs | (spoiled ? (int)0x80000000u : 0);
+    tag |= __shfl_xor(tag, 32, 64) & (int)0x80000000u;
+
+    // App. D's merge of the wavefronts' partial softmaxes: the upper half into the lower half until one is left
+    auto put = [&](int buf) {
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) s_o[buf][db * 16 + r][lane] = o[db][r];
+        s_m[buf][lane] = m; s_l[buf][lane] = l; s_np[buf][lane] = tag;
+    };
+    auto take = [&](int buf) {
+        const float m2 = s_m[buf][lane], l2 = s_l[buf][lane];
+        const int t2 = s_np[buf][lane];
+        const float m_new = fmaxf(m, m2);
+        const float a1 = (m == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m - m_new), a2 = (m2 == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m2 - m_new);
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) o[db][r] = o[db][r] * a1 + s_o[buf][db * 16 + r][lane] * a2;
+        l = l * a1 + l2 * a2;
+        m = m_new;
+        tag = (((tag & 0x7fffffff) + (t2 & 0x7fffffff)) & 0x7fffffff) | ((tag | t2) & (int)0x80000000u);
+    };
+#pragma unroll
+    for (int half = NW / 2; half >= 1; half >>= 1) {
+        if (wave >= half && wave < 2 * half) put(wave - half);
+        __syncthreads();
+        if (wave < half) take(wave);
+        __syncthreads();
+    }
+    if (wave != 0) return;
+    if (!rvalid) return;
+    // an empty row (launch restricted to one pair set): out = 0, lse = -inf
+    const float inv = (tag < 0) ? __uint_as_float(0x7fc00000u) : (l > 0.f) ? 1.f / l : (l == 0.f) ? 0.f : l;
+    uint16_t* orow = out + (size_t)b * L.os[0] + (size_t)h * L.os[1] + (size_t)qpos * L.os[2];
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int r4 = 0; r4 < 4; ++r4) {
+            const int c = db * 32 + 8 * r4 + 4 * hh;
+            if (D % 32 != 0 && c >= D) continue;
+            uint2 val;
+            val.x = bits16((elem_t)(o[db][4 * r4] * inv)) | (bits16((elem_t)(o[db][4 * r4 + 1] * inv)) << 16);
+            val.y = bits16((elem_t)(o[db][4 * r4 + 2] * inv)) | (bits16((elem_t)(o[db][4 * r4 + 3] * inv)) << 16);
+            *(uint2*)(orow + c) = val;
+        }
+    if (hh == 0) {
+        if (lse) lse[(size_t)bhq * L.n + qpos] = fmaf(m, LN2, logf(l));
+        if (row_pairs) row_pairs[(size_t)bhq * L.n + qpos] = tag & 0x7fffffff;
+    }
+}
+
+}  // namespace
+
+// Where one launch of short chains beats the staged tiles: while (nearly) every work-group of 32 rows has a compute unit of
+// its own.  Attention alone, tiled / this kernel (us): 12 heads of 64 at 512 tokens (192 groups) 20.9 / 13.5, at 1024 (384)
+// 28.1 / 23.7, at 1536 (576) 35.7 / 42.9; 32/8 heads of 128 at 256 tokens (256) 21.3 / 17.3, at 512 (512) 26.4 / 35.3;
+// 40 heads of 96 at 256 tokens (320) 20.0 / 17.2; 15 heads of 80 at 768 (360) 27.1 / 26.5; 2 heads of 64 at 4096 (256) 71.5 / 62.6.
+bool short_attention(const Layout& L)
+{
+    const long long groups = (long long)L.B * L.Hq * ((L.n + 31) / 32);
+    const bool fits = L.dtype != 0 && L.NC == 1 && (L.masked || L.dense) && !L.soft && !L.local_only && !L.merge_prev && L.BQ == 128 &&
+                      L.d <= 128 && (uint64_t)L.ks[2] * 2 < (1u << 24) && (uint64_t)L.n * (uint64_t)L.ks[2] * 2 < 0xffffffffull;
+    return fits && L.n <= 4096 && groups <= (L.d <= 64 ? 384 : 320);
+}
+
+hipError_t launch_attn_short(const Layout& L, const HeadMap& hm, const void* q, const void* k, const void* v, char* ws,
+                             void* out, float* lse, int32_t* row_pairs, hipStream_t st)
+{
+    int default_map = (L.Hq % L.Hkv == 0) ? 1 : 0;
+    for (int h = 0; default_map && h < L.Hq; ++h) default_map = hm.kv[h] == h / (L.Hq / L.Hkv);
+    const unsigned blocks = (unsigned)((size_t)L.NT * 4 * L.B * L.Hq);        // four quarters of every 128-row tile
+#define FOCUS_SHORT(D_)                                                                                                   \
+    case D_:                                                                                                              \
+        if (L.dtype == 2)                                                                                                 \
+            hipLaunchKernelGGL((attn_short_kernel<D_, true>), dim3(blocks), dim3(512), 0, st, L, hm, default_map,         \
+                               (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, (const char*)ws, (uint16_t*)out, lse, row_pairs); \
+        else                                                                                                              \
+            hipLaunchKernelGGL((attn_short_kernel<D_, false>), dim3(blocks), dim3(512), 0, st, L, hm, default_map,        \
+                               (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, (const char*)ws, (uint16_t*)out, lse, row_pairs); \
+        break;
+    switch (L.d) {
+        FOCUS_SHORT(64) FOCUS_SHORT(80) FOCUS_SHORT(96) FOCUS_SHORT(128)
+        default: return hipErrorInvalidValue;
+    }
+#undef FOCUS_SHORT
+    return hipGetLastError();
+}
+
+}  // namespace focus

@@ -12,11 +12,11 @@ from tests import test_gpu_instantiations as inst
 pytestmark = pytest.mark.gpu
 
 
-def _check(wl, inp=None):
+def _check(wl, inp=None, tol=None):
     inp = inp if inp is not None else workloads.make_inputs(wl, "cuda")
     res = harness.run_gpu(wl, inp)
     mq, mk = harness.check_assign(wl, inp, res)
-    harness.check_attn(wl, inp, res, mq, mk)
+    harness.check_attn(wl, inp, res, mq, mk, tol=tol)
     harness.check_pair_totals(wl, res, mq, mk)
     return res
 
@@ -34,10 +34,42 @@ def test_masked_tile_edges(n, w, K, topk, causal, dtype, d, softcap):
     _check(workloads.Workload("m", 300 + n, 1, 4, 2, n, d, dtype, K, topk, w, causal=causal, softcap=softcap, mixture=3))
 
 
-def test_masked_rows_with_large_norms_take_the_running_reference():
+# the same edges with enough heads that the tiles run instead of the kernel for a few work-groups of 32 rows
+@pytest.mark.parametrize("n", [2, 33, 65, 129, 257])
+@pytest.mark.parametrize("w,K,topk,causal,dtype,d,softcap", [
+    (1, 4, 1, True, "bf16", 64, 0.0), (29, 8, 2, True, "bf16", 128, 0.0), (70, 8, 4, False, "f16", 80, 0.0),
+    (1, 16, 2, False, "bf16", 64, 0.0), (250, 32, 5, True, "bf16", 96, 30.0)])
+def test_masked_tile_edges_many_heads(n, w, K, topk, causal, dtype, d, softcap):
+    if w >= n:
+        w = max(1, n - 1)
+    wl = workloads.Workload("m", 310 + n, 8, 64, 8, n, d, dtype, K, topk, w, causal=causal, softcap=softcap, mixture=3)
+    inp = workloads.make_inputs(wl, "cuda")
+    # Rows of one or two keys among 512 heads meet the rounding of the scaled query rows in full: one half ulp (2^-9,
+    # 2^-12) per component moves a logit by at most that times scale * |q| * |k|, the probability by one half ulp more;
+    # an output then moves by at most max|v| times that, plus its own rounding.
+    half_ulp = {"bf16": 2.0 ** -9, "f16": 2.0 ** -12}[dtype]
+    norm = lambda t: t.float().norm(dim=-1).max().item()
+    delta = half_ulp * (1.0 + norm(inp["q"]) * norm(inp["k"]) / d ** 0.5)
+    vmax = inp["v"].float().abs().max().item()
+    tol = dict(lse=max(harness.TOL[dtype]["lse"], delta), out_max=max(harness.TOL[dtype]["out_max"], vmax * (delta + half_ulp)))
+    _check(wl, inp, tol)
+
+
+CASES_M = [c for c in inst.CASES4 if not c[4]]
+
+
+@pytest.mark.parametrize("d,softcap,pairs,dtype,coarse,noref", CASES_M)
+def test_masked_instantiations_all_rows(d, softcap, pairs, dtype, coarse, noref):
+    """Every compiled form of the tiled kernel on the masked layout (24 heads: more than the short kernel takes)."""
+    wl = workloads.Workload("instm", 94, 3, 8, 2, 520 + d // 4, d, dtype, 8, 3, 48, softcap=50.0 if softcap else 0.0, mixture=4)
+    inst.run_case(wl, pairs, big_norms=not noref)
+
+
+@pytest.mark.parametrize("B", [1, 20])
+def test_masked_rows_with_large_norms_take_the_running_reference(B):
     """Key norms past the bound of the form without a reference: disallowed keys with the largest logits must not
     move the row's reference (their probabilities would drown the allowed ones)."""
-    wl = workloads.Workload("m", 331, 1, 2, 1, 400, 64, "bf16", 4, 1, 16)
+    wl = workloads.Workload("m", 331, B, 2, 1, 400, 64, "bf16", 4, 1, 16)
     inp = workloads.make_inputs(wl, "cuda")
     inp["q"] *= 8.0
     inp["k"] *= 8.0
@@ -45,7 +77,7 @@ def test_masked_rows_with_large_norms_take_the_running_reference():
     ws = focus.alloc_workspace(p)
     outs = []
     for vector in (False, True):
-        out, lse = torch.empty_like(inp["q"]), torch.empty((1, 2, 400), dtype=torch.float32, device="cuda")
+        out, lse = torch.empty_like(inp["q"]), torch.empty((B, 2, 400), dtype=torch.float32, device="cuda")
         focus.focus_assign(p, inp["q"], inp["k"], inp["centroids"], ws)
         focus.focus_attn_fwd(p, inp["q"], inp["k"], inp["v"], ws, out, lse, vector=vector)
         outs.append((out.float(), lse))
@@ -72,11 +104,11 @@ def test_class_tiles_against_the_masked_layout(n, K, topk, w, monkeypatch):
     assert torch.equal(masked["row_pairs"], classes["row_pairs"])
 
 
-@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("f16", 80), ("f32", 64), ("f32", 256)])
-def test_spoiled_values_reach_only_the_rows_that_attend_them(dtype, d):
+@pytest.mark.parametrize("dtype,d,B", [("bf16", 128, 1), ("bf16", 128, 6), ("f16", 80, 1), ("f16", 80, 6), ("bf16", 64, 1), ("f32", 64, 1), ("f32", 256, 1)])
+def test_spoiled_values_reach_only_the_rows_that_attend_them(dtype, d, B):
     """V rows with NaN or infinities: the masked tiles visit every key of the causal prefix, with probability zero
     where the pair is not allowed, and 0 * inf must not spoil those rows."""
-    wl = workloads.Workload("m", 350, 1, 4, 2, 700, d, dtype, 8, 1, 40, mixture=3)
+    wl = workloads.Workload("m", 350, B, 4, 2, 700, d, dtype, 8, 1, 40, mixture=3)
     inp = workloads.make_inputs(wl, "cuda")
     bad_keys = (3, 100, 333, 500)
     for j, x in zip(bad_keys, (float("nan"), float("inf"), -float("inf"), float("inf"))):
