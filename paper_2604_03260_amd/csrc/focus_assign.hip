@@ -668,9 +668,9 @@ __global__ __launch_bounds__(SB) void scatter_kernel(Layout L, int which, const 
 
 // ---------------------------------------------------------------- membership given per token
 // The paper's router assigns one membership per token of a layer, shared by all heads and by the
-// query and key roles (Sec. 2).  One work-group per (sort block, batch element) turns the token
-// masks into class ids and histograms once and writes them for every query and KV head, in the
-// same places score_topk fills.  A mask that is not a topk-subset of the K groups would index
+// query and key roles (Sec. 2).  A work-group turns the token masks of a sort block of a batch element into
+// class ids and histograms and writes them for its share of the query and KV heads (heads z, z + gridDim.z, ..),
+// in the same places score_topk fills.  A mask that is not a topk-subset of the K groups would index
 // outside the class tables: it is replaced by the first topk groups and counted.
 __global__ __launch_bounds__(SB) void token_classes_kernel(Layout L, const uint32_t* __restrict__ token_masks,
                                                            char* __restrict__ ws, int32_t* __restrict__ invalid_count)
@@ -692,7 +692,7 @@ __global__ __launch_bounds__(SB) void token_classes_kernel(Layout L, const uint3
         const uint32_t allowed = (K == 32) ? 0xffffffffu : ((1u << K) - 1u);
         if ((mask & ~allowed) != 0u || __popc(mask) != L.topk) {
             mask = (L.topk == 32) ? 0xffffffffu : ((1u << L.topk) - 1u);
-            if (invalid_count) atomicAdd(invalid_count, 1);
+            if (invalid_count && blockIdx.z == 0) atomicAdd(invalid_count, 1);
         }
         if (L.coarse) {
             cls = class_of_mask(mask, 0, 1, L.S);
@@ -711,7 +711,7 @@ __global__ __launch_bounds__(SB) void token_classes_kernel(Layout L, const uint3
         uint32_t* masks = (uint32_t*)(ws + (is_query ? L.off_mq : L.off_mk));
         uint8_t* clsarr = (uint8_t*)(ws + (is_query ? L.off_qcls : L.off_kcls));
         const size_t cls_stride = is_query ? (size_t)n : (size_t)L.nblk * SB;
-        for (int h = 0; h < H; ++h) {
+        for (int h = blockIdx.z; h < H; h += gridDim.z) {
             const size_t bh = (size_t)b * H + h;
             if (pos < n) {
                 masks[bh * n + pos] = mask;
@@ -837,7 +837,10 @@ hipError_t launch_assign_tokens(const Layout& L, const uint32_t* token_masks, co
 {
     launch_assign_init(L, nullptr, ws, st);
     if (invalid_count) hipLaunchKernelGGL(fill_i32_kernel, dim3(1), dim3(64), 0, st, invalid_count, (size_t)1, 0);
-    hipLaunchKernelGGL(token_classes_kernel, dim3(L.nblk, L.B), dim3(SB), 0, st, L, token_masks, ws, invalid_count);
+    // the heads of a sort block are split until there are a few work-groups per compute unit (128 blocks x 40 heads: one
+    // work-group for all heads wrote for 11 us, eight for 5)
+    const int zsplit = (int)std::max<long long>(1, std::min<long long>(std::max(L.Hq, L.Hkv), 1024 / ((long long)L.nblk * L.B)));
+    hipLaunchKernelGGL(token_classes_kernel, dim3(L.nblk, L.B, zsplit), dim3(SB), 0, st, L, token_masks, ws, invalid_count);
     if (!own_scan(L)) hipLaunchKernelGGL(scan_plan_kernel, dim3(L.B * (L.Hq + L.Hkv)), dim3(SCAN_THREADS), 0, st, L, ws);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
