@@ -68,20 +68,59 @@ __device__ inline double wave_sum(double x)
     return x;
 }
 
-// top-k of the first K of KP register values by rank counting; ties go to the smaller index
+// Sums of KP columns over a wavefront at once: every step halves the columns a lane carries until one is left (of lane
+// bits 5, 4, ..), 7 exchanges for 4 columns instead of 24.  Returns the sum of column wave_column<KP>(lane).
+template <int KP>
+__device__ inline int wave_column(int lane)
+{
+    int c = 0;
+    for (int w = KP / 2, off = 32; w >= 1; w >>= 1, off >>= 1) c += (lane & off) ? w : 0;
+    return c;
+}
+template <int KP>
+__device__ inline double wave_sum_columns(const double (&x)[KP], int lane)
+{
+    static_assert(KP >= 2 && KP <= 32 && (KP & (KP - 1)) == 0, "a power of two");
+    double y[KP];
+#pragma unroll
+    for (int g = 0; g < KP; ++g) y[g] = x[g];
+    int off = 32;
+#pragma unroll
+    for (int w = KP / 2; w >= 1; w >>= 1, off >>= 1) {
+        const bool up = (lane & off) != 0;
+#pragma unroll
+        for (int g = 0; g < w; ++g) {
+            const double send = up ? y[g] : y[g + w];
+            y[g] = __dadd_rn(up ? y[g + w] : y[g], __shfl_xor(send, off, 64));
+        }
+    }
+#pragma unroll
+    for (; off >= 1; off >>= 1) y[0] = __dadd_rn(y[0], __shfl_xor(y[0], off, 64));
+    return y[0];
+}
+
+// top-k of the first K of KP register values: the best value topk times, ties to the smaller index (strictly greater
+// replaces).  A NaN among the scores gives the first topk groups.  (Comparing all pairs, unrolled, spilled 1700 registers
+// at 32 groups.)
 template <int KP>
 __device__ inline uint32_t topk_mask(const double (&s)[KP], int K, int topk)
 {
+    bool nan = false;
+#pragma unroll
+    for (int g = 0; g < KP; ++g) nan = nan || (g < K && s[g] != s[g]);
     uint32_t m = 0;
+    for (int t = 0; t < topk; ++t) {
+        double best = 0.0;
+        uint32_t bit = 0;
 #pragma unroll
-    for (int g = 0; g < KP; ++g) {
-        int beaten = 0;
-#pragma unroll
-        for (int o = 0; o < KP; ++o)
-            if (o != g) beaten += (o < K && (s[o] > s[g] || (s[o] == s[g] && o < g))) ? 1 : 0;
-        if (g < K && beaten < topk) m |= (1u << g);
+        for (int g = 0; g < KP; ++g) {
+            const bool take = g < K && !((m >> g) & 1u) && (bit == 0u || s[g] > best);
+            best = take ? s[g] : best;
+            bit = take ? 1u << g : bit;
+        }
+        m |= bit;
     }
-    if (__popc(m) != topk) m = (topk == 32) ? 0xffffffffu : ((1u << topk) - 1u);   // a NaN among the scores
+    if (nan) m = (topk == 32) ? 0xffffffffu : ((1u << topk) - 1u);
     return m;
 }
 
@@ -355,10 +394,9 @@ __global__ __launch_bounds__(256) void sinkhorn_pass_kernel(RouteLayout R, int p
         }
     }
     if (last && pass > 0) return;
-#pragma unroll
-    for (int g = 0; g < KP; ++g) {
-        const double s = wave_sum(cs[g]);
-        if (lane == 0) s_part[wave][g] = s;
+    {
+        const double s = wave_sum_columns<KP>(cs, lane);
+        if ((lane & (64 / KP - 1)) == 0) s_part[wave][wave_column<KP>(lane)] = s;
     }
     __syncthreads();
     if (tid < K) mine[tid] = __dadd_rn(__dadd_rn(s_part[0][tid], s_part[1][tid]), __dadd_rn(s_part[2][tid], s_part[3][tid]));
