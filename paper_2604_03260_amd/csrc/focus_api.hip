@@ -71,6 +71,9 @@ bool prefer_masked(const focus::Layout& L, double none, bool two_pass)
         visits += std::ceil(n / BQ) * ((w + BQ) / KT + fixed);
     else
         visits += tiles * NC * none * (std::min(per, (w + std::min(n, NC * BQ)) / NC) * 2.0 * half / KT + lost);
+    // coarse classes test every pair of every tile: 1.3 to 1.6 of the estimate (8 heads of 128, K=32 top-2: class 21.3 /
+    // masked 7.4 ms at 65536 tokens, 49.9 / 29.4 ms at 131072, where the bare estimate has the two equal)
+    if (L.coarse) visits *= 1.4;
     return visits > std::ceil(n / BQ) * (n * half / KT + 1.0 + fixed) * masked_visit;
 }
 

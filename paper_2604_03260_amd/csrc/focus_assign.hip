@@ -21,7 +21,8 @@
 //                (key rows, 16-bit types) the class-ordered copy of the key rows
 //                with the largest squared key norm of the head.
 // Memberships given per token (focus_assign_tokens) take token_classes in place
-// of score_topk.
+// of score_topk.  Layouts without classes (masked) leave the scan out where the scatter launch can add up
+// the histograms itself, and take score_linear in place of assign_init and score_topk where that is faster.
 #include "focus_internal.h"
 #include "focus_score.h"
 #include <hip/hip_bf16.h>

@@ -1,5 +1,5 @@
-// fp32 vector attention kernel (no matrix cores): the path for fp32 inputs and an
-// independent on-device cross-check of the MFMA kernel for bf16 inputs.
+// fp32 vector attention kernel (no matrix cores): the independent on-device cross-check of the matrix-core kernels
+// in every type, and the path of the fp32 (and 256-component) soft gate.
 //
 // One work-group owns one query tile (<= L.BQ queries of one membership class) and
 // handles it in passes of BQ_VECTOR rows.
