@@ -182,7 +182,7 @@ def measure(torch, focus, workloads, wl, steps, warmup, dense_steps, keep=False,
     sclk = clock.summary(*r.t_timed) if clock else None
     half = wl.dtype in ("bf16", "f16")          # both 16-bit types run on the matrix cores at the same peak
     peak = BF16_MFMA_PEAK_TFLOPS if half else FP32_VECTOR_PEAK_TFLOPS
-    kernel = "attn_mfma_kernel" if half else "attn_simple_kernel"
+    kernel = "attn_mfma_kernel" if half else "attn_f32_kernel"
     tflops_attn = useful_flop / (ms_attn * 1e-3) / 1e12
     gbs_assign = assign_bytes(wl) / (ms_assign * 1e-3) / 1e9
     res = {
