@@ -107,14 +107,12 @@ constexpr float CAP_CUBIC_Z = 0.15f;        // ... and to z^3 (the z^5 term is t
 __host__ __device__ constexpr int slot_to_key16(int p16) { return 8 * ((p16 % 8) / 4) + 4 * (p16 / 8) + (p16 % 8) % 4; }
 
 // ---------------------------------------------------------------- gathers into class order
-// any of the eight 16-bit values infinite or NaN
-__device__ inline bool nonfinite8(const uint4& u, bool f16)
+// zeros in the place of infinities and NaN among two 16-bit values
+__device__ inline uint32_t finite_pair(uint32_t w, uint32_t exp_mask)
 {
-    const uint32_t w[4] = {u.x, u.y, u.z, u.w}, m = f16 ? 0x7c00u : 0x7f80u;
-    bool bad = false;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) bad = bad || (w[e] & m) == m || ((w[e] >> 16) & m) == m;
-    return bad;
+    const uint32_t lo = (w & exp_mask) == exp_mask ? 0u : w & 0xffffu;
+    const uint32_t hi = ((w >> 16) & exp_mask) == exp_mask ? 0u : w & 0xffff0000u;
+    return lo | hi;
 }
 
 template <int D>
@@ -137,8 +135,14 @@ __global__ __launch_bounds__(NTHR) void gather_vt_kernel(Layout L, const uint16_
         uint4 val = make_uint4(0, 0, 0, 0);
         if (kp != KPOS_PAD && ch < cin) val = src[(size_t)kp * pitch + ch];
         // Masked layout: every key of the causal prefix is visited, with a zero probability where it is not allowed,
-        // and 0 * inf would spoil rows that do not attend it.  Such V rows go in as zeros and are marked.
-        if (L.masked && nonfinite8(val, L.dtype == 2)) atomicOr(&s_bad[row >> 5], 1u << (row & 31));
+        // and 0 * inf would spoil rows that do not attend it.  Such components go in as zeros and the key is marked:
+        // the attention kernel adds them to the rows that do attend it (add_nonfinite_values).
+        if (L.masked) {
+            const uint32_t em = L.dtype == 2 ? 0x7c00u : 0x7f80u;
+            const uint4 fin = make_uint4(finite_pair(val.x, em), finite_pair(val.y, em), finite_pair(val.z, em), finite_pair(val.w, em));
+            if (fin.x != val.x || fin.y != val.y || fin.z != val.z || fin.w != val.w) atomicOr(&s_bad[row >> 5], 1u << (row & 31));
+            val = fin;
+        }
         uint32_t* d32 = (uint32_t*)(s_v + row * RS + ch * 8);   // RS even -> 4-byte aligned
         d32[0] = val.x; d32[1] = val.y; d32[2] = val.z; d32[3] = val.w;
     }
@@ -151,7 +155,7 @@ __global__ __launch_bounds__(NTHR) void gather_vt_kernel(Layout L, const uint16_
         for (int j = 0; j < 8; ++j) {
             const int p = c * 8 + j;
             const int key = (p / 16) * 16 + slot_to_key16(p % 16);
-            e[j] = ((s_bad[key >> 5] >> (key & 31)) & 1u) ? (uint16_t)0 : s_v[key * RS + drow];
+            e[j] = s_v[key * RS + drow];
         }
         uint4 val;
         val.x = e[0] | ((uint32_t)e[1] << 16); val.y = e[2] | ((uint32_t)e[3] << 16);
@@ -185,6 +189,60 @@ template <int D> struct TileGeom {
     static constexpr int V_LDS = D * VROW;              // bytes of a V^T stage, a multiple of 1024
     static_assert(K_LDS % 1024 == 0 && V_LDS % 1024 == 0, "stages are filled in 1-KB wave loads");
 };
+
+// Masked layout: the values that were staged as zeros because they are not finite, added to the rows that attend their
+// keys (o is not yet divided by the row sum; a positive factor keeps an infinity).  Runs once per tile and only where a
+// row of the wavefront attends such a key: walks the marks of the keys that the tile visited (kb: the bits of the head's
+// key tiles) and reads the marked rows of v, the values of the head.
+template <int DB, bool F16>
+__device__ inline void add_nonfinite_values(const Layout& L, const unsigned* kb, int tile0, int tiles, int qpos, unsigned mq_row,
+                                            const unsigned* mk, const uint16_t* v, int hh, f32x16 (&o)[DB])
+{
+    typedef typename Half<F16>::T elem_t;
+    constexpr uint32_t EXP = F16 ? 0x7c00u : 0x7f80u;
+    const int kb_row = L.K + 1;
+    const int lane = threadIdx.x & 63, end = 4 * (tile0 + tiles);    // per key tile: two units of 32 keys, two half-waves
+#pragma unroll 1
+    for (int w0 = 4 * tile0; w0 < end; w0 += 64) {
+        const unsigned mine = w0 + lane < end ? kb[(size_t)(w0 + lane) * kb_row + L.K] : 0u;
+        unsigned long long some = __ballot(mine != 0u);
+        unsigned marks = 0u;
+        int w = w0;
+#pragma unroll 1
+        while (some != 0ull || marks != 0u) {
+            if (marks == 0u) {
+                const int src = __builtin_ctzll(some);
+                some &= some - 1ull;
+                marks = (unsigned)__builtin_amdgcn_readlane((int)mine, src);
+                w = w0 + src;
+            }
+            const int bit = __builtin_ctz(marks);
+            marks &= marks - 1u;
+            const int r = 2 * (bit & 15) + (bit >> 4);               // inverse of pack_unit_bits
+            const int kj = (w >> 2) * KT + ((w >> 1) & 1) * 32 + 8 * (r / 4) + 4 * (w & 1) + r % 4;
+            const int dlt = qpos - kj;
+            const bool share = (mq_row & mk[kj]) != 0u;
+            const bool loc = L.causal ? (dlt >= 0 && dlt < L.window) : (dlt < L.window && -dlt < L.window);
+            const bool cz = L.causal ? dlt >= 0 : true;
+            const bool in = L.pair_set == 0 ? cz && (share || loc) : L.pair_set == 1 ? cz && share : loc && !share;
+            const uint16_t* row = v + (size_t)kj * L.ks[2];
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int r4 = 0; r4 < 4; ++r4) {
+                    const int c = db * 32 + 8 * r4 + 4 * hh;
+                    if (c >= L.d) continue;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const uint16_t bits = row[c + e];
+                        elem_t x;
+                        __builtin_memcpy(&x, &bits, 2);
+                        if (in && qpos >= 0 && (bits & EXP) == EXP) o[db][4 * r4 + e] += (float)x;
+                    }
+                }
+        }
+    }
+}
 
 template <int D, int PM, int SOFT>
 struct Smem {
@@ -271,10 +329,11 @@ __device__ inline void pin_operands(V8 (&a)[N])
 // NOREF: the softmax without a reference (head of this file).  Every launch runs the kernel twice: the NOREF
 // instantiation first, whose work-groups check their bound, leave a flag (1 = done here, 0 = not mine) and do
 // the tile or return; then the other instantiation, whose work-groups return at once where the flag says done.
+// (v: the values as the caller holds them; the masked form alone reads them, and only where some are not finite.)
 template <int D, int KS, int DB, int MFMA_WAVES, bool SOFTCAP, bool PAIRS, bool F16, int PM, int SOFT, bool NOREF>
 __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT == 2) ? 1 : 8 / MFMA_WAVES) void attn_mfma_kernel(
-    Layout L, HeadMap hm, int default_map, const uint16_t* __restrict__ q, const float* __restrict__ g,
-    char* ws_rw, uint16_t* __restrict__ out, float* __restrict__ lse,
+    Layout L, HeadMap hm, int default_map, const uint16_t* __restrict__ q, const uint16_t* __restrict__ v,
+    const float* __restrict__ g, char* ws_rw, uint16_t* __restrict__ out, float* __restrict__ lse,
     int32_t* __restrict__ row_pairs)
 {
     const char* ws = ws_rw;              // everything but the flag of this work-group is only read
@@ -476,7 +535,7 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT == 2) ? 1 : 8 / 
     const unsigned lds_g0 = lds_addr_of(&S.gk[0]);
     // masked: where this lane's half-wave finds the words of its row's first two groups; the groups after those
     const int kb_row = L.K + 1, kb_words = 4 * kb_row;   // words per half-wave of a unit, per key tile
-    unsigned vbad = 0u;                                  // the row attends a key whose V row is not finite
+    unsigned vbad = 0u;                                  // the row attends a key with values that are not finite
     const char* kb_base = ws + L.off_kbits + (size_t)bhk * (L.NKP / KT) * (kb_words * 4);
     unsigned mq_rest = 0u;
     int kb_g0 = 0, kb_g1 = 0;
@@ -932,11 +991,15 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT == 2) ? 1 : 8 / 
     // ---- epilogue
     const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
     if constexpr (PAIRS) npairs += __shfl_xor(npairs, 32, 64);
-    if constexpr (MASKED) vbad |= (unsigned)__shfl_xor((int)vbad, 32, 64);
+    if constexpr (MASKED) {
+        vbad |= (unsigned)__shfl_xor((int)vbad, 32, 64);
+        if (__any(vbad != 0u))
+            add_nonfinite_values<DB, F16>(L, (const unsigned*)kb_base, __builtin_amdgcn_readfirstlane(S.plan.t0[0]), total, qpos, mq_row,
+                                          (const unsigned*)(ws + L.off_mk) + (size_t)bhk * L.n,
+                                          v + (size_t)b * L.ks[0] + (size_t)hm.kv[h] * L.ks[1], hh, o);
+    }
     if (!rvalid) return;
     float inv = (l_tot > 0.f) ? 1.f / l_tot : 0.f;            // an empty row (restricted pair set): out = 0, lse = -inf
-    // (masked: V rows that are not finite were staged as zeros, so that rows which do not attend them stay right)
-    if (MASKED && vbad != 0u) inv = __uint_as_float(0x7fc00000u);
     uint16_t* orow = out + (size_t)b * L.os[0] + (size_t)h * L.os[1] + (size_t)qpos * L.os[2];
     // Second pass of a two-pass launch: this row's result over the pairs inside the window is in out / lse
     // (16-bit, natural log).  out = (e^{l1} o1 + e^{l2} o2) / (e^{l1} + e^{l2}), App. D's merge, in log2 units.
@@ -987,31 +1050,31 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT == 2) ? 1 : 8 / 
 }
 
 template <int D, int KS, int DB, int WAVES, bool SOFTCAP, bool PAIRS, bool F16, int PM, int SOFT = 0>
-hipError_t launch_one(const Layout& L, const HeadMap& hm, int default_map, const void* q, char* ws, void* out,
+hipError_t launch_one(const Layout& L, const HeadMap& hm, int default_map, const void* q, const void* v, char* ws, void* out,
                       float* lse, int32_t* row_pairs, hipStream_t st, const float* g = nullptr)
 {
     const unsigned grid = (unsigned)((size_t)L.NT * L.B * L.Hq);
     if constexpr (SOFT == 0)
         hipLaunchKernelGGL((attn_mfma_kernel<D, KS, DB, WAVES, SOFTCAP, PAIRS, F16, PM, SOFT, true>), dim3(grid),
-                           dim3(64 * WAVES), 0, st, L, hm, default_map, (const uint16_t*)q, g, ws, (uint16_t*)out, lse,
+                           dim3(64 * WAVES), 0, st, L, hm, default_map, (const uint16_t*)q, (const uint16_t*)v, g, ws, (uint16_t*)out, lse,
                            row_pairs);
     hipLaunchKernelGGL((attn_mfma_kernel<D, KS, DB, WAVES, SOFTCAP, PAIRS, F16, PM, SOFT, false>), dim3(grid),
-                       dim3(64 * WAVES), 0, st, L, hm, default_map, (const uint16_t*)q, g, ws, (uint16_t*)out, lse,
+                       dim3(64 * WAVES), 0, st, L, hm, default_map, (const uint16_t*)q, (const uint16_t*)v, g, ws, (uint16_t*)out, lse,
                        row_pairs);
     return hipGetLastError();
 }
 
 template <int D, int KS, int DB, int WAVES, bool F16, int PM>
-hipError_t launch_w(const Layout& L, const HeadMap& hm, int default_map, const void* q, char* ws, void* out,
+hipError_t launch_w(const Layout& L, const HeadMap& hm, int default_map, const void* q, const void* v, char* ws, void* out,
                     float* lse, int32_t* row_pairs, hipStream_t st)
 {
     const bool sc = L.softcap > 0.f, pairs = row_pairs != nullptr;
     if (sc) {
-        return pairs ? launch_one<D, KS, DB, WAVES, true, true, F16, PM>(L, hm, default_map, q, ws, out, lse, row_pairs, st)
-                     : launch_one<D, KS, DB, WAVES, true, false, F16, PM>(L, hm, default_map, q, ws, out, lse, row_pairs, st);
+        return pairs ? launch_one<D, KS, DB, WAVES, true, true, F16, PM>(L, hm, default_map, q, v, ws, out, lse, row_pairs, st)
+                     : launch_one<D, KS, DB, WAVES, true, false, F16, PM>(L, hm, default_map, q, v, ws, out, lse, row_pairs, st);
     }
-    return pairs ? launch_one<D, KS, DB, WAVES, false, true, F16, PM>(L, hm, default_map, q, ws, out, lse, row_pairs, st)
-                 : launch_one<D, KS, DB, WAVES, false, false, F16, PM>(L, hm, default_map, q, ws, out, lse, row_pairs, st);
+    return pairs ? launch_one<D, KS, DB, WAVES, false, true, F16, PM>(L, hm, default_map, q, v, ws, out, lse, row_pairs, st)
+                 : launch_one<D, KS, DB, WAVES, false, false, F16, PM>(L, hm, default_map, q, v, ws, out, lse, row_pairs, st);
 }
 
 template <int D, int KS, int DB>
@@ -1027,27 +1090,27 @@ hipError_t launch_d(const Layout& L, const HeadMap& hm, int default_map, const v
         if constexpr (D == 256) return hipErrorInvalidValue;
         else
         if (L.K <= 16)
-            return f16 ? launch_one<D, KS, DB, 4, false, false, true, PM_EXACT, 1>(L, hm, default_map, q, ws, out, lse, nullptr, st, g)
-                       : launch_one<D, KS, DB, 4, false, false, false, PM_EXACT, 1>(L, hm, default_map, q, ws, out, lse, nullptr, st, g);
+            return f16 ? launch_one<D, KS, DB, 4, false, false, true, PM_EXACT, 1>(L, hm, default_map, q, v, ws, out, lse, nullptr, st, g)
+                       : launch_one<D, KS, DB, 4, false, false, false, PM_EXACT, 1>(L, hm, default_map, q, v, ws, out, lse, nullptr, st, g);
         else
-            return f16 ? launch_one<D, KS, DB, 4, false, false, true, PM_EXACT, 2>(L, hm, default_map, q, ws, out, lse, nullptr, st, g)
-                       : launch_one<D, KS, DB, 4, false, false, false, PM_EXACT, 2>(L, hm, default_map, q, ws, out, lse, nullptr, st, g);
+            return f16 ? launch_one<D, KS, DB, 4, false, false, true, PM_EXACT, 2>(L, hm, default_map, q, v, ws, out, lse, nullptr, st, g)
+                       : launch_one<D, KS, DB, 4, false, false, false, PM_EXACT, 2>(L, hm, default_map, q, v, ws, out, lse, nullptr, st, g);
     }
     // the query tile size fixed by focus_assign selects the work-group shape: 4 or 8 wavefronts
     if constexpr (D != 256) {
         if (L.BQ == 256)
-            return f16 ? launch_w<D, KS, DB, 8, true, PM_EXACT>(L, hm, default_map, q, ws, out, lse, row_pairs, st)
-                       : launch_w<D, KS, DB, 8, false, PM_EXACT>(L, hm, default_map, q, ws, out, lse, row_pairs, st);
+            return f16 ? launch_w<D, KS, DB, 8, true, PM_EXACT>(L, hm, default_map, q, v, ws, out, lse, row_pairs, st)
+                       : launch_w<D, KS, DB, 8, false, PM_EXACT>(L, hm, default_map, q, v, ws, out, lse, row_pairs, st);
     }
     if (L.BQ != 128) return hipErrorInvalidValue;
     if (L.masked)                        // one class, membership tested per pair
-        return f16 ? launch_w<D, KS, DB, 4, true, PM_MASKED>(L, hm, default_map, q, ws, out, lse, row_pairs, st)
-                   : launch_w<D, KS, DB, 4, false, PM_MASKED>(L, hm, default_map, q, ws, out, lse, row_pairs, st);
+        return f16 ? launch_w<D, KS, DB, 4, true, PM_MASKED>(L, hm, default_map, q, v, ws, out, lse, row_pairs, st)
+                   : launch_w<D, KS, DB, 4, false, PM_MASKED>(L, hm, default_map, q, v, ws, out, lse, row_pairs, st);
     if (L.coarse)                        // coarse classes always use 128-row tiles
-        return f16 ? launch_w<D, KS, DB, 4, true, PM_COARSE>(L, hm, default_map, q, ws, out, lse, row_pairs, st)
-                   : launch_w<D, KS, DB, 4, false, PM_COARSE>(L, hm, default_map, q, ws, out, lse, row_pairs, st);
-    return f16 ? launch_w<D, KS, DB, 4, true, PM_EXACT>(L, hm, default_map, q, ws, out, lse, row_pairs, st)
-               : launch_w<D, KS, DB, 4, false, PM_EXACT>(L, hm, default_map, q, ws, out, lse, row_pairs, st);
+        return f16 ? launch_w<D, KS, DB, 4, true, PM_COARSE>(L, hm, default_map, q, v, ws, out, lse, row_pairs, st)
+                   : launch_w<D, KS, DB, 4, false, PM_COARSE>(L, hm, default_map, q, v, ws, out, lse, row_pairs, st);
+    return f16 ? launch_w<D, KS, DB, 4, true, PM_EXACT>(L, hm, default_map, q, v, ws, out, lse, row_pairs, st)
+               : launch_w<D, KS, DB, 4, false, PM_EXACT>(L, hm, default_map, q, v, ws, out, lse, row_pairs, st);
 }
 
 }  // namespace
