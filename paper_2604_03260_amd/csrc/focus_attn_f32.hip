@@ -48,7 +48,7 @@ __global__ __launch_bounds__(64 * NW, D <= 128 ? 2 : 1) void attn_f32_kernel(Lay
     __shared__ TilePlan P;
     __shared__ float s_o[NW / 2][DB * 16][64];         // partial results on their way between the wavefronts
     __shared__ float s_m[NW / 2][64], s_l[NW / 2][64];
-    __shared__ int s_np[NW / 2][64];                   // pair count, bit 31: the row attends a non-finite value
+    __shared__ int s_np[NW / 2][64];
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -102,7 +102,6 @@ __global__ __launch_bounds__(64 * NW, D <= 128 ? 2 : 1) void attn_f32_kernel(Lay
         for (int r = 0; r < 16; ++r) o[db][r] = 0.f;
     float m = -INFINITY, l = 0.f;
     int npairs = 0;
-    bool spoiled = false;
 
     // far_end: keys below it lie outside every row's window and are causal for all of them (one class, position order)
     const int first_pos = P.row0 + quarter * 32;
@@ -226,27 +225,42 @@ __global__ __launch_bounds__(64 * NW, D <= 128 ? 2 : 1) void attn_f32_kernel(Lay
 #pragma unroll
         for (int r0 = 0; r0 < 16; r0 += VG) {
             if constexpr (VG < 16) load_v(r0);
-            // A value that is not finite would reach the rows that do not attend it through 0 * inf: where the unit
-            // is not attended as a whole it is taken out, and the rows that do attend its key end as NaN.
+            // A value that is not finite would reach the rows that do not attend it through 0 * inf.  Where the unit is
+            // not attended as a whole such values are taken out of the product and added to the rows that do attend
+            // their keys, component by component, as the product would have: the matrix cores count per row and
+            // component the attended infinities of either sign (a NaN counts as both) and, as 0 * inf, those whose
+            // probability is zero.
             if (!all_ok) {
                 bool any_bad = false;
 #pragma unroll
                 for (int r = 0; r < VG; ++r)
 #pragma unroll
                     for (int db = 0; db < DB; ++db) any_bad = any_bad | !__builtin_isfinite(vv[r][db]);
-                if (__any(any_bad)) {
-#pragma unroll
-                    for (int r = 0; r < VG; ++r) {
-                        bool bad = false;
+                if (__builtin_expect(__any(any_bad), 0)) {
+#pragma unroll 1
+                    for (int kind = 0; kind < 3; ++kind) {               // +inf, -inf, probability zero
+                        const float add = kind == 0 ? INFINITY : kind == 1 ? -INFINITY : __uint_as_float(0x7fc00000u);
+                        const unsigned flip = kind == 1 ? 0x80000000u : 0u, keep = kind == 2 ? 0x7fffffffu : 0xffffffffu;
 #pragma unroll
                         for (int db = 0; db < DB; ++db) {
-                            const bool nf = !__builtin_isfinite(vv[r][db]);
-                            bad = bad || nf;
-                            vv[r][db] = nf ? 0.f : vv[r][db];
+                            f32x16 cnt;
+#pragma unroll
+                            for (int r = 0; r < 16; ++r) cnt[r] = 0.f;
+#pragma unroll
+                            for (int r = 0; r < VG; ++r) {
+                                const bool at = ((ok >> (r0 + r)) & 1u) && (kind < 2 || s[r0 + r] == 0.f);
+                                const float x = __uint_as_float((__float_as_uint(vv[r][db]) ^ flip) & keep);
+                                cnt = __builtin_amdgcn_mfma_f32_32x32x2f32(x < INFINITY ? 0.f : 1.f, at ? 1.f : 0.f, cnt, 0, 0, 0);
+                            }
+#pragma unroll
+                            for (int r = 0; r < 16; ++r) o[db][r] = cnt[r] > 0.f ? o[db][r] + add : o[db][r];
+                            __builtin_amdgcn_sched_barrier(0);       // (one block at a time: the registers are few)
                         }
-                        const unsigned long long bal = __ballot(bad);
-                        if ((unsigned)(hh ? bal >> 32 : bal) != 0u && ((ok >> (r0 + r)) & 1u)) spoiled = true;
                     }
+#pragma unroll
+                    for (int r = 0; r < VG; ++r)
+#pragma unroll
+                        for (int db = 0; db < DB; ++db) vv[r][db] = __builtin_isfinite(vv[r][db]) ? vv[r][db] : 0.f;
                 }
             }
 #pragma unroll
@@ -259,8 +273,6 @@ __global__ __launch_bounds__(64 * NW, D <= 128 ? 2 : 1) void attn_f32_kernel(Lay
     }
     l += __shfl_xor(l, 32, 64);
     npairs += __shfl_xor(npairs, 32, 64);
-    int tag = npairs | (spoiled ? (int)0x80000000u : 0);
-    tag |= __shfl_xor(tag, 32, 64) & (int)0x80000000u;
 
     // App. D's merge of the wavefronts' partial softmaxes: the upper half into the lower half until one is left
     auto put = [&](int buf) {
@@ -268,11 +280,10 @@ __global__ __launch_bounds__(64 * NW, D <= 128 ? 2 : 1) void attn_f32_kernel(Lay
         for (int db = 0; db < DB; ++db)
 #pragma unroll
             for (int r = 0; r < 16; ++r) s_o[buf][db * 16 + r][lane] = o[db][r];
-        s_m[buf][lane] = m; s_l[buf][lane] = l; s_np[buf][lane] = tag;
+        s_m[buf][lane] = m; s_l[buf][lane] = l; s_np[buf][lane] = npairs;
     };
     auto take = [&](int buf) {
         const float m2 = s_m[buf][lane], l2 = s_l[buf][lane];
-        const int t2 = s_np[buf][lane];
         const float m_new = fmaxf(m, m2);
         const float a1 = (m == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m - m_new), a2 = (m2 == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m2 - m_new);
 #pragma unroll
@@ -281,7 +292,7 @@ __global__ __launch_bounds__(64 * NW, D <= 128 ? 2 : 1) void attn_f32_kernel(Lay
             for (int r = 0; r < 16; ++r) o[db][r] = o[db][r] * a1 + s_o[buf][db * 16 + r][lane] * a2;
         l = l * a1 + l2 * a2;
         m = m_new;
-        tag = (((tag & 0x7fffffff) + (t2 & 0x7fffffff)) & 0x7fffffff) | ((tag | t2) & (int)0x80000000u);
+        npairs += s_np[buf][lane];
     };
 #pragma unroll
     for (int half = NW / 2; half >= 1; half >>= 1) {
@@ -293,7 +304,7 @@ __global__ __launch_bounds__(64 * NW, D <= 128 ? 2 : 1) void attn_f32_kernel(Lay
     if (wave != 0) return;
     if (!rvalid) return;
     // an empty row (launch restricted to one pair set): out = 0, lse = -inf
-    const float inv = (tag < 0) ? __uint_as_float(0x7fc00000u) : (l > 0.f) ? 1.f / l : (l == 0.f) ? 0.f : l;
+    const float inv = (l > 0.f) ? 1.f / l : (l == 0.f) ? 0.f : l;
     float* orow = out + (size_t)b * L.os[0] + (size_t)h * L.os[1] + (size_t)qpos * L.os[2];
 #pragma unroll
     for (int db = 0; db < DB; ++db)
@@ -305,7 +316,7 @@ __global__ __launch_bounds__(64 * NW, D <= 128 ? 2 : 1) void attn_f32_kernel(Lay
         }
     if (hh == 0) {
         if (lse) lse[(size_t)bhq * L.n + qpos] = fmaf(m, LN2, logf(l));
-        if (row_pairs) row_pairs[(size_t)bhq * L.n + qpos] = tag & 0x7fffffff;
+        if (row_pairs) row_pairs[(size_t)bhq * L.n + qpos] = npairs;
     }
 }
 

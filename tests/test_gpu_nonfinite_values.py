@@ -69,3 +69,11 @@ def check(dtype, d, B, n, w, causal=True, softcap=0.0, pair_set=focus.FOCUS_PAIR
     ("bf16", 128, 6, dict(pair_set=focus.FOCUS_PAIRS_SHARED, K=16, topk=3)), ("bf16", 64, 8, dict(pair_set=focus.FOCUS_PAIRS_CROSS_LOCAL))])
 def test_masked_tiles(dtype, d, B, w, kw):
     check(dtype, d, B, 700, w, **kw)
+
+
+# fp32: every head dim (those above 96 hold a quarter of a unit's values at a time), both numbers of wavefronts
+@pytest.mark.parametrize("n,w", [(700, 40), (700, 300), (642, 5000)])
+@pytest.mark.parametrize("d,B,kw", [(64, 1, {}), (64, 8, dict(causal=False)), (80, 1, dict(softcap=20.0)), (96, 6, {}), (128, 1, {}),
+                                    (256, 1, {}), (256, 1, dict(causal=False, K=16, topk=3))])
+def test_f32(d, B, n, w, kw):
+    check("f32", d, B, n, w, **kw)
