@@ -22,13 +22,13 @@ template <bool F16> struct Half16;
 template <> struct Half16<false> {
     typedef __bf16 T;
     typedef bf16x8 V8;
-    static constexpr uint32_t EXP = 0x7f80u;
+    static constexpr uint32_t EXP = 0x7f80u, ONE = 0x3f80u;
     static __device__ inline f32x16 mfma(V8 a, V8 b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0); }
 };
 template <> struct Half16<true> {
     typedef _Float16 T;
     typedef f16x8 V8;
-    static constexpr uint32_t EXP = 0x7c00u;
+    static constexpr uint32_t EXP = 0x7c00u, ONE = 0x3c00u;
     static __device__ inline f32x16 mfma(V8 a, V8 b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0); }
 };
 template <typename T> __device__ inline uint32_t bits16(T x)
@@ -38,6 +38,22 @@ template <typename T> __device__ inline uint32_t bits16(T x)
     return b;
 }
 constexpr float LOG2E = 1.4426950408889634f, LN2 = 0.6931471805599453f;
+
+// Ones where the two 16-bit values of x are +inf or NaN, zeros elsewhere.
+template <bool F16>
+__device__ inline uint32_t inf_or_nan_marks(uint32_t x)
+{
+    typedef typename Half16<F16>::T elem_t;
+    uint32_t m = 0u;
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+        const uint16_t b = (uint16_t)(x >> (16 * e));
+        elem_t h;
+        __builtin_memcpy(&h, &b, 2);
+        m |= !(h < (elem_t)INFINITY) ? Half16<F16>::ONE << (16 * e) : 0u;
+    }
+    return m;
+}
 
 // max of the two half-waves (lane l and lane l^32 hold the same query row)
 __device__ inline float both_halves_max(float x)
@@ -62,7 +78,7 @@ __global__ __launch_bounds__(512, 2) void attn_short_kernel(Layout L, HeadMap hm
     __shared__ TilePlanT<1> P;
     __shared__ float s_o[NW / 2][DB * 16][64];         // partial results on their way between the wavefronts
     __shared__ float s_m[NW / 2][64], s_l[NW / 2][64];
-    __shared__ int s_np[NW / 2][64];                   // pair count, bit 31: the row attends a non-finite value
+    __shared__ int s_np[NW / 2][64];
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -111,7 +127,6 @@ __global__ __launch_bounds__(512, 2) void attn_short_kernel(Layout L, HeadMap hm
         for (int r = 0; r < 16; ++r) o[db][r] = 0.f;
     float m = -INFINITY, l = 0.f;
     int npairs = 0;
-    bool spoiled = false;
 
     for (int u = wave; u < 2 * P.total; u += NW) {
         const int tile = P.t0[0] + (u >> 1), slot0 = tile * KT + (u & 1) * 32;
@@ -198,8 +213,10 @@ __global__ __launch_bounds__(512, 2) void attn_short_kernel(Layout L, HeadMap hm
             l += (float)p0 + (float)p1;
             pw[r2] = bits16(p0) | (bits16(p1) << 16);
         }
-        // A value that is not finite would reach the rows that do not attend it through 0 * inf: where the unit is not
-        // attended as a whole it is taken out, and the rows that do attend its key end as NaN.
+        // A value that is not finite would reach the rows that do not attend it through 0 * inf.  Where the unit is not
+        // attended as a whole such values are taken out of the product and added to the rows that do attend their keys,
+        // component by component, as the product would have: the matrix cores count per row and component the attended
+        // infinities of either sign (a NaN counts as both) and, as 0 * inf, those whose probability is zero.
         if (!all_ok) {
             bool any_bad = false;
 #pragma unroll
@@ -207,19 +224,45 @@ __global__ __launch_bounds__(512, 2) void attn_short_kernel(Layout L, HeadMap hm
 #pragma unroll
                 for (int db = 0; db < DB; ++db)
                     any_bad = any_bad | ((vv[r2][db] & HT::EXP) == HT::EXP) | (((vv[r2][db] >> 16) & HT::EXP) == HT::EXP);
-            if (__any(any_bad)) {
+            if (__builtin_expect(__any(any_bad), 0)) {
+#pragma unroll 1
+                for (int kind = 0; kind < 3; ++kind) {                   // +inf, -inf, probability zero
+                    const float add = kind == 0 ? INFINITY : kind == 1 ? -INFINITY : __uint_as_float(0x7fc00000u);
+                    const uint32_t flip = kind == 1 ? 0x80008000u : 0u, keep = kind == 2 ? 0x7fff7fffu : 0xffffffffu;
+                    uint32_t at[8];                                      // the attended keys, two to a register
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    bool bad = false;
+                    for (int r2 = 0; r2 < 8; ++r2) {
+                        const bool lo = ((ok >> (2 * r2)) & 1u) && (kind < 2 || (pw[r2] & 0xffffu) == 0u);
+                        const bool hi = ((ok >> (2 * r2 + 1)) & 1u) && (kind < 2 || (pw[r2] >> 16) == 0u);
+                        at[r2] = (lo ? HT::ONE : 0u) | (hi ? HT::ONE << 16 : 0u);
+                    }
 #pragma unroll
                     for (int db = 0; db < DB; ++db) {
-                        const bool nf = ((vv[r / 2][db] >> (16 * (r % 2))) & HT::EXP) == HT::EXP;
-                        bad = bad || nf;
-                        vv[r / 2][db] = nf ? vv[r / 2][db] & (r % 2 ? 0xffffu : 0xffff0000u) : vv[r / 2][db];
+                        f32x16 cnt;
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) cnt[r] = 0.f;
+#pragma unroll
+                        for (int t = 0; t < 2; ++t) {
+                            u32x4 mk, ak;
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) {
+                                mk[e] = inf_or_nan_marks<F16>((vv[4 * t + e][db] ^ flip) & keep);
+                                ak[e] = at[4 * t + e];
+                            }
+                            cnt = HT::mfma(__builtin_bit_cast(V8, mk), __builtin_bit_cast(V8, ak), cnt);
+                        }
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) o[db][r] = cnt[r] > 0.f ? o[db][r] + add : o[db][r];
+                        __builtin_amdgcn_sched_barrier(0);       // (one block at a time: the registers are few)
                     }
-                    const unsigned long long bal = __ballot(bad);
-                    if ((unsigned)(hh ? bal >> 32 : bal) != 0u && ((ok >> r) & 1u)) spoiled = true;
                 }
+#pragma unroll
+                for (int r2 = 0; r2 < 8; ++r2)
+#pragma unroll
+                    for (int db = 0; db < DB; ++db) {
+                        const uint32_t x = vv[r2][db];
+                        vv[r2][db] = ((x & HT::EXP) == HT::EXP ? 0u : x & 0xffffu) | (((x >> 16) & HT::EXP) == HT::EXP ? 0u : x & 0xffff0000u);
+                    }
             }
         }
 #pragma unroll
@@ -236,8 +279,6 @@ __global__ __launch_bounds__(512, 2) void attn_short_kernel(Layout L, HeadMap hm
     }
     l += __shfl_xor(l, 32, 64);
     npairs += __shfl_xor(npairs, 32, 64);
-    int tag = npairs | (spoiled ? (int)0x80000000u : 0);
-    tag |= __shfl_xor(tag, 32, 64) & (int)0x80000000u;
 
     // App. D's merge of the wavefronts' partial softmaxes: the upper half into the lower half until one is left
     auto put = [&](int buf) {
@@ -245,11 +286,10 @@ __global__ __launch_bounds__(512, 2) void attn_short_kernel(Layout L, HeadMap hm
         for (int db = 0; db < DB; ++db)
 #pragma unroll
             for (int r = 0; r < 16; ++r) s_o[buf][db * 16 + r][lane] = o[db][r];
-        s_m[buf][lane] = m; s_l[buf][lane] = l; s_np[buf][lane] = tag;
+        s_m[buf][lane] = m; s_l[buf][lane] = l; s_np[buf][lane] = npairs;
     };
     auto take = [&](int buf) {
         const float m2 = s_m[buf][lane], l2 = s_l[buf][lane];
-        const int t2 = s_np[buf][lane];
         const float m_new = fmaxf(m, m2);
         const float a1 = (m == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m - m_new), a2 = (m2 == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m2 - m_new);
 #pragma unroll
@@ -258,7 +298,7 @@ __global__ __launch_bounds__(512, 2) void attn_short_kernel(Layout L, HeadMap hm
             for (int r = 0; r < 16; ++r) o[db][r] = o[db][r] * a1 + s_o[buf][db * 16 + r][lane] * a2;
         l = l * a1 + l2 * a2;
         m = m_new;
-        tag = (((tag & 0x7fffffff) + (t2 & 0x7fffffff)) & 0x7fffffff) | ((tag | t2) & (int)0x80000000u);
+        npairs += s_np[buf][lane];
     };
 #pragma unroll
     for (int half = NW / 2; half >= 1; half >>= 1) {
@@ -270,7 +310,7 @@ __global__ __launch_bounds__(512, 2) void attn_short_kernel(Layout L, HeadMap hm
     if (wave != 0) return;
     if (!rvalid) return;
     // an empty row (launch restricted to one pair set): out = 0, lse = -inf
-    const float inv = (tag < 0) ? __uint_as_float(0x7fc00000u) : (l > 0.f) ? 1.f / l : (l == 0.f) ? 0.f : l;
+    const float inv = (l > 0.f) ? 1.f / l : (l == 0.f) ? 0.f : l;
     uint16_t* orow = out + (size_t)b * L.os[0] + (size_t)h * L.os[1] + (size_t)qpos * L.os[2];
 #pragma unroll
     for (int db = 0; db < DB; ++db)
@@ -285,7 +325,7 @@ __global__ __launch_bounds__(512, 2) void attn_short_kernel(Layout L, HeadMap hm
         }
     if (hh == 0) {
         if (lse) lse[(size_t)bhq * L.n + qpos] = fmaf(m, LN2, logf(l));
-        if (row_pairs) row_pairs[(size_t)bhq * L.n + qpos] = tag & 0x7fffffff;
+        if (row_pairs) row_pairs[(size_t)bhq * L.n + qpos] = npairs;
     }
 }
 

@@ -71,6 +71,15 @@ def test_masked_tiles(dtype, d, B, w, kw):
     check(dtype, d, B, 700, w, **kw)
 
 
+# the kernel for a few work-groups of 32 rows: masked and dense layouts (a window past the end), one and two keys' worth
+# of rows past a unit
+@pytest.mark.parametrize("n,w", [(700, 40), (700, 300), (545, 544), (642, 5000), (130, 20)])
+@pytest.mark.parametrize("dtype,d,kw", [("bf16", 64, {}), ("f16", 80, {}), ("bf16", 96, dict(softcap=30.0)), ("f16", 128, {}),
+                                        ("bf16", 128, dict(causal=False)), ("f16", 64, dict(K=16, topk=3))])
+def test_short_sequences(dtype, d, n, w, kw):
+    check(dtype, d, 1, n, w, **kw)
+
+
 # fp32: every head dim (those above 96 hold a quarter of a unit's values at a time), both numbers of wavefronts
 @pytest.mark.parametrize("n,w", [(700, 40), (700, 300), (642, 5000)])
 @pytest.mark.parametrize("d,B,kw", [(64, 1, {}), (64, 8, dict(causal=False)), (80, 1, dict(softcap=20.0)), (96, 6, {}), (128, 1, {}),
