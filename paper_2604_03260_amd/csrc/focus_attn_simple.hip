@@ -90,14 +90,16 @@ __global__ __launch_bounds__(BQ_VECTOR * (D / 32)) void attn_simple_kernel(Layou
             const int r0 = tile * KT + sub * SUB;
             __syncthreads();
             if (tid < SUB) s_kpos[tid] = kpos_all[r0 + tid];
+            bool bad = false;                            // a value of this step that is not finite
             for (int e = tid; e < SUB * D; e += NTHR) {
                 const int kk = e / D, t = e % D;
                 const int kp = kpos_all[r0 + kk];
                 const bool real = kp != KPOS_PAD && t < d;
                 s_k[e] = real ? to_f32<T>(kbase[(size_t)kp * kpitch + t]) : 0.f;
                 s_v[e] = real ? to_f32<T>(vbase[(size_t)kp * kpitch + t]) : 0.f;
+                bad = bad || !__builtin_isfinite(s_v[e]);
             }
-            __syncthreads();
+            bad = __syncthreads_or(bad);
             float s[SUB];
             float mx = -INFINITY;
 #pragma unroll
@@ -144,6 +146,13 @@ __global__ __launch_bounds__(BQ_VECTOR * (D / 32)) void attn_simple_kernel(Layou
             if (m_new == -INFINITY) continue;            // nothing allowed yet for this row
             const float alpha = expf(m - m_new);         // m = -inf gives 0
             float psum = 0.f;
+            // (0 * inf must not reach a row that does not attend the key)
+            uint32_t attended = 0xffffffffu;
+            if (bad) {
+                attended = 0u;
+#pragma unroll
+                for (int kk = 0; kk < SUB; ++kk) attended |= s[kk] != -INFINITY ? 1u << kk : 0u;
+            }
 #pragma unroll
             for (int kk = 0; kk < SUB; ++kk) {
                 s[kk] = expf(s[kk] - m_new);             // masked: exp(-inf) = 0
@@ -157,6 +166,7 @@ __global__ __launch_bounds__(BQ_VECTOR * (D / 32)) void attn_simple_kernel(Layou
             for (int kk = 0; kk < SUB; ++kk) {
                 const float* vr = s_v + kk * D + part * 32;
                 const float pk = s[kk];
+                if (bad && !((attended >> kk) & 1u)) continue;
 #pragma unroll
                 for (int e = 0; e < 32; ++e) o[e] = fmaf(pk, vr[e], o[e]);
             }

@@ -86,3 +86,12 @@ def test_short_sequences(dtype, d, n, w, kw):
                                     (256, 1, {}), (256, 1, dict(causal=False, K=16, topk=3))])
 def test_f32(d, B, n, w, kw):
     check("f32", d, B, n, w, **kw)
+
+
+@pytest.mark.parametrize("tiles", [None, "0"])
+@pytest.mark.parametrize("dtype,d", [("f32", 64), ("bf16", 128), ("f16", 80), ("bf16", 256)])
+def test_vector_kernel(dtype, d, tiles, monkeypatch):
+    """The masked layout and tiles of one class (where a tile's rows differ in what they attend)."""
+    if tiles:
+        monkeypatch.setenv("FOCUS_TWO_PASS", tiles)
+    check(dtype, d, 1, 600, 90, vector=True)
