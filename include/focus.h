@@ -103,8 +103,10 @@ focus_status focus_assign(const focus_params *p, const void *q, const void *k,
  * it that share a group over class-ordered tiles) and merges the two partial
  * softmaxes of every row through their log-sum-exp (App. D's merge): the same exact
  * softmax, each allowed pair once; focus_workspace_size and focus_assign account
- * for the second layout.  Short sequences run over tiles in
- * position order with the memberships tested per pair (an estimate from n, K, topk and the window chooses).
+ * for the second layout.  Short sequences, and longer ones whose many membership sets
+ * would leave class-ordered tiles mostly empty (K = 16, topk = 3 at any length), run over tiles in
+ * position order with the memberships tested per pair; an estimate from the parameters alone, for
+ * memberships spread evenly over the groups, chooses.
  * The environment variable FOCUS_TWO_PASS=0/1 (one / two passes over class-ordered tiles), read when a
  * call derives its layout, overrides that choice (tests and measurements; it must
  * not change between focus_workspace_size, focus_assign and focus_attn_fwd).  out [B,Hq,n,d] in p->dtype.  lse (nullable) [B,Hq,n]

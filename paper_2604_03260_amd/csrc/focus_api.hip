@@ -51,30 +51,39 @@ double window_waste(const focus::Layout& L, double none)
 
 // Masked layout (one class in position order, memberships tested per pair) instead of tiles of one class each?
 // The masked kernel visits every key tile of the causal prefix; class tiles skip what cannot be allowed, but a class
-// leaves its last query tile partly empty, meets every key class in at least one tile, and pays more per tile at the
-// edges.  Counted in visits of a 128-row tile to a 64-key tile, with uniform memberships; the constants (half a
-// tile lost per key class met, a work-group's fixed cost of 12 visits, a masked visit at 0.9 of a class visit) are
-// fitted to 147 measured pairs, K = 4 .. 32, top 1 .. 3, 512 .. 131072 tokens, 12 .. 128 heads, d = 64 and 128:
-// the choice is never more than 1 % slower than the other one on them.  Both sides, at 32/8 heads of 128 (us):
-//   K=4 top-2:  class 216 / masked 153 at 4096 tokens, 1994 / 1994 at 16384, 6666 / 7792 at 32768;
-//   K=8 top-1:  190 / 150 at 4096, 366 / 506 at 8192;    K=8 top-3: 11630 / 8020 at 32768;
-//   K=16 top-2: 1831 / 152 at 4096, 4923 / 7432 at 32768;   K=16 top-3 (3 x 15/5 heads of 80, 5003 tokens, with the bucketing): 12580 / 410.
-bool prefer_masked(const focus::Layout& L, double none, bool two_pass)
+// leaves its last query tile partly empty (half a tile on average), and a tile loses part of a visit where it meets a key
+// class (lost; lost_window where only the window is walked), pays for the per-class launches and tables of the
+// bucketing (launches, shared by the heads), and two passes pay a second walk over the window.  Counted in visits of a
+// 128-row tile to a 64-key tile, for memberships that are uniform over the groups (with few live classes the class
+// tiles would visit less than estimated: the masked layout then takes up to the number of live disjoint classes as
+// long); `visit` is a masked visit in class visits.
+// The constants are fitted to measured pairs (focus_assign + focus_attn_fwd of both layouts; 1 to 8 sequences, 4 to 40 heads of
+// 64 to 256, K = 4 .. 32, top 1 .. 4, windows 64 .. 4096, with and without a softcap).  How often the choice was more than 2 %
+// slower than the other layout, and by how much at most:
+//   one pass, causal      922 pairs,   256 .. 262144 tokens:  10, 1.09x     two passes  631, 16384 .. 262144: 20, 1.18x
+//   one pass, non-causal  672 pairs,   512 ..  49152 tokens:  14, 1.14x     coarse      400,   256 .. 262144:  0
+//   fp32 causal           288 pairs,   256 ..  16384 tokens:   3, 1.04x     non-causal  230,   256 ..   8192: 10, 1.25x
+// Non-causal launches of a few hundred work-groups end in steps of whole rounds of the chip, which no visit count sees.
+// Both sides at 16/4 heads of 128, w=1024 (us): K=4 top-2: class 1125 / masked 1096 at 16384 tokens, 1549 / 1620 at 20000,
+// 3545 / 4132 at 32768;  K=8 top-3: 1967 / 1145, 5747 / 4294 at 32768;  coarse K=32 top-2 at 8/2 heads: 84900 / 68900 at 196608.
+struct LayoutCost { double lost, visit, lost_window, launches; };
+
+bool prefer_masked(const focus::Layout& L, double none, bool two_pass, int BQ)
 {
-    const double n = L.n, w = L.window, NC = L.NC, KT = focus::KT, BQ = focus::BQ_VECTOR;
+    static const LayoutCost ONE = {5.4, 1.28, 2.1, 300.0}, TWO = {3.0, 1.22, 0.0, 150.0}, NONCAUSAL = {2.0, 1.27, 1.55, 4400.0},
+                            COARSE = {0.6, 0.415, 0.0, 0.0}, F32 = {8.7, 2.19, 0.0, 3400.0}, F32_NONCAUSAL = {1.5, 1.3, 0.0, 440.0};
+    const LayoutCost& c = L.dtype == FOCUS_F32 ? (L.causal ? F32 : F32_NONCAUSAL) : L.coarse ? COARSE : two_pass ? TWO
+                          : L.causal ? ONE : NONCAUSAL;
+    const double n = L.n, w = L.window, NC = L.NC, KT = focus::KT, rows = focus::BQ_VECTOR;
     const double half = L.causal ? 0.5 : 1.0;                // share of the keys a row sees, on average
     const double share = 1.0 - none;                         // share of the key classes that meet a query class
-    const double per = n / NC, lost = 0.5, fixed = 12.0, masked_visit = 0.9;
-    const double tiles = NC * std::ceil(n / (NC * BQ));
-    double visits = tiles * (NC * share * (per * half / KT + lost) + fixed);
+    const double per = n / NC, tiles = n / rows + 0.5 * NC * BQ / rows;
+    double visits = tiles * NC * share * (per * half / KT + c.lost) + c.launches / ((double)L.B * L.Hq);
     if (two_pass)
-        visits += std::ceil(n / BQ) * ((w + BQ) / KT + fixed);
+        visits += n / rows * (w + rows) / KT;
     else
-        visits += tiles * NC * none * (std::min(per, (w + std::min(n, NC * BQ)) / NC) * 2.0 * half / KT + lost);
-    // coarse classes test every pair of every tile: 1.3 to 1.6 of the estimate (8 heads of 128, K=32 top-2: class 21.3 /
-    // masked 7.4 ms at 65536 tokens, 49.9 / 29.4 ms at 131072, where the bare estimate has the two equal)
-    if (L.coarse) visits *= 1.4;
-    return visits > std::ceil(n / BQ) * (n * half / KT + 1.0 + fixed) * masked_visit;
+        visits += tiles * NC * none * (std::min(per, ((L.causal ? w : 2.0 * w) + std::min(n, NC * BQ)) / NC) / KT + c.lost_window);
+    return visits > n / rows * n * half / KT * c.visit;
 }
 
 // Validates the params and derives the workspace layout and the head map.
@@ -169,7 +178,8 @@ focus_status make_layout(const focus_params* p, focus::Layout* L, focus::HeadMap
         const int force = (env && (env[0] == '0' || env[0] == '1')) ? env[0] - '0' : -1;
         const bool can_two = !L->coarse && p->causal && p->dtype != FOCUS_F32;
         L->two_pass = can_two && (force >= 0 ? force == 1 : p->n >= 16384 && window_waste(*L, none) >= 0.04);
-        if (force != 0 && !(force == 1 && can_two) && prefer_masked(*L, none, L->two_pass != 0)) {
+        const int bq = (L->two_pass && can256 && p->n >= LONG_N_TWO_PASS) ? 256 : L->BQ;
+        if (force != 0 && !(force == 1 && can_two) && prefer_masked(*L, none, L->two_pass != 0, bq)) {
             L->masked = 1;
             L->two_pass = 0;
             L->coarse = 1;

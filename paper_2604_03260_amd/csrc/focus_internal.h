@@ -65,8 +65,8 @@ struct Layout {
     int coarse;                // C(K,topk) exceeds MAX_CLASSES: classes are sets of S super-groups (group g folds
     int S;                     // onto g % S), a superset test; the kernels then test the real masks per pair
     int masked;                // one class in position order, every pair outside the window tested against the two
-                               // membership masks (coarse with S = 1): short sequences, where classes would leave
-                               // tiles mostly empty (see prefer_masked in focus_api.hip)
+                               // membership masks (coarse with S = 1): where classes would leave tiles mostly empty,
+                               // in short sequences and at any length with many sets (see prefer_masked in focus_api.hip)
     int pair_set;              // which pairs a launch attends: 0 the whole mask, 1 only pairs that share a group
                                // (set A of App. D), 2 only window pairs that share none (set B), 3 pairs that share
                                // a group and lie outside the window (second pass of a two-pass launch)
