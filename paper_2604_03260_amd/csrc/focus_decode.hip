@@ -920,13 +920,7 @@ constexpr float DEC_RESCALE_THRESHOLD = 8.f;
 
 // CH: entries of the walk a work-group resolves at a time (the long or the short chunk: the short one when the
 // launch would otherwise leave most of the chip idle, one round per wavefront and four times the work-groups).
-// PIPE: the next round's K rows are requested as soon as this round's are multiplied, its V rows as soon as this round's
-// are in LDS (through registers), so that loads are in flight during the softmax and both products.  Takes two
-// wavefronts per SIMD instead of three, so it is for launches that have no more than that (or a few, which start as the
-// first ones end): 8 KV heads x 32768 keys of 128
-// (520 work-groups) 30.1 -> 28.4 us a launch, 44.1 -> 41.5 a step; with more work-groups a third resident one covers more (8 x 131072: 78
-// without, 84 with it).
-template <bool F16, int D, int CH, bool PIPE>
+template <bool F16, int D, int CH>
 __global__ __launch_bounds__(256) void decode_attn_gqa_mfma_kernel(DecodeLayout L, int Gall, int pos_arg, const int* __restrict__ pos_dev,
                                                                    int span, const uint16_t* __restrict__ q_new,
                                                                    const uint16_t* __restrict__ kc, const uint16_t* __restrict__ vc,
@@ -946,7 +940,6 @@ __global__ __launch_bounds__(256) void decode_attn_gqa_mfma_kernel(DecodeLayout 
     constexpr int PW = D + 4;
     constexpr int KPT = CH >= 256 ? CH / 256 : 1;
     constexpr int RSTEP = 4 * 32;                 // keys of one round of the four wavefronts
-    static_assert(!PIPE || D <= 128, "the rows of a round of 256 components do not fit the registers");
     constexpr int GMAX = 16;                      // query heads per work-group: the columns of the products
     constexpr int RED_BYTES = GMAX * 4 * PW * 4;
     constexpr int BUF_BYTES = 4 * VBYTES > RED_BYTES ? 4 * VBYTES : RED_BYTES;
@@ -1025,10 +1018,17 @@ __global__ __launch_bounds__(256) void decode_attn_gqa_mfma_kernel(DecodeLayout 
     const int nk = decode_resolve_chunk<KPT, GMAX, uint16_t>(s_walk, nseg, v0, min(vtotal - v0, CH), lo_w, lists, L.n, mk, gq,
                                                              (1u << G) - 1u, L.topk == 1, s_j, s_hb, CH + RSTEP, s_wcnt);
 
-    // K rows of the two blocks of a round -> registers (lane: key l%16 of either block, components 8*(l/16) .. +8)
-    V8 ka[KB], kb2[KB];
-    auto load_k = [&](int r0) {
+    for (int r0 = wave * 32; r0 < nk; r0 += RSTEP) {
+        // the V rows of the round -> LDS (wave load i holds keys i*RPI ..+RPI of the round)
+        // (a wave load past the 32nd key fetches rows of the next round or row 0: read by nobody)
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            const int jv = max(s_j[r0 + i * RPI + dlane / LPR], 0);
+            lds_dma16(vbase, (unsigned)jv * (unsigned)RB + (unsigned)(dlane % LPR) * 16u, lds_v + i * IPITCH);
+        }
+        // the K rows of the two blocks -> registers
         const int ja = max(s_j[r0 + m16], 0), jb = max(s_j[r0 + 16 + m16], 0);
+        V8 ka[KB], kb2[KB];
 #pragma unroll
         for (int kb = 0; kb < KB; ++kb) {
             dec_u32x4 wa = {0u, 0u, 0u, 0u}, wb = {0u, 0u, 0u, 0u};
@@ -1039,22 +1039,6 @@ __global__ __launch_bounds__(256) void decode_attn_gqa_mfma_kernel(DecodeLayout 
             ka[kb] = __builtin_bit_cast(V8, wa);
             kb2[kb] = __builtin_bit_cast(V8, wb);
         }
-    };
-    // V rows of a round: wave load i holds keys i*RPI ..+RPI (past the 32nd key: rows of the next round or row 0, read by nobody)
-    dec_u32x4 vreg[PIPE ? NI : 1];
-    auto load_v = [&](int r0) {
-#pragma unroll
-        for (int i = 0; i < NI; ++i) {
-            const int jv = max(s_j[r0 + i * RPI + dlane / LPR], 0);
-            const unsigned off = (unsigned)jv * (unsigned)RB + (unsigned)(dlane % LPR) * 16u;
-            if constexpr (PIPE) vreg[i] = *(const dec_u32x4*)((const char*)vbase + off);
-            else lds_dma16(vbase, off, lds_v + i * IPITCH);
-        }
-    };
-    if (PIPE && wave * 32 < nk) { load_k(wave * 32); load_v(wave * 32); }
-    for (int r0 = wave * 32; r0 < nk; r0 += RSTEP) {
-        const bool more = r0 + RSTEP < nk;
-        if constexpr (!PIPE) { load_v(r0); load_k(r0); }
         const uint64_t hba = *(const uint64_t*)(&s_hb[r0 + 4 * qg]);           // 16 head bits for each of the four keys
         const uint64_t hbb = *(const uint64_t*)(&s_hb[r0 + 16 + 4 * qg]);
         dec_f32x4 sa = {0.f, 0.f, 0.f, 0.f}, sb = {0.f, 0.f, 0.f, 0.f};
@@ -1063,7 +1047,6 @@ __global__ __launch_bounds__(256) void decode_attn_gqa_mfma_kernel(DecodeLayout 
             sa = HT::mfma(ka[kb], qv[kb], sa);
             sb = HT::mfma(kb2[kb], qv[kb], sb);
         }
-        if (PIPE && more) load_k(r0 + RSTEP);
         float x[8];
         float mloc = -INFINITY;
 #pragma unroll
@@ -1096,18 +1079,7 @@ __global__ __launch_bounds__(256) void decode_attn_gqa_mfma_kernel(DecodeLayout 
             pw[e2] = HT::pack2(__builtin_amdgcn_exp2f(x[2 * e2] - mr), __builtin_amdgcn_exp2f(x[2 * e2 + 1] - mr), psum);
         lsum += psum;
         const V8 pb = __builtin_bit_cast(V8, pw);
-        if constexpr (PIPE) {
-            // a wavefront's LDS accesses run in order: no barrier, only the compiler must keep the order
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-#pragma unroll
-            for (int i = 0; i < NI; ++i) *(dec_u32x4*)(s_buf + wave * VBYTES + i * IPITCH + lane * 16) = vreg[i];
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            if (more) load_v(r0 + RSTEP);
-        } else {
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");          // the V rows have landed
-        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");              // the V rows have landed
 #pragma unroll
         for (int blk = 0; blk < NB; ++blk) {
             dec_u32x4 vw;
@@ -1319,12 +1291,11 @@ static hipError_t decode_step_d(const DecodeLayout& L, const HeadMap& hm, int po
                     grid.x = nparts;
                 }
                 constexpr bool f16 = std::is_same<T, f16_bits>::value;
-#define FOCUS_DEC_MFMA(CH_, P_) hipLaunchKernelGGL((decode_attn_gqa_mfma_kernel<f16, D, CH_, P_>), grid, dim3(256), 0, s, L, G, pos, pos_dev, span, \
-                                                   (const uint16_t*)q_new, (const uint16_t*)kc, (const uint16_t*)vc, (const char*)st, part)
-                if (ch == DEC_CHUNK_SHORT) FOCUS_DEC_MFMA(DEC_CHUNK_SHORT, false);
-                else if (ch == 2 * DEC_CHUNK_SHORT) FOCUS_DEC_MFMA(2 * DEC_CHUNK_SHORT, false);
-                else if (D <= 128 && (long)grid.x * grid.y <= 2 * 256 + 32) FOCUS_DEC_MFMA(DEC_CHUNK, (D <= 128));
-                else FOCUS_DEC_MFMA(DEC_CHUNK, false);
+#define FOCUS_DEC_MFMA(CH_) hipLaunchKernelGGL((decode_attn_gqa_mfma_kernel<f16, D, CH_>), grid, dim3(256), 0, s, L, G, pos, pos_dev, span, \
+                                               (const uint16_t*)q_new, (const uint16_t*)kc, (const uint16_t*)vc, (const char*)st, part)
+                if (ch == DEC_CHUNK_SHORT) FOCUS_DEC_MFMA(DEC_CHUNK_SHORT);
+                else if (ch == 2 * DEC_CHUNK_SHORT) FOCUS_DEC_MFMA(2 * DEC_CHUNK_SHORT);
+                else FOCUS_DEC_MFMA(DEC_CHUNK);
 #undef FOCUS_DEC_MFMA
                 hipLaunchKernelGGL((decode_merge_kernel<T, D>), dim3(L.B * L.Hq), dim3(256), 0, s, L, pos, pos_dev, nparts, part, out,
                                    lse, row_pairs);
