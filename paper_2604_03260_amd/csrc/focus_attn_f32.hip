@@ -162,6 +162,23 @@ __global__ __launch_bounds__(64 * NW, D <= 128 ? 2 : 1) void attn_f32_kernel(Lay
         }
         return rvalid ? ok : 0u;
     };
+    auto load_v = [&](const Unit& U, int r0, float (&vv)[VG][DB]) {
+#pragma unroll
+        for (int r = 0; r < VG; ++r) {
+            const float* vr = row_at(vbase, min(key_pos(U, r0 + r), L.n - 1));
+#pragma unroll
+            for (int db = 0; db < DB; ++db) vv[r][db] = (D % 32 == 0 || db * 32 + n32 < D) ? vr[db * 32] : 0.f;
+        }
+    };
+    auto any_nonfinite = [&](const float (&vv)[VG][DB]) -> bool {
+        bool bad = false;
+#pragma unroll
+        for (int r = 0; r < VG; ++r)
+#pragma unroll
+            for (int db = 0; db < DB; ++db) bad = bad | !__builtin_isfinite(vv[r][db]);
+        return __any(bad);
+    };
+    bool again = false;                           // (uniform) values were taken out of a product
     for (int u = wave; u < 2 * P.total; u += NW) {
         Unit U;
         fetch(U, u);
@@ -169,14 +186,6 @@ __global__ __launch_bounds__(64 * NW, D <= 128 ? 2 : 1) void attn_f32_kernel(Lay
         if (!__any(ok != 0u)) continue;                                  // nothing here for any of the 32 rows
         const bool all_ok = !__any(rvalid && ok != 0xffffu);
         float vv[VG][DB];
-        auto load_v = [&](int r0) {
-#pragma unroll
-            for (int r = 0; r < VG; ++r) {
-                const float* vr = row_at(vbase, min(key_pos(U, r0 + r), L.n - 1));
-#pragma unroll
-                for (int db = 0; db < DB; ++db) vv[r][db] = (D % 32 == 0 || db * 32 + n32 < D) ? vr[db * 32] : 0.f;
-            }
-        };
         // keys, and the values with them: those arrive while the scores are computed
         float4 kf[H / 4];
         {
@@ -184,7 +193,7 @@ __global__ __launch_bounds__(64 * NW, D <= 128 ? 2 : 1) void attn_f32_kernel(Lay
 #pragma unroll
             for (int c = 0; c < H / 4; ++c) kf[c] = *(const float4*)(kr + 4 * c);
         }
-        if constexpr (VG == 16) load_v(0);
+        if constexpr (VG == 16) load_v(U, 0, vv);
         f32x16 s;
 #pragma unroll
         for (int r = 0; r < 16; ++r) s[r] = 0.f;
@@ -224,44 +233,15 @@ __global__ __launch_bounds__(64 * NW, D <= 128 ? 2 : 1) void attn_f32_kernel(Lay
         }
 #pragma unroll
         for (int r0 = 0; r0 < 16; r0 += VG) {
-            if constexpr (VG < 16) load_v(r0);
-            // A value that is not finite would reach the rows that do not attend it through 0 * inf.  Where the unit is
-            // not attended as a whole such values are taken out of the product and added to the rows that do attend
-            // their keys, component by component, as the product would have: the matrix cores count per row and
-            // component the attended infinities of either sign (a NaN counts as both) and, as 0 * inf, those whose
-            // probability is zero.
-            if (!all_ok) {
-                bool any_bad = false;
+            if constexpr (VG < 16) load_v(U, r0, vv);
+            // A value that is not finite would reach the rows that do not attend it through 0 * inf: where the unit is
+            // not attended as a whole it is taken out here and added below to the rows that do attend its key.
+            if (!all_ok && any_nonfinite(vv)) {
+                again = true;
 #pragma unroll
                 for (int r = 0; r < VG; ++r)
 #pragma unroll
-                    for (int db = 0; db < DB; ++db) any_bad = any_bad | !__builtin_isfinite(vv[r][db]);
-                if (__builtin_expect(__any(any_bad), 0)) {
-#pragma unroll 1
-                    for (int kind = 0; kind < 3; ++kind) {               // +inf, -inf, probability zero
-                        const float add = kind == 0 ? INFINITY : kind == 1 ? -INFINITY : __uint_as_float(0x7fc00000u);
-                        const unsigned flip = kind == 1 ? 0x80000000u : 0u, keep = kind == 2 ? 0x7fffffffu : 0xffffffffu;
-#pragma unroll
-                        for (int db = 0; db < DB; ++db) {
-                            f32x16 cnt;
-#pragma unroll
-                            for (int r = 0; r < 16; ++r) cnt[r] = 0.f;
-#pragma unroll
-                            for (int r = 0; r < VG; ++r) {
-                                const bool at = ((ok >> (r0 + r)) & 1u) && (kind < 2 || s[r0 + r] == 0.f);
-                                const float x = __uint_as_float((__float_as_uint(vv[r][db]) ^ flip) & keep);
-                                cnt = __builtin_amdgcn_mfma_f32_32x32x2f32(x < INFINITY ? 0.f : 1.f, at ? 1.f : 0.f, cnt, 0, 0, 0);
-                            }
-#pragma unroll
-                            for (int r = 0; r < 16; ++r) o[db][r] = cnt[r] > 0.f ? o[db][r] + add : o[db][r];
-                            __builtin_amdgcn_sched_barrier(0);       // (one block at a time: the registers are few)
-                        }
-                    }
-#pragma unroll
-                    for (int r = 0; r < VG; ++r)
-#pragma unroll
-                        for (int db = 0; db < DB; ++db) vv[r][db] = __builtin_isfinite(vv[r][db]) ? vv[r][db] : 0.f;
-                }
+                    for (int db = 0; db < DB; ++db) vv[r][db] = __builtin_isfinite(vv[r][db]) ? vv[r][db] : 0.f;
             }
 #pragma unroll
             for (int r = 0; r < VG; ++r)
@@ -270,6 +250,41 @@ __global__ __launch_bounds__(64 * NW, D <= 128 ? 2 : 1) void attn_f32_kernel(Lay
                     o[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(vv[r][db], s[r0 + r], o[db], 0, 0, 0);
         }
         npairs += __popc(ok);
+    }
+    // Infinities and NaN that were taken out, component by component: the matrix cores count, per row and component, the
+    // infinities of either sign that the row attends (a NaN counts as both).  A walk of its own, so that the registers
+    // it takes are not taken from the one above.
+    if (again) {
+        cur = 0;
+#pragma unroll 1
+        for (int u = wave; u < 2 * P.total; u += NW) {
+            Unit U;
+            fetch(U, u);
+            const unsigned ok = pairs_of(U);
+            if (!__any(ok != 0u) || !__any(rvalid && ok != 0xffffu)) continue;
+#pragma unroll
+            for (int r0 = 0; r0 < 16; r0 += VG) {
+                float vv[VG][DB];
+                load_v(U, r0, vv);
+                if (!any_nonfinite(vv)) continue;
+#pragma unroll 1
+                for (int neg = 0; neg < 2; ++neg) {
+                    const unsigned flip = neg ? 0x80000000u : 0u;
+#pragma unroll
+                    for (int db = 0; db < DB; ++db) {
+                        f32x16 cnt;
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) cnt[r] = 0.f;
+#pragma unroll
+                        for (int r = 0; r < VG; ++r)
+                            cnt = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(__float_as_uint(vv[r][db]) ^ flip) < INFINITY ? 0.f : 1.f,
+                                                                       (ok >> (r0 + r)) & 1u ? 1.f : 0.f, cnt, 0, 0, 0);
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) o[db][r] = cnt[r] > 0.f ? o[db][r] + (neg ? -INFINITY : INFINITY) : o[db][r];
+                    }
+                }
+            }
+        }
     }
     l += __shfl_xor(l, 32, 64);
     npairs += __shfl_xor(npairs, 32, 64);

@@ -128,43 +128,38 @@ __global__ __launch_bounds__(512, 2) void attn_short_kernel(Layout L, HeadMap hm
     float m = -INFINITY, l = 0.f;
     int npairs = 0;
 
-    for (int u = wave; u < 2 * P.total; u += NW) {
-        const int tile = P.t0[0] + (u >> 1), slot0 = tile * KT + (u & 1) * 32;
-        const bool interior = tile >= P.ibeg[0] && tile < P.iend[0];
-        // which pairs of the unit count, bit r = score r: key slot0 + 8*(r/4) + 4*hh + r%4
+    // which pairs of unit u count, bit r = score r: key slot0 + 8*(r/4) + 4*hh + r%4.  Without branches per pair: a key is
+    // causal from distance first on, inside the window where (distance + woff) < wlim, and the set of pairs decides
+    // whether shared pairs count (by_share) and window pairs that share count as such (loc_any); dense: every pair shares.
+    const int set = L.masked ? L.pair_set : 0;
+    const bool dense = !L.masked, by_share = set != 2, by_window = set != 1, loc_any = set == 0;
+    const int first = L.causal ? 0 : -0x7fffffff, woff = L.causal ? 0 : w - 1;
+    const unsigned wlim = L.causal ? (unsigned)w : 2u * (unsigned)w - 1u;
+    auto pairs_of = [&](int u, int& slot0) -> unsigned {
+        const int tile = P.t0[0] + (u >> 1);
+        slot0 = tile * KT + (u & 1) * 32;
         unsigned ok = 0xffffu;
-        if (!interior) {
+        if (!(tile >= P.ibeg[0] && tile < P.iend[0])) {
             ok = 0u;
 #pragma unroll
             for (int r4 = 0; r4 < 4; ++r4) {
                 uint4 km4 = make_uint4(0u, 0u, 0u, 0u);
-                if (L.masked) km4 = *(const uint4*)(kmsk + slot0 + 8 * r4 + 4 * hh);
+                if (!dense) km4 = *(const uint4*)(kmsk + slot0 + 8 * r4 + 4 * hh);
                 const uint32_t km[4] = {km4.x, km4.y, km4.z, km4.w};
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const int kj = slot0 + 8 * r4 + 4 * hh + e, dlt = qpos - kj;
-                    const bool share = !L.masked || (mq_row & km[e]) != 0u;
-                    const bool loc = L.causal ? (dlt >= 0 && dlt < w) : (dlt < w && -dlt < w);
-                    const bool cz = L.causal ? dlt >= 0 : true;
-                    bool in = cz && (share || loc);
-                    if (L.masked && L.pair_set != 0) in = (L.pair_set == 1) ? (cz && share) : (loc && !share);
-                    ok |= (kj < L.n && in) ? 1u << (4 * r4 + e) : 0u;
+                    const bool share = dense | ((mq_row & km[e]) != 0u);
+                    const bool loc = (unsigned)(dlt + woff) < wlim;
+                    const bool in = (by_share & share & (dlt >= first)) | (by_window & loc & (loc_any | !share));
+                    ok |= ((kj < L.n) & in) ? 1u << (4 * r4 + e) : 0u;
                 }
             }
         }
-        if (!rvalid) ok = 0u;
-        if (!__any(ok != 0u)) continue;                                  // nothing here for any of the 32 rows
-        const bool all_ok = !__any(rvalid && ok != 0xffffu);
-
-        // keys, and the values with them: those arrive while the scores are computed
-        V8 kf[KS];
-        {
-            const char* kr = kbase + __umul24((unsigned)min(slot0 + n32, L.n - 1), pitch_bytes);
-#pragma unroll
-            for (int c = 0; c < KS; ++c) kf[c] = *(const V8*)(kr + 32 * c);
-        }
-        // values of this half-wave's 16 keys, component 32*db + l%32, two keys to a register
-        uint32_t vv[8][DB];
+        return rvalid ? ok : 0u;
+    };
+    // values of a half-wave's 16 keys of a unit, component 32*db + l%32, two keys to a register
+    auto load_v = [&](int slot0, uint32_t (&vv)[8][DB]) {
 #pragma unroll
         for (int r2 = 0; r2 < 8; ++r2) {
             const int k0 = slot0 + 8 * (r2 / 2) + 4 * hh + 2 * (r2 % 2);
@@ -177,6 +172,33 @@ __global__ __launch_bounds__(512, 2) void attn_short_kernel(Layout L, HeadMap hm
                 vv[r2][db] = lo | (hi << 16);
             }
         }
+    };
+    auto any_nonfinite = [&](const uint32_t (&vv)[8][DB]) -> bool {
+        bool bad = false;
+#pragma unroll
+        for (int r2 = 0; r2 < 8; ++r2)
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+                bad = bad | ((vv[r2][db] & HT::EXP) == HT::EXP) | (((vv[r2][db] >> 16) & HT::EXP) == HT::EXP);
+        return __any(bad);
+    };
+
+    bool again = false;                           // (uniform) values were taken out of a product
+    for (int u = wave; u < 2 * P.total; u += NW) {
+        int slot0;
+        const unsigned ok = pairs_of(u, slot0);
+        if (!__any(ok != 0u)) continue;                                  // nothing here for any of the 32 rows
+        const bool all_ok = !__any(rvalid && ok != 0xffffu);
+
+        // keys, and the values with them: those arrive while the scores are computed
+        V8 kf[KS];
+        {
+            const char* kr = kbase + __umul24((unsigned)min(slot0 + n32, L.n - 1), pitch_bytes);
+#pragma unroll
+            for (int c = 0; c < KS; ++c) kf[c] = *(const V8*)(kr + 32 * c);
+        }
+        uint32_t vv[8][DB];
+        load_v(slot0, vv);
         f32x16 s;
 #pragma unroll
         for (int r = 0; r < 16; ++r) s[r] = 0.f;
@@ -213,57 +235,17 @@ __global__ __launch_bounds__(512, 2) void attn_short_kernel(Layout L, HeadMap hm
             l += (float)p0 + (float)p1;
             pw[r2] = bits16(p0) | (bits16(p1) << 16);
         }
-        // A value that is not finite would reach the rows that do not attend it through 0 * inf.  Where the unit is not
-        // attended as a whole such values are taken out of the product and added to the rows that do attend their keys,
-        // component by component, as the product would have: the matrix cores count per row and component the attended
-        // infinities of either sign (a NaN counts as both) and, as 0 * inf, those whose probability is zero.
-        if (!all_ok) {
-            bool any_bad = false;
+        // A value that is not finite would reach the rows that do not attend it through 0 * inf: where the unit is not
+        // attended as a whole it is taken out here and added below to the rows that do attend its key.
+        if (!all_ok && any_nonfinite(vv)) {
+            again = true;
 #pragma unroll
             for (int r2 = 0; r2 < 8; ++r2)
 #pragma unroll
-                for (int db = 0; db < DB; ++db)
-                    any_bad = any_bad | ((vv[r2][db] & HT::EXP) == HT::EXP) | (((vv[r2][db] >> 16) & HT::EXP) == HT::EXP);
-            if (__builtin_expect(__any(any_bad), 0)) {
-#pragma unroll 1
-                for (int kind = 0; kind < 3; ++kind) {                   // +inf, -inf, probability zero
-                    const float add = kind == 0 ? INFINITY : kind == 1 ? -INFINITY : __uint_as_float(0x7fc00000u);
-                    const uint32_t flip = kind == 1 ? 0x80008000u : 0u, keep = kind == 2 ? 0x7fff7fffu : 0xffffffffu;
-                    uint32_t at[8];                                      // the attended keys, two to a register
-#pragma unroll
-                    for (int r2 = 0; r2 < 8; ++r2) {
-                        const bool lo = ((ok >> (2 * r2)) & 1u) && (kind < 2 || (pw[r2] & 0xffffu) == 0u);
-                        const bool hi = ((ok >> (2 * r2 + 1)) & 1u) && (kind < 2 || (pw[r2] >> 16) == 0u);
-                        at[r2] = (lo ? HT::ONE : 0u) | (hi ? HT::ONE << 16 : 0u);
-                    }
-#pragma unroll
-                    for (int db = 0; db < DB; ++db) {
-                        f32x16 cnt;
-#pragma unroll
-                        for (int r = 0; r < 16; ++r) cnt[r] = 0.f;
-#pragma unroll
-                        for (int t = 0; t < 2; ++t) {
-                            u32x4 mk, ak;
-#pragma unroll
-                            for (int e = 0; e < 4; ++e) {
-                                mk[e] = inf_or_nan_marks<F16>((vv[4 * t + e][db] ^ flip) & keep);
-                                ak[e] = at[4 * t + e];
-                            }
-                            cnt = HT::mfma(__builtin_bit_cast(V8, mk), __builtin_bit_cast(V8, ak), cnt);
-                        }
-#pragma unroll
-                        for (int r = 0; r < 16; ++r) o[db][r] = cnt[r] > 0.f ? o[db][r] + add : o[db][r];
-                        __builtin_amdgcn_sched_barrier(0);       // (one block at a time: the registers are few)
-                    }
+                for (int db = 0; db < DB; ++db) {
+                    const uint32_t x = vv[r2][db];
+                    vv[r2][db] = ((x & HT::EXP) == HT::EXP ? 0u : x & 0xffffu) | (((x >> 16) & HT::EXP) == HT::EXP ? 0u : x & 0xffff0000u);
                 }
-#pragma unroll
-                for (int r2 = 0; r2 < 8; ++r2)
-#pragma unroll
-                    for (int db = 0; db < DB; ++db) {
-                        const uint32_t x = vv[r2][db];
-                        vv[r2][db] = ((x & HT::EXP) == HT::EXP ? 0u : x & 0xffffu) | (((x >> 16) & HT::EXP) == HT::EXP ? 0u : x & 0xffff0000u);
-                    }
-            }
         }
 #pragma unroll
         for (int t = 0; t < 2; ++t) {                                    // 16 keys each
@@ -276,6 +258,46 @@ __global__ __launch_bounds__(512, 2) void attn_short_kernel(Layout L, HeadMap hm
             }
         }
         npairs += __popc(ok);
+    }
+    // Infinities and NaN that were taken out, component by component: the matrix cores count, per row and component, the
+    // infinities of either sign that the row attends (a NaN counts as both).  A walk of its own, so that the registers
+    // it takes are not taken from the one above.
+    if (again) {
+#pragma unroll 1
+        for (int u = wave; u < 2 * P.total; u += NW) {
+            int slot0;
+            const unsigned ok = pairs_of(u, slot0);
+            if (!__any(ok != 0u) || !__any(rvalid && ok != 0xffffu)) continue;
+            uint32_t vv[8][DB];
+            load_v(slot0, vv);
+            if (!any_nonfinite(vv)) continue;
+            uint32_t at[8];                                              // the attended keys, two to a register
+#pragma unroll
+            for (int r2 = 0; r2 < 8; ++r2)
+                at[r2] = ((ok >> (2 * r2)) & 1u ? HT::ONE : 0u) | ((ok >> (2 * r2 + 1)) & 1u ? HT::ONE << 16 : 0u);
+#pragma unroll 1
+            for (int neg = 0; neg < 2; ++neg) {
+                const uint32_t flip = neg ? 0x80008000u : 0u;
+#pragma unroll
+                for (int db = 0; db < DB; ++db) {
+                    f32x16 cnt;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) cnt[r] = 0.f;
+#pragma unroll
+                    for (int t = 0; t < 2; ++t) {
+                        u32x4 mk, ak;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            mk[e] = inf_or_nan_marks<F16>(vv[4 * t + e][db] ^ flip);
+                            ak[e] = at[4 * t + e];
+                        }
+                        cnt = HT::mfma(__builtin_bit_cast(V8, mk), __builtin_bit_cast(V8, ak), cnt);
+                    }
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) o[db][r] = cnt[r] > 0.f ? o[db][r] + (neg ? -INFINITY : INFINITY) : o[db][r];
+                }
+            }
+        }
     }
     l += __shfl_xor(l, 32, 64);
     npairs += __shfl_xor(npairs, 32, 64);
