@@ -353,16 +353,22 @@ __global__ __launch_bounds__(512, 2) void attn_short_kernel(Layout L, HeadMap hm
 
 }  // namespace
 
-// Where one launch of short chains beats the staged tiles: while (nearly) every work-group of 32 rows has a compute unit of
-// its own.  Attention alone, tiled / this kernel (us): 12 heads of 64 at 512 tokens (192 groups) 20.9 / 13.5, at 1024 (384)
-// 28.1 / 23.7, at 1536 (576) 35.7 / 42.9; 32/8 heads of 128 at 256 tokens (256) 21.3 / 17.3, at 512 (512) 26.4 / 35.3;
-// 40 heads of 96 at 256 tokens (320) 20.0 / 17.2; 15 heads of 80 at 768 (360) 27.1 / 26.5; 2 heads of 64 at 4096 (256) 71.5 / 62.6.
+// Where one launch of short chains beats the staged tiles: while every work-group of 32 rows has a compute unit of its own.
+// Causal launches may have some more (their work-groups differ in length and the first ones end early; 64 components leave
+// room for two on a unit), non-causal ones no more: their 257th waits for a whole walk.  Past 64 components the walk itself
+// is slower per key on the masked layout, so that it may not be long; 96 of them fill the 32-component blocks that 80 leave empty.
+// Attention alone, tiled / this kernel (us), masked layout, K = 4 top-2, measured over 128 .. 8192 tokens and 48 .. 1024 groups:
+//   64:  512 tokens, 192 groups 20.3 / 12.6;  1024, 384 27.8 / 22.3;  4096, 256 70.2 / 57.8;  non-causal 1024, 256 26.9 / 20.0, 288 27.5 / 35.3
+//   80:  2048, 256 47.5 / 45.9;  4096, 256 80.8 / 82.7;      96: 1024, 320 33.1 / 23.0
+//   128: 256, 256 21.0 / 15.8;  1024, 256 34.3 / 33.4;  2048, 256 53.9 / 56.6, dense 47.7 / 41.9;  non-causal 512, 256 25.4 / 22.7, 288 26.4 / 39.5
 bool short_attention(const Layout& L)
 {
     const long long groups = (long long)L.B * L.Hq * ((L.n + 31) / 32);
     const bool fits = L.dtype != 0 && L.NC == 1 && (L.masked || L.dense) && !L.soft && !L.local_only && !L.merge_prev && L.BQ == 128 &&
                       L.d <= 128 && (uint64_t)L.ks[2] * 2 < (1u << 24) && (uint64_t)L.n * (uint64_t)L.ks[2] * 2 < 0xffffffffull;
-    return fits && L.n <= 4096 && groups <= (L.d <= 64 ? 384 : 320);
+    const int most = L.causal ? (L.d <= 64 ? 384 : (L.d == 128 && L.n <= 256) ? 256 : 320) : (L.d <= 64 && L.n <= 256) ? 384 : 256;
+    const int longest = (L.dense || L.d == 64 || L.d == 96) ? 4096 : L.d == 80 ? 2048 : 1024;
+    return fits && groups <= most && L.n <= longest;
 }
 
 hipError_t launch_attn_short(const Layout& L, const HeadMap& hm, const void* q, const void* k, const void* v, char* ws,
