@@ -411,7 +411,7 @@ hipError_t launch_project(const RouteLayout& R, const void* hidden, const float*
     const int cb = (R.dg + 15) / 16, rc = 128 / (int)sizeof(T);
     const size_t stage = 2 * ((size_t)nw * 16 * A_ROW + (size_t)rc * (cb * 16 + (cb > 1 ? 16 : 0)) * 4);
     const size_t tail = (size_t)nw * 16 * (R.dg + 1 + (R.K | 1)) * sizeof(double);
-    const size_t lds = stage > tail ? stage : tail;      // at most 51 KB (8 wavefronts, d_g <= 16) or 51 KB (4, d_g = 64)
+    const size_t lds = stage > tail ? stage : tail;      // at most 51 KB (8 wavefronts, d_g <= 16) or 58 KB (4, d_g = 64, 16-bit rows)
 #define FOCUS_PROJ(DG, NW)                                                                                   \
     hipLaunchKernelGGL((route_project_kernel<T, DG, NW>), grid, dim3(64 * NW), lds, st, R, (const T*)hidden, wg, \
                        cent, ws, masks, soft)

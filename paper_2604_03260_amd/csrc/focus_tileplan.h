@@ -108,8 +108,7 @@ __device__ inline bool plan_query_tile(const Layout& L, const char* __restrict__
     const uint32_t mymask = clsmask[c];
     for (int c2 = tid; c2 < NC; c2 += nthr) {
         const int pre_hi = kbc[(size_t)bh_i * NC + c2] + P.cnt_hi[c2];
-        // the local layout's one class holds every key: all of them count as "window only" there
-        const bool inter = !L.local_only && (clsmask[c2] & mymask) != 0;
+        const bool inter = (clsmask[c2] & mymask) != 0;
         const int koff = kco[c2];
         int a = 0, b = 0;
         // Coarse classes that share a super-group hold pairs of both sets: set B then visits their window span
@@ -148,10 +147,6 @@ __device__ inline bool plan_query_tile(const Layout& L, const char* __restrict__
             const int lo_blk = (x_in <= 0) ? 0 : min(L.nblk, (x_in + SB - 1) / SB);
             ib = max(a, (koff + kbc[(size_t)lo_blk * NC + c2] + KT - 1) / KT);
             ie = min(b, (koff + cnt_below) / KT);
-            if (L.local_only) {          // position order: slot = position, so the bounds are exact per key tile
-                ib = max(a, (max(x_in, 0) + KT - 1) / KT);
-                ie = min(b, (i_lo + 1) / KT);
-            }
             if (ie < ib) ie = ib;
         }
         P.ibeg[c2] = ib;
