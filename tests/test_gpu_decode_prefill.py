@@ -75,8 +75,8 @@ def test_prefill_from_token_masks_is_exact():
 
 @pytest.mark.parametrize("d,dtype,K,topk", [(64, "bf16", 4, 2), (80, "f16", 8, 1), (96, "bf16", 8, 2), (128, "f16", 4, 2)])
 def test_step_with_rows_of_the_next_round_in_flight(d, dtype, K, topk):
-    """Launches of 400 to 544 work-groups of 512-entry chunks keep the next round's rows in flight: a ragged last chunk,
-    scan and list walks, against attention in float64 over the state's own memberships."""
+    """Launches of about 430 work-groups of 512-entry chunks (the longest ones, with two work-groups on most compute units):
+    a ragged last chunk, scan and list walks, against attention in float64 over the state's own memberships."""
     B, Hq, Hkv, n = 1, 16, 8, 27000 + d
     dt = {"bf16": torch.bfloat16, "f16": torch.float16}[dtype]
     g = torch.Generator(device="cuda")

@@ -89,6 +89,14 @@ def test_route_small(B, n, dm, dg, K, topk, dtype, iters):
     check_route(wl, rin, iters)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("n,dm,K,topk,iters", [(333, 264, 32, 4, 10), (64, 72, 4, 1, 0)])
+def test_route_64_outputs_of_16_bit_rows(dtype, n, dm, K, topk, iters):
+    """The largest staging buffers of the projection (58 KB)."""
+    wl = workloads.Workload("r", 62, 2, 1, 1, n, 64, dtype, K, topk, 16, mixture=3)
+    check_route(wl, workloads.make_router_inputs(wl, "cuda", d_model=dm, d_g=64), iters)
+
+
 def test_route_is_deterministic():
     wl = workloads.Workload("r", 61, 2, 1, 1, 3000, 64, "bf16", 8, 2, 16)
     rin = workloads.make_router_inputs(wl, "cuda", d_model=512)
