@@ -57,12 +57,12 @@ double window_waste(const focus::Layout& L, double none)
 // 128-row tile to a 64-key tile, for memberships that are uniform over the groups (with few live classes the class
 // tiles would visit less than estimated: the masked layout then takes up to the number of live disjoint classes as
 // long); `visit` is a masked visit in class visits.
-// The constants are fitted to measured pairs (focus_assign + focus_attn_fwd of both layouts; 1 to 8 sequences, 4 to 40 heads of
-// 64 to 256, K = 4 .. 32, top 1 .. 4, windows 64 .. 4096, with and without a softcap).  How often the choice was more than 2 %
+// The constants are fitted to 6196 measured pairs (focus_assign + focus_attn_fwd of both layouts; 1 to 8 sequences, 3 to 64 heads
+// of 64 to 256, K = 4 .. 32, top 1 .. 4, windows 64 .. 4096, with and without a softcap).  How often the choice was more than 2 %
 // slower than the other layout, and by how much at most:
-//   one pass, causal      922 pairs,   256 .. 262144 tokens:  10, 1.09x     two passes  631, 16384 .. 262144: 20, 1.18x
-//   one pass, non-causal  672 pairs,   512 ..  49152 tokens:  14, 1.14x     coarse      400,   256 .. 262144:  0
-//   fp32 causal           288 pairs,   256 ..  16384 tokens:   3, 1.04x     non-causal  230,   256 ..   8192: 10, 1.25x
+//   one pass, causal     1981 pairs,   256 .. 262144 tokens:  29, 1.14x     two passes  664, 16384 .. 262144: 22, 1.18x
+//   one pass, non-causal 1752 pairs,   300 ..  49152 tokens:  39, 1.18x     coarse      396,   256 .. 262144:  0
+//   fp32 causal           748 pairs,   256 ..  65536 tokens:   7, 1.10x     non-causal  655,   256 ..  32768: 22, 1.25x
 // Non-causal launches of a few hundred work-groups end in steps of whole rounds of the chip, which no visit count sees.
 // Both sides at 16/4 heads of 128, w=1024 (us): K=4 top-2: class 1125 / masked 1096 at 16384 tokens, 1549 / 1620 at 20000,
 // 3545 / 4132 at 32768;  K=8 top-3: 1967 / 1145, 5747 / 4294 at 32768;  coarse K=32 top-2 at 8/2 heads: 84900 / 68900 at 196608.
@@ -70,8 +70,8 @@ struct LayoutCost { double lost, visit, lost_window, launches; };
 
 bool prefer_masked(const focus::Layout& L, double none, bool two_pass, int BQ)
 {
-    static const LayoutCost ONE = {5.4, 1.28, 2.1, 300.0}, TWO = {3.0, 1.22, 0.0, 150.0}, NONCAUSAL = {2.0, 1.27, 1.55, 4400.0},
-                            COARSE = {0.6, 0.415, 0.0, 0.0}, F32 = {8.7, 2.19, 0.0, 3400.0}, F32_NONCAUSAL = {1.5, 1.3, 0.0, 440.0};
+    static const LayoutCost ONE = {6.3, 1.365, 2.5, 0.0}, TWO = {3.0, 1.22, 0.0, 0.0}, NONCAUSAL = {2.15, 1.22, 1.35, 3400.0},
+                            COARSE = {0.6, 0.415, 0.0, 0.0}, F32 = {2.2, 1.1, 0.0, 720.0}, F32_NONCAUSAL = {1.05, 1.27, 0.0, 430.0};
     const LayoutCost& c = L.dtype == FOCUS_F32 ? (L.causal ? F32 : F32_NONCAUSAL) : L.coarse ? COARSE : two_pass ? TWO
                           : L.causal ? ONE : NONCAUSAL;
     const double n = L.n, w = L.window, NC = L.NC, KT = focus::KT, rows = focus::BQ_VECTOR;
