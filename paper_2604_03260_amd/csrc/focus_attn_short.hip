@@ -6,7 +6,8 @@
 // V staged by a launch before it and a second launch for rows that need a softmax reference, and walks up to n/64 tiles
 // one after the other in work-groups that are too few to fill the chip: at 512 tokens all of it is latency.
 // Here a chain is n/256 units and there is one launch.  V is read row-major with 2-byte loads, which is why the tiled
-// kernel wins as soon as throughput counts (see short_attention below).
+// kernel wins as soon as throughput counts (see short_attention below).  With 128 components 15 to 17 of the registers of a
+// unit's operands spill (64 to 72 bytes of scratch a lane).
 #include "focus_internal.h"
 #include "focus_tileplan.h"
 
