@@ -33,7 +33,8 @@ template <> __device__ inline uint16_t from_f32<uint16_t>(float v) { return f32_
 template <> __device__ inline f16_bits from_f32<f16_bits>(float v) { return f16_bits{f32_to_f16_bits(v)}; }
 
 // SUB: keys per inner step (the fp32 staging of a step's keys and values fills 2 * SUB * D * 4 bytes of LDS)
-template <typename T, int D, int SUB>
+// SOFT: the soft gate, a kernel of its own because the watch for values that are not finite costs 3 %
+template <typename T, int D, int SUB, bool SOFT>
 __global__ __launch_bounds__(BQ_VECTOR * (D / 32)) void attn_simple_kernel(Layout L, HeadMap hm, const T* __restrict__ q,
                                                                     const T* __restrict__ k, const T* __restrict__ v,
                                                                     const float* __restrict__ g,
@@ -97,9 +98,10 @@ __global__ __launch_bounds__(BQ_VECTOR * (D / 32)) void attn_simple_kernel(Layou
                 const bool real = kp != KPOS_PAD && t < d;
                 s_k[e] = real ? to_f32<T>(kbase[(size_t)kp * kpitch + t]) : 0.f;
                 s_v[e] = real ? to_f32<T>(vbase[(size_t)kp * kpitch + t]) : 0.f;
-                bad = bad || !__builtin_isfinite(s_v[e]);
+                if constexpr (!SOFT) bad = bad || !__builtin_isfinite(s_v[e]);
             }
-            bad = __syncthreads_or(bad);
+            if constexpr (SOFT) __syncthreads();
+            else bad = __syncthreads_or(bad);
             float s[SUB];
             float mx = -INFINITY;
 #pragma unroll
@@ -114,7 +116,7 @@ __global__ __launch_bounds__(BQ_VECTOR * (D / 32)) void attn_simple_kernel(Layou
                 if (cap > 0.f) x = cap * tanhf(x / cap);
                 const int kp = s_kpos[kk];
                 const int dlt = qpos - kp;               // pads sit at INT_MAX
-                if (L.soft) {
+                if constexpr (SOFT) {
                     // Sec. 2 Eq. 2: every causal pair; outside the window the score is scaled by
                     // sigmoid(lambda * g_i . g_j) = 1 / (1 + 2^(gate_slope * g_i . g_j))
                     const bool okc = rvalid && kp != KPOS_PAD && dlt >= 0;
@@ -296,9 +298,11 @@ hipError_t launch_attn_simple(const Layout& L, const HeadMap& hm, const void* q,
                               const float* g, char* ws, void* out, float* lse, int32_t* row_pairs, hipStream_t st)
 {
     dim3 grid(L.NT, L.B * L.Hq);
-#define FOCUS_LAUNCH_SIMPLE(T, D, SUB)                                                                 \
-    hipLaunchKernelGGL((attn_simple_kernel<T, D, SUB>), grid, dim3(BQ_VECTOR*(D / 32)), 0, st, L, hm, (const T*)q, \
+#define FOCUS_LAUNCH_SIMPLE_S(T, D, SUB, SOFT)                                                         \
+    hipLaunchKernelGGL((attn_simple_kernel<T, D, SUB, SOFT>), grid, dim3(BQ_VECTOR*(D / 32)), 0, st, L, hm, (const T*)q, \
                        (const T*)k, (const T*)v, g, (const char*)ws, (T*)out, lse, row_pairs)
+#define FOCUS_LAUNCH_SIMPLE(T, D, SUB)                                                                 \
+    do { if (L.soft) FOCUS_LAUNCH_SIMPLE_S(T, D, SUB, true); else FOCUS_LAUNCH_SIMPLE_S(T, D, SUB, false); } while (0)
 #define FOCUS_LAUNCH_SIMPLE_T(T)                                                                       \
     do {                                                                                               \
         if (L.dp == 64) FOCUS_LAUNCH_SIMPLE(T, 64, 32);                                                \
@@ -310,6 +314,7 @@ hipError_t launch_attn_simple(const Layout& L, const HeadMap& hm, const void* q,
     else FOCUS_LAUNCH_SIMPLE_T(uint16_t);
 #undef FOCUS_LAUNCH_SIMPLE_T
 #undef FOCUS_LAUNCH_SIMPLE
+#undef FOCUS_LAUNCH_SIMPLE_S
     return hipGetLastError();
 }
 
