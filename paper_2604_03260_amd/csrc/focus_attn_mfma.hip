@@ -1041,7 +1041,7 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT == 2) ? 1 : 8 / 
         }
     }
     if constexpr (MASKED) {
-        if (__any(vbad != 0u))
+        if (__builtin_expect(__any(vbad != 0u), 0))
             add_nonfinite_values<F16>(L, (const unsigned*)kb_base, __builtin_amdgcn_readfirstlane(S.plan.t0[0]), total, qpos, mq_row,
                                       (const unsigned*)(ws + L.off_mk) + (size_t)bhk * L.n,
                                       v + (size_t)b * L.ks[0] + (size_t)hm.kv[h] * L.ks[1], hh, orow);
