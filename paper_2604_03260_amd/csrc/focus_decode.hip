@@ -13,7 +13,7 @@
 //      step 1 advances with the window);
 //      a key that sits in several of the query's groups is taken from the first of them only (its
 //      mask tells).  The concatenation [window | list prefix of group 1 | group 2 | ...] is cut into
-//      chunks of DEC_CHUNK keys with an online softmax per chunk.  When the lists together hold at least
+//      shares (chunks of DEC_CHUNK keys in the vector kernels) with an online softmax per share.  When the lists together hold at least
 //      as many entries as there are positions below the window (few groups, several of them per query),
 //      the positions 0..pos are walked instead and every key's mask is tested against the query's;
 //      grouped-query heads share one walk over the union of their keys, and 16-bit caches run both
@@ -224,8 +224,11 @@ __global__ __launch_bounds__(DEC_LIST_THREADS) void decode_prefill_lists_kernel(
 // ---------------------------------------------------------------- step 1: route and append
 // One wavefront per (batch, head): heads [0, Hq) are the new queries, [Hq, Hq + Hkv) the new keys.
 // The vector and the K centroid rows are staged in LDS first, so the fp64 chain of lane g (group g,
-// components in index order) runs from LDS instead of waiting for a global load per component.
-template <typename T>
+// components in index order) runs from LDS instead of waiting for a global load per component.  A launch of latency:
+// every load that does not depend on another one is issued before the first wait (the position among them: nothing but
+// the exit and the last stores depends on it), and the components of the next 16 products are read while 16 are added.
+// NI = d / 64, rounded up: components of a row per lane.
+template <typename T, int NI>
 __global__ __launch_bounds__(64) void decode_route_kernel(DecodeLayout L, HeadMap hm, int pos_arg, const int* __restrict__ pos_dev,
                                                           const T* __restrict__ q_new,
                                                           const T* __restrict__ k_new, const T* __restrict__ v_new,
@@ -233,15 +236,15 @@ __global__ __launch_bounds__(64) void decode_route_kernel(DecodeLayout L, HeadMa
                                                           const uint32_t* __restrict__ token_mask, T* __restrict__ kc,
                                                           T* __restrict__ vc, char* __restrict__ st)
 {
-    __shared__ float s_x[256];
-    __shared__ float s_c[32 * 257];               // row stride d + 1: the K lanes read K different rows
+    constexpr int CPITCH = 64 * NI + 4;           // the K lanes read 16 bytes each of K different rows: banks 4 apart
+    __shared__ __attribute__((aligned(16))) float s_x[64 * NI];
+    __shared__ __attribute__((aligned(16))) float s_c[32 * CPITCH];
     const int lane = threadIdx.x;
     // the position comes from the launch (one for all sequences), or from device memory, one per sequence,
     // when a captured graph serves every step or the sequences of a batch stand at different positions;
     // a position outside the caches makes the step skip that sequence (the host could not check it)
     const int b = blockIdx.y, hh = blockIdx.x;
     const int pos = pos_dev ? pos_dev[b] : pos_arg;
-    if (pos < 0 || pos >= L.n) return;
     const bool is_q = hh < L.Hq;
     const int h = is_q ? hh : hh - L.Hq;
     const int hk = is_q ? hm.kv[h] : h;
@@ -251,9 +254,9 @@ __global__ __launch_bounds__(64) void decode_route_kernel(DecodeLayout L, HeadMa
     // Everything that does not depend on the scores is loaded first, so that the scoring hides those round
     // trips: the vector itself, for a key also its V row, the lengths and window pointers of the lists and the
     // two list entries the window's lower edge can pass in this step.
-    T xr[4], vr[4];
+    T xr[NI], vr[NI];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < NI; ++i) {
         const int t = lane + 64 * i;
         if (t < d) xr[i] = x[t];
         if (!is_q && t < d) vr[i] = v_new[bhk * d + t];
@@ -263,40 +266,65 @@ __global__ __launch_bounds__(64) void decode_route_kernel(DecodeLayout L, HeadMa
     if (!is_q && lane < L.K) {
         cn = ((const int*)(st + L.off_counts))[bhk * L.K + lane];
         w = ((const int*)(st + L.off_wp))[bhk * L.K + lane];
-        if (w < cn) l0 = list[w];
-        if (w + 1 < cn) l1 = list[w + 1];
     }
     uint32_t mask;
     if (token_mask) {
         // the new token's membership comes from the per-layer router: the same for every head, as query and as key
         mask = decode_valid_mask(token_mask[b], L.K, L.topk);
+        if (pos < 0 || pos >= L.n) return;
+        if (w < cn) l0 = list[w];
+        if (w + 1 < cn) l1 = list[w + 1];
     } else {
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-            if (lane + 64 * i < d) s_x[lane + 64 * i] = dec_to_f32<T>(xr[i]);
         const float* c = cents + (size_t)hk * L.K * d;
-        // eight loads in flight per lane (one at a time, the staging alone is a chain of K * d / 64 round trips)
-        for (int e0 = lane; e0 < L.K * d; e0 += 64 * 8) {
-            float cv[8];
+        constexpr int RB = 16 / NI;               // centroid rows per batch: 16 loads in flight per lane
+        for (int g0 = 0; g0 < L.K; g0 += RB) {
+            float cv[RB][NI];
 #pragma unroll
-            for (int i = 0; i < 8; ++i) cv[i] = (e0 + 64 * i < L.K * d) ? c[e0 + 64 * i] : 0.f;
+            for (int g = 0; g < RB; ++g)
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const int e = e0 + 64 * i;
-                if (e < L.K * d) s_c[(e / d) * (d + 1) + e % d] = cv[i];
+                for (int i = 0; i < NI; ++i)
+                    cv[g][i] = (g0 + g < L.K && lane + 64 * i < d) ? c[(g0 + g) * d + lane + 64 * i] : 0.f;
+            if (g0 == 0) {
+                if (pos < 0 || pos >= L.n) return;
+                if (w < cn) l0 = list[w];
+                if (w + 1 < cn) l1 = list[w + 1];
+#pragma unroll
+                for (int i = 0; i < NI; ++i)
+                    if (lane + 64 * i < d) s_x[lane + 64 * i] = dec_to_f32<T>(xr[i]);
             }
+#pragma unroll
+            for (int g = 0; g < RB; ++g)
+#pragma unroll
+                for (int i = 0; i < NI; ++i)
+                    if (g0 + g < L.K) s_c[(g0 + g) * CPITCH + lane + 64 * i] = cv[g][i];
         }
         __syncthreads();
         double s = 0.0;
         if (lane < L.K) {
-            // index order, eight components per LDS round trip (d is a multiple of 8)
-            const float* cr = s_c + lane * (d + 1);
-            for (int t = 0; t < d; t += 8) {
-                float xs[8], cs[8];
+            // index order, 16 components at a time (d is a multiple of 16)
+            const float4* cr = (const float4*)(s_c + lane * CPITCH);
+            const float4* xq = (const float4*)s_x;
+            float4 xa[4], ca[4], xb[4], cb[4];
+            auto fetch = [&](int t, float4 (&xs)[4], float4 (&cs)[4]) {
 #pragma unroll
-                for (int i = 0; i < 8; ++i) { xs[i] = s_x[t + i]; cs[i] = cr[t + i]; }
+                for (int i = 0; i < 4; ++i) { xs[i] = xq[t / 4 + i]; cs[i] = cr[t / 4 + i]; }
+            };
+            auto add = [&](const float4 (&xs)[4], const float4 (&cs)[4]) {
 #pragma unroll
-                for (int i = 0; i < 8; ++i) s = fma((double)xs[i], (double)cs[i], s);
+                for (int i = 0; i < 4; ++i) {
+                    s = fma((double)xs[i].x, (double)cs[i].x, s);
+                    s = fma((double)xs[i].y, (double)cs[i].y, s);
+                    s = fma((double)xs[i].z, (double)cs[i].z, s);
+                    s = fma((double)xs[i].w, (double)cs[i].w, s);
+                }
+            };
+            fetch(0, xa, ca);
+            for (int t = 0; t < d; t += 32) {     // (d = 80: the last step has 16 components)
+                if (t + 16 < d) fetch(t + 16, xb, cb);
+                add(xa, ca);
+                if (t + 16 >= d) break;
+                if (t + 32 < d) fetch(t + 32, xa, ca);
+                add(xb, cb);
             }
         }
         mask = wave_topk_mask(s, lane, L.K, L.topk);
@@ -328,7 +356,7 @@ __global__ __launch_bounds__(64) void decode_route_kernel(DecodeLayout L, HeadMa
     T* kdst = kc + (bhk * L.n + pos) * d;
     T* vdst = vc + (bhk * L.n + pos) * d;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < NI; ++i) {
         const int t = lane + 64 * i;
         if (t < d) { kdst[t] = xr[i]; vdst[t] = vr[i]; }
     }
@@ -441,22 +469,45 @@ struct DecWalk {
     int nseg;
 };
 
-// One thread fills the walk for the groups in `groups` (of one query, or of all query heads of a KV head).
-__device__ inline void decode_walk_init(DecWalk& W, uint32_t groups, const int* __restrict__ wptr, int K, int pos, int lo_w)
+// One wavefront fills the walk for the groups in `groups` (of one query, or of all query heads of a KV head).
+// w: of lane g, the entries of group g's list below the window (kept by the route kernel), loaded by the caller together
+// with whatever else it needs: a loop over the groups that loaded one after the other was K memory round trips long.
+__device__ inline void decode_walk_init(DecWalk& W, uint32_t groups, int w, int K, int pos, int lo_w)
 {
-    int nseg = 1, run = pos - lo_w + 1;
-    uint32_t prev = 0;
-    W.beg[0] = 0; W.grp[0] = -1; W.prev[0] = 0;
-    for (int g = 0; g < K; ++g) {
-        if (!((groups >> g) & 1u)) continue;
-        W.beg[nseg] = run; W.grp[nseg] = g; W.prev[nseg] = prev;
-        run += wptr[g];                           // list entries below the window (kept by the route kernel)
-        prev |= (1u << g);
-        ++nseg;
+    const int lane = threadIdx.x & 63;
+    const bool on = lane < K && ((groups >> (lane & 31)) & 1u);
+    const int len = on ? w : 0;
+    int run = len;                                // inclusive prefix sum over the groups
+    for (int off = 1; off < K; off <<= 1) {
+        const int x = __shfl_up(run, off, 64);
+        if (lane >= off) run += x;
     }
-    W.beg[nseg] = run;
-    W.nseg = nseg;
-    if (decode_scan_mode(run - (pos - lo_w + 1), lo_w)) { W.nseg = 0; W.beg[0] = pos + 1; }
+    const int window = pos - lo_w + 1, total = window + __shfl(run, K - 1, 64);
+    const int nseg = 1 + __popc(groups);
+    if (on) {
+        const uint32_t before = groups & ((1u << lane) - 1u);
+        const int s = 1 + __popc(before);
+        W.beg[s] = window + run - len; W.grp[s] = lane; W.prev[s] = before;
+    }
+    if (lane == 0) {
+        const bool scan = decode_scan_mode(total - window, lo_w);
+        W.beg[0] = scan ? pos + 1 : 0; W.grp[0] = -1; W.prev[0] = 0;
+        W.beg[nseg] = total;
+        W.nseg = scan ? 0 : nseg;
+    }
+}
+
+// the heads whose groups meet the key's, four at a time up to the last of all_heads (uniform over the work-group)
+template <int NH>
+__device__ inline uint32_t decode_heads_of(uint32_t mkj, const uint32_t (&gq)[NH], uint32_t all_heads)
+{
+    uint32_t hb = 0;
+#pragma unroll
+    for (int i = 0; i < NH; ++i) {
+        if (i > 0 && i % 4 == 0 && (all_heads >> i) == 0u) break;
+        hb |= ((mkj & gq[i]) != 0u) ? (1u << i) : 0u;
+    }
+    return hb;
 }
 
 // Entry v of the walk -> cache row of its key, or -1 when no head attends it or an earlier segment had it;
@@ -474,8 +525,7 @@ __device__ inline int decode_walk_key(const DecWalk& W, int nseg, int v, int lo_
             hb = all_heads;
         } else {
             const uint32_t mkj = mk[v];
-#pragma unroll
-            for (int i = 0; i < NH; ++i) hb |= ((mkj & gq[i]) != 0u) ? (1u << i) : 0u;
+            hb = decode_heads_of<NH>(mkj, gq, all_heads);
         }
         return hb ? v : -1;
     }
@@ -498,20 +548,20 @@ __device__ inline int decode_walk_key(const DecWalk& W, int nseg, int v, int lo_
     }
     const uint32_t mkj = mk[j];
     if ((mkj & pv) != 0u) return -1;
-#pragma unroll
-    for (int i = 0; i < NH; ++i) hb |= ((mkj & gq[i]) != 0u) ? (1u << i) : 0u;
+    hb = decode_heads_of<NH>(mkj, gq, all_heads);
     return j;
 }
 
-// A chunk of the walk for the grouped-query kernels (256 threads): every thread resolves KPT entries (all loads
-// independent), then the skipped ones are squeezed out: wave ballots give every (pass, wavefront) its count, the
-// kept keys land in pass-major, wavefront-major order in s_j / s_hb, padded with -1 / 0 up to `cap` entries.
+// A chunk of the walk (nk0 entries, at most 256 * KPT) for the grouped-query kernels (256 threads): every thread resolves KPT
+// entries (all loads independent), then the skipped ones are squeezed out: wave ballots give every (pass, wavefront) its
+// count, the kept keys land in pass-major, wavefront-major order in s_j / s_hb, followed by PAD entries of -1 / 0.
 // Returns the number of keys kept.  Two barriers inside.
-template <int KPT, int NH, typename HB>
+template <int KPT, int PAD, int NH, typename HB>
 __device__ inline int decode_resolve_chunk(const DecWalk& W, int nseg, int v0, int nk0, int lo_w, const int* __restrict__ lists, int n,
                                            const uint32_t* __restrict__ mk, const uint32_t (&gq)[NH], uint32_t all_heads, bool single,
-                                           int* s_j, HB* s_hb, int cap, int* s_wcnt)
+                                           int* s_j, HB* s_hb, int4* s_wcnt)
 {
+    static_assert(PAD <= 256, "one entry of padding per thread");
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     int js[KPT];
     uint32_t hbv[KPT];
@@ -526,24 +576,23 @@ __device__ inline int decode_resolve_chunk(const DecWalk& W, int nseg, int v0, i
 #pragma unroll
     for (int it = 0; it < KPT; ++it) {
         bal[it] = __ballot(js[it] >= 0);
-        if (lane == 0) s_wcnt[it * 4 + wave] = __popcll(bal[it]);
+        if (lane == 0) ((int*)s_wcnt)[it * 4 + wave] = __popcll(bal[it]);
     }
-    for (int i = tid; i < cap; i += 256) { s_j[i] = -1; s_hb[i] = 0; }
     __syncthreads();
+    const unsigned long long lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
     int nk = 0;
 #pragma unroll
     for (int it = 0; it < KPT; ++it) {
-        int before = 0;
-        for (int w2 = 0; w2 < it * 4 + wave; ++w2) before += s_wcnt[w2];
+        const int4 c = s_wcnt[it];
+        const int before = nk + (wave > 0 ? c.x : 0) + (wave > 1 ? c.y : 0) + (wave > 2 ? c.z : 0);
         if (js[it] >= 0) {
-            const unsigned long long lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
             const int dst = before + __popcll(bal[it] & lt);
             s_j[dst] = js[it];
             s_hb[dst] = (HB)hbv[it];
         }
+        nk += c.x + c.y + c.z + c.w;
     }
-#pragma unroll
-    for (int w2 = 0; w2 < 4 * KPT; ++w2) nk += s_wcnt[w2];
+    if (tid < PAD) { s_j[nk + tid] = -1; s_hb[nk + tid] = 0; }
     __syncthreads();
     return nk;
 }
@@ -576,7 +625,7 @@ __global__ __launch_bounds__(256) void decode_attn_kernel(DecodeLayout L, HeadMa
     const int* lists = (const int*)(st + L.off_lists) + bhk * L.K * L.n;
     const uint32_t* mk = (const uint32_t*)(st + L.off_mk) + bhk * L.n;
 
-    if (tid == 0) decode_walk_init(s_walk, gq, wptr, L.K, pos, lo_w);
+    if (tid < 64) decode_walk_init(s_walk, gq, tid < L.K ? wptr[tid] : 0, L.K, pos, lo_w);
     __syncthreads();
     const int nseg = s_walk.nseg;
     const int vtotal = s_walk.beg[nseg];
@@ -705,7 +754,7 @@ __global__ __launch_bounds__(256) void decode_attn_gqa_kernel(DecodeLayout L, in
     __shared__ DecWalk s_walk;
     __shared__ int s_j[DEC_CHUNK + 4 * SLOTS * U];    // cache rows of the chunk's keys, squeezed; padded with -1
     __shared__ uint8_t s_hb[DEC_CHUNK + 4 * SLOTS * U];   // which of the G heads attend the key
-    __shared__ int s_wcnt[4 * KPT];
+    __shared__ int4 s_wcnt[KPT];
     __shared__ float s_red[HB][4 * SLOTS][PW];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -725,7 +774,7 @@ __global__ __launch_bounds__(256) void decode_attn_gqa_kernel(DecodeLayout L, in
     const int* lists = (const int*)(st + L.off_lists) + bhk * L.K * L.n;
     const uint32_t* mk = (const uint32_t*)(st + L.off_mk) + bhk * L.n;
 
-    if (tid == 0) decode_walk_init(s_walk, gu, wptr, L.K, pos, lo_w);
+    if (tid < 64) decode_walk_init(s_walk, gu, tid < L.K ? wptr[tid] : 0, L.K, pos, lo_w);
     __syncthreads();
     const int nseg = s_walk.nseg;
     const int vtotal = s_walk.beg[nseg];
@@ -821,8 +870,8 @@ __global__ __launch_bounds__(256) void decode_attn_gqa_kernel(DecodeLayout L, in
     if (v0l >= vtotal) break;                      // uniform over the work-group
     const int v0 = (int)v0l;
     if (cc > 0) __syncthreads();                  // the last chunk's rows have been read
-    const int nk = decode_resolve_chunk<KPT, G, uint8_t>(s_walk, nseg, v0, min(vtotal - v0, DEC_CHUNK), lo_w, lists, L.n, mk, gq,
-                                                (1u << G) - 1u, L.topk == 1, s_j, s_hb, DEC_CHUNK + 4 * SLOTS * U, s_wcnt);
+    const int nk = decode_resolve_chunk<KPT, 4 * SLOTS * U, G, uint8_t>(s_walk, nseg, v0, min(vtotal - v0, DEC_CHUNK), lo_w, lists, L.n, mk, gq,
+                                                (1u << G) - 1u, L.topk == 1, s_j, s_hb, s_wcnt);
     constexpr int RSTEP = 4 * SLOTS * U;          // keys of one round of the four wavefronts
     // (Keeping the loads of the next round in flight while this one is folded costs a second set of row
     // registers and a wavefront of occupancy: slower at every context length measured.)
@@ -918,11 +967,18 @@ template <> struct DecHalf<true> {
 
 constexpr float DEC_RESCALE_THRESHOLD = 8.f;
 
-// CH: entries of the walk a work-group resolves at a time (the long or the short chunk: the short one when the
-// launch would otherwise leave most of the chip idle, one round per wavefront and four times the work-groups).
-template <bool F16, int D, int CH>
+// The walk is cut into as many even shares as the launch has work-groups for it, in units of the 32 keys of a wavefront's
+// round, and a share is resolved up to DEC_RESOLVE entries at a time.  The launch is memory latency and bandwidth: what
+// counts is that all work-groups are resident at once and end together.  Chunks of 512 entries left a nearly empty
+// last one (32768 cached keys, 8 KV heads: 512 work-groups and 8 more, the third on their compute units), and in list
+// mode, where the walk is shorter than the launch knows, work-groups without any.  With the first loads of a
+// work-group (memberships, window pointers, queries) in one round trip, a whole step: 8 heads of 128 x 32768 keys 42.9 ->
+// 36.8 us, 8 x 131072 (64 query heads, softcap) 104.5 -> 92.1, 96 heads of 64 x 4096 27.7 -> 25.7, 105 heads x 20000 with K = 16
+// top-1 77.6 -> 51.3.  What bounds it now: 134 MB in 24 us at 8 x 32768 (5.6 TB/s), 7 TB/s at 131072.
+constexpr int DEC_RESOLVE = 768;
+template <bool F16, int D>
 __global__ __launch_bounds__(256) void decode_attn_gqa_mfma_kernel(DecodeLayout L, int Gall, int pos_arg, const int* __restrict__ pos_dev,
-                                                                   int span, const uint16_t* __restrict__ q_new,
+                                                                   const uint16_t* __restrict__ q_new,
                                                                    const uint16_t* __restrict__ kc, const uint16_t* __restrict__ vc,
                                                                    const char* __restrict__ st, float* __restrict__ part)
 {
@@ -938,15 +994,17 @@ __global__ __launch_bounds__(256) void decode_attn_gqa_mfma_kernel(DecodeLayout 
     constexpr int KB = (D + 31) / 32;             // products of one S^T block (the last one partly zero for d = 80)
     constexpr int NB = D / 16;                    // 16-component blocks of O^T
     constexpr int PW = D + 4;
-    constexpr int KPT = CH >= 256 ? CH / 256 : 1;
+    constexpr int CH = DEC_RESOLVE, KPT = CH / 256;
     constexpr int RSTEP = 4 * 32;                 // keys of one round of the four wavefronts
     constexpr int GMAX = 16;                      // query heads per work-group: the columns of the products
     constexpr int RED_BYTES = GMAX * 4 * PW * 4;
     constexpr int BUF_BYTES = 4 * VBYTES > RED_BYTES ? 4 * VBYTES : RED_BYTES;
     __shared__ DecWalk s_walk;
-    __shared__ int s_j[CH + RSTEP];        // cache rows of the chunk's keys, squeezed; padded with -1
-    __shared__ __attribute__((aligned(8))) uint16_t s_hb[CH + RSTEP];  // which heads attend the key; 0 in the padding
-    __shared__ int s_wcnt[4 * KPT];
+    constexpr int PAD = 64;                // a round begins inside the kept keys and reads at most 36 entries
+    static_assert(NI * RPI <= 36, "entries that the wave loads of a round touch");
+    __shared__ int s_j[CH + PAD];          // cache rows of the chunk's keys, squeezed; padded with -1
+    __shared__ __attribute__((aligned(8))) uint16_t s_hb[CH + PAD];    // which heads attend the key; 0 in the padding
+    __shared__ int4 s_wcnt[KPT];
     __shared__ __attribute__((aligned(16))) char s_buf[BUF_BYTES];   // V rows of the rounds; the partials at the end
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -960,28 +1018,12 @@ __global__ __launch_bounds__(256) void decode_attn_gqa_mfma_kernel(DecodeLayout 
     const int G = min(GMAX, Gall - sub * GMAX);
     const int b = (int)(bhk / L.Hkv), hk = (int)(bhk % L.Hkv);
     const int pos = pos_dev ? pos_dev[b] : pos_arg;
-    if (pos < 0 || pos >= L.n) return;
     const size_t bhq0 = (size_t)b * L.Hq + (size_t)hk * Gall + (size_t)sub * GMAX;
-    const int lo_w = max(0, pos - L.window + 1);
-    uint32_t gq[GMAX];
-    uint32_t gu = 0;
-#pragma unroll
-    for (int i = 0; i < GMAX; ++i) { gq[i] = (i < G) ? ((const uint32_t*)(st + L.off_mq))[bhq0 + i] : 0u; gu |= gq[i]; }
-    const int* wptr = (const int*)(st + L.off_wp) + bhk * L.K;
     const int* lists = (const int*)(st + L.off_lists) + bhk * L.K * L.n;
     const uint32_t* mk = (const uint32_t*)(st + L.off_mk) + bhk * L.n;
-
-    if (tid == 0) decode_walk_init(s_walk, gu, wptr, L.K, pos, lo_w);
-    __syncthreads();
-    const int nseg = s_walk.nseg;
-    const int vtotal = s_walk.beg[nseg];
-    if ((long)chunk * CH >= vtotal) {
-        for (int i = 0; i < G; ++i) {
-            float* mypart = part + ((bhq0 + i) * L.max_parts + chunk) * PW;
-            for (int e = tid; e < PW; e += 256) mypart[e] = (e == D) ? -INFINITY : 0.f;
-        }
-        return;
-    }
+    // the queries' memberships, the window pointers and the query rows in one memory round trip
+    const uint32_t mq_lane = lane < G ? ((const uint32_t*)(st + L.off_mq))[bhq0 + lane] : 0u;
+    const int wp_lane = lane < L.K ? ((const int*)(st + L.off_wp))[bhk * L.K + lane] : 0;
     // B operand of S^T: the query heads, column m16 (zero past G)
     V8 qv[KB];
 #pragma unroll
@@ -989,6 +1031,25 @@ __global__ __launch_bounds__(256) void decode_attn_gqa_mfma_kernel(DecodeLayout 
         dec_u32x4 w = {0u, 0u, 0u, 0u};
         if (m16 < G && 32 * kb + 8 * qg < D) w = *(const dec_u32x4*)(q_new + (bhq0 + m16) * D + 32 * kb + 8 * qg);
         qv[kb] = __builtin_bit_cast(V8, w);
+    }
+    if (pos < 0 || pos >= L.n) return;
+    const int lo_w = max(0, pos - L.window + 1);
+    uint32_t gq[GMAX];
+    uint32_t gu = 0;
+#pragma unroll
+    for (int i = 0; i < GMAX; ++i) { gq[i] = (uint32_t)__builtin_amdgcn_readlane((int)mq_lane, i); gu |= gq[i]; }
+    if (wave == 0) decode_walk_init(s_walk, gu, wp_lane, L.K, pos, lo_w);
+    __syncthreads();
+    const int nseg = s_walk.nseg;
+    const int vtotal = s_walk.beg[nseg];
+    const int units = (vtotal + 31) / 32;
+    const int u_beg = (int)((long)units * chunk / gridDim.x), u_end = (int)((long)units * (chunk + 1) / gridDim.x);
+    if (u_beg == u_end) {
+        for (int i = 0; i < G; ++i) {
+            float* mypart = part + ((bhq0 + i) * L.max_parts + chunk) * PW;
+            for (int e = tid; e < PW; e += 256) mypart[e] = (e == D) ? -INFINITY : 0.f;
+        }
+        return;
     }
     dec_f32x4 oacc[NB];
 #pragma unroll
@@ -1009,14 +1070,12 @@ __global__ __launch_bounds__(256) void decode_attn_gqa_mfma_kernel(DecodeLayout 
         vrow[e] = (key / RPI) * IPITCH + (key % RPI) * RB + 2 * m16;
     }
 
-    for (int cc = 0; cc < span; ++cc) {
-    // chunks chunk, chunk + gridDim.x, ...: however short the walk turns out, its chunks spread over the work-groups
-    const long v0l = ((long)chunk + (long)cc * gridDim.x) * CH;
-    if (v0l >= vtotal) break;                      // uniform over the work-group
-    const int v0 = (int)v0l;
-    if (cc > 0) __syncthreads();                  // the last chunk's keys have been read
-    const int nk = decode_resolve_chunk<KPT, GMAX, uint16_t>(s_walk, nseg, v0, min(vtotal - v0, CH), lo_w, lists, L.n, mk, gq,
-                                                             (1u << G) - 1u, L.topk == 1, s_j, s_hb, CH + RSTEP, s_wcnt);
+    const int passes = (u_end - u_beg + CH / 32 - 1) / (CH / 32);
+    const int v_end = min(vtotal, u_end * 32), v_len = (u_end - u_beg + passes - 1) / passes * 32;
+    for (int v0 = u_beg * 32; v0 < v_end; v0 += v_len) {
+    if (v0 > u_beg * 32) __syncthreads();         // the last pass's keys have been read
+    const int nk = decode_resolve_chunk<KPT, PAD, GMAX, uint16_t>(s_walk, nseg, v0, min(v_end - v0, v_len), lo_w, lists, L.n, mk, gq,
+                                                                  (1u << G) - 1u, L.topk == 1, s_j, s_hb, s_wcnt);
 
     for (int r0 = wave * 32; r0 < nk; r0 += RSTEP) {
         // the V rows of the round -> LDS (wave load i holds keys i*RPI ..+RPI of the round)
@@ -1151,13 +1210,12 @@ __global__ __launch_bounds__(256) void decode_merge_kernel(DecodeLayout L, int p
     __shared__ float s_acc[NG][D + 4];
     const int tid = threadIdx.x, t = tid % TPG, grp = tid / TPG, bhq = blockIdx.x;
     const int pos = pos_dev ? pos_dev[bhq / L.Hq] : pos_arg;
-    if (pos < 0 || pos >= L.n) return;                // the other kernels of the step skipped this sequence too
     const float* p0 = part + (size_t)bhq * L.max_parts * PW;
     // every group of threads folds its share of the partials against a running maximum of its own (one pass over
     // the partials, four of them in flight per group); the groups then meet in LDS
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
     float mrun = -INFINITY, lsum = 0.f, csum = 0.f;
-    constexpr int MU = 4;
+    constexpr int MU = 8;
     for (int c0 = grp; grp < NG && c0 < nchunks; c0 += NG * MU) {
         float4 tail[MU], ov[MU];
 #pragma unroll
@@ -1191,6 +1249,9 @@ __global__ __launch_bounds__(256) void decode_merge_kernel(DecodeLayout L, int p
         if (t == 0) { s_acc[grp][D] = lsum; s_acc[grp][D + 1] = csum; s_acc[grp][D + 2] = mrun; }
     }
     __syncthreads();
+    // the other kernels of the step skipped a position outside the caches too (asked for here, so that the first loads of
+    // the partials don't wait for the position)
+    if (pos < 0 || pos >= L.n) return;
     if (tid < D) {
         float mx = -INFINITY;
 #pragma unroll
@@ -1262,8 +1323,8 @@ static hipError_t decode_step_d(const DecodeLayout& L, const HeadMap& hm, int po
     bool grouped = default_map && (G == 1 || G == 2 || G == 4 || G == 8);
     // upper bound of the key sequence known on the host: pos + 1 entries.  The lists are walked only while they
     // hold fewer entries than there are positions below the window, the positions themselves otherwise.
-    // (With the position in device memory: the bound of the last position the caches can hold; work-groups
-    // past the real sequence leave an empty partial.)
+    // (With the position in device memory: the bound of the last position the caches can hold; the real sequence is
+    // shared out on the device, or in the vector kernels work-groups past it leave an empty partial.)
     if (pos_dev) pos = L.n - 1;
     int nchunks = std::min(L.max_chunks, (pos + DEC_CHUNK) / DEC_CHUNK);
     // a work-group walks `span` chunks and leaves one partial: at most DEC_MAX_PARTS partials per head, so the
@@ -1277,26 +1338,20 @@ static hipError_t decode_step_d(const DecodeLayout& L, const HeadMap& hm, int po
         if constexpr (sizeof(T) == 2) {
             if ((size_t)L.n * D * 2 <= 0xffffffffull) {
                 grid.y = L.B * L.Hkv * ((G + 15) / 16);
-                // shorter chunks (fewer rounds per wavefront) while all their work-groups are resident at once, three
-                // per CU: below that the long chunks leave most of the chip idle (4096 cached tokens: 27 -> 20 us)
-                int ch = DEC_CHUNK;
-                for (int c = DEC_CHUNK_SHORT; c < DEC_CHUNK; c *= 2) {
-                    const int nc = (pos + c) / c;
-                    if ((long)nc * grid.y <= 3 * 256 && nc <= L.max_parts) { ch = c; break; }
-                }
-                if (ch != DEC_CHUNK) {
-                    nchunks = (pos + ch) / ch;
-                    span = 1;                                                // one chunk, one partial per work-group
-                    nparts = nchunks;
-                    grid.x = nparts;
-                }
+                // Work-groups per head.  Up to 128 heads: as many as are resident at once and no more, three per compute unit
+                // (two at 512-byte rows: LDS) where that leaves every wavefront four rounds, else two, none with less
+                // than a round per wavefront.  A step in us with two / three per unit and with 512-entry chunks: 8 heads x 32768
+                // 37.2 / 38.8 / 43.2; 8 x 131072 98 / 93 / 104; 96 x 4096 29.6 / 26.5 / 27.4; 4 x 2 heads of 256 x 30000 60 / 67 / 60.
+                // More heads: whole heads per slot no longer come out even (300 heads x 4000: 97 / 71 / 66; 256 x 9000: 217 /
+                // 215 / 206), chunks of 512 entries that the dispatcher hands out do better.
+                const long rows = grid.y, units = (pos + 32) / 32, all = rows * units;
+                const long slots = (D < 256 && all >= 3 * 256 * 16) ? 3 * 256 : 2 * 256;
+                long parts = rows <= 128 ? slots / rows : (units + 15) / 16;
+                nparts = (int)std::max<long>(1, std::min(std::min(parts, (units + 3) / 4), (long)L.max_parts));
+                grid.x = nparts;
                 constexpr bool f16 = std::is_same<T, f16_bits>::value;
-#define FOCUS_DEC_MFMA(CH_) hipLaunchKernelGGL((decode_attn_gqa_mfma_kernel<f16, D, CH_>), grid, dim3(256), 0, s, L, G, pos, pos_dev, span, \
-                                               (const uint16_t*)q_new, (const uint16_t*)kc, (const uint16_t*)vc, (const char*)st, part)
-                if (ch == DEC_CHUNK_SHORT) FOCUS_DEC_MFMA(DEC_CHUNK_SHORT);
-                else if (ch == 2 * DEC_CHUNK_SHORT) FOCUS_DEC_MFMA(2 * DEC_CHUNK_SHORT);
-                else FOCUS_DEC_MFMA(DEC_CHUNK);
-#undef FOCUS_DEC_MFMA
+                hipLaunchKernelGGL((decode_attn_gqa_mfma_kernel<f16, D>), grid, dim3(256), 0, s, L, G, pos, pos_dev,
+                                   (const uint16_t*)q_new, (const uint16_t*)kc, (const uint16_t*)vc, (const char*)st, part);
                 hipLaunchKernelGGL((decode_merge_kernel<T, D>), dim3(L.B * L.Hq), dim3(256), 0, s, L, pos, pos_dev, nparts, part, out,
                                    lse, row_pairs);
                 return hipGetLastError();
@@ -1319,8 +1374,10 @@ static hipError_t decode_step_t(const DecodeLayout& L, const HeadMap& hm, int po
                                 const void* v_new, const float* cents, const uint32_t* token_mask, void* kc, void* vc, char* st, void* out,
                                 float* lse, int32_t* row_pairs, hipStream_t s)
 {
-    hipLaunchKernelGGL(decode_route_kernel<T>, dim3(L.Hq + L.Hkv, L.B), dim3(64), 0, s, L, hm, pos, pos_dev, (const T*)q_new,
-                       (const T*)k_new, (const T*)v_new, cents, token_mask, (T*)kc, (T*)vc, st);
+#define FOCUS_DEC_ROUTE(NI_) hipLaunchKernelGGL((decode_route_kernel<T, NI_>), dim3(L.Hq + L.Hkv, L.B), dim3(64), 0, s, L, hm, pos, pos_dev, (const T*)q_new, \
+                       (const T*)k_new, (const T*)v_new, cents, token_mask, (T*)kc, (T*)vc, st)
+    if (L.d <= 64) FOCUS_DEC_ROUTE(1); else if (L.d <= 128) FOCUS_DEC_ROUTE(2); else FOCUS_DEC_ROUTE(4);
+#undef FOCUS_DEC_ROUTE
 #define FOCUS_DEC_D(D_) decode_step_d<T, D_>(L, hm, pos, pos_dev, (const T*)q_new, (const T*)kc, (const T*)vc, st, (T*)out, lse, row_pairs, s)
     switch (L.d) {
         case 64: return FOCUS_DEC_D(64);

@@ -187,12 +187,8 @@ struct RouteLayout {
 };
 
 // Shapes and state offsets of the incremental (one token per step) path.
-#ifndef FOCUS_DEC_CHUNK
-#define FOCUS_DEC_CHUNK 512
-#endif
-constexpr int DEC_CHUNK = FOCUS_DEC_CHUNK;   // keys of the key sequence a work-group of the decode attention resolves at a time
-constexpr int DEC_CHUNK_SHORT = 128;         // ... in launches that would otherwise leave most of the chip idle (128 or 256)
-static_assert(DEC_CHUNK == 4 * DEC_CHUNK_SHORT, "the launch picks among DEC_CHUNK_SHORT, twice that, and DEC_CHUNK");
+constexpr int DEC_CHUNK = 512;               // keys of the key sequence a work-group of the vector decode attention resolves at a time
+constexpr int DEC_CHUNK_SHORT = 128;         // keys of the smallest share of a work-group: one round for each wavefront
 constexpr int DEC_MAX_PARTS = 384;           // partial results per head the merge reads at most
 struct DecodeLayout {
     int B, Hq, Hkv, n, d;      // n = capacity of the caches
