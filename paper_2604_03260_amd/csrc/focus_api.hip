@@ -247,7 +247,6 @@ focus_status make_layout(const focus_params* p, focus::Layout* L, focus::HeadMap
     L->off_qco = take(BHq * (L->NC + 1) * 4);
     L->off_kco = take(BHk * (L->NC + 1) * 4);
     L->off_clsmask = take((size_t)L->NC * 4);
-    L->off_cent64 = take((size_t)p->Hkv * (((size_t)p->d * L->elem + 127) / 128 * (128 / L->elem)) * 32 * 8);
     L->off_qperm = take(BHq * L->NQP * 4);
     L->off_kpos = take(BHk * L->NKP * 4);
     L->off_kmsk = L->coarse ? take(BHk * L->NKP * 4) : off;

@@ -3,10 +3,9 @@
 // "Efficiency at inference"; the stable sort by group of App. D done as a
 // counting sort).
 //
-// Four launches per focus_assign call, the work item everywhere a (sort block of
+// Three launches per focus_assign call, the work item everywhere a (sort block of
 // SB positions, batch*head) pair:
-//   assign_init  centroids to fp64, the key-norm slots to zero (a few us);
-//   score_topk   streams q (or k) once, scores every token against the K centroids of its KV
+//   score        streams q (or k) once, scores every token against the K centroids of its KV
 //                head in fp64 (products are exact in fp64, added in index order,
 //                so the result is reproducible bit for bit), keeps the top-k
 //                groups, writes the membership mask, the class id and the
@@ -21,8 +20,8 @@
 //                (key rows, 16-bit types) the class-ordered copy of the key rows
 //                with the largest squared key norm of the head.
 // Memberships given per token (focus_assign_tokens) take token_classes in place
-// of score_topk.  Layouts without classes (masked) leave the scan out where the scatter launch can add up
-// the histograms itself, and take score_linear in place of assign_init and score_topk where that is faster.
+// of score.  Layouts without classes (masked) leave the scan out where the scatter launch can add up
+// the histograms itself.
 #include "focus_internal.h"
 #include "focus_score.h"
 #include <hip/hip_bf16.h>
@@ -32,8 +31,6 @@
 namespace focus {
 
 namespace {
-
-__device__ inline float bf16_bits_to_f32(uint16_t b) { return __uint_as_float(((uint32_t)b) << 16); }
 
 // Pascal's triangle up to C(32, .), built at compile time: the class of a token is the colex rank of
 // its membership set, a sum of binomials.
@@ -53,13 +50,6 @@ constexpr BinomTable make_binom_table()
 }
 __device__ __constant__ BinomTable g_binom = make_binom_table();
 
-// ---------------------------------------------------------------- score + top-k
-constexpr int ROW_CHUNK_BYTES = 128;                 // bytes of every row staged per phase
-constexpr int ROW_STRIDE = ROW_CHUNK_BYTES + 16;     // padded LDS row stride
-
-
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-
 // The kernels of the bucketing serve the query side, the key side, or both in one launch (which = 1, 0, -1):
 // with both, the rows [0, B*Hq) of the launch are query (batch, head) pairs and the B*Hkv after them key pairs.
 constexpr int MAX_GRID_ROWS = 65535;
@@ -67,6 +57,19 @@ __device__ inline int side_of_row(const Layout& L, int which, unsigned row) { re
 __device__ inline int row_in_side(const Layout& L, int which, unsigned row)
 {
     return (which < 0 && row >= (unsigned)(L.B * L.Hq)) ? (int)row - L.B * L.Hq : (int)row;
+}
+
+// class of a membership: the colex rank of the set among all topk-subsets (coarse: of its set of super-groups)
+__device__ inline int token_class(const Layout& L, uint32_t mask)
+{
+    if (L.coarse) return class_of_mask(mask, 0, 1, L.S);
+    int cls = 0;
+    if (!L.dense) {
+        int j = 0;
+        for (int g = 0; g < L.K; ++g)
+            if ((mask >> g) & 1u) { ++j; cls += (int)g_binom.v[g * 33 + j]; }
+    }
+    return cls;
 }
 
 // ---------------------------------------------------------------- scan over sort blocks + per-row plan
@@ -246,190 +249,43 @@ __global__ __launch_bounds__(SCAN_THREADS) void scan_plan_kernel(Layout L, char*
     scan_and_plan_row<SCAN_THREADS>(L, is_query, bh, ws, s_tmp, SCAN_PLAN_TMP_INTS);
 }
 
-template <typename T, int KMAX>
-__global__ __launch_bounds__(SB) void score_topk_kernel(Layout L, HeadMap hm, const T* __restrict__ xq,
-                                                        const T* __restrict__ xk,
-                                                        const double* __restrict__ cent64, int which, int nbw,
-                                                        char* __restrict__ ws)
+// ---------------------------------------------------------------- score + top-k
+// Memberships of one sort block on the fp64 matrix cores (focus_score.h), its group histogram and, on layouts with classes
+// (CLS), the class of every token and the class histogram.
+template <typename T, int KM, bool CLS>
+__global__ __launch_bounds__(SB) void score_kernel(Layout L, HeadMap hm, const T* __restrict__ xq, const T* __restrict__ xk,
+                                                   const float* __restrict__ cents, int which, char* __restrict__ ws)
 {
-    __shared__ __align__(16) char s_rows[SB * ROW_STRIDE];
-    __shared__ int s_hist_c[MAX_CLASSES];
-    __shared__ int s_hist_g[32];
-
-    const int tid = threadIdx.x;
-    const int blk0 = blockIdx.x * nbw;          // nbw consecutive sort blocks per work-group
-    const int is_query = side_of_row(L, which, blockIdx.y);
-    const int bh = row_in_side(L, which, blockIdx.y);
-    const T* x = is_query ? xq : xk;
-    const int H = is_query ? L.Hq : L.Hkv;
-    const int h = bh % H;
-    const int hk = is_query ? hm.kv[h] : h;
-    const int d = L.d, K = L.K, n = L.n;
-    constexpr int EPC = 16 / sizeof(T);                              // elements per 16-byte chunk
-    constexpr int CPR = ROW_CHUNK_BYTES / 16;                        // chunks per staged row = loads per thread
-    const int row_bytes = d * (int)sizeof(T);
-    const int phases = (row_bytes + ROW_CHUNK_BYTES - 1) / ROW_CHUNK_BYTES;   // the last one may be partly past the row
-    const int dcent = phases * (ROW_CHUNK_BYTES / (int)sizeof(T));              // rows of the (zero-padded) centroid table
-    const int nb_here = min(nbw, L.nblk - blk0);
-    const int total_steps = nb_here * phases;                        // (block, 128-byte column phase) pairs
-
-    // centroids of this KV head as fp64 [d][KMAX]: a wave-uniform, read-only table -> scalar loads,
-    // the values feed v_fma_f64 straight from SGPRs
-    const double* __restrict__ cd = cent64 + (size_t)hk * dcent * KMAX;
-    for (int e = tid; e < MAX_CLASSES; e += SB) s_hist_c[e] = 0;
-    if (tid < 32) s_hist_g[tid] = 0;
-    __syncthreads();                                                 // (the steps below have no barrier of their own)
-
-    double acc[KMAX];
-#pragma unroll
-    for (int g = 0; g < KMAX; ++g) acc[g] = 0.0;
-
-    uint32_t* masks = (uint32_t*)(ws + (is_query ? L.off_mq : L.off_mk));
-    uint8_t* clsarr = (uint8_t*)(ws + (is_query ? L.off_qcls : L.off_kcls));
-    const size_t cls_stride = is_query ? (size_t)n : (size_t)L.nblk * SB;
-    // rows are row_bytes long; where they start comes from the strides of q (or of k)
-    const long long* xs = is_query ? L.qs : L.ks;
-    const size_t row_pitch = (size_t)xs[2] * sizeof(T);
-    const char* xbase = (const char*)x + ((size_t)(bh / H) * xs[0] + (size_t)h * xs[1]) * sizeof(T);
-
-    // Register staging of the next step: its global loads fly while the current step is computed.
-    // Coalesced: consecutive threads fetch consecutive 16-byte chunks of a 128-byte row segment.
-    u32x4 st[CPR];
-#define FOCUS_SCORE_LOAD(STEP)                                                                       \
-    do {                                                                                             \
-        const int bi_ = (STEP) / phases, ph_ = (STEP) % phases;                                      \
-        const int rows_ = min(SB, n - (blk0 + bi_) * SB);                                            \
-        const char* g_ = xbase + (size_t)(blk0 + bi_) * SB * row_pitch + ph_ * ROW_CHUNK_BYTES;      \
-        _Pragma("unroll") for (int i = 0; i < CPR; ++i) {                                            \
-            const int cid_ = (tid & ~63) * CPR + i * 64 + (tid & 63);   /* chunk of this wavefront's 64 rows */ \
-            const int r_ = cid_ / CPR, cc_ = cid_ % CPR;                                             \
-            const u32x4 z_ = {0u, 0u, 0u, 0u};                                                       \
-            const bool in_ = r_ < rows_ && ph_ * ROW_CHUNK_BYTES + cc_ * 16 < row_bytes;                 \
-            st[i] = in_ ? *(const u32x4*)(g_ + (size_t)r_ * row_pitch + cc_ * 16) : z_;              \
-        }                                                                                            \
-    } while (0)
-
-    FOCUS_SCORE_LOAD(0);
-    for (int step = 0; step < total_steps; ++step) {
-        const int bi = step / phases, ph = step % phases;
-        // Every wavefront stages and reads its own 64 rows: LDS executes a wavefront's accesses in order, so no
-        // barrier is needed, only the compiler must keep the order.
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-#pragma unroll
-        for (int i = 0; i < CPR; ++i) {
-            const int cid = (tid & ~63) * CPR + i * 64 + (tid & 63);
-            *(u32x4*)(s_rows + (cid / CPR) * ROW_STRIDE + (cid % CPR) * 16) = st[i];
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        if (step + 1 < total_steps) FOCUS_SCORE_LOAD(step + 1);
-        const int tbase = ph * (ROW_CHUNK_BYTES / (int)sizeof(T));
-#pragma unroll 1
-        for (int cc = 0; cc < CPR; ++cc) {
-            const u32x4 val = *(const u32x4*)(s_rows + tid * ROW_STRIDE + cc * 16);
-            double xv[EPC];
-            if constexpr (sizeof(T) == 4) {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) xv[e] = (double)__uint_as_float(val[e]);
-            } else if constexpr (std::is_same<T, f16_bits>::value) {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    xv[2 * e] = (double)f16_bits_to_f32((uint16_t)(val[e] & 0xffffu));
-                    xv[2 * e + 1] = (double)f16_bits_to_f32((uint16_t)(val[e] >> 16));
-                }
-            } else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    xv[2 * e] = (double)bf16_bits_to_f32((uint16_t)(val[e] & 0xffffu));
-                    xv[2 * e + 1] = (double)bf16_bits_to_f32((uint16_t)(val[e] >> 16));
-                }
-            }
-#pragma unroll
-            for (int e = 0; e < EPC; ++e) {
-                const double* cr = cd + (size_t)(tbase + cc * EPC + e) * KMAX;
-#pragma unroll
-                for (int g = 0; g < KMAX; ++g) acc[g] = fma(xv[e], cr[g], acc[g]);
-            }
-        }
-        if (ph != phases - 1) continue;
-
-        // ---- a sort block is complete: top-k by rank counting; ties go to the smaller group index
-        const int blk = blk0 + bi;
-        const int pos = blk * SB + tid;
-        uint32_t mask = 0;
-#pragma unroll
-        for (int g = 0; g < KMAX; ++g) {
-            if (g < K) {
-                int beaten = 0;
-#pragma unroll
-                for (int o = 0; o < KMAX; ++o) {
-                    if (o < K && o != g)
-                        beaten += (acc[o] > acc[g] || (acc[o] == acc[g] && o < g)) ? 1 : 0;
-                }
-                if (beaten < L.topk) mask |= (1u << g);
-            }
-        }
-        // A NaN score loses no comparison and would add its group to the topk others: a membership that is not
-        // a topk-subset has no class.  Such a token (only a NaN can cause it) takes the first topk groups.
-        if (__popc(mask) != L.topk) mask = (L.topk == 32) ? 0xffffffffu : ((1u << L.topk) - 1u);
-#pragma unroll
-        for (int g = 0; g < KMAX; ++g) acc[g] = 0.0;
-        // class = colex rank of the membership set among all topk-subsets
-        int cls = 0;
-        if (L.coarse) {
-            cls = class_of_mask(mask, 0, 1, L.S);
-        } else if (!L.dense) {
-            int j = 0;
-            for (int g = 0; g < K; ++g)
-                if ((mask >> g) & 1u) { ++j; cls += (int)g_binom.v[g * 33 + j]; }
-        }
-        if (pos < n) {
-            masks[(size_t)bh * n + pos] = mask;
-            clsarr[(size_t)bh * cls_stride + pos] = (uint8_t)cls;
-            atomicAdd(&s_hist_c[cls], 1);
-            for (int g = 0; g < K; ++g)
-                if ((mask >> g) & 1u) atomicAdd(&s_hist_g[g], 1);
-        }
-        __syncthreads();
-        int* bc = (int*)(ws + (is_query ? L.off_qbc : L.off_kbc)) + ((size_t)bh * (L.nblk + 1) + blk) * L.NC;
-        int* bg = (int*)(ws + (is_query ? L.off_qbg : L.off_kbg)) + ((size_t)bh * (L.nblk + 1) + blk) * K;
-        for (int c = tid; c < L.NC; c += SB) { bc[c] = s_hist_c[c]; s_hist_c[c] = 0; }
-        if (tid < K) { bg[tid] = s_hist_g[tid]; s_hist_g[tid] = 0; }
-        __syncthreads();                                             // cleared before the next block's atomics
-    }
-#undef FOCUS_SCORE_LOAD
-}
-
-// ---------------------------------------------------------------- scores of a masked layout
-// Memberships and group histograms of one sort block on the fp64 matrix cores (focus_score.h), for layouts without
-// classes: no fp64 centroid table, so no launch before it.  The products run on 16 columns whatever K is: faster than the
-// vector form above 8 groups (3 x 20 heads x 5003 tokens of 80, K = 16: 65 -> 44 us) and where the launch is a
-// matter of latency; with 4 groups and thousands of sort blocks the vector form wins (96 x 2 heads x 4096 of 64: 30 us).
-template <typename T, int KM>
-__global__ __launch_bounds__(SB) void score_linear_kernel(Layout L, HeadMap hm, const T* __restrict__ xq, const T* __restrict__ xk,
-                                                          const float* __restrict__ cents, char* __restrict__ ws)
-{
-    __shared__ __align__(16) char s_a[4][SCORE_LDS];
+    __shared__ __align__(16) char s_a[4][score_lds(KM)];
     __shared__ int s_h[4][32];
-    extern __shared__ float s_c[];
+    __shared__ int s_hist_c[CLS ? MAX_CLASSES : 1];
+    extern __shared__ __align__(16) char s_cent[];
+    score_cent_t<KM>* s_c = (score_cent_t<KM>*)s_cent;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int blk = blockIdx.x, K = L.K, n = L.n;
-    const int is_query = side_of_row(L, -1, blockIdx.y);
-    const int bh = row_in_side(L, -1, blockIdx.y);
+    const int is_query = side_of_row(L, which, blockIdx.y);
+    const int bh = row_in_side(L, which, blockIdx.y);
     const int H = is_query ? L.Hq : L.Hkv, h = bh % H, hk = is_query ? hm.kv[h] : h;
     const long long* xs = is_query ? L.qs : L.ks;
-    score_stage_centroids<KM>(cents + (size_t)hk * K * L.d, s_c, K, L.d);
     // (the scatter launch after this one raises these)
     if (!is_query && blk == 0 && tid < KN2_SLOTS) ((unsigned*)(ws + L.off_kn2))[(size_t)bh * KN2_SLOTS + tid] = 0u;
-    __syncthreads();
     const int j0 = blk * SB + wave * 64, rows = min(64, n - j0);
-    uint32_t m = 0;
-    if (rows > 0) {
-        const T* x = (is_query ? xq : xk) + (size_t)(bh / H) * xs[0] + (size_t)h * xs[1] + (size_t)j0 * xs[2];
-        m = score_rows_topk<T, KM>((const char*)x, (size_t)xs[2] * sizeof(T), rows, L.d, s_c, s_a[wave], K, L.topk);
-        if (lane < rows) ((uint32_t*)(ws + (is_query ? L.off_mq : L.off_mk)))[(size_t)bh * n + j0 + lane] = m;
+    const T* x = (is_query ? xq : xk) + (size_t)(bh / H) * xs[0] + (size_t)h * xs[1] + (size_t)j0 * xs[2];
+    const uint32_t m = score_rows_topk<T, KM>((const char*)x, (size_t)xs[2] * sizeof(T), rows, L.d, s_c, s_a[wave], K, L.topk, [&]() {
+        score_stage_centroids<KM>(cents + (size_t)hk * K * L.d, s_c, K, L.d);
+        if constexpr (CLS)
+            for (int e = tid; e < L.NC; e += SB) s_hist_c[e] = 0;
+        __syncthreads();
+    });
+    if (lane < rows) {
+        ((uint32_t*)(ws + (is_query ? L.off_mq : L.off_mk)))[(size_t)bh * n + j0 + lane] = m;
+        if constexpr (CLS) {
+            const int cls = token_class(L, m);
+            const size_t cls_stride = is_query ? (size_t)n : (size_t)L.nblk * SB;
+            ((uint8_t*)(ws + (is_query ? L.off_qcls : L.off_kcls)))[(size_t)bh * cls_stride + j0 + lane] = (uint8_t)cls;
+            atomicAdd(&s_hist_c[cls], 1);
+        }
     }
     for (int g = 0; g < K; ++g) {
         const unsigned long long has = __ballot((m >> g) & 1u);
@@ -439,25 +295,11 @@ __global__ __launch_bounds__(SB) void score_linear_kernel(Layout L, HeadMap hm, 
     if (tid < K)
         ((int*)(ws + (is_query ? L.off_qbg : L.off_kbg)))[((size_t)bh * (L.nblk + 1) + blk) * K + tid] =
             s_h[0][tid] + s_h[1][tid] + s_h[2][tid] + s_h[3][tid];
-    if (tid == 0) ((int*)(ws + (is_query ? L.off_qbc : L.off_kbc)))[(size_t)bh * (L.nblk + 1) + blk] = min(SB, n - blk * SB);
-}
-
-// ---------------------------------------------------------------- start of an assign pass
-// The largest-key-norm slots to zero and, when centroids are given, their fp64 table: one small launch.
-__global__ __launch_bounds__(256) void assign_init_kernel(unsigned* __restrict__ zeros, size_t nzeros,
-                                                          const float* __restrict__ cents,
-                                                          double* __restrict__ cent64, int Hkv, int K, int d, int dcent, int kmax)
-{
-    const size_t step = (size_t)gridDim.x * blockDim.x;
-    const size_t i0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    for (size_t i = i0; i < nzeros; i += step) zeros[i] = 0u;
-    if (cents) {
-        const size_t total = (size_t)Hkv * dcent * kmax;
-        for (size_t e = i0; e < total; e += step) {
-            const int g = (int)(e % kmax), t = (int)((e / kmax) % dcent), hk = (int)(e / ((size_t)kmax * dcent));
-            cent64[e] = (g < K && t < d) ? (double)cents[((size_t)hk * K + g) * d + t] : 0.0;
-        }
-    }
+    int* bc = (int*)(ws + (is_query ? L.off_qbc : L.off_kbc)) + ((size_t)bh * (L.nblk + 1) + blk) * L.NC;
+    if constexpr (CLS)
+        for (int c = tid; c < L.NC; c += SB) bc[c] = s_hist_c[c];
+    else if (tid == 0)
+        bc[0] = min(SB, n - blk * SB);
 }
 
 __global__ void fill_i32_kernel(int* __restrict__ p, size_t count, int value)
@@ -485,7 +327,7 @@ __device__ inline float chunk_norm2(const uint4& val, bool f16)
 
 // k: the key rows (16-bit types) for the class-ordered copy the matrix-core attention kernel reads, or NULL.
 // The copy also leaves the largest squared key norm of the (batch, KV head) in the workspace (off_kn2: KN2_SLOTS
-// partial maxima per head, cleared by assign_init): a non-negative float orders like its bit pattern, so one
+// partial maxima per head, cleared by the score kernel): a non-negative float orders like its bit pattern, so one
 // atomicMax on the bits per work-group does it, and a NaN or infinite norm ends up above every finite one.
 // LINEAR (masked layouts): one class, slot = position.  OWN_SCAN: no scan launch ran; the work-group adds up the group
 // histograms of the row's sort blocks itself (a few thousand integers at most), and sort block 0 writes the row's counts.
@@ -671,7 +513,7 @@ __global__ __launch_bounds__(SB) void scatter_kernel(Layout L, int which, const 
 // The paper's router assigns one membership per token of a layer, shared by all heads and by the
 // query and key roles (Sec. 2).  A work-group turns the token masks of a sort block of a batch element into
 // class ids and histograms and writes them for its share of the query and KV heads (heads z, z + gridDim.z, ..),
-// in the same places score_topk fills.  A mask that is not a topk-subset of the K groups would index
+// in the same places the score kernel fills.  A mask that is not a topk-subset of the K groups would index
 // outside the class tables: it is replaced by the first topk groups and counted.
 __global__ __launch_bounds__(SB) void token_classes_kernel(Layout L, const uint32_t* __restrict__ token_masks,
                                                            char* __restrict__ ws, int32_t* __restrict__ invalid_count)
@@ -695,13 +537,7 @@ __global__ __launch_bounds__(SB) void token_classes_kernel(Layout L, const uint3
             mask = (L.topk == 32) ? 0xffffffffu : ((1u << L.topk) - 1u);
             if (invalid_count && blockIdx.z == 0) atomicAdd(invalid_count, 1);
         }
-        if (L.coarse) {
-            cls = class_of_mask(mask, 0, 1, L.S);
-        } else if (!L.dense) {
-            int j = 0;
-            for (int g = 0; g < K; ++g)
-                if ((mask >> g) & 1u) { ++j; cls += (int)g_binom.v[g * 33 + j]; }
-        }
+        cls = token_class(L, mask);
         atomicAdd(&s_hist_c[cls], 1);
         for (int g = 0; g < K; ++g)
             if ((mask >> g) & 1u) atomicAdd(&s_hist_g[g], 1);
@@ -726,56 +562,29 @@ __global__ __launch_bounds__(SB) void token_classes_kernel(Layout L, const uint3
     }
 }
 
-// Sort blocks per work-group of the scoring launch: up to four (a work-group prefetches its next block while it
-// computes), fewer when that would leave the chip with less than a few work-groups per slot to balance with.
-int score_blocks_per_group(long long items)
-{
-    const long long slots = 256 * 4;
-    int nbw = 4;
-    while (nbw > 1 && items / nbw < 4 * slots) nbw >>= 1;
-    return nbw;
-}
-
 // scores and memberships of the queries and of the keys, one launch: query rows first, key rows after them
-template <typename T>
-hipError_t launch_score(const Layout& L, const HeadMap& hm, const void* q, const void* k, char* ws, hipStream_t st)
+template <typename T, int KM>
+hipError_t launch_score(const Layout& L, const HeadMap& hm, const void* q, const void* k, const float* centroids, char* ws, hipStream_t st)
 {
-    const int kmax = L.K <= 4 ? 4 : L.K <= 8 ? 8 : L.K <= 16 ? 16 : 32;
-    const double* cent64 = (const double*)(ws + L.off_cent64);
+    const size_t lds = score_cent_bytes(KM, L.d);                    // with the staging space below 87 KB
     // (more rows than one launch can have: the two sides one after the other)
     const bool both = L.B * (L.Hq + L.Hkv) <= MAX_GRID_ROWS;
     for (int which = both ? -1 : 1; which >= -1; --which) {
-        const int rows = which < 0 ? L.B * (L.Hq + L.Hkv) : which ? L.B * L.Hq : L.B * L.Hkv;
-        const int nbw = score_blocks_per_group((long long)rows * L.nblk);
-        dim3 grid((L.nblk + nbw - 1) / nbw, rows);
-#define FOCUS_SCORE(KM_) hipLaunchKernelGGL((score_topk_kernel<T, KM_>), grid, dim3(SB), 0, st, L, hm, (const T*)q, (const T*)k, cent64, which, nbw, ws)
-        switch (kmax) {
-            case 4: FOCUS_SCORE(4); break;
-            case 8: FOCUS_SCORE(8); break;
-            case 16: FOCUS_SCORE(16); break;
-            default: FOCUS_SCORE(32); break;
-        }
-#undef FOCUS_SCORE
+        const dim3 grid(L.nblk, which < 0 ? L.B * (L.Hq + L.Hkv) : which ? L.B * L.Hq : L.B * L.Hkv);
+        if (L.masked) hipLaunchKernelGGL((score_kernel<T, KM, false>), grid, dim3(SB), lds, st, L, hm, (const T*)q, (const T*)k, centroids, which, ws);
+        else hipLaunchKernelGGL((score_kernel<T, KM, true>), grid, dim3(SB), lds, st, L, hm, (const T*)q, (const T*)k, centroids, which, ws);
         if (which <= 0) break;
     }
     return hipGetLastError();
 }
 
-}  // namespace
-
-namespace {
-
-// the key-norm slots to zero and, with centroids given, their fp64 table [Hkv][dcent][kmax]
-void launch_assign_init(const Layout& L, const float* centroids, char* ws, hipStream_t st)
+template <typename T>
+hipError_t launch_score_k(const Layout& L, const HeadMap& hm, const void* q, const void* k, const float* centroids, char* ws, hipStream_t st)
 {
-    const size_t nzeros = (size_t)L.B * L.Hkv * KN2_SLOTS;           // the largest-key-norm slots
-    const int kmax = L.K <= 4 ? 4 : L.K <= 8 ? 8 : L.K <= 16 ? 16 : 32;
-    const int row_bytes = L.d * L.elem;
-    const int dcent = (row_bytes + ROW_CHUNK_BYTES - 1) / ROW_CHUNK_BYTES * (ROW_CHUNK_BYTES / L.elem);
-    const size_t work = std::max(nzeros, centroids ? (size_t)L.Hkv * dcent * kmax : (size_t)0);
-    const int grid = (int)std::min((size_t)1024, (work + 255) / 256);
-    hipLaunchKernelGGL(assign_init_kernel, dim3(grid), dim3(256), 0, st, (unsigned*)(ws + L.off_kn2), nzeros,
-                       centroids, (double*)(ws + L.off_cent64), L.Hkv, L.K, L.d, dcent, kmax);
+    if (L.K <= 4) return launch_score<T, 4>(L, hm, q, k, centroids, ws, st);
+    if (L.K <= 8) return launch_score<T, 8>(L, hm, q, k, centroids, ws, st);
+    if (L.K <= 16) return launch_score<T, 16>(L, hm, q, k, centroids, ws, st);
+    return launch_score<T, 32>(L, hm, q, k, centroids, ws, st);
 }
 
 // Masked layouts need no class tables and no job list: where a row's group histograms are few, the scatter launch adds
@@ -804,30 +613,9 @@ hipError_t launch_scatter(const Layout& L, const void* k, char* ws, hipStream_t 
 hipError_t launch_assign(const Layout& L, const HeadMap& hm, const void* q, const void* k,
                          const float* centroids, char* ws, hipStream_t st)
 {
-    hipError_t e;
-    const long long sort_blocks = (long long)L.B * (L.Hq + L.Hkv) * L.nblk;
-    if (L.masked && L.B * (L.Hq + L.Hkv) <= MAX_GRID_ROWS && (L.K > 8 || sort_blocks <= 512)) {
-        const int km = L.K <= 4 ? 4 : L.K <= 8 ? 8 : L.K <= 16 ? 16 : 32;
-        const dim3 grid(L.nblk, L.B * (L.Hq + L.Hkv));
-        const size_t lds = (size_t)L.d * score_wp(km) * 4;           // with the staging space below 87 KB
-#define FOCUS_SCORE_L(T_, KM_) hipLaunchKernelGGL((score_linear_kernel<T_, KM_>), grid, dim3(SB), lds, st, L, hm, (const T_*)q, (const T_*)k, centroids, ws)
-#define FOCUS_SCORE_LT(T_)                                                                                               \
-    { if (km == 4) FOCUS_SCORE_L(T_, 4); else if (km == 8) FOCUS_SCORE_L(T_, 8);                                          \
-      else if (km == 16) FOCUS_SCORE_L(T_, 16); else FOCUS_SCORE_L(T_, 32); }
-        if (L.dtype == 0) FOCUS_SCORE_LT(float)
-        else if (L.dtype == 2) FOCUS_SCORE_LT(f16_bits)
-        else FOCUS_SCORE_LT(uint16_t)
-#undef FOCUS_SCORE_LT
-#undef FOCUS_SCORE_L
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        if (!own_scan(L)) hipLaunchKernelGGL(scan_plan_kernel, dim3(L.B * (L.Hq + L.Hkv)), dim3(SCAN_THREADS), 0, st, L, ws);
-        return launch_scatter(L, k, ws, st);
-    }
-    launch_assign_init(L, centroids, ws, st);
-    if (L.dtype == 0) e = launch_score<float>(L, hm, q, k, ws, st);
-    else if (L.dtype == 2) e = launch_score<f16_bits>(L, hm, q, k, ws, st);
-    else e = launch_score<uint16_t>(L, hm, q, k, ws, st);
+    const hipError_t e = L.dtype == 0 ? launch_score_k<float>(L, hm, q, k, centroids, ws, st)
+                         : L.dtype == 2 ? launch_score_k<f16_bits>(L, hm, q, k, centroids, ws, st)
+                                        : launch_score_k<uint16_t>(L, hm, q, k, centroids, ws, st);
     if (e != hipSuccess) return e;
     if (!own_scan(L)) hipLaunchKernelGGL(scan_plan_kernel, dim3(L.B * (L.Hq + L.Hkv)), dim3(SCAN_THREADS), 0, st, L, ws);
     return launch_scatter(L, k, ws, st);
@@ -836,7 +624,8 @@ hipError_t launch_assign(const Layout& L, const HeadMap& hm, const void* q, cons
 hipError_t launch_assign_tokens(const Layout& L, const uint32_t* token_masks, const void* k, char* ws,
                                 int32_t* invalid_count, hipStream_t st)
 {
-    launch_assign_init(L, nullptr, ws, st);
+    const size_t nzeros = (size_t)L.B * L.Hkv * KN2_SLOTS;           // the largest-key-norm slots
+    hipLaunchKernelGGL(fill_i32_kernel, dim3((unsigned)std::min<size_t>(1024, (nzeros + 255) / 256)), dim3(256), 0, st, (int*)(ws + L.off_kn2), nzeros, 0);
     if (invalid_count) hipLaunchKernelGGL(fill_i32_kernel, dim3(1), dim3(64), 0, st, invalid_count, (size_t)1, 0);
     // the heads of a sort block are split until there are a few work-groups per compute unit (128 blocks x 40 heads: one
     // work-group for all heads wrote for 11 us, eight for 5)

@@ -121,17 +121,18 @@ template <typename T, int KM>
 __global__ __launch_bounds__(256) void decode_prefill_score_kernel(DecodeLayout L, int n_ctx, const T* __restrict__ kc,
                                                                    const float* __restrict__ cents, char* __restrict__ st)
 {
-    __shared__ __align__(16) char s_a[4][SCORE_LDS];
-    extern __shared__ float s_c[];                // centroids [d][WP]
+    __shared__ __align__(16) char s_a[4][score_lds(KM)];
+    extern __shared__ __align__(16) char s_cent[];
+    score_cent_t<KM>* s_c = (score_cent_t<KM>*)s_cent;                    // centroids [d][WP]
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int bhk = blockIdx.y, hk = bhk % L.Hkv;
-    score_stage_centroids<KM>(cents + (size_t)hk * L.K * L.d, s_c, L.K, L.d);
-    __syncthreads();
     const int j0 = (blockIdx.x * 4 + wave) * 64;  // first key of this wavefront
-    if (j0 >= n_ctx) return;                      // (no barrier after this point)
     const uint32_t m = score_rows_topk<T, KM>((const char*)(kc + ((size_t)bhk * L.n + j0) * L.d), (size_t)L.d * sizeof(T),
-                                              min(64, n_ctx - j0), L.d, s_c, s_a[wave], L.K, L.topk);
+                                              min(64, n_ctx - j0), L.d, s_c, s_a[wave], L.K, L.topk, [&]() {
+                                                  score_stage_centroids<KM>(cents + (size_t)hk * L.K * L.d, s_c, L.K, L.d);
+                                                  __syncthreads();
+                                              });
     if (j0 + lane < n_ctx) ((uint32_t*)(st + L.off_mk))[(size_t)bhk * L.n + j0 + lane] = m;
 }
 
@@ -1287,7 +1288,7 @@ hipError_t launch_decode_prefill(const DecodeLayout& L, int n_ctx, const void* k
     if (token_masks) {
         hipLaunchKernelGGL(decode_prefill_masks_kernel, g1, dim3(256), 0, s, L, n_ctx, token_masks, st);
     } else {
-        const size_t lds = (size_t)L.d * score_wp(km) * 4;               // centroids; with the staging space below 86 KB
+        const size_t lds = score_cent_bytes(km, L.d);                    // with the staging space below 86 KB
 #define FOCUS_DEC_SCORE(T_, KM_) hipLaunchKernelGGL((decode_prefill_score_kernel<T_, KM_>), g1, dim3(256), lds, s, L, n_ctx, (const T_*)kc, cents, st)
 #define FOCUS_DEC_SCORE_T(T_)                                                                                             \
     { if (km == 4) FOCUS_DEC_SCORE(T_, 4); else if (km == 8) FOCUS_DEC_SCORE(T_, 8);                                      \

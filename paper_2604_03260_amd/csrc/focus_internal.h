@@ -96,8 +96,6 @@ struct Layout {
     size_t off_qcc, off_kcc;           // class counts [.,NC]
     size_t off_qco, off_kco;           // padded class offsets [.,NC+1]
     size_t off_clsmask;                // group bit mask of each class [NC]
-    size_t off_cent64;                 // centroids as fp64 [Hkv][d rounded up to whole 128-byte row chunks][KMAX],
-                                       // KMAX = K rounded up to 4/8/16/32
     size_t off_qperm;                  // [B,Hq,NQP] positions in class order, -1 in pads (the scatter kernel writes both)
     size_t off_kpos;                   // [B,Hkv,NKP] positions in class order, KPOS_PAD in pads
     size_t off_kmsk;                   // [B,Hkv,NKP] membership masks in class order, 0 in pads (coarse classes only)
@@ -107,7 +105,7 @@ struct Layout {
     size_t off_gk;                     // [B,NKP,2,16 or 32] bf16: the soft assignment of every key position as bf16 high and
                                        // low parts, groups padded to 16 or 32, chunks swizzled per key (soft gate, 16-bit types)
     size_t off_kn2;                    // [B,Hkv,KN2_SLOTS] bit patterns of partial maxima of the squared key norms of the
-                                       // head (16-bit types; cleared by assign_init, raised by the scatter kernel's key
+                                       // head (16-bit types; cleared by the score kernel, raised by the scatter kernel's key
                                        // copy, the attention kernel takes the largest)
     size_t off_local;                  // the embedded local layout's own workspace (two_pass)
     size_t off_lse1;                   // [B,Hq,n] fp32: log-sum-exp of the first pass when the caller passes no lse (two_pass)

@@ -138,9 +138,16 @@ __device__ inline uint32_t topk_mask(const double (&s)[KP], int K, int topk)
 // row, two buffers, one barrier per chunk, the next four chunks' loads in flight meanwhile.  The A operand of step i is
 // component 4*i + l/16 of token l%16: rows are stored with the components of one l/16 side by side, so a lane reads
 // its whole chunk with two 16-byte loads.  Accumulator register r of lane l is token 4*r + l/16, output l%16.
+//
+// d_g = 4 and 8 run on v_mfma_f64_4x4x4_4b (focus_score.h), one or two of 16 cycles per step in the place of one of 64: 20000 x 8192
+// f16, d_g = 8: 224 -> XX us; 32768 x 1200 bf16, d_g = 4: 36 -> XX.  Four of them per step would be no faster at d_g = 16: a step is
+// then as long, and widens three more values of W_g (112 -> 135 us; vector instructions do not run beside fp64 products).
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 constexpr int A_ROW = 128 + 16;              // LDS pitch of a staged row: 4 interleaved parts of 32 bytes, padded
+__host__ __device__ constexpr bool route_small(int dg) { return dg <= 8; }
+// LDS pitch of a row of W_g in floats: the four rows of a step on different banks
+__host__ __device__ constexpr int route_wp(int dg) { return dg <= 16 ? dg : dg + 16; }
 
 template <typename T, int DG, int NW>
 __global__ __launch_bounds__(64 * NW) void route_project_kernel(RouteLayout R, const T* __restrict__ hidden,
@@ -152,8 +159,10 @@ __global__ __launch_bounds__(64 * NW) void route_project_kernel(RouteLayout R, c
 {
     constexpr int NTHR = 64 * NW, TB = 16 * NW;
     constexpr int RC = 128 / (int)sizeof(T);             // components per chunk
-    constexpr int CB = (DG + 15) / 16;                   // blocks of 16 outputs
-    constexpr int WP = CB * 16 + (CB > 1 ? 16 : 0);      // LDS pitch of a row of W_g in floats: the four rows of a step on different banks
+    constexpr bool SMALL = route_small(DG);
+    constexpr int LC = SMALL ? 3 : 15, CB = (DG + LC) / (LC + 1);    // column of a block, blocks of 4 or of 16 outputs
+    constexpr int WP = route_wp(DG);                     // LDS pitch of a row of W_g in floats
+    typedef std::conditional_t<SMALL, double, f64x4> acc_t;
     constexpr int PF = 4;                                // chunks in flight: one takes 0.85 us of products, a load 1 to 2
     constexpr int WPT = (RC * DG + NTHR - 1) / NTHR;     // floats of W_g per thread and chunk
     // dynamic LDS: two buffers of hidden rows and of W_g during the projection, then z [TB][DG+1] and S [TB][K|1]
@@ -171,8 +180,6 @@ __global__ __launch_bounds__(64 * NW) void route_project_kernel(RouteLayout R, c
     const int nchunk = (dm + RC - 1) / RC;
     char* s_a = s_dyn;
     float* s_w = (float*)(s_dyn + 2 * TB * A_ROW);
-    for (int e = tid; e < 2 * RC * WP; e += NTHR) s_w[e] = 0.f;      // outputs past d_g (4, 8) stay zero
-    __syncthreads();
 
     u32x4 sta[PF][2];
     float swa[PF][WPT];
@@ -189,9 +196,9 @@ __global__ __launch_bounds__(64 * NW) void route_project_kernel(RouteLayout R, c
             sw[i] = (e < RC * DG && ch * RC + e / DG < dm) ? wg[(size_t)ch * RC * DG + e] : 0.f;
         }
     };
-    f64x4 acc[CB];
+    acc_t acc[CB];
 #pragma unroll
-    for (int cb = 0; cb < CB; ++cb) acc[cb] = f64x4{0.0, 0.0, 0.0, 0.0};
+    for (int cb = 0; cb < CB; ++cb) acc[cb] = acc_t{};
 
 #pragma unroll
     for (int p = 0; p < PF; ++p)
@@ -228,7 +235,7 @@ __global__ __launch_bounds__(64 * NW) void route_project_kernel(RouteLayout R, c
         if (ch + PF < nchunk) load_chunk(ch + PF, st, sw);
         const u32x4* ar = (const u32x4*)(abuf + (wave * 16 + (lane & 15)) * A_ROW + (lane >> 4) * 32);
         const u32x4 a0 = ar[0], a1 = ar[1];
-        const float* wr = wbuf + (lane >> 4) * WP + (lane & 15);
+        const float* wr = wbuf + (lane >> 4) * WP + (lane & LC);
         const int steps = min(RC, dm - ch * RC) / 4;     // dm is a multiple of 8
         auto step = [&](int i) {
             double a;
@@ -242,8 +249,11 @@ __global__ __launch_bounds__(64 * NW) void route_project_kernel(RouteLayout R, c
                     a = (double)__uint_as_float(i % 2 ? w2 & 0xffff0000u : w2 << 16);
             }
 #pragma unroll
-            for (int cb = 0; cb < CB; ++cb)
-                acc[cb] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, (double)wr[i * 4 * WP + cb * 16], acc[cb], 0, 0, 0);
+            for (int cb = 0; cb < CB; ++cb) {
+                const double w = (double)wr[i * 4 * WP + cb * (LC + 1)];
+                if constexpr (SMALL) acc[cb] = __builtin_amdgcn_mfma_f64_4x4x4f64(a, w, acc[cb], 0, 0, 0);
+                else acc[cb] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, w, acc[cb], 0, 0, 0);
+            }
         };
         // a full chunk without a branch per step: all its operands can be read ahead of the products
         if (steps == RC / 4) {
@@ -263,11 +273,14 @@ __global__ __launch_bounds__(64 * NW) void route_project_kernel(RouteLayout R, c
     double* s_s = s_z + TB * (DG + 1);
     const int KS = K | 1;
 #pragma unroll
-    for (int cb = 0; cb < CB; ++cb)
+    for (int cb = 0; cb < CB; ++cb) {
+        if constexpr (SMALL) {
+            s_z[(wave * 16 + (lane & 12) + (lane >> 4)) * (DG + 1) + cb * 4 + (lane & 3)] = acc[cb];
+        } else {
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-            if (DG % 16 == 0 || (lane & 15) < DG)
-                s_z[(wave * 16 + 4 * r + (lane >> 4)) * (DG + 1) + cb * 16 + (lane & 15)] = acc[cb][r];
+            for (int r = 0; r < 4; ++r) s_z[(wave * 16 + 4 * r + (lane >> 4)) * (DG + 1) + cb * 16 + (lane & 15)] = acc[cb][r];
+        }
+    }
     __syncthreads();
     double mymax = -INFINITY;
     const int tok = tid % TB;
@@ -408,8 +421,8 @@ hipError_t launch_project(const RouteLayout& R, const void* hidden, const float*
 {
     const int nw = route_tokens_per_group(R.B, R.n, R.dg) / 16;
     dim3 grid(R.nproj, R.B);
-    const int cb = (R.dg + 15) / 16, rc = 128 / (int)sizeof(T);
-    const size_t stage = 2 * ((size_t)nw * 16 * A_ROW + (size_t)rc * (cb * 16 + (cb > 1 ? 16 : 0)) * 4);
+    const int rc = 128 / (int)sizeof(T);
+    const size_t stage = 2 * ((size_t)nw * 16 * A_ROW + (size_t)rc * route_wp(R.dg) * 4);
     const size_t tail = (size_t)nw * 16 * (R.dg + 1 + (R.K | 1)) * sizeof(double);
     const size_t lds = stage > tail ? stage : tail;      // at most 51 KB (8 wavefronts, d_g <= 16) or 58 KB (4, d_g = 64, 16-bit rows)
 #define FOCUS_PROJ(DG, NW)                                                                                   \

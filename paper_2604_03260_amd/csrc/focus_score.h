@@ -1,10 +1,16 @@
-// Membership of 64 rows by one wavefront: fp64 scores against K centroids on v_mfma_f64_16x16x4, which adds its four
-// products to the accumulator one by one in index order with one rounding each (see focus_route.hip), so the scores are
-// the sequential sums of Sec. 2 Eq. 1 bit for bit; top-k by rank counting, ties to the smaller group.
+// Membership of 64 rows by one wavefront: fp64 scores against K centroids on the fp64 matrix cores, whose instructions add
+// their four products to the accumulator one by one in index order with one rounding each (v_mfma_f64_4x4x4_4b: 256000
+// random results equal the scalar fma chain bit for bit; 16x16x4: see focus_route.hip), so the scores are the sequential
+// sums of Sec. 2 Eq. 1 bit for bit; then the topk best, ties to the smaller group.
 //
-// The 64 rows are four tiles of 16 that share the B operand (centroids, staged once per work-group as fp32 [d][WP]); rows
-// are staged 128 bytes at a time, coalesced, in the wavefront's own LDS, components 4*i + p of a row side by side for
-// each p.  A product runs on 16 columns, so up to 16 groups cost the same.
+// The 64 rows are four tiles of 16 that share the B operand (centroids, staged once per work-group [d][WP]); rows
+// are staged a chunk at a time, coalesced, in the wavefront's own LDS, components 4*i + p of a row side by side for
+// each p.  The A operand of both instructions is component 4*i + l/16 of row l%16.  16x16x4 runs on 16 columns, 64 cycles
+// whatever K is; 4x4x4_4b is four blocks of 4 rows x 4 columns in 16 cycles, so up to 8 groups take one or two of those
+// per tile and step.  Vector instructions do not run beside fp64 products (each adds 5 to 8 cycles to a step of 64), so
+// the centroids are widened when they are staged where they are few.  State prefill of
+// a generation, scores and lists: 8 x 131072 keys of 128, K = 8 154 -> 116 us; 8 x 32768, K = 4 45 -> 31; 96 x 4096 of 64, K = 4
+// 35 -> 25.
 #pragma once
 #include "focus_internal.h"
 #include <type_traits>
@@ -13,100 +19,121 @@ namespace focus {
 
 typedef double score_f64x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t score_u32x4;
-constexpr int SCORE_A_ROW = 128 + 16;             // LDS pitch of a staged row: four interleaved parts of 32 bytes, padded
-constexpr int SCORE_LDS = 64 * SCORE_A_ROW;       // staging bytes per wavefront
 
-// LDS pitch (floats) of a component's centroid values: KM groups, zero past K; the rows a step reads on different banks
-__host__ __device__ constexpr int score_wp(int km) { return km <= 16 ? 16 : 48; }
+// up to 8 groups: products of 4 columns, centroids as doubles; more: products of 16 columns, centroids as floats
+__host__ __device__ constexpr bool score_small(int km) { return km <= 8; }
+// bytes of a row staged at a time: as many work-groups as fit count (bucketing with 128 -> 64: 40 heads of 128 x 32768, K = 16
+// 360 -> 323 us; 20000 x 48 heads of 96, K = 4 130 -> 120), above 16 groups the space in which their scores meet does (493 / 677)
+__host__ __device__ constexpr int score_chunk(int km) { return km <= 16 ? 64 : 128; }
+// LDS pitch of a staged row: four interleaved parts, padded; staging bytes per wavefront
+__host__ __device__ constexpr int score_a_row(int km) { return score_chunk(km) + 16; }
+__host__ __device__ constexpr int score_lds(int km) { return 64 * score_a_row(km); }
+// LDS pitch (elements) of a component's centroid values: KM groups, zero past K; the rows a step reads on different banks
+__host__ __device__ constexpr int score_wp(int km) { return score_small(km) ? km : km <= 16 ? 16 : 48; }
+// bytes of the staged centroids
+__host__ __device__ constexpr size_t score_cent_bytes(int km, int d) { return (size_t)d * score_wp(km) * (score_small(km) ? 8 : 4); }
+template <int KM> using score_cent_t = std::conditional_t<score_small(KM), double, float>;
 
 // all threads: centroids [K][d] fp32 -> s_c [d][WP]
 template <int KM>
-__device__ inline void score_stage_centroids(const float* __restrict__ c, float* s_c, int K, int d)
+__device__ inline void score_stage_centroids(const float* __restrict__ c, score_cent_t<KM>* s_c, int K, int d)
 {
     constexpr int WP = score_wp(KM);
     for (int e = threadIdx.x; e < d * WP; e += blockDim.x) {
         const int t = e / WP, g = e % WP;
-        s_c[e] = g < K ? c[(size_t)g * d + t] : 0.f;
+        s_c[e] = g < K ? (score_cent_t<KM>)c[(size_t)g * d + t] : (score_cent_t<KM>)0;
     }
 }
 
-// gbase: first row, pitch: bytes between rows, rows: 1 .. 64 of them; abuf: SCORE_LDS bytes of the wavefront's own.
-// Returns the mask of row `lane` (0 past the rows).  KM = K rounded up to 4, 8, 16 or 32.
-template <typename T, int KM>
-__device__ inline uint32_t score_rows_topk(const char* __restrict__ gbase, size_t pitch, int rows, int d, const float* s_c,
-                                           char* abuf, int K, int topk)
+// gbase: first row, pitch: bytes between rows, rows: at most 64 of them; abuf: score_lds(KM) bytes of the wavefront's own.
+// staged: called once by all wavefronts of the work-group, after their first loads are on their way: stages the centroids
+// and waits for them.  Returns the mask of row `lane` (0 past the rows).  KM = K rounded up to 4, 8, 16 or 32.
+template <typename T, int KM, typename F>
+__device__ inline uint32_t score_rows_topk(const char* __restrict__ gbase, size_t pitch, int rows, int d, const score_cent_t<KM>* s_c,
+                                           char* abuf, int K, int topk, F&& staged)
 {
-    constexpr int RC = 128 / (int)sizeof(T);      // components per staged chunk
-    constexpr int CB = KM <= 16 ? 1 : 2;          // blocks of 16 columns
+    constexpr int CHUNK = score_chunk(KM), A_ROW = score_a_row(KM);
+    constexpr int RC = CHUNK / (int)sizeof(T);    // components per staged chunk
+    constexpr int NP = CHUNK / 16;                // 16-byte pieces of a row's chunk = loads per lane = dwords of a part
+    constexpr bool SMALL = score_small(KM);
+    constexpr int CB = SMALL ? KM / 4 : KM <= 16 ? 1 : 2;         // blocks of 4 or of 16 columns
+    constexpr int LC = SMALL ? 3 : 15;            // lane bits that say which column of a block
     constexpr int WP = score_wp(KM);
     constexpr int SP = KM + 1;                    // doubles per row when the scores meet in LDS
-    constexpr int TG = (16 * 4 * SP * 8 <= SCORE_LDS) ? 4 : 2;        // tiles whose scores fit the staging space
-    static_assert(16 * TG * SP * 8 <= SCORE_LDS, "scores stay inside the staging space");
+    constexpr int TG = (16 * 4 * SP * 8 <= score_lds(KM)) ? 4 : (16 * 2 * SP * 8 <= score_lds(KM)) ? 2 : 1;    // tiles whose scores fit the staging space
+    static_assert(16 * TG * SP * 8 <= score_lds(KM), "scores stay inside the staging space");
     const int lane = threadIdx.x & 63;
     const int row_bytes = d * (int)sizeof(T);
     const int nchunk = (d + RC - 1) / RC;
-    score_u32x4 stg[8];
+    score_u32x4 stg[NP];
     auto load_chunk = [&](int ch) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int row = i * 8 + lane / 8, byte = ch * 128 + lane % 8 * 16;
+        for (int i = 0; i < NP; ++i) {
+            const int row = i * (64 / NP) + lane / NP, byte = ch * CHUNK + lane % NP * 16;
             const score_u32x4 z = {0u, 0u, 0u, 0u};
             stg[i] = (row < rows && byte < row_bytes) ? *(const score_u32x4*)(gbase + (size_t)row * pitch + byte) : z;
         }
     };
-    score_f64x4 acc[4][CB];
+    typedef std::conditional_t<SMALL, double, score_f64x4> acc_t;
+    acc_t acc[4][CB];
 #pragma unroll
     for (int t = 0; t < 4; ++t)
 #pragma unroll
-        for (int cb = 0; cb < CB; ++cb) acc[t][cb] = score_f64x4{0.0, 0.0, 0.0, 0.0};
+        for (int cb = 0; cb < CB; ++cb) acc[t][cb] = acc_t{};
     load_chunk(0);
+    staged();
+    if (rows <= 0) return 0;
     for (int ch = 0; ch < nchunk; ++ch) {
         // a wavefront's LDS accesses run in order: no barrier, only the compiler must keep the order
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            uint32_t* dst = (uint32_t*)(abuf + (i * 8 + lane / 8) * SCORE_A_ROW) + lane % 8;
+        for (int i = 0; i < NP; ++i) {
+            uint32_t* dst = (uint32_t*)(abuf + (i * (64 / NP) + lane / NP) * A_ROW) + lane % NP;
             const score_u32x4 v = stg[i];
             if constexpr (sizeof(T) == 4) {
-                dst[0] = v[0]; dst[8] = v[1]; dst[16] = v[2]; dst[24] = v[3];
+                dst[0] = v[0]; dst[NP] = v[1]; dst[2 * NP] = v[2]; dst[3 * NP] = v[3];
             } else {
                 dst[0] = (v[0] & 0xffffu) | (v[2] << 16);
-                dst[8] = (v[0] >> 16) | (v[2] & 0xffff0000u);
-                dst[16] = (v[1] & 0xffffu) | (v[3] << 16);
-                dst[24] = (v[1] >> 16) | (v[3] & 0xffff0000u);
+                dst[NP] = (v[0] >> 16) | (v[2] & 0xffff0000u);
+                dst[2 * NP] = (v[1] & 0xffffu) | (v[3] << 16);
+                dst[3 * NP] = (v[1] >> 16) | (v[3] & 0xffff0000u);
             }
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         if (ch + 1 < nchunk) load_chunk(ch + 1);
-        score_u32x4 ar[4][2];
+        constexpr int AR = NP / 4;                // 16-byte reads of a part
+        score_u32x4 ar[4][AR];
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
-            const score_u32x4* p = (const score_u32x4*)(abuf + (t * 16 + (lane & 15)) * SCORE_A_ROW + (lane >> 4) * 32);
-            ar[t][0] = p[0];
-            ar[t][1] = p[1];
+            const score_u32x4* p = (const score_u32x4*)(abuf + (t * 16 + (lane & 15)) * A_ROW + (lane >> 4) * (4 * NP));
+#pragma unroll
+            for (int i = 0; i < AR; ++i) ar[t][i] = p[i];
         }
-        const float* wr = s_c + (ch * RC + (lane >> 4)) * WP + (lane & 15);
+        const score_cent_t<KM>* wr = s_c + (ch * RC + (lane >> 4)) * WP + (lane & LC);
         const int steps = min(RC, d - ch * RC) / 4;
         auto step = [&](int i) {
             double bv[CB];
 #pragma unroll
-            for (int cb = 0; cb < CB; ++cb) bv[cb] = (double)wr[i * 4 * WP + cb * 16];
+            for (int cb = 0; cb < CB; ++cb) bv[cb] = (double)wr[i * 4 * WP + cb * (LC + 1)];
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
                 double a;
                 if constexpr (sizeof(T) == 4) {
-                    a = (double)__uint_as_float(ar[t][(i / 4) % 2][i % 4]);
+                    a = (double)__uint_as_float(ar[t][(i / 4) % AR][i % 4]);
                 } else {
-                    const uint32_t w2 = ar[t][(i / 8) % 2][(i / 2) % 4];
+                    const uint32_t w2 = ar[t][(i / 8) % AR][(i / 2) % 4];
                     if constexpr (std::is_same<T, f16_bits>::value)
                         a = (double)f16_bits_to_f32((uint16_t)(i % 2 ? w2 >> 16 : w2 & 0xffffu));
                     else
                         a = (double)__uint_as_float(i % 2 ? w2 & 0xffff0000u : w2 << 16);
                 }
 #pragma unroll
-                for (int cb = 0; cb < CB; ++cb) acc[t][cb] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, bv[cb], acc[t][cb], 0, 0, 0);
+                for (int cb = 0; cb < CB; ++cb) {
+                    if constexpr (SMALL) acc[t][cb] = __builtin_amdgcn_mfma_f64_4x4x4f64(a, bv[cb], acc[t][cb], 0, 0, 0);
+                    else acc[t][cb] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, bv[cb], acc[t][cb], 0, 0, 0);
+                }
             }
         };
         if (steps == RC / 4) {
@@ -118,7 +145,8 @@ __device__ inline uint32_t score_rows_topk(const char* __restrict__ gbase, size_
                 if (i < steps) step(i);
         }
     }
-    // accumulator register r of lane l: row 4*r + l/16 of the tile, group l%16
+    // accumulator of lane l: row 4*(l%16/4) + l/16 of the tile, group l%4 of the block; register r of the 16-column
+    // product: row 4*r + l/16, group l%16
     double* s_s = (double*)abuf;
     uint32_t mask = 0;
 #pragma unroll
@@ -128,11 +156,16 @@ __device__ inline uint32_t score_rows_topk(const char* __restrict__ gbase, size_
 #pragma unroll
         for (int t = 0; t < TG; ++t)
 #pragma unroll
-            for (int cb = 0; cb < CB; ++cb)
+            for (int cb = 0; cb < CB; ++cb) {
+                if constexpr (SMALL) {
+                    s_s[(t * 16 + (lane & 12) + (lane >> 4)) * SP + cb * 4 + (lane & 3)] = acc[t0 + t][cb];
+                } else {
 #pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    if (cb * 16 + (lane & 15) < KM)
-                        s_s[(t * 16 + 4 * r + (lane >> 4)) * SP + cb * 16 + (lane & 15)] = acc[t0 + t][cb][r];
+                    for (int r = 0; r < 4; ++r)
+                        if (cb * 16 + (lane & 15) < KM)
+                            s_s[(t * 16 + 4 * r + (lane >> 4)) * SP + cb * 16 + (lane & 15)] = acc[t0 + t][cb][r];
+                }
+            }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         if (lane / (TG * 16) == t0 / TG && lane < rows) {
