@@ -378,15 +378,15 @@ focus_status make_decode_layout(const focus_params* p, focus::DecodeLayout* L, f
     return FOCUS_OK;
 }
 
-// The embedded local layout of a two-pass problem: every token in one class, position order (the bucketing with a
-// constant membership, as the soft gate uses it), with its own class-ordered -- here: position-ordered -- key copy.
+// The embedded local layout of a two-pass problem: every token in one class, position order, with its own key copy.
+// Called after the bucketing of the problem itself, whose largest key norms it takes over.
 hipError_t assign_local_layout(const focus_params* p, const focus::Layout& L, const void* k, char* ws, hipStream_t st)
 {
     if (!L.two_pass) return hipSuccess;
     focus::Layout L2;
     focus::HeadMap hm2;
     if (make_layout(p, &L2, &hm2, false, true) != FOCUS_OK) return hipErrorInvalidValue;
-    return focus::launch_assign_tokens(L2, nullptr, k, ws + L.off_local, nullptr, st);
+    return focus::launch_position_layout(L2, k, (const unsigned*)(ws + L.off_kn2), ws + L.off_local, st);
 }
 
 }  // namespace
@@ -576,11 +576,13 @@ focus_status soft_launch(const focus_params* p, float lambda, const float* g, co
     // 512-byte key rows, so that shape goes through the vector kernel (correct, slow)
     if (p->d == 256) vector = true;
     hipStream_t s = (hipStream_t)stream;
-    // one class holding every token, in position order: the bucketing with a constant membership
-    hipError_t e = focus::launch_assign_tokens(L, nullptr, k, (char*)workspace, nullptr, s);
-    if (e == hipSuccess && L.dtype != FOCUS_F32 && !vector) e = focus::launch_soft_gather_g(L, g, (char*)workspace, s);
+    // one class holding every token, in position order (the vector kernel reads it through the tables of the bucketing)
+    const bool tiled = L.dtype != FOCUS_F32 && !vector;
+    hipError_t e = tiled ? focus::launch_position_layout(L, k, nullptr, (char*)workspace, s)
+                         : focus::launch_assign_tokens(L, nullptr, k, (char*)workspace, nullptr, s);
+    if (e == hipSuccess && tiled) e = focus::launch_soft_gather_g(L, g, (char*)workspace, s);
     if (e == hipSuccess) {
-        if (L.dtype != FOCUS_F32 && !vector)
+        if (tiled)
             e = focus::launch_attn_mfma(L, hm, q, k, v, g, (char*)workspace, out, lse, nullptr, s);
         else
             e = focus::launch_attn_simple(L, hm, q, k, v, g, (char*)workspace, out, lse, nullptr, s);

@@ -327,7 +327,7 @@ __device__ inline float chunk_norm2(const uint4& val, bool f16)
 
 // k: the key rows (16-bit types) for the class-ordered copy the matrix-core attention kernel reads, or NULL.
 // The copy also leaves the largest squared key norm of the (batch, KV head) in the workspace (off_kn2: KN2_SLOTS
-// partial maxima per head, cleared by the score kernel): a non-negative float orders like its bit pattern, so one
+// partial maxima per head, cleared by the kernel before it): a non-negative float orders like its bit pattern, so one
 // atomicMax on the bits per work-group does it, and a NaN or infinite norm ends up above every finite one.
 // LINEAR (masked layouts): one class, slot = position.  OWN_SCAN: no scan launch ran; the work-group adds up the group
 // histograms of the row's sort blocks itself (a few thousand integers at most), and sort block 0 writes the row's counts.
@@ -509,6 +509,28 @@ __global__ __launch_bounds__(SB) void scatter_kernel(Layout L, int which, const 
     }
 }
 
+// ---------------------------------------------------------------- one class in position order
+// What the tiled kernel reads of a layout in which every token is in one class and no membership counts (the soft gate, the
+// window pass of a two-pass launch): the keys' positions and their copy, in one launch.  The bucketing with a constant
+// membership did the same in three, with lists, histograms and a scan that nobody read (8192 tokens, 8 heads of 128:
+// 41 us before, 11 now).  kn2: the largest key norms of the same keys, found by the bucketing before; NULL: not needed.
+__global__ __launch_bounds__(SB) void position_layout_kernel(Layout L, const uint4* __restrict__ k, const unsigned* __restrict__ kn2,
+                                                             char* __restrict__ ws)
+{
+    const int tid = threadIdx.x, bh = blockIdx.y, p0 = blockIdx.x * SB, p1 = min(L.NKP, p0 + SB);
+    const int CPR = L.dp / 8, cin = L.d / 8;          // 16-byte chunks per row of the copy, of k
+    if (p0 + tid < p1) ((int*)(ws + L.off_kpos))[(size_t)bh * L.NKP + p0 + tid] = p0 + tid < L.n ? p0 + tid : KPOS_PAD;
+    if (kn2 && blockIdx.x == 0 && tid < KN2_SLOTS)
+        ((unsigned*)(ws + L.off_kn2))[(size_t)bh * KN2_SLOTS + tid] = kn2[(size_t)bh * KN2_SLOTS + tid];
+    const uint4* src = k + ((size_t)(bh / L.Hkv) * L.ks[0] + (size_t)(bh % L.Hkv) * L.ks[1]) / 8;
+    const size_t pitch = (size_t)L.ks[2] / 8;
+    uint4* dst = (uint4*)(ws + L.off_kc) + ((size_t)bh * L.NKP + p0) * CPR;
+    for (int id = tid; id < (p1 - p0) * CPR; id += SB) {
+        const int p = p0 + id / CPR, ch = id % CPR;
+        dst[id] = (p < L.n && ch < cin) ? src[(size_t)p * pitch + ch] : make_uint4(0, 0, 0, 0);
+    }
+}
+
 // ---------------------------------------------------------------- membership given per token
 // The paper's router assigns one membership per token of a layer, shared by all heads and by the
 // query and key roles (Sec. 2).  A work-group turns the token masks of a sort block of a batch element into
@@ -526,6 +548,8 @@ __global__ __launch_bounds__(SB) void token_classes_kernel(Layout L, const uint3
     const int pos = blk * SB + tid;
     for (int e = tid; e < MAX_CLASSES; e += SB) s_hist_c[e] = 0;
     if (tid < 32) s_hist_g[tid] = 0;
+    if (blk == 0 && blockIdx.z == 0)              // (the scatter launch raises these)
+        for (int e = tid; e < L.Hkv * KN2_SLOTS; e += SB) ((unsigned*)(ws + L.off_kn2))[(size_t)b * L.Hkv * KN2_SLOTS + e] = 0u;
     __syncthreads();
     uint32_t mask = 0;
     int cls = 0;
@@ -621,11 +645,15 @@ hipError_t launch_assign(const Layout& L, const HeadMap& hm, const void* q, cons
     return launch_scatter(L, k, ws, st);
 }
 
+hipError_t launch_position_layout(const Layout& L, const void* k, const unsigned* kn2, char* ws, hipStream_t st)
+{
+    hipLaunchKernelGGL(position_layout_kernel, dim3((L.NKP + SB - 1) / SB, L.B * L.Hkv), dim3(SB), 0, st, L, (const uint4*)k, kn2, ws);
+    return hipGetLastError();
+}
+
 hipError_t launch_assign_tokens(const Layout& L, const uint32_t* token_masks, const void* k, char* ws,
                                 int32_t* invalid_count, hipStream_t st)
 {
-    const size_t nzeros = (size_t)L.B * L.Hkv * KN2_SLOTS;           // the largest-key-norm slots
-    hipLaunchKernelGGL(fill_i32_kernel, dim3((unsigned)std::min<size_t>(1024, (nzeros + 255) / 256)), dim3(256), 0, st, (int*)(ws + L.off_kn2), nzeros, 0);
     if (invalid_count) hipLaunchKernelGGL(fill_i32_kernel, dim3(1), dim3(64), 0, st, invalid_count, (size_t)1, 0);
     // the heads of a sort block are split until there are a few work-groups per compute unit (128 blocks x 40 heads: one
     // work-group for all heads wrote for 11 us, eight for 5)

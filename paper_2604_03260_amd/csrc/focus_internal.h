@@ -107,7 +107,7 @@ struct Layout {
     size_t off_gk;                     // [B,NKP,2,16 or 32] bf16: the soft assignment of every key position as bf16 high and
                                        // low parts, groups padded to 16 or 32, chunks swizzled per key (soft gate, 16-bit types)
     size_t off_kn2;                    // [B,Hkv,KN2_SLOTS] bit patterns of partial maxima of the squared key norms of the
-                                       // head (16-bit types; cleared by the score kernel, raised by the scatter kernel's key
+                                       // head (16-bit types; cleared with the memberships, raised by the scatter kernel's key
                                        // copy, the attention kernel takes the largest)
     size_t off_local;                  // the embedded local layout's own workspace (two_pass)
     size_t off_lse1;                   // [B,Hq,n] fp32: log-sum-exp of the first pass when the caller passes no lse (two_pass)
@@ -220,6 +220,8 @@ constexpr size_t ROUTE_STATIC_SCRATCH_BYTES = (size_t)16 << 20;
 hipError_t route_static_scratch(char** ptr);
 hipError_t launch_assign_tokens(const Layout& L, const uint32_t* token_masks, const void* k, char* ws,
                                 int32_t* invalid_count, hipStream_t st);
+// positions and key copy of a layout of one class in position order (16-bit types, tiled kernel only)
+hipError_t launch_position_layout(const Layout& L, const void* k, const unsigned* kn2, char* ws, hipStream_t st);
 hipError_t launch_assign(const Layout& L, const HeadMap& hm, const void* q, const void* k,
                          const float* centroids, char* ws, hipStream_t st);
 hipError_t launch_attn_simple(const Layout& L, const HeadMap& hm, const void* q, const void* k,
