@@ -256,7 +256,7 @@ template <typename T, int KM, bool CLS>
 __global__ __launch_bounds__(SB) void score_kernel(Layout L, HeadMap hm, const T* __restrict__ xq, const T* __restrict__ xk,
                                                    const float* __restrict__ cents, int which, char* __restrict__ ws)
 {
-    __shared__ __align__(16) char s_a[4][score_lds(KM)];
+    __shared__ __align__(16) char s_a[4][score_lds(score_chunk<T>(KM))];
     __shared__ int s_h[4][32];
     __shared__ int s_hist_c[CLS ? MAX_CLASSES : 1];
     extern __shared__ __align__(16) char s_cent[];
@@ -272,7 +272,7 @@ __global__ __launch_bounds__(SB) void score_kernel(Layout L, HeadMap hm, const T
     if (!is_query && blk == 0 && tid < KN2_SLOTS) ((unsigned*)(ws + L.off_kn2))[(size_t)bh * KN2_SLOTS + tid] = 0u;
     const int j0 = blk * SB + wave * 64, rows = min(64, n - j0);
     const T* x = (is_query ? xq : xk) + (size_t)(bh / H) * xs[0] + (size_t)h * xs[1] + (size_t)j0 * xs[2];
-    const uint32_t m = score_rows_topk<T, KM>((const char*)x, (size_t)xs[2] * sizeof(T), rows, L.d, s_c, s_a[wave], K, L.topk, [&]() {
+    const uint32_t m = score_rows_topk<T, KM, score_chunk<T>(KM)>((const char*)x, (size_t)xs[2] * sizeof(T), rows, L.d, s_c, s_a[wave], K, L.topk, [&]() {
         score_stage_centroids<KM>(cents + (size_t)hk * K * L.d, s_c, K, L.d);
         if constexpr (CLS)
             for (int e = tid; e < L.NC; e += SB) s_hist_c[e] = 0;
@@ -300,6 +300,78 @@ __global__ __launch_bounds__(SB) void score_kernel(Layout L, HeadMap hm, const T
         for (int c = tid; c < L.NC; c += SB) bc[c] = s_hist_c[c];
     else if (tid == 0)
         bc[0] = min(SB, n - blk * SB);
+}
+
+// ---------------------------------------------------------------- short rows in one launch
+// The whole bucketing of a (batch, head) row of a masked layout by one work-group, 64 tokens per wavefront: memberships, group
+// counts and lists, positions.  For attention kernels that read k in place (no key copy, no bits, no norms).  All of it is
+// latency: the launch between scores and lists costs more than spreading a row over several compute units saves
+// (12 + 12 heads of 64, K = 4: 512 tokens 18.7 -> 7.9 us with the key copy left out, 10.7 in two launches).
+template <typename T, int KM, int NW>
+__global__ __launch_bounds__(64 * NW) void bucket_row_kernel(Layout L, HeadMap hm, const T* __restrict__ xq, const T* __restrict__ xk,
+                                                             const float* __restrict__ cents, char* __restrict__ ws)
+{
+    __shared__ __align__(16) char s_a[NW][score_lds(64)];
+    __shared__ int s_w[NW][KM];
+    extern __shared__ __align__(16) char s_cent[];
+    score_cent_t<KM>* s_c = (score_cent_t<KM>*)s_cent;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int is_query = side_of_row(L, -1, blockIdx.x), bh = row_in_side(L, -1, blockIdx.x);
+    const int K = L.K, n = L.n;
+    const int H = is_query ? L.Hq : L.Hkv, h = bh % H, hk = is_query ? hm.kv[h] : h;
+    const long long* xs = is_query ? L.qs : L.ks;
+    const int pos = wave * 64 + lane;
+    const T* x = (is_query ? xq : xk) + (size_t)(bh / H) * xs[0] + (size_t)h * xs[1] + (size_t)(wave * 64) * xs[2];
+    const uint32_t m = score_rows_topk<T, KM, 64>((const char*)x, (size_t)xs[2] * sizeof(T), min(64, n - wave * 64), L.d, s_c, s_a[wave], K,
+                                              L.topk, [&]() {
+                                                  score_stage_centroids<KM>(cents + (size_t)hk * K * L.d, s_c, K, L.d);
+                                                  __syncthreads();
+                                              });
+    for (int g = 0; g < K; ++g) {
+        const unsigned long long has = __ballot((m >> g) & 1u);
+        if (lane == 0) s_w[wave][g] = __popcll(has);
+    }
+    __syncthreads();
+    // lane g: entries of group g in all and before this wavefront, then where its list begins
+    int total = 0, before = 0;
+    if (lane < K) {
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            const int c = s_w[w][lane];
+            total += c;
+            before += w < wave ? c : 0;
+        }
+    }
+    int go = total;                               // inclusive prefix sum over the groups: they lie back to back in the list
+    for (int off = 1; off < K; off <<= 1) {
+        const int y = __shfl_up(go, off, 64);
+        if (lane >= off) go += y;
+    }
+    go -= total;
+    if (wave == 0 && lane < K) {
+        ((int*)(ws + (is_query ? L.off_qgc : L.off_kgc)))[(size_t)bh * K + lane] = total;
+        int* goff = (int*)(ws + (is_query ? L.off_qgo : L.off_kgo)) + (size_t)bh * (K + 1);
+        goff[lane] = go;
+        if (lane == K - 1) goff[K] = go + total;
+    }
+    const unsigned long long lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+    int* lists = (int*)(ws + (is_query ? L.off_qgl : L.off_kgl)) + (size_t)bh * L.topk * n;
+    for (int g = 0; g < K; ++g) {
+        const unsigned long long has = __ballot((m >> g) & 1u);
+        const int first = __builtin_amdgcn_readlane(go + before, g);
+        if ((m >> g) & 1u) lists[first + __popcll(has & lt)] = pos;
+    }
+    if (pos < n) ((uint32_t*)(ws + (is_query ? L.off_mq : L.off_mk)))[(size_t)bh * n + pos] = m;
+    const int plen = is_query ? L.NQP : L.NKP;
+    for (int p = tid; p < plen; p += 64 * NW) {       // (the first round holds every token)
+        if (is_query) {
+            ((int*)(ws + L.off_qperm))[(size_t)bh * L.NQP + p] = p < n ? p : -1;
+        } else {
+            ((int*)(ws + L.off_kpos))[(size_t)bh * L.NKP + p] = p < n ? p : KPOS_PAD;
+            ((uint32_t*)(ws + L.off_kmsk))[(size_t)bh * L.NKP + p] = p < n ? m : 0u;
+        }
+    }
 }
 
 __global__ void fill_i32_kernel(int* __restrict__ p, size_t count, int value)
@@ -611,6 +683,34 @@ hipError_t launch_score_k(const Layout& L, const HeadMap& hm, const void* q, con
     return launch_score<T, 32>(L, hm, q, k, centroids, ws, st);
 }
 
+// One launch where a row is little enough work for one compute unit (scores are n * d products of 4 or 8 groups; above 8
+// groups 16 columns are computed).  Bucketing, one launch / two (us): 12 + 12 heads of 64, K = 4: 512 tokens 7.9 / 10.7, 1024 10.5 / 11.6;
+// 8 + 2 of 128: K = 4 512 tokens 10.0 / 12.3, 700 12.1 / 11.9, 1024 14.4 / 12.1; K = 8 512 13.0 / 15.2, 1024 19.2 / 15.1; K = 16 512
+// 21.7 / 22.7; 16 + 4 of 256 in fp32, 512, K = 16 34 / 32; 768 rows of 64 in fp32, K = 4: 512 28 / 32, 1024 58 / 55.
+bool short_rows(const Layout& L)
+{
+    return L.masked && (L.dtype == 0 || short_attention(L)) && (long long)L.n * L.d <= 65536 && L.n <= (L.K <= 8 ? 1024 : L.K <= 16 ? 512 : 0) &&
+           (L.n <= 512 || L.B * (L.Hq + L.Hkv) <= 512);
+}
+
+template <typename T, int KM, int NW>
+hipError_t launch_bucket_rows(const Layout& L, const HeadMap& hm, const void* q, const void* k, const float* centroids, char* ws, hipStream_t st)
+{
+    hipLaunchKernelGGL((bucket_row_kernel<T, KM, NW>), dim3(L.B * (L.Hq + L.Hkv)), dim3(64 * NW), score_cent_bytes(KM, L.d), st, L, hm,
+                       (const T*)q, (const T*)k, centroids, ws);
+    return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_bucket_rows_k(const Layout& L, const HeadMap& hm, const void* q, const void* k, const float* centroids, char* ws, hipStream_t st)
+{
+#define FOCUS_ROWS(KM_) (L.n <= 512 ? launch_bucket_rows<T, KM_, 8>(L, hm, q, k, centroids, ws, st) : launch_bucket_rows<T, KM_, 16>(L, hm, q, k, centroids, ws, st))
+    if (L.K <= 4) return FOCUS_ROWS(4);
+    if (L.K <= 8) return FOCUS_ROWS(8);
+    return launch_bucket_rows<T, 16, 8>(L, hm, q, k, centroids, ws, st);
+#undef FOCUS_ROWS
+}
+
 // Masked layouts need no class tables and no job list: where a row's group histograms are few, the scatter launch adds
 // them up itself and the scan launch (10 us of latency, one work-group per row) is left out.
 bool own_scan(const Layout& L) { return L.masked && (long long)L.nblk * L.K <= 4096; }
@@ -620,7 +720,7 @@ hipError_t launch_scatter(const Layout& L, const void* k, char* ws, hipStream_t 
 {
     // query side and key side in the same launch: rows [0, B*Hq) and the B*Hkv rows after them
     // (more rows than one launch can have: the two sides one after the other)
-    const uint16_t* kcopy = L.dtype != 0 ? (const uint16_t*)k : nullptr;   // class-ordered key copy for the MFMA kernel
+    const uint16_t* kcopy = L.dtype != 0 && !short_attention(L) ? (const uint16_t*)k : nullptr;   // key copy for the tiled kernel
     const bool both = L.B * (L.Hq + L.Hkv) <= MAX_GRID_ROWS;
     for (int which = both ? -1 : 1; which >= -1; --which) {
         const int rows = which < 0 ? L.B * (L.Hq + L.Hkv) : which ? L.B * L.Hq : L.B * L.Hkv;
@@ -637,6 +737,10 @@ hipError_t launch_scatter(const Layout& L, const void* k, char* ws, hipStream_t 
 hipError_t launch_assign(const Layout& L, const HeadMap& hm, const void* q, const void* k,
                          const float* centroids, char* ws, hipStream_t st)
 {
+    if (short_rows(L))
+        return L.dtype == 0 ? launch_bucket_rows_k<float>(L, hm, q, k, centroids, ws, st)
+               : L.dtype == 2 ? launch_bucket_rows_k<f16_bits>(L, hm, q, k, centroids, ws, st)
+                              : launch_bucket_rows_k<uint16_t>(L, hm, q, k, centroids, ws, st);
     const hipError_t e = L.dtype == 0 ? launch_score_k<float>(L, hm, q, k, centroids, ws, st)
                          : L.dtype == 2 ? launch_score_k<f16_bits>(L, hm, q, k, centroids, ws, st)
                                         : launch_score_k<uint16_t>(L, hm, q, k, centroids, ws, st);

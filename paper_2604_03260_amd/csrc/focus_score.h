@@ -23,11 +23,12 @@ typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t score_u3
 // up to 8 groups: products of 4 columns, centroids as doubles; more: products of 16 columns, centroids as floats
 __host__ __device__ constexpr bool score_small(int km) { return km <= 8; }
 // bytes of a row staged at a time: as many work-groups as fit count (bucketing with 128 -> 64: 40 heads of 128 x 32768, K = 16
-// 360 -> 323 us; 20000 x 48 heads of 96, K = 4 130 -> 120), above 16 groups the space in which their scores meet does (493 / 677)
-__host__ __device__ constexpr int score_chunk(int km) { return km <= 16 ? 64 : 128; }
+// 360 -> 323 us; 20000 x 48 heads of 96, K = 4 130 -> 120), above 16 groups the space in which their scores meet does (493 / 677);
+// 32-bit rows have half as many components in it (96 heads of 64 x 1024, K = 16: 23.4 / 21.9 with 128)
+template <typename T> __host__ __device__ constexpr int score_chunk(int km) { return km <= 16 && sizeof(T) == 2 ? 64 : 128; }
 // LDS pitch of a staged row: four interleaved parts, padded; staging bytes per wavefront
-__host__ __device__ constexpr int score_a_row(int km) { return score_chunk(km) + 16; }
-__host__ __device__ constexpr int score_lds(int km) { return 64 * score_a_row(km); }
+__host__ __device__ constexpr int score_a_row(int chunk) { return chunk + 16; }
+__host__ __device__ constexpr int score_lds(int chunk) { return 64 * score_a_row(chunk); }
 // LDS pitch (elements) of a component's centroid values: KM groups, zero past K; the rows a step reads on different banks
 __host__ __device__ constexpr int score_wp(int km) { return score_small(km) ? km : km <= 16 ? 16 : 48; }
 // bytes of the staged centroids
@@ -45,14 +46,14 @@ __device__ inline void score_stage_centroids(const float* __restrict__ c, score_
     }
 }
 
-// gbase: first row, pitch: bytes between rows, rows: at most 64 of them; abuf: score_lds(KM) bytes of the wavefront's own.
+// gbase: first row, pitch: bytes between rows, rows: at most 64 of them; abuf: score_lds(CHUNK) bytes of the wavefront's own.
 // staged: called once by all wavefronts of the work-group, after their first loads are on their way: stages the centroids
 // and waits for them.  Returns the mask of row `lane` (0 past the rows).  KM = K rounded up to 4, 8, 16 or 32.
-template <typename T, int KM, typename F>
+template <typename T, int KM, int CHUNK, typename F>
 __device__ inline uint32_t score_rows_topk(const char* __restrict__ gbase, size_t pitch, int rows, int d, const score_cent_t<KM>* s_c,
                                            char* abuf, int K, int topk, F&& staged)
 {
-    constexpr int CHUNK = score_chunk(KM), A_ROW = score_a_row(KM);
+    constexpr int A_ROW = score_a_row(CHUNK);
     constexpr int RC = CHUNK / (int)sizeof(T);    // components per staged chunk
     constexpr int NP = CHUNK / 16;                // 16-byte pieces of a row's chunk = loads per lane = dwords of a part
     constexpr bool SMALL = score_small(KM);
@@ -60,8 +61,8 @@ __device__ inline uint32_t score_rows_topk(const char* __restrict__ gbase, size_
     constexpr int LC = SMALL ? 3 : 15;            // lane bits that say which column of a block
     constexpr int WP = score_wp(KM);
     constexpr int SP = KM + 1;                    // doubles per row when the scores meet in LDS
-    constexpr int TG = (16 * 4 * SP * 8 <= score_lds(KM)) ? 4 : (16 * 2 * SP * 8 <= score_lds(KM)) ? 2 : 1;    // tiles whose scores fit the staging space
-    static_assert(16 * TG * SP * 8 <= score_lds(KM), "scores stay inside the staging space");
+    constexpr int TG = (16 * 4 * SP * 8 <= score_lds(CHUNK)) ? 4 : (16 * 2 * SP * 8 <= score_lds(CHUNK)) ? 2 : 1;    // tiles whose scores fit the staging space
+    static_assert(16 * TG * SP * 8 <= score_lds(CHUNK), "scores stay inside the staging space");
     const int lane = threadIdx.x & 63;
     const int row_bytes = d * (int)sizeof(T);
     const int nchunk = (d + RC - 1) / RC;
