@@ -161,7 +161,6 @@ focus_status make_layout(const focus_params* p, focus::Layout* L, focus::HeadMap
     }
     // 16-bit types at long n: 256-row tiles (8 wavefronts share every K/V tile: half the L2->LDS traffic per FLOP,
     // which is what bounds the kernel once a KV head's K/V no longer sits in L2/MALL)
-    L->dp = (p->d <= 64) ? 64 : (p->d <= 128) ? 128 : 256;
     const bool can256 = p->dtype != FOCUS_F32 && p->d <= 128 && !L->coarse && !soft;   // shapes with an 8-wavefront kernel
     L->BQ = (can256 && p->n >= LONG_N) ? 256 : BQ_VECTOR;
     // Two passes (see attn_launch) where the rows of a class tile spread over so many positions that the window
@@ -264,8 +263,8 @@ focus_status make_layout(const focus_params* p, focus::Layout* L, focus::HeadMap
     L->off_kn2 = take(BHk * focus::KN2_SLOTS * 4);
     L->off_nrflag = take(BHq * L->NT * 4);
     if (p->dtype != FOCUS_F32) {
-        L->off_kc = take(BHk * L->NKP * (size_t)L->dp * 2);
-        L->off_vt = take(BHk * L->NKP * (size_t)L->dp * 2);
+        L->off_kc = take(BHk * L->NKP * (size_t)p->d * 2);
+        L->off_vt = take(BHk * L->NKP * (size_t)p->d * 2);
     } else {
         L->off_kc = L->off_vt = off;
     }

@@ -525,7 +525,7 @@ __global__ __launch_bounds__(SB) void scatter_kernel(Layout L, int which, const 
     const int* cnt = (const int*)(ws + (is_query ? L.off_qcc : L.off_kcc)) + (size_t)bh * NC;
     const int plen = is_query ? L.NQP : L.NKP;
     const bool copy_k = !is_query && k != nullptr;
-    const int CPR = L.dp / 8;                        // 16-byte chunks per row of the key copy (8, 16 or 32)
+    const int CPR = L.d / 8;                         // 16-byte chunks per row of k and of the key copy
     uint4* kc = (uint4*)(ws + L.off_kc) + (size_t)bh * L.NKP * CPR;
     for (int c = LINEAR ? L.nblk - 1 - blk : blk; c <= NC; c += L.nblk) {      // (LINEAR: NC = 1, left to the last sort blocks)
         const int end0 = LINEAR ? min(plen, (n + KT - 1) / KT * KT) : 0;
@@ -543,27 +543,27 @@ __global__ __launch_bounds__(SB) void scatter_kernel(Layout L, int which, const 
             for (int id = tid; id < (p1 - p0) * CPR; id += SB) kc[(size_t)p0 * CPR + id] = make_uint4(0, 0, 0, 0);
     }
 
-    // ---- key rows: this sort block's rows into their class-ordered places, d padded with zeros to dp
+    // ---- key rows: this sort block's rows into their class-ordered places
     if (!copy_k) return;
     s_dest[tid] = dest;
     __syncthreads();
-    const int cin = L.d / 8;                         // chunks of a source row
+    const int lpr = CPR <= 8 ? 8 : CPR <= 16 ? 16 : 32;              // lanes per row, the last ones idle at d = 80 and 96
     const bool f16 = L.dtype == 2;
     // source rows through the strides of k (multiples of 8 elements = one 16-byte chunk)
     const uint4* src = (const uint4*)k + ((size_t)(bh / L.Hkv) * L.ks[0] + (size_t)(bh % L.Hkv) * L.ks[1] + (size_t)blk * SB * L.ks[2]) / 8;
     const size_t pitch = (size_t)L.ks[2] / 8;
     unsigned n2max = 0u;
-    for (int id = tid; id < SB * CPR; id += SB) {
-        const int row = id / CPR, ch = id % CPR;
+    for (int id = tid; id < SB * lpr; id += SB) {
+        const int row = id / lpr, ch = id % lpr;
         const int dd = s_dest[row];
         uint4 val = make_uint4(0, 0, 0, 0);
-        if (dd >= 0) {
-            if (ch < cin) val = src[(size_t)row * pitch + ch];
+        if (dd >= 0 && ch < CPR) {
+            val = src[(size_t)row * pitch + ch];
             kc[(size_t)dd * CPR + ch] = val;
         }
-        // the CPR chunks of a row sit in CPR consecutive lanes (CPR a power of two <= 32, rows do not straddle waves)
+        // the chunks of a row sit in lpr consecutive lanes (a power of two <= 32, rows do not straddle waves)
         float n2 = chunk_norm2(val, f16);
-        for (int off = 1; off < CPR; off <<= 1) n2 += __shfl_xor(n2, off, 64);
+        for (int off = 1; off < lpr; off <<= 1) n2 += __shfl_xor(n2, off, 64);
         const unsigned bits = __float_as_uint(n2) & 0x7fffffffu;     // a NaN may carry a sign bit
         n2max = bits > n2max ? bits : n2max;
     }
@@ -590,7 +590,7 @@ __global__ __launch_bounds__(SB) void position_layout_kernel(Layout L, const uin
                                                              char* __restrict__ ws)
 {
     const int tid = threadIdx.x, bh = blockIdx.y, p0 = blockIdx.x * SB, p1 = min(L.NKP, p0 + SB);
-    const int CPR = L.dp / 8, cin = L.d / 8;          // 16-byte chunks per row of the copy, of k
+    const int CPR = L.d / 8;                          // 16-byte chunks per row
     if (p0 + tid < p1) ((int*)(ws + L.off_kpos))[(size_t)bh * L.NKP + p0 + tid] = p0 + tid < L.n ? p0 + tid : KPOS_PAD;
     if (kn2 && blockIdx.x == 0 && tid < KN2_SLOTS)
         ((unsigned*)(ws + L.off_kn2))[(size_t)bh * KN2_SLOTS + tid] = kn2[(size_t)bh * KN2_SLOTS + tid];
@@ -599,7 +599,7 @@ __global__ __launch_bounds__(SB) void position_layout_kernel(Layout L, const uin
     uint4* dst = (uint4*)(ws + L.off_kc) + ((size_t)bh * L.NKP + p0) * CPR;
     for (int id = tid; id < (p1 - p0) * CPR; id += SB) {
         const int p = p0 + id / CPR, ch = id % CPR;
-        dst[id] = (p < L.n && ch < cin) ? src[(size_t)p * pitch + ch] : make_uint4(0, 0, 0, 0);
+        dst[id] = p < L.n ? src[(size_t)p * pitch + ch] : make_uint4(0, 0, 0, 0);
     }
 }
 

@@ -8,9 +8,9 @@
 //   Kc [B*Hkv][NKP][D]            keys, row-major: a key tile is one contiguous block
 //   Vt [B*Hkv][NKP/KT][D][KT]     values, transposed per key tile (KT = 64 keys), the 16 keys of
 //                                 every 16-key group stored in MFMA k-slot order
-// D is the head dim rounded up to 64, 128 or 256 (zero columns / rows past it); the kernel runs
-// KS = d/16 k-steps of Q K^T and DB = ceil(d/32) row blocks of O^T, so a head dim of 80 or 96
-// pays for its own products only.
+// D is the head dim; the kernel runs KS = d/16 k-steps of Q K^T and DB = ceil(d/32) row blocks of O^T, so a
+// head dim of 80 or 96 pays for its own products and its own bytes only (copied into rows of 128 components the tile DMA of
+// d = 80 was 1.5 times as long: 3 x 15/5 heads of 80 x 5003 tokens, K = 16 top-3: 312 -> 279 us; 15/5 x 32768, K = 4 top-2: 3016 -> 2619).
 // One work-group = MFMA_WAVES wavefronts = one query tile of 32*MFMA_WAVES rows of one class;
 // each wavefront owns 32 query rows.  The scores are computed transposed,
 // S^T = K Q^T with v_mfma_f32_32x32x16_bf16 (A = K rows from LDS, B = Q rows held
@@ -122,7 +122,6 @@ __global__ __launch_bounds__(NTHR) void gather_vt_kernel(Layout L, const uint16_
     constexpr int RS = D + 2;                        // padded LDS row stride in elements
     __shared__ uint16_t s_v[KT * RS];
     __shared__ unsigned s_bad[KT / 32];
-    const int cin = L.d / 8;
     const int tile = blockIdx.x, bhk = blockIdx.y, tid = threadIdx.x;
     const int* kpos = (const int*)(ws + L.off_kpos) + (size_t)bhk * L.NKP + (size_t)tile * KT;
     const uint4* src = (const uint4*)v + ((size_t)(bhk / L.Hkv) * L.ks[0] + (size_t)(bhk % L.Hkv) * L.ks[1]) / 8;
@@ -133,7 +132,7 @@ __global__ __launch_bounds__(NTHR) void gather_vt_kernel(Layout L, const uint16_
         const int row = id / CPR, ch = id % CPR;
         const int kp = kpos[row];
         uint4 val = make_uint4(0, 0, 0, 0);
-        if (kp != KPOS_PAD && ch < cin) val = src[(size_t)kp * pitch + ch];
+        if (kp != KPOS_PAD) val = src[(size_t)kp * pitch + ch];
         // Masked layout: every key of the causal prefix is visited, with a zero probability where it is not allowed,
         // and 0 * inf would spoil rows that do not attend it.  Such components go in as zeros and the key is marked:
         // the attention kernel adds them to the rows that do attend it (add_nonfinite_values).
@@ -186,8 +185,11 @@ template <int D> struct TileGeom {
     static constexpr int KROW = D * 2 + 16;             // pitch of a key row
     static constexpr int VROW = KT * 2 + 16;            // pitch of a V^T row (KT keys)
     static constexpr int K_LDS = KT * KROW;             // bytes of a K stage, a multiple of 1024
-    static constexpr int V_LDS = D * VROW;              // bytes of a V^T stage, a multiple of 1024
-    static_assert(K_LDS % 1024 == 0 && V_LDS % 1024 == 0, "stages are filled in 1-KB wave loads");
+    // V^T: 1-KB wave loads that cover its D rows, and bytes of a stage.  The products read whole blocks of 32 rows: with 80
+    // components the last 16 of them hold whatever is there, which reaches only rows of O^T that are not stored.
+    static constexpr int V_LOADS = (D * VROW + 1023) / 1024;
+    static constexpr int V_LDS = V_LOADS * 1024 > (D + 31) / 32 * 32 * VROW ? V_LOADS * 1024 : (D + 31) / 32 * 32 * VROW;
+    static_assert(K_LDS % 1024 == 0 && V_LDS % 16 == 0, "stages are filled in 1-KB wave loads");
 };
 
 // Masked layout: the values that were staged as zeros because they are not finite, added to the stored rows that attend
@@ -309,7 +311,7 @@ __device__ inline void pin_operands(V8 (&a)[N])
     for (int i = 0; i < N; ++i) asm volatile("" : "+v"(a[i]));
 }
 
-// D: row length of the class-ordered copies (64, 128, 256); KS: MFMAs of one QK^T unit = d / 16;
+// D: head dim; KS: MFMAs of one QK^T unit = d / 16;
 // DB: 32-row blocks of O^T = ceil(d / 32).  With 512-byte key rows the operands of a phase alone
 // take 128 registers, so that shape runs one wavefront per SIMD with the full register file.
 // COARSE: membership classes are sets of super-groups; a key class that shares one with the rows' class
@@ -346,7 +348,7 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT == 2) ? 1 : 8 / 
     typedef typename HT::V2 V2;
     constexpr bool COARSE = PM == PM_COARSE, MASKED = PM == PM_MASKED;
     __shared__ Smem<D, PM, SOFT> S;
-    static_assert(KS * 16 <= D && DB * 32 <= D, "the products stay inside the copied rows");
+    static_assert(KS * 16 == D && DB == (D + 31) / 32, "the products cover the copied rows");
     // With 512-byte key rows the operands of a whole phase would not fit the vector registers next to
     // Q, so that shape fetches and multiplies them in two halves (HV = 2); the others in one go.
     constexpr int KG = SOFT == 1 ? 1 : 2;        // soft gate: k-steps of 16 groups
@@ -359,7 +361,7 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT == 2) ? 1 : 8 / 
     constexpr int TILE_BYTES = KT * D * 2;      // bytes of a K tile and of a V^T tile in global memory
     constexpr int KROW = TileGeom<D>::KROW, VROW = TileGeom<D>::VROW;
     constexpr int K_LDS = TileGeom<D>::K_LDS, V_LDS = TileGeom<D>::V_LDS;
-    constexpr int NKB = K_LDS / 1024, NVB = V_LDS / 1024;             // 1-KB wave loads per stage
+    constexpr int NKB = K_LDS / 1024, NVB = TileGeom<D>::V_LOADS;     // 1-KB wave loads per stage
     constexpr int NKI = (NKB + MFMA_WAVES - 1) / MFMA_WAVES;          // ... per wavefront (the last may be missing)
     constexpr int NVI = (NVB + MFMA_WAVES - 1) / MFMA_WAVES;
     constexpr int ATHR = 64 * MFMA_WAVES;                // threads of the work-group
@@ -516,7 +518,7 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT == 2) ? 1 : 8 / 
 
     // per-lane source offsets of the DMA: wave `wave` fills the 1-KB LDS blocks wave + MFMA_WAVES * i of a
     // stage; LDS byte o of a stage belongs to row o / pitch; its bytes past the row's data are padding and
-    // fetch the row's last chunk again
+    // fetch the row's last chunk again (and a last wave load that reaches past the rows the last row)
     unsigned voff_k[NKI], voff_v[NVI];
 #pragma unroll
     for (int i = 0; i < NKI; ++i) {
@@ -526,7 +528,7 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT == 2) ? 1 : 8 / 
 #pragma unroll
     for (int i = 0; i < NVI; ++i) {
         const int o = (wave + MFMA_WAVES * i) * 1024 + lane * 16;
-        voff_v[i] = (unsigned)((o / VROW) * (KT * 2) + min(o % VROW, KT * 2 - 16));
+        voff_v[i] = (unsigned)(min(o / VROW, D - 1) * (KT * 2) + min(o % VROW, KT * 2 - 16));
     }
     const unsigned lds_k0 = lds_addr_of(&S.k[0][0]), lds_v0 = lds_addr_of(&S.vt[0][0]);
     const unsigned lds_kp0 = lds_addr_of(&S.kpos[0][0]);
@@ -1165,8 +1167,8 @@ hipError_t launch_attn_mfma(const Layout& L, const HeadMap& hm, const void* q, c
     if ((size_t)L.NT * L.B * L.Hq > 0x7fffffffull) return hipErrorInvalidValue;
     switch (L.d) {
         case 64: return launch_d<64, 4, 2>(L, hm, default_map, q, v, g, ws, out, lse, row_pairs, st);
-        case 80: return launch_d<128, 5, 3>(L, hm, default_map, q, v, g, ws, out, lse, row_pairs, st);
-        case 96: return launch_d<128, 6, 3>(L, hm, default_map, q, v, g, ws, out, lse, row_pairs, st);
+        case 80: return launch_d<80, 5, 3>(L, hm, default_map, q, v, g, ws, out, lse, row_pairs, st);
+        case 96: return launch_d<96, 6, 3>(L, hm, default_map, q, v, g, ws, out, lse, row_pairs, st);
         case 128: return launch_d<128, 8, 4>(L, hm, default_map, q, v, g, ws, out, lse, row_pairs, st);
         case 256: return launch_d<256, 16, 8>(L, hm, default_map, q, v, g, ws, out, lse, row_pairs, st);
         default: return hipErrorInvalidValue;

@@ -305,8 +305,8 @@ hipError_t launch_attn_simple(const Layout& L, const HeadMap& hm, const void* q,
     do { if (L.soft) FOCUS_LAUNCH_SIMPLE_S(T, D, SUB, true); else FOCUS_LAUNCH_SIMPLE_S(T, D, SUB, false); } while (0)
 #define FOCUS_LAUNCH_SIMPLE_T(T)                                                                       \
     do {                                                                                               \
-        if (L.dp == 64) FOCUS_LAUNCH_SIMPLE(T, 64, 32);                                                \
-        else if (L.dp == 128) FOCUS_LAUNCH_SIMPLE(T, 128, 32);                                         \
+        if (L.d <= 64) FOCUS_LAUNCH_SIMPLE(T, 64, 32);                                                \
+        else if (L.d <= 128) FOCUS_LAUNCH_SIMPLE(T, 128, 32);                                         \
         else FOCUS_LAUNCH_SIMPLE(T, 256, 16);                                                          \
     } while (0)
     if (L.dtype == 0) FOCUS_LAUNCH_SIMPLE_T(float);
