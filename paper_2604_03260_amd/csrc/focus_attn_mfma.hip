@@ -295,6 +295,19 @@ __device__ inline void static_for(F&& f)
         static_for<I + 1, N>(f);
     }
 }
+// a 4-byte word the same way; wait_lds_words<N>: the four words are there when at most N later reads are not (reads of a
+// wavefront arrive in order)
+__device__ inline unsigned lds_read4_async(unsigned addr)
+{
+    unsigned r;
+    asm volatile("ds_read_b32 %0, %1" : "=v"(r) : "v"(addr));
+    return r;
+}
+template <int N>
+__device__ inline void wait_lds_words(unsigned (&w)[4])
+{
+    asm volatile("s_waitcnt lgkmcnt(%4)" : "+v"(w[0]), "+v"(w[1]), "+v"(w[2]), "+v"(w[3]) : "n"(N < 15 ? N : 15));
+}
 // s_waitcnt lgkmcnt(0) tied to every register of an operand array (N = 4..16 registers of 16 bytes)
 template <typename V8, int N>
 __device__ inline void wait_lds_operands(V8 (&a)[N])
@@ -538,21 +551,26 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT == 2) ? 1 : 8 / 
     const unsigned lds_km0 = lds_addr_of(&S.kmsk[0]);
     const unsigned lds_kb0 = lds_addr_of(&S.kbits[0]);
     const unsigned lds_g0 = lds_addr_of(&S.gk[0]);
-    // masked: where this lane's half-wave finds the words of its row's first two groups; the groups after those
+    // masked: where this lane's half-wave finds the words of its row's first three groups and the marks of values that
+    // are not finite; the groups after those
     const int kb_row = L.K + 1, kb_words = 4 * kb_row;   // words per half-wave of a unit, per key tile
     unsigned vbad = 0u;                                  // the row attends a key with values that are not finite
     const char* kb_base = ws + L.off_kbits + (size_t)bhk * (L.NKP / KT) * (kb_words * 4);
     unsigned mq_rest = 0u;
-    int kb_g0 = 0, kb_g1 = 0;
+    unsigned kb_g0 = 0, kb_g1 = 0, kb_g2 = 0, kb_bad = 0;
     if constexpr (MASKED) {
         mq_rest = mq_row;
-        kb_g0 = mq_rest ? __builtin_ctz(mq_rest) : 0;
-        mq_rest &= mq_rest - 1u;
-        kb_g1 = mq_rest ? __builtin_ctz(mq_rest) : kb_g0;
-        mq_rest &= mq_rest - 1u;                         // (0 - 1 keeps 0: a row without groups, past the tile's end)
-        kb_g0 += hh * kb_row;
-        kb_g1 += hh * kb_row;
+        kb_g0 = next_group(kb_lane);
+        kb_g1 = next_group(kb_g0);
+        kb_g2 = next_group(kb_g1);
+        kb_bad = kb_lane + (unsigned)L.K * 4u;
     }
+        const unsigned kb_lane = lds_kb0 + (unsigned)(hh * kb_row) * 4u;
+        auto next_group = [&](unsigned before) -> unsigned {         // the same word again where there is no other group
+            const unsigned at = mq_rest ? kb_lane + (unsigned)__builtin_ctz(mq_rest) * 4u : before;
+            mq_rest &= mq_rest - 1u;                     // (0 - 1 keeps 0: a row without groups, past the tile's end)
+            return at;
+        };
 
 #define F4_DMA_K(TILE, STAGE)                                                                        \
     do {                                                                                             \
@@ -624,6 +642,15 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT == 2) ? 1 : 8 / 
         GOUT = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ag[0], gql[0], GOUT, 0, 0, 0);                \
         GOUT = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ag[KG], gqh[0], GOUT, 0, 0, 0);                \
         if constexpr (KG == 2) if (kg2) {                                                            \
+    // masked: the words of unit U, read before the operands so that the pairs are worked out while those are in flight
+#define F4_READ_BITS(KPB, U)                                                                         \
+    if constexpr (MASKED) {                                                                          \
+        const unsigned at_ = (unsigned)((KPB) * (KBITS_MAX * 4) + (U) * 8 * kb_row);                  \
+        bits[0] = lds_read4_async(kb_g0 + at_);                                                      \
+        bits[1] = lds_read4_async(kb_g1 + at_);                                                      \
+        bits[2] = lds_read4_async(kb_g2 + at_);                                                      \
+        bits[3] = lds_read4_async(kb_bad + at_);                                                     \
+    }
             GOUT = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ag[1], gqh[KG - 1], GOUT, 0, 0, 0);            \
             GOUT = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ag[1], gql[KG - 1], GOUT, 0, 0, 0);            \
             GOUT = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ag[2 * KG - 1], gqh[KG - 1], GOUT, 0, 0, 0);            \
@@ -731,6 +758,7 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT == 2) ? 1 : 8 / 
         wait_lds_operands(ak);
 #pragma unroll
         for (int ks = 0; ks < KSH; ++ks) s0 = HT::mfma(ak[ks], qreg[KSH + ks], s0);
+    unsigned bits[4];
     }
 
     // softmax step on one unit's scores: SIN (f32x16, consumed) -> POUT (2 x bf16x8), split in two parts.
@@ -781,11 +809,12 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT == 2) ? 1 : 8 / 
     if (SOFT) {                          /* masked above */                                              \
     } else if constexpr (MASKED) {                                                                       \
         /* the membership word of this lane's 16 keys: bit p of the low (high) half is score 2p (2p + 1) */ \
-        const unsigned* kb_ = &S.kbits[(KPB) * KBITS_MAX + (U) * 2 * kb_row];                            \
+        wait_lds_words<KSH + NPVH>(bits);                                                                \
         mword = 0xffffffffu;                                                                             \
         if (!interior) {                                                                                 \
-            unsigned sh_ = kb_[kb_g0] | kb_[kb_g1];                                                      \
-            if (L.topk > 2) {                                                                            \
+            unsigned sh_ = bits[0] | bits[1] | bits[2];                                                  \
+            if (L.topk > 3) {                                                                            \
+                const unsigned* kb_ = &S.kbits[(KPB) * KBITS_MAX + ((U) * 2 + hh) * kb_row];             \
                 unsigned m_ = mq_rest;                                                                   \
                 for (int i_ = 2; i_ < L.topk; ++i_) {                                                    \
                     sh_ |= kb_[hh * kb_row + (m_ ? __builtin_ctz(m_) : 0)] & (m_ ? 0xffffffffu : 0u);       \
@@ -810,7 +839,7 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT == 2) ? 1 : 8 / 
                     SIN[r] = (mword & (1u << (r / 2 + (r & 1) * 16))) ? SIN[r] : -INFINITY;              \
             }                                                                                            \
         }                                                                                                \
-        vbad |= mword & kb_[hh * kb_row + L.K];                                                          \
+        vbad |= mword & bits[3];                                                                         \
         if constexpr (PAIRS) npairs += __popc(mword) >> (interior ? 1 : 0);                              \
     } else if (!interior) {                                                                              \
         _Pragma("unroll") for (int r4 = 0; r4 < 4; ++r4) {                                               \
@@ -929,6 +958,7 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT == 2) ? 1 : 8 / 
         F4_PIN2(p0);                                                                                     \
         /* one barrier per tile: all are done with K(t), V(t-1); K(t+1), V(t) have landed */             \
         if (!(FOCUS_ABLATE & 16)) F4_WAIT_DMA();                                                         \
+        F4_READ_BITS(kb_cur, 0)                                                                          \
         if (!(FOCUS_ABLATE & 1)) __syncthreads();                                                        \
         if (!(FOCUS_ABLATE & 4)) {                                                                       \
             F4_DMA_K(tl2, sc);                                                                           \
@@ -955,6 +985,7 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT == 2) ? 1 : 8 / 
         F4_PIN2(p1);                                                                                     \
         kb_cur = (kb_cur == 2) ? 0 : kb_cur + 1;                                                         \
         pk0 = pk1;                                                                                       \
+        F4_READ_BITS(kb_cur, 1)                                                                          \
         pk1 = pk2;                                                                                       \
         pk2 = next_tile();                                                                               \
     }
@@ -1010,6 +1041,7 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT == 2) ? 1 : 8 / 
         w1 = __builtin_amdgcn_exp2f(lse1_l2 - top);
         const float w2 = __builtin_amdgcn_exp2f(lse2_l2 - top);
         const float den = 1.f / (w1 + w2);
+#undef F4_READ_BITS
         inv *= w2 * den;
         w1 *= den;
         lse2_l2 = top + __builtin_amdgcn_logf(w1 / den + w2);
