@@ -213,6 +213,11 @@ focus_status make_layout(const focus_params* p, focus::Layout* L, focus::HeadMap
             if (dst[t][2] < p->d) return fail(FOCUS_EINVAL, "%s[2] is smaller than d: rows overlap", names[t]);
         }
     }
+    // Keys read in place: the copy and its launch time are saved, a tile visit is up to 1 % longer (runtime pitch, the check
+    // for the last rows; 2.8 % where rows lie 4000 bytes apart), so only while the walk is short.  Whole pass, copied / in
+    // place (us): 8 x 12 heads of 64 x 4096 327 / 315; 32/8 of 128 x 4096 183 / 175; 14/2 of 64 x 8192, K = 8 top-3 183 / 180;
+    // 3 x 15/5 of 80 x 5003 out of one projection 313 / 308.
+    L->k_direct = (L->masked || soft) && p->dtype != FOCUS_F32 && p->n <= 8192 && L->ks[2] < (1 << 23);
     L->nblk = (p->n + SB - 1) / SB;
     // class-major launch order only where the heads' K and V are far beyond the caches (see plan_heads_kernel)
     L->class_major = (L->BQ == 256 && p->n >= LONG_N) ? 1 : 0;
@@ -263,7 +268,7 @@ focus_status make_layout(const focus_params* p, focus::Layout* L, focus::HeadMap
     L->off_kn2 = take(BHk * focus::KN2_SLOTS * 4);
     L->off_nrflag = take(BHq * L->NT * 4);
     if (p->dtype != FOCUS_F32) {
-        L->off_kc = take(BHk * L->NKP * (size_t)p->d * 2);
+        L->off_kc = L->k_direct ? off : take(BHk * L->NKP * (size_t)p->d * 2);
         L->off_vt = take(BHk * L->NKP * (size_t)p->d * 2);
     } else {
         L->off_kc = L->off_vt = off;

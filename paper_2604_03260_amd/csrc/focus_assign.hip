@@ -251,10 +251,11 @@ __global__ __launch_bounds__(SCAN_THREADS) void scan_plan_kernel(Layout L, char*
 
 // ---------------------------------------------------------------- score + top-k
 // Memberships of one sort block on the fp64 matrix cores (focus_score.h), its group histogram and, on layouts with classes
-// (CLS), the class of every token and the class histogram.
+// (CLS), the class of every token and the class histogram.  norms: the largest squared key norm of the block goes into the
+// block's own slot (at most KN2_SLOTS blocks; layouts whose keys are not copied by the scatter launch).
 template <typename T, int KM, bool CLS>
 __global__ __launch_bounds__(SB) void score_kernel(Layout L, HeadMap hm, const T* __restrict__ xq, const T* __restrict__ xk,
-                                                   const float* __restrict__ cents, int which, char* __restrict__ ws)
+                                                   const float* __restrict__ cents, int which, int norms, char* __restrict__ ws)
 {
     __shared__ __align__(16) char s_a[4][score_lds(score_chunk<T>(KM))];
     __shared__ int s_h[4][32];
@@ -268,8 +269,12 @@ __global__ __launch_bounds__(SB) void score_kernel(Layout L, HeadMap hm, const T
     const int bh = row_in_side(L, which, blockIdx.y);
     const int H = is_query ? L.Hq : L.Hkv, h = bh % H, hk = is_query ? hm.kv[h] : h;
     const long long* xs = is_query ? L.qs : L.ks;
-    // (the scatter launch after this one raises these)
-    if (!is_query && blk == 0 && tid < KN2_SLOTS) ((unsigned*)(ws + L.off_kn2))[(size_t)bh * KN2_SLOTS + tid] = 0u;
+    // (the scatter launch after this one raises these; with norms every block writes its own slot)
+    unsigned* kn2 = (unsigned*)(ws + L.off_kn2) + (size_t)bh * KN2_SLOTS;
+    if (!is_query && blk == 0 && tid < KN2_SLOTS && (!norms || tid >= L.nblk)) kn2[tid] = 0u;
+    const bool want_norms = !CLS && sizeof(T) == 2 && norms && !is_query;
+    __shared__ unsigned s_n2[4];
+    unsigned n2 = 0u;
     const int j0 = blk * SB + wave * 64, rows = min(64, n - j0);
     const T* x = (is_query ? xq : xk) + (size_t)(bh / H) * xs[0] + (size_t)h * xs[1] + (size_t)j0 * xs[2];
     const uint32_t m = score_rows_topk<T, KM, score_chunk<T>(KM)>((const char*)x, (size_t)xs[2] * sizeof(T), rows, L.d, s_c, s_a[wave], K, L.topk, [&]() {
@@ -277,7 +282,8 @@ __global__ __launch_bounds__(SB) void score_kernel(Layout L, HeadMap hm, const T
         if constexpr (CLS)
             for (int e = tid; e < L.NC; e += SB) s_hist_c[e] = 0;
         __syncthreads();
-    });
+    }, want_norms ? &n2 : nullptr);
+    if (want_norms && lane == 0) s_n2[wave] = n2;
     if (lane < rows) {
         ((uint32_t*)(ws + (is_query ? L.off_mq : L.off_mk)))[(size_t)bh * n + j0 + lane] = m;
         if constexpr (CLS) {
@@ -295,6 +301,7 @@ __global__ __launch_bounds__(SB) void score_kernel(Layout L, HeadMap hm, const T
     if (tid < K)
         ((int*)(ws + (is_query ? L.off_qbg : L.off_kbg)))[((size_t)bh * (L.nblk + 1) + blk) * K + tid] =
             s_h[0][tid] + s_h[1][tid] + s_h[2][tid] + s_h[3][tid];
+    if (want_norms && tid == 0) kn2[blk] = max(max(s_n2[0], s_n2[1]), max(s_n2[2], s_n2[3]));
     int* bc = (int*)(ws + (is_query ? L.off_qbc : L.off_kbc)) + ((size_t)bh * (L.nblk + 1) + blk) * L.NC;
     if constexpr (CLS)
         for (int c = tid; c < L.NC; c += SB) bc[c] = s_hist_c[c];
@@ -404,7 +411,7 @@ __device__ inline float chunk_norm2(const uint4& val, bool f16)
 // LINEAR (masked layouts): one class, slot = position.  OWN_SCAN: no scan launch ran; the work-group adds up the group
 // histograms of the row's sort blocks itself (a few thousand integers at most), and sort block 0 writes the row's counts.
 template <bool LINEAR, bool OWN_SCAN>
-__global__ __launch_bounds__(SB) void scatter_kernel(Layout L, int which, const uint16_t* __restrict__ k, char* __restrict__ ws)
+__global__ __launch_bounds__(SB) void scatter_kernel(Layout L, int which, const uint16_t* __restrict__ k, int norms_done, char* __restrict__ ws)
 {
     static_assert(LINEAR || !OWN_SCAN, "class offsets come from the scan launch");
     __shared__ int s_wc[LINEAR ? 1 : 4][LINEAR ? 1 : MAX_CLASSES];
@@ -524,7 +531,7 @@ __global__ __launch_bounds__(SB) void scatter_kernel(Layout L, int which, const 
     // (class NC stands for the unused end of the arrays).  qperm -1, kpos KPOS_PAD, masks and key rows zero.
     const int* cnt = (const int*)(ws + (is_query ? L.off_qcc : L.off_kcc)) + (size_t)bh * NC;
     const int plen = is_query ? L.NQP : L.NKP;
-    const bool copy_k = !is_query && k != nullptr;
+    const bool copy_k = !is_query && k != nullptr && !(LINEAR && L.k_direct);      // else at most the norms
     const int CPR = L.d / 8;                         // 16-byte chunks per row of k and of the key copy
     uint4* kc = (uint4*)(ws + L.off_kc) + (size_t)bh * L.NKP * CPR;
     for (int c = LINEAR ? L.nblk - 1 - blk : blk; c <= NC; c += L.nblk) {      // (LINEAR: NC = 1, left to the last sort blocks)
@@ -544,7 +551,7 @@ __global__ __launch_bounds__(SB) void scatter_kernel(Layout L, int which, const 
     }
 
     // ---- key rows: this sort block's rows into their class-ordered places
-    if (!copy_k) return;
+    if (!copy_k && (is_query || k == nullptr || norms_done)) return;
     s_dest[tid] = dest;
     __syncthreads();
     const int lpr = CPR <= 8 ? 8 : CPR <= 16 ? 16 : 32;              // lanes per row, the last ones idle at d = 80 and 96
@@ -559,7 +566,7 @@ __global__ __launch_bounds__(SB) void scatter_kernel(Layout L, int which, const 
         uint4 val = make_uint4(0, 0, 0, 0);
         if (dd >= 0 && ch < CPR) {
             val = src[(size_t)row * pitch + ch];
-            kc[(size_t)dd * CPR + ch] = val;
+            if (copy_k) kc[(size_t)dd * CPR + ch] = val;
         }
         // the chunks of a row sit in lpr consecutive lanes (a power of two <= 32, rows do not straddle waves)
         float n2 = chunk_norm2(val, f16);
@@ -597,6 +604,7 @@ __global__ __launch_bounds__(SB) void position_layout_kernel(Layout L, const uin
     const uint4* src = k + ((size_t)(bh / L.Hkv) * L.ks[0] + (size_t)(bh % L.Hkv) * L.ks[1]) / 8;
     const size_t pitch = (size_t)L.ks[2] / 8;
     uint4* dst = (uint4*)(ws + L.off_kc) + ((size_t)bh * L.NKP + p0) * CPR;
+    if (L.k_direct) return;                           // (the tiled kernel reads the keys in place)
     for (int id = tid; id < (p1 - p0) * CPR; id += SB) {
         const int p = p0 + id / CPR, ch = id % CPR;
         dst[id] = p < L.n ? src[(size_t)p * pitch + ch] : make_uint4(0, 0, 0, 0);
@@ -660,27 +668,27 @@ __global__ __launch_bounds__(SB) void token_classes_kernel(Layout L, const uint3
 
 // scores and memberships of the queries and of the keys, one launch: query rows first, key rows after them
 template <typename T, int KM>
-hipError_t launch_score(const Layout& L, const HeadMap& hm, const void* q, const void* k, const float* centroids, char* ws, hipStream_t st)
+hipError_t launch_score(const Layout& L, const HeadMap& hm, const void* q, const void* k, const float* centroids, int norms, char* ws, hipStream_t st)
 {
     const size_t lds = score_cent_bytes(KM, L.d);                    // with the staging space below 87 KB
     // (more rows than one launch can have: the two sides one after the other)
     const bool both = L.B * (L.Hq + L.Hkv) <= MAX_GRID_ROWS;
     for (int which = both ? -1 : 1; which >= -1; --which) {
         const dim3 grid(L.nblk, which < 0 ? L.B * (L.Hq + L.Hkv) : which ? L.B * L.Hq : L.B * L.Hkv);
-        if (L.masked) hipLaunchKernelGGL((score_kernel<T, KM, false>), grid, dim3(SB), lds, st, L, hm, (const T*)q, (const T*)k, centroids, which, ws);
-        else hipLaunchKernelGGL((score_kernel<T, KM, true>), grid, dim3(SB), lds, st, L, hm, (const T*)q, (const T*)k, centroids, which, ws);
+        if (L.masked) hipLaunchKernelGGL((score_kernel<T, KM, false>), grid, dim3(SB), lds, st, L, hm, (const T*)q, (const T*)k, centroids, which, norms, ws);
+        else hipLaunchKernelGGL((score_kernel<T, KM, true>), grid, dim3(SB), lds, st, L, hm, (const T*)q, (const T*)k, centroids, which, norms, ws);
         if (which <= 0) break;
     }
     return hipGetLastError();
 }
 
 template <typename T>
-hipError_t launch_score_k(const Layout& L, const HeadMap& hm, const void* q, const void* k, const float* centroids, char* ws, hipStream_t st)
+hipError_t launch_score_k(const Layout& L, const HeadMap& hm, const void* q, const void* k, const float* centroids, int norms, char* ws, hipStream_t st)
 {
-    if (L.K <= 4) return launch_score<T, 4>(L, hm, q, k, centroids, ws, st);
-    if (L.K <= 8) return launch_score<T, 8>(L, hm, q, k, centroids, ws, st);
-    if (L.K <= 16) return launch_score<T, 16>(L, hm, q, k, centroids, ws, st);
-    return launch_score<T, 32>(L, hm, q, k, centroids, ws, st);
+    if (L.K <= 4) return launch_score<T, 4>(L, hm, q, k, centroids, norms, ws, st);
+    if (L.K <= 8) return launch_score<T, 8>(L, hm, q, k, centroids, norms, ws, st);
+    if (L.K <= 16) return launch_score<T, 16>(L, hm, q, k, centroids, norms, ws, st);
+    return launch_score<T, 32>(L, hm, q, k, centroids, norms, ws, st);
 }
 
 // One launch where a row is little enough work for one compute unit (scores are n * d products of 4 or 8 groups; above 8
@@ -716,7 +724,7 @@ hipError_t launch_bucket_rows_k(const Layout& L, const HeadMap& hm, const void* 
 bool own_scan(const Layout& L) { return L.masked && (long long)L.nblk * L.K <= 4096; }
 
 // from class ids, block prefixes and the per-row plan to the class-ordered arrays, group lists and key copy
-hipError_t launch_scatter(const Layout& L, const void* k, char* ws, hipStream_t st)
+hipError_t launch_scatter(const Layout& L, const void* k, int norms_done, char* ws, hipStream_t st)
 {
     // query side and key side in the same launch: rows [0, B*Hq) and the B*Hkv rows after them
     // (more rows than one launch can have: the two sides one after the other)
@@ -724,9 +732,9 @@ hipError_t launch_scatter(const Layout& L, const void* k, char* ws, hipStream_t 
     const bool both = L.B * (L.Hq + L.Hkv) <= MAX_GRID_ROWS;
     for (int which = both ? -1 : 1; which >= -1; --which) {
         const int rows = which < 0 ? L.B * (L.Hq + L.Hkv) : which ? L.B * L.Hq : L.B * L.Hkv;
-        if (own_scan(L)) hipLaunchKernelGGL((scatter_kernel<true, true>), dim3(L.nblk, rows), dim3(SB), 0, st, L, which, kcopy, ws);
-        else if (L.masked) hipLaunchKernelGGL((scatter_kernel<true, false>), dim3(L.nblk, rows), dim3(SB), 0, st, L, which, kcopy, ws);
-        else hipLaunchKernelGGL((scatter_kernel<false, false>), dim3(L.nblk, rows), dim3(SB), 0, st, L, which, kcopy, ws);
+        if (own_scan(L)) hipLaunchKernelGGL((scatter_kernel<true, true>), dim3(L.nblk, rows), dim3(SB), 0, st, L, which, kcopy, norms_done, ws);
+        else if (L.masked) hipLaunchKernelGGL((scatter_kernel<true, false>), dim3(L.nblk, rows), dim3(SB), 0, st, L, which, kcopy, norms_done, ws);
+        else hipLaunchKernelGGL((scatter_kernel<false, false>), dim3(L.nblk, rows), dim3(SB), 0, st, L, which, kcopy, norms_done, ws);
         if (which <= 0) break;
     }
     return hipGetLastError();
@@ -741,12 +749,14 @@ hipError_t launch_assign(const Layout& L, const HeadMap& hm, const void* q, cons
         return L.dtype == 0 ? launch_bucket_rows_k<float>(L, hm, q, k, centroids, ws, st)
                : L.dtype == 2 ? launch_bucket_rows_k<f16_bits>(L, hm, q, k, centroids, ws, st)
                               : launch_bucket_rows_k<uint16_t>(L, hm, q, k, centroids, ws, st);
-    const hipError_t e = L.dtype == 0 ? launch_score_k<float>(L, hm, q, k, centroids, ws, st)
-                         : L.dtype == 2 ? launch_score_k<f16_bits>(L, hm, q, k, centroids, ws, st)
-                                        : launch_score_k<uint16_t>(L, hm, q, k, centroids, ws, st);
+    // keys that stay where they are: their norms come with the scores where every sort block has a slot of its own
+    const int norms = L.k_direct && L.nblk <= KN2_SLOTS ? 1 : 0;
+    const hipError_t e = L.dtype == 0 ? launch_score_k<float>(L, hm, q, k, centroids, norms, ws, st)
+                         : L.dtype == 2 ? launch_score_k<f16_bits>(L, hm, q, k, centroids, norms, ws, st)
+                                        : launch_score_k<uint16_t>(L, hm, q, k, centroids, norms, ws, st);
     if (e != hipSuccess) return e;
     if (!own_scan(L)) hipLaunchKernelGGL(scan_plan_kernel, dim3(L.B * (L.Hq + L.Hkv)), dim3(SCAN_THREADS), 0, st, L, ws);
-    return launch_scatter(L, k, ws, st);
+    return launch_scatter(L, k, norms, ws, st);
 }
 
 hipError_t launch_position_layout(const Layout& L, const void* k, const unsigned* kn2, char* ws, hipStream_t st)
@@ -766,7 +776,7 @@ hipError_t launch_assign_tokens(const Layout& L, const uint32_t* token_masks, co
     if (!own_scan(L)) hipLaunchKernelGGL(scan_plan_kernel, dim3(L.B * (L.Hq + L.Hkv)), dim3(SCAN_THREADS), 0, st, L, ws);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    return launch_scatter(L, k, ws, st);
+    return launch_scatter(L, k, 0, ws, st);
 }
 
 }  // namespace focus

@@ -349,10 +349,10 @@ __device__ inline void pin_operands(V8 (&a)[N])
 // the tile or return; then the other instantiation, whose work-groups return at once where the flag says done.
 // (v: the values as the caller holds them; the masked form alone reads them, and only where some are not finite.)
 template <int D, int KS, int DB, int MFMA_WAVES, bool SOFTCAP, bool PAIRS, bool F16, int PM, int SOFT, bool NOREF>
-__global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT == 2) ? 1 : 8 / MFMA_WAVES) void attn_mfma_kernel(
+__global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT == 2) ? 1 : (D == 64 && MFMA_WAVES == 4 && NOREF) ? 3 : 8 / MFMA_WAVES) void attn_mfma_kernel(
     Layout L, HeadMap hm, int default_map, const uint16_t* __restrict__ q, const uint16_t* __restrict__ v,
     const float* __restrict__ g, char* ws_rw, uint16_t* __restrict__ out, float* __restrict__ lse,
-    int32_t* __restrict__ row_pairs)
+    int32_t* __restrict__ row_pairs, const uint16_t* __restrict__ k)
 {
     const char* ws = ws_rw;              // everything but the flag of this work-group is only read
     typedef Half<F16> HT;
@@ -523,7 +523,15 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT == 2) ? 1 : 8 / 
     const float cap_poly_lim = (L.softcap > 0.f) ? CAP_POLY_Z / cap_a : 0.f;
     const float cap_cubic_lim = (L.softcap > 0.f) ? CAP_CUBIC_Z / cap_a : 0.f;
 
-    const char* kc_base = ws + L.off_kc + (size_t)bhk * L.NKP * (D * 2);
+    // the keys: the class-ordered copy, or (one class in position order, k_direct) k itself; rows past the last position are
+    // then read as the last one again, their pairs are masked
+    constexpr bool MAY_DIRECT = MASKED || SOFT != 0;
+    const bool direct = MAY_DIRECT && L.k_direct;
+    const unsigned kpitch = direct ? (unsigned)L.ks[2] * 2u : (unsigned)(D * 2);
+    const size_t ktile_bytes = MAY_DIRECT ? (size_t)kpitch * KT : (size_t)TILE_BYTES;
+    const int k_full = direct ? L.n / KT : 0x7fffffff;           // tiles below it are whole
+    const char* kc_base = direct ? (const char*)(k + (size_t)b * L.ks[0] + (size_t)hm.kv[h] * L.ks[1])
+                                 : ws + L.off_kc + (size_t)bhk * L.NKP * (D * 2);
     const char* vt_base = ws + L.off_vt + (size_t)bhk * L.NKP * (D * 2);
     const char* kpos_base = ws + L.off_kpos + (size_t)bhk * L.NKP * 4;
     const char* kmsk_base = ws + L.off_kmsk + (size_t)bhk * L.NKP * 4;
@@ -536,7 +544,7 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT == 2) ? 1 : 8 / 
 #pragma unroll
     for (int i = 0; i < NKI; ++i) {
         const int o = (wave + MFMA_WAVES * i) * 1024 + lane * 16;
-        voff_k[i] = (unsigned)((o / KROW) * (D * 2) + min(o % KROW, D * 2 - 16));
+        voff_k[i] = (unsigned)(o / KROW) * (MAY_DIRECT ? kpitch : (unsigned)(D * 2)) + (unsigned)min(o % KROW, D * 2 - 16);
     }
 #pragma unroll
     for (int i = 0; i < NVI; ++i) {
@@ -559,25 +567,37 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT == 2) ? 1 : 8 / 
     unsigned mq_rest = 0u;
     unsigned kb_g0 = 0, kb_g1 = 0, kb_g2 = 0, kb_bad = 0;
     if constexpr (MASKED) {
-        mq_rest = mq_row;
-        kb_g0 = next_group(kb_lane);
-        kb_g1 = next_group(kb_g0);
-        kb_g2 = next_group(kb_g1);
-        kb_bad = kb_lane + (unsigned)L.K * 4u;
-    }
         const unsigned kb_lane = lds_kb0 + (unsigned)(hh * kb_row) * 4u;
         auto next_group = [&](unsigned before) -> unsigned {         // the same word again where there is no other group
             const unsigned at = mq_rest ? kb_lane + (unsigned)__builtin_ctz(mq_rest) * 4u : before;
             mq_rest &= mq_rest - 1u;                     // (0 - 1 keeps 0: a row without groups, past the tile's end)
             return at;
         };
+        mq_rest = mq_row;
+        kb_g0 = next_group(kb_lane);
+        kb_g1 = next_group(kb_g0);
+        kb_g2 = next_group(kb_g1);
+        kb_bad = kb_lane + (unsigned)L.K * 4u;
+    }
 
 #define F4_DMA_K(TILE, STAGE)                                                                        \
     do {                                                                                             \
-        const char* src_ = kc_base + (size_t)(TILE) * TILE_BYTES;                                    \
-        _Pragma("unroll") for (int i = 0; i < NKI; ++i)                                              \
-            if ((i + 1) * MFMA_WAVES <= NKB || wave + MFMA_WAVES * i < NKB)                          \
-                lds_dma16(src_, voff_k[i], lds_k0 + (STAGE) * K_LDS + (wave + MFMA_WAVES * i) * 1024);   \
+        const char* src_ = kc_base + (size_t)(TILE) * ktile_bytes;                                   \
+        if (MAY_DIRECT && (TILE) >= k_full) {            /* rows past the last position */           \
+            const int left_ = L.n - (TILE) * KT;                                                     \
+            int o0_ = lane * 16;                                                                     \
+            asm volatile("" : "+v"(o0_));                /* worked out here, not kept in registers all along */ \
+            _Pragma("unroll") for (int i = 0; i < NKI; ++i) {                                        \
+                const int o_ = o0_ + (wave + MFMA_WAVES * i) * 1024;                                 \
+                if ((i + 1) * MFMA_WAVES <= NKB || wave + MFMA_WAVES * i < NKB)                      \
+                    lds_dma16(src_, (unsigned)min(o_ / KROW, left_ - 1) * kpitch + (unsigned)min(o_ % KROW, D * 2 - 16), \
+                              lds_k0 + (STAGE) * K_LDS + (wave + MFMA_WAVES * i) * 1024);            \
+            }                                                                                        \
+        } else {                                                                                     \
+            _Pragma("unroll") for (int i = 0; i < NKI; ++i)                                          \
+                if ((i + 1) * MFMA_WAVES <= NKB || wave + MFMA_WAVES * i < NKB)                      \
+                    lds_dma16(src_, voff_k[i], lds_k0 + (STAGE) * K_LDS + (wave + MFMA_WAVES * i) * 1024);   \
+        }                                                                                            \
         if constexpr (SOFT) {            /* the keys' soft assignments travel with the key tile */          \
             const char* gsrc_ = gk_base + (size_t)(TILE) * (KT * GROW);                              \
             _Pragma("unroll") for (int i = 0; i < KT * GROW / 1024 / MFMA_WAVES; ++i)                 \
@@ -622,6 +642,15 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT == 2) ? 1 : 8 / 
             DST[i2] = lds_read16_async_at<V8, ((HALF) * DBH + i2 / 2) * 32 * VROW + (U) * 64 + (i2 % 2) * 32>(a_); \
         });                                                                                          \
     }
+    // masked: the words of unit U, read before the operands so that the pairs are worked out while those are in flight
+#define F4_READ_BITS(KPB, U)                                                                         \
+    if constexpr (MASKED) {                                                                          \
+        const unsigned at_ = (unsigned)((KPB) * (KBITS_MAX * 4) + (U) * 8 * kb_row);                  \
+        bits[0] = lds_read4_async(kb_g0 + at_);                                                      \
+        bits[1] = lds_read4_async(kb_g1 + at_);                                                      \
+        bits[2] = lds_read4_async(kb_g2 + at_);                                                      \
+        bits[3] = lds_read4_async(kb_bad + at_);                                                     \
+    }
     // soft gate: high parts of the two k-steps, then the low parts, of the 32 keys of unit U
 #define F4_READ_G(KST, U)                                                                            \
     if constexpr (SOFT) {                                                                            \
@@ -642,15 +671,6 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT == 2) ? 1 : 8 / 
         GOUT = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ag[0], gql[0], GOUT, 0, 0, 0);                \
         GOUT = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ag[KG], gqh[0], GOUT, 0, 0, 0);                \
         if constexpr (KG == 2) if (kg2) {                                                            \
-    // masked: the words of unit U, read before the operands so that the pairs are worked out while those are in flight
-#define F4_READ_BITS(KPB, U)                                                                         \
-    if constexpr (MASKED) {                                                                          \
-        const unsigned at_ = (unsigned)((KPB) * (KBITS_MAX * 4) + (U) * 8 * kb_row);                  \
-        bits[0] = lds_read4_async(kb_g0 + at_);                                                      \
-        bits[1] = lds_read4_async(kb_g1 + at_);                                                      \
-        bits[2] = lds_read4_async(kb_g2 + at_);                                                      \
-        bits[3] = lds_read4_async(kb_bad + at_);                                                     \
-    }
             GOUT = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ag[1], gqh[KG - 1], GOUT, 0, 0, 0);            \
             GOUT = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ag[1], gql[KG - 1], GOUT, 0, 0, 0);            \
             GOUT = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ag[2 * KG - 1], gqh[KG - 1], GOUT, 0, 0, 0);            \
@@ -738,6 +758,7 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT == 2) ? 1 : 8 / 
     ones2[0] = (elem_t)1.0f;
     ones2[1] = (elem_t)1.0f;
     V8 ak[KSH], av[NPVH];
+    unsigned bits[4];
     bf16x8 ag[2 * KG];
     f32x16 g0acc, g1acc;
 #pragma unroll
@@ -758,7 +779,6 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT == 2) ? 1 : 8 / 
         wait_lds_operands(ak);
 #pragma unroll
         for (int ks = 0; ks < KSH; ++ks) s0 = HT::mfma(ak[ks], qreg[KSH + ks], s0);
-    unsigned bits[4];
     }
 
     // softmax step on one unit's scores: SIN (f32x16, consumed) -> POUT (2 x bf16x8), split in two parts.
@@ -816,12 +836,11 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT == 2) ? 1 : 8 / 
             if (L.topk > 3) {                                                                            \
                 const unsigned* kb_ = &S.kbits[(KPB) * KBITS_MAX + ((U) * 2 + hh) * kb_row];             \
                 unsigned m_ = mq_rest;                                                                   \
-                for (int i_ = 2; i_ < L.topk; ++i_) {                                                    \
-                    sh_ |= kb_[hh * kb_row + (m_ ? __builtin_ctz(m_) : 0)] & (m_ ? 0xffffffffu : 0u);       \
+                _Pragma("unroll 1") for (int i_ = 3; i_ < L.topk; ++i_) {                                \
+                    sh_ |= kb_[m_ ? __builtin_ctz(m_) : 0] & (m_ ? 0xffffffffu : 0u);                    \
                     m_ &= m_ - 1u;                                                                       \
                 }                                                                                        \
             }                                                                                            \
-            sh_ = mq_row ? sh_ : 0u;                                                                     \
             if (!shares_) {              /* the diagonal or the window's edge: positions decide too */    \
                 /* upto[x + 1]: the scores whose key lies at or below offset x of the lane's first key (32 and 28 apart) */ \
                 const int kp0_ = (int)(pk0 & TILE_MASK) * KT + (U) * 32 + 4 * hh;                        \
@@ -939,6 +958,7 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT == 2) ? 1 : 8 / 
         const int tl2 = (int)(pk2 & TILE_MASK);                                                          \
         const int kb_nn = (kb_cur >= 1) ? kb_cur - 1 : 2;    /* (t+2) mod 3 */                           \
         /* phase A: VALU softmax(S0) -> P0 ; MFMA O += V(t-1,u1) P1 and S1 = K(t,u1) Q^T */              \
+        F4_READ_BITS(kb_cur, 0)                                                                          \
         F4_READ_V(av, sn, 1, 0)                                                                          \
         F4_READ_K(ak, sc, 1, 0)                                                                          \
         F4_READ_G(sc, 1)                                                                                 \
@@ -958,7 +978,6 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT == 2) ? 1 : 8 / 
         F4_PIN2(p0);                                                                                     \
         /* one barrier per tile: all are done with K(t), V(t-1); K(t+1), V(t) have landed */             \
         if (!(FOCUS_ABLATE & 16)) F4_WAIT_DMA();                                                         \
-        F4_READ_BITS(kb_cur, 0)                                                                          \
         if (!(FOCUS_ABLATE & 1)) __syncthreads();                                                        \
         if (!(FOCUS_ABLATE & 4)) {                                                                       \
             F4_DMA_K(tl2, sc);                                                                           \
@@ -966,6 +985,7 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT == 2) ? 1 : 8 / 
             F4_DMA_KPOS(tl2, kb_nn);                                                                     \
         }                                                                                                \
         /* phase B: VALU softmax(S1) -> P1 ; MFMA O += V(t,u0) P0 and S0 = K(t+1,u0) Q^T */              \
+        F4_READ_BITS(kb_cur, 1)                                                                          \
         F4_READ_V(av, sc, 0, 0)                                                                          \
         F4_READ_K(ak, sn, 0, 0)                                                                          \
         F4_READ_G(sn, 0)                                                                                 \
@@ -985,7 +1005,6 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT == 2) ? 1 : 8 / 
         F4_PIN2(p1);                                                                                     \
         kb_cur = (kb_cur == 2) ? 0 : kb_cur + 1;                                                         \
         pk0 = pk1;                                                                                       \
-        F4_READ_BITS(kb_cur, 1)                                                                          \
         pk1 = pk2;                                                                                       \
         pk2 = next_tile();                                                                               \
     }
@@ -1022,6 +1041,7 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT == 2) ? 1 : 8 / 
 #undef F4_PIN2
 #undef F4_WAIT_OPERANDS
 #undef F4_READ_G
+#undef F4_READ_BITS
 #undef F4_GATE_MFMAS
 
     // ---- epilogue
@@ -1041,7 +1061,6 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT == 2) ? 1 : 8 / 
         w1 = __builtin_amdgcn_exp2f(lse1_l2 - top);
         const float w2 = __builtin_amdgcn_exp2f(lse2_l2 - top);
         const float den = 1.f / (w1 + w2);
-#undef F4_READ_BITS
         inv *= w2 * den;
         w1 *= den;
         lse2_l2 = top + __builtin_amdgcn_logf(w1 / den + w2);
@@ -1087,35 +1106,35 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT == 2) ? 1 : 8 / 
 }
 
 template <int D, int KS, int DB, int WAVES, bool SOFTCAP, bool PAIRS, bool F16, int PM, int SOFT = 0>
-hipError_t launch_one(const Layout& L, const HeadMap& hm, int default_map, const void* q, const void* v, char* ws, void* out,
+hipError_t launch_one(const Layout& L, const HeadMap& hm, int default_map, const void* q, const void* k, const void* v, char* ws, void* out,
                       float* lse, int32_t* row_pairs, hipStream_t st, const float* g = nullptr)
 {
     const unsigned grid = (unsigned)((size_t)L.NT * L.B * L.Hq);
     if constexpr (SOFT == 0)
         hipLaunchKernelGGL((attn_mfma_kernel<D, KS, DB, WAVES, SOFTCAP, PAIRS, F16, PM, SOFT, true>), dim3(grid),
                            dim3(64 * WAVES), 0, st, L, hm, default_map, (const uint16_t*)q, (const uint16_t*)v, g, ws, (uint16_t*)out, lse,
-                           row_pairs);
+                           row_pairs, (const uint16_t*)k);
     hipLaunchKernelGGL((attn_mfma_kernel<D, KS, DB, WAVES, SOFTCAP, PAIRS, F16, PM, SOFT, false>), dim3(grid),
                        dim3(64 * WAVES), 0, st, L, hm, default_map, (const uint16_t*)q, (const uint16_t*)v, g, ws, (uint16_t*)out, lse,
-                       row_pairs);
+                       row_pairs, (const uint16_t*)k);
     return hipGetLastError();
 }
 
 template <int D, int KS, int DB, int WAVES, bool F16, int PM>
-hipError_t launch_w(const Layout& L, const HeadMap& hm, int default_map, const void* q, const void* v, char* ws, void* out,
+hipError_t launch_w(const Layout& L, const HeadMap& hm, int default_map, const void* q, const void* k, const void* v, char* ws, void* out,
                     float* lse, int32_t* row_pairs, hipStream_t st)
 {
     const bool sc = L.softcap > 0.f, pairs = row_pairs != nullptr;
     if (sc) {
-        return pairs ? launch_one<D, KS, DB, WAVES, true, true, F16, PM>(L, hm, default_map, q, v, ws, out, lse, row_pairs, st)
-                     : launch_one<D, KS, DB, WAVES, true, false, F16, PM>(L, hm, default_map, q, v, ws, out, lse, row_pairs, st);
+        return pairs ? launch_one<D, KS, DB, WAVES, true, true, F16, PM>(L, hm, default_map, q, k, v, ws, out, lse, row_pairs, st)
+                     : launch_one<D, KS, DB, WAVES, true, false, F16, PM>(L, hm, default_map, q, k, v, ws, out, lse, row_pairs, st);
     }
-    return pairs ? launch_one<D, KS, DB, WAVES, false, true, F16, PM>(L, hm, default_map, q, v, ws, out, lse, row_pairs, st)
-                 : launch_one<D, KS, DB, WAVES, false, false, F16, PM>(L, hm, default_map, q, v, ws, out, lse, row_pairs, st);
+    return pairs ? launch_one<D, KS, DB, WAVES, false, true, F16, PM>(L, hm, default_map, q, k, v, ws, out, lse, row_pairs, st)
+                 : launch_one<D, KS, DB, WAVES, false, false, F16, PM>(L, hm, default_map, q, k, v, ws, out, lse, row_pairs, st);
 }
 
 template <int D, int KS, int DB>
-hipError_t launch_d(const Layout& L, const HeadMap& hm, int default_map, const void* q, const void* v, const float* g,
+hipError_t launch_d(const Layout& L, const HeadMap& hm, int default_map, const void* q, const void* k, const void* v, const float* g,
                     char* ws, void* out, float* lse, int32_t* row_pairs, hipStream_t st)
 {
     dim3 ggrid(L.NKP / KT, L.B * L.Hkv);
@@ -1127,27 +1146,27 @@ hipError_t launch_d(const Layout& L, const HeadMap& hm, int default_map, const v
         if constexpr (D == 256) return hipErrorInvalidValue;
         else
         if (L.K <= 16)
-            return f16 ? launch_one<D, KS, DB, 4, false, false, true, PM_EXACT, 1>(L, hm, default_map, q, v, ws, out, lse, nullptr, st, g)
-                       : launch_one<D, KS, DB, 4, false, false, false, PM_EXACT, 1>(L, hm, default_map, q, v, ws, out, lse, nullptr, st, g);
+            return f16 ? launch_one<D, KS, DB, 4, false, false, true, PM_EXACT, 1>(L, hm, default_map, q, k, v, ws, out, lse, nullptr, st, g)
+                       : launch_one<D, KS, DB, 4, false, false, false, PM_EXACT, 1>(L, hm, default_map, q, k, v, ws, out, lse, nullptr, st, g);
         else
-            return f16 ? launch_one<D, KS, DB, 4, false, false, true, PM_EXACT, 2>(L, hm, default_map, q, v, ws, out, lse, nullptr, st, g)
-                       : launch_one<D, KS, DB, 4, false, false, false, PM_EXACT, 2>(L, hm, default_map, q, v, ws, out, lse, nullptr, st, g);
+            return f16 ? launch_one<D, KS, DB, 4, false, false, true, PM_EXACT, 2>(L, hm, default_map, q, k, v, ws, out, lse, nullptr, st, g)
+                       : launch_one<D, KS, DB, 4, false, false, false, PM_EXACT, 2>(L, hm, default_map, q, k, v, ws, out, lse, nullptr, st, g);
     }
     // the query tile size fixed by focus_assign selects the work-group shape: 4 or 8 wavefronts
     if constexpr (D != 256) {
         if (L.BQ == 256)
-            return f16 ? launch_w<D, KS, DB, 8, true, PM_EXACT>(L, hm, default_map, q, v, ws, out, lse, row_pairs, st)
-                       : launch_w<D, KS, DB, 8, false, PM_EXACT>(L, hm, default_map, q, v, ws, out, lse, row_pairs, st);
+            return f16 ? launch_w<D, KS, DB, 8, true, PM_EXACT>(L, hm, default_map, q, k, v, ws, out, lse, row_pairs, st)
+                       : launch_w<D, KS, DB, 8, false, PM_EXACT>(L, hm, default_map, q, k, v, ws, out, lse, row_pairs, st);
     }
     if (L.BQ != 128) return hipErrorInvalidValue;
     if (L.masked)                        // one class, membership tested per pair
-        return f16 ? launch_w<D, KS, DB, 4, true, PM_MASKED>(L, hm, default_map, q, v, ws, out, lse, row_pairs, st)
-                   : launch_w<D, KS, DB, 4, false, PM_MASKED>(L, hm, default_map, q, v, ws, out, lse, row_pairs, st);
+        return f16 ? launch_w<D, KS, DB, 4, true, PM_MASKED>(L, hm, default_map, q, k, v, ws, out, lse, row_pairs, st)
+                   : launch_w<D, KS, DB, 4, false, PM_MASKED>(L, hm, default_map, q, k, v, ws, out, lse, row_pairs, st);
     if (L.coarse)                        // coarse classes always use 128-row tiles
-        return f16 ? launch_w<D, KS, DB, 4, true, PM_COARSE>(L, hm, default_map, q, v, ws, out, lse, row_pairs, st)
-                   : launch_w<D, KS, DB, 4, false, PM_COARSE>(L, hm, default_map, q, v, ws, out, lse, row_pairs, st);
-    return f16 ? launch_w<D, KS, DB, 4, true, PM_EXACT>(L, hm, default_map, q, v, ws, out, lse, row_pairs, st)
-               : launch_w<D, KS, DB, 4, false, PM_EXACT>(L, hm, default_map, q, v, ws, out, lse, row_pairs, st);
+        return f16 ? launch_w<D, KS, DB, 4, true, PM_COARSE>(L, hm, default_map, q, k, v, ws, out, lse, row_pairs, st)
+                   : launch_w<D, KS, DB, 4, false, PM_COARSE>(L, hm, default_map, q, k, v, ws, out, lse, row_pairs, st);
+    return f16 ? launch_w<D, KS, DB, 4, true, PM_EXACT>(L, hm, default_map, q, k, v, ws, out, lse, row_pairs, st)
+               : launch_w<D, KS, DB, 4, false, PM_EXACT>(L, hm, default_map, q, k, v, ws, out, lse, row_pairs, st);
 }
 
 }  // namespace
@@ -1189,7 +1208,6 @@ hipError_t launch_soft_gather_g(const Layout& L, const float* g, char* ws, hipSt
 hipError_t launch_attn_mfma(const Layout& L, const HeadMap& hm, const void* q, const void* k, const void* v,
                             const float* g, char* ws, void* out, float* lse, int32_t* row_pairs, hipStream_t st)
 {
-    (void)k;
     int default_map = 1;
     const int G = L.Hq / L.Hkv;
     if (L.Hq % L.Hkv != 0) default_map = 0;
@@ -1198,11 +1216,11 @@ hipError_t launch_attn_mfma(const Layout& L, const HeadMap& hm, const void* q, c
             if (hm.kv[h] != h / G) default_map = 0;
     if ((size_t)L.NT * L.B * L.Hq > 0x7fffffffull) return hipErrorInvalidValue;
     switch (L.d) {
-        case 64: return launch_d<64, 4, 2>(L, hm, default_map, q, v, g, ws, out, lse, row_pairs, st);
-        case 80: return launch_d<80, 5, 3>(L, hm, default_map, q, v, g, ws, out, lse, row_pairs, st);
-        case 96: return launch_d<96, 6, 3>(L, hm, default_map, q, v, g, ws, out, lse, row_pairs, st);
-        case 128: return launch_d<128, 8, 4>(L, hm, default_map, q, v, g, ws, out, lse, row_pairs, st);
-        case 256: return launch_d<256, 16, 8>(L, hm, default_map, q, v, g, ws, out, lse, row_pairs, st);
+        case 64: return launch_d<64, 4, 2>(L, hm, default_map, q, k, v, g, ws, out, lse, row_pairs, st);
+        case 80: return launch_d<80, 5, 3>(L, hm, default_map, q, k, v, g, ws, out, lse, row_pairs, st);
+        case 96: return launch_d<96, 6, 3>(L, hm, default_map, q, k, v, g, ws, out, lse, row_pairs, st);
+        case 128: return launch_d<128, 8, 4>(L, hm, default_map, q, k, v, g, ws, out, lse, row_pairs, st);
+        case 256: return launch_d<256, 16, 8>(L, hm, default_map, q, k, v, g, ws, out, lse, row_pairs, st);
         default: return hipErrorInvalidValue;
     }
 }

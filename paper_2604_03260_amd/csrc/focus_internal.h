@@ -56,7 +56,8 @@ struct Layout {
     int causal;                // 1: keys j <= i, local = i-w < j <= i; 0: every j, local = |i-j| < w
     int dtype;                 // 0 fp32, 1 bf16, 2 fp16
     int elem;                  // bytes per element
-    int unused_dp;             // (see `unused` below)
+    int k_direct;              // masked and soft-gate layouts of 16-bit types: the tiled kernel reads the keys in place, through
+                               // the strides of k (a wavefront's tile addresses fit 32 bits); no key copy
     int BQ;                    // query rows per attention tile (128; 256 for 16-bit types at n >= LONG_N, d <= 128)
     int NC;                    // number of membership classes (1 in dense mode)
     int dense;                 // every causal pair allowed: one class, no masks beyond causal
@@ -113,7 +114,7 @@ struct Layout {
     size_t off_lse1;                   // [B,Hq,n] fp32: log-sum-exp of the first pass when the caller passes no lse (two_pass)
     size_t off_nrflag;                 // [B,Hq,NT] per work-group of the attention launch: 1 = the no-reference
                                        // instantiation did the tile, 0 = left to the other one (16-bit types)
-    size_t off_kc;                     // [B,Hkv,NKP,d] keys in class order (16-bit types)
+    size_t off_kc;                     // [B,Hkv,NKP,d] keys in class order (16-bit types, unless k_direct)
     size_t off_vt;                     // [B,Hkv,NKP/KT,d,KT] values, transposed per key tile (16-bit types)
     size_t total;
 };

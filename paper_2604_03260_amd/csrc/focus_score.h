@@ -46,12 +46,32 @@ __device__ inline void score_stage_centroids(const float* __restrict__ c, score_
     }
 }
 
+// acc + the sum of the squares of the eight 16-bit values of a piece
+template <typename T>
+__device__ inline float score_piece_norm2(const score_u32x4& v, float acc)
+{
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        if constexpr (std::is_same<T, f16_bits>::value) {
+            typedef __attribute__((__vector_size__(2 * sizeof(_Float16)))) _Float16 h2;
+            const h2 x = __builtin_bit_cast(h2, (uint32_t)v[e]);
+            acc = __builtin_amdgcn_fdot2(x, x, acc, false);
+        } else {
+            typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 b2;
+            const b2 x = __builtin_bit_cast(b2, (uint32_t)v[e]);
+            acc = __builtin_amdgcn_fdot2_f32_bf16(x, x, acc, false);
+        }
+    }
+    return acc;
+}
+
 // gbase: first row, pitch: bytes between rows, rows: at most 64 of them; abuf: score_lds(CHUNK) bytes of the wavefront's own.
 // staged: called once by all wavefronts of the work-group, after their first loads are on their way: stages the centroids
-// and waits for them.  Returns the mask of row `lane` (0 past the rows).  KM = K rounded up to 4, 8, 16 or 32.
+// and waits for them.  n2max: NULL, or takes the bit pattern of the largest squared norm of the rows (16-bit types; a
+// non-negative float orders like its bit pattern, a NaN or infinite norm ends up above every finite one).  Returns the mask of row `lane` (0 past the rows).  KM = K rounded up to 4, 8, 16 or 32.
 template <typename T, int KM, int CHUNK, typename F>
 __device__ inline uint32_t score_rows_topk(const char* __restrict__ gbase, size_t pitch, int rows, int d, const score_cent_t<KM>* s_c,
-                                           char* abuf, int K, int topk, F&& staged)
+                                           char* abuf, int K, int topk, F&& staged, unsigned* n2max = nullptr)
 {
     constexpr int A_ROW = score_a_row(CHUNK);
     constexpr int RC = CHUNK / (int)sizeof(T);    // components per staged chunk
@@ -83,7 +103,13 @@ __device__ inline uint32_t score_rows_topk(const char* __restrict__ gbase, size_
         for (int cb = 0; cb < CB; ++cb) acc[t][cb] = acc_t{};
     load_chunk(0);
     staged();
-    if (rows <= 0) return 0;
+    if (rows <= 0) {
+        if (n2max) *n2max = 0u;
+        return 0;
+    }
+    float n2[NP];
+#pragma unroll
+    for (int i = 0; i < NP; ++i) n2[i] = 0.f;
     for (int ch = 0; ch < nchunk; ++ch) {
         // a wavefront's LDS accesses run in order: no barrier, only the compiler must keep the order
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -103,6 +129,12 @@ __device__ inline uint32_t score_rows_topk(const char* __restrict__ gbase, size_
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
+        if constexpr (sizeof(T) == 2) {
+            if (n2max) {
+#pragma unroll
+                for (int i = 0; i < NP; ++i) n2[i] = score_piece_norm2<T>(stg[i], n2[i]);
+            }
+        }
         if (ch + 1 < nchunk) load_chunk(ch + 1);
         constexpr int AR = NP / 4;                // 16-byte reads of a part
         score_u32x4 ar[4][AR];
@@ -144,6 +176,24 @@ __device__ inline uint32_t score_rows_topk(const char* __restrict__ gbase, size_
 #pragma unroll
             for (int i = 0; i < RC / 4; ++i)
                 if (i < steps) step(i);
+        }
+    }
+    if constexpr (sizeof(T) == 2) {
+        if (n2max) {
+            unsigned top = 0u;
+#pragma unroll
+            for (int i = 0; i < NP; ++i) {
+#pragma unroll
+                for (int off = 1; off < NP; off <<= 1) n2[i] += __shfl_xor(n2[i], off, 64);
+                const unsigned bits = __float_as_uint(n2[i]) & 0x7fffffffu;      // a NaN may carry a sign bit
+                top = bits > top ? bits : top;
+            }
+#pragma unroll
+            for (int off = NP; off <= 32; off <<= 1) {
+                const unsigned o = (unsigned)__shfl_xor((int)top, off, 64);
+                top = o > top ? o : top;
+            }
+            *n2max = top;
         }
     }
     // accumulator of lane l: row 4*(l%16/4) + l/16 of the tile, group l%4 of the block; register r of the 16-column
