@@ -146,8 +146,10 @@ typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 constexpr int A_ROW = 128 + 16;              // LDS pitch of a staged row: 4 interleaved parts of 32 bytes, padded
 __host__ __device__ constexpr bool route_small(int dg) { return dg <= 8; }
-// LDS pitch of a row of W_g in floats: the four rows of a step on different banks
+// LDS pitch of a row of W_g (elements): the four rows of a step on different banks
 __host__ __device__ constexpr int route_wp(int dg) { return dg <= 16 ? dg : dg + 16; }
+// ... which is widened when it is staged where the space allows it, not by every wavefront at every step
+template <int DG> using route_w_t = std::conditional_t<DG <= 16, double, float>;
 
 template <typename T, int DG, int NW>
 __global__ __launch_bounds__(64 * NW) void route_project_kernel(RouteLayout R, const T* __restrict__ hidden,
@@ -161,7 +163,8 @@ __global__ __launch_bounds__(64 * NW) void route_project_kernel(RouteLayout R, c
     constexpr int RC = 128 / (int)sizeof(T);             // components per chunk
     constexpr bool SMALL = route_small(DG);
     constexpr int LC = SMALL ? 3 : 15, CB = (DG + LC) / (LC + 1);    // column of a block, blocks of 4 or of 16 outputs
-    constexpr int WP = route_wp(DG);                     // LDS pitch of a row of W_g in floats
+    constexpr int WP = route_wp(DG);
+    typedef route_w_t<DG> w_t;
     typedef std::conditional_t<SMALL, double, f64x4> acc_t;
     constexpr int PF = 4;                                // chunks in flight: one takes 0.85 us of products, a load 1 to 2
     constexpr int WPT = (RC * DG + NTHR - 1) / NTHR;     // floats of W_g per thread and chunk
@@ -179,7 +182,7 @@ __global__ __launch_bounds__(64 * NW) void route_project_kernel(RouteLayout R, c
     const char* gbase = (const char*)hidden + ((size_t)b * n + tok0) * row_bytes;
     const int nchunk = (dm + RC - 1) / RC;
     char* s_a = s_dyn;
-    float* s_w = (float*)(s_dyn + 2 * TB * A_ROW);
+    w_t* s_w = (w_t*)(s_dyn + 2 * TB * A_ROW);
 
     u32x4 sta[PF][2];
     float swa[PF][WPT];
@@ -211,7 +214,7 @@ __global__ __launch_bounds__(64 * NW) void route_project_kernel(RouteLayout R, c
         u32x4 (&st)[2] = sta[p];
         float (&sw)[WPT] = swa[p];
         char* abuf = s_a + (ch & 1) * (TB * A_ROW);
-        float* wbuf = s_w + (ch & 1) * (RC * WP);
+        w_t* wbuf = s_w + (ch & 1) * (RC * WP);
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             const int pid = i * 64 + lane;
@@ -229,13 +232,13 @@ __global__ __launch_bounds__(64 * NW) void route_project_kernel(RouteLayout R, c
 #pragma unroll
         for (int i = 0; i < WPT; ++i) {
             const int e = i * NTHR + tid;
-            if (e < RC * DG) wbuf[(e / DG) * WP + e % DG] = sw[i];
+            if (e < RC * DG) wbuf[(e / DG) * WP + e % DG] = (w_t)sw[i];
         }
         __syncthreads();               // also orders these writes after every wave's reads two chunks ago
         if (ch + PF < nchunk) load_chunk(ch + PF, st, sw);
         const u32x4* ar = (const u32x4*)(abuf + (wave * 16 + (lane & 15)) * A_ROW + (lane >> 4) * 32);
         const u32x4 a0 = ar[0], a1 = ar[1];
-        const float* wr = wbuf + (lane >> 4) * WP + (lane & LC);
+        const w_t* wr = wbuf + (lane >> 4) * WP + (lane & LC);
         const int steps = min(RC, dm - ch * RC) / 4;     // dm is a multiple of 8
         auto step = [&](int i) {
             double a;
@@ -436,9 +439,9 @@ hipError_t launch_project(const RouteLayout& R, const void* hidden, const float*
     const int nw = route_tokens_per_group(R.B, R.n, R.dg) / 16;
     dim3 grid(R.nproj, R.B);
     const int rc = 128 / (int)sizeof(T);
-    const size_t stage = 2 * ((size_t)nw * 16 * A_ROW + (size_t)rc * route_wp(R.dg) * 4);
+    const size_t stage = 2 * ((size_t)nw * 16 * A_ROW + (size_t)rc * route_wp(R.dg) * (R.dg <= 16 ? 8 : 4));
     const size_t tail = (size_t)nw * 16 * (R.dg + 1 + (R.K | 1)) * sizeof(double);
-    const size_t lds = stage > tail ? stage : tail;      // at most 51 KB (8 wavefronts, d_g <= 16) or 58 KB (4, d_g = 64, 16-bit rows)
+    const size_t lds = stage > tail ? stage : tail;      // at most 53 KB (8 wavefronts, d_g <= 16) or 59 KB (4, d_g = 64, 16-bit rows)
 #define FOCUS_PROJ(DG, NW)                                                                                   \
     hipLaunchKernelGGL((route_project_kernel<T, DG, NW>), grid, dim3(64 * NW), lds, st, R, (const T*)hidden, wg, \
                        cent, ws, masks, soft)
