@@ -130,9 +130,9 @@ __device__ inline uint32_t topk_mask(const double (&s)[KP], int K, int topk)
 // by the bit-exact router tests), so one instruction is four steps of the same sum as before for 16 tokens x 16 outputs.
 // The vector form of this kernel (a lane per token, W_g through scalar loads) reached 17 % of the fp64 rate at 32768
 // tokens, held by the issue of fp64 instructions (one per 16 cycles and wavefront) and by the scalar loads; a matrix
-// instruction keeps the fp64 units busy for 64 cycles by itself.  32768 x 4096 bf16, d_g = 16: 306 -> 117 us
-// (37 TFLOP/s, what one dependent chain per wavefront and two wavefronts per SIMD reach with registers alone; the sum of
-// a token is one chain); 1024 tokens 275 -> 78 us, 131072 tokens 521 -> 411 us, d_g = 64 x 2048: 306 -> 177 us.
+// instruction keeps the fp64 units busy for 64 cycles by itself.  32768 x 4096 bf16, d_g = 16: 306 -> 104 us
+// (41 TFLOP/s; products alone reach 60 to 73 on this chip, and every widening of a value adds to them); 1024 tokens 275 -> 73 us,
+// 131072 tokens 521 -> 353 us, d_g = 64 x 2048: 306 -> 177 us.
 //
 // A work-group is NW wavefronts of 16 tokens.  Hidden rows and W_g (fp32) pass through LDS in chunks of 128 bytes per
 // row, two buffers, one barrier per chunk, the next four chunks' loads in flight meanwhile.  The A operand of step i is
@@ -140,7 +140,7 @@ __device__ inline uint32_t topk_mask(const double (&s)[KP], int K, int topk)
 // its whole chunk with two 16-byte loads.  Accumulator register r of lane l is token 4*r + l/16, output l%16.
 //
 // d_g = 4 and 8 run on v_mfma_f64_4x4x4_4b (focus_score.h), one or two of 16 cycles per step in the place of one of 64: 20000 x 8192
-// f16, d_g = 8: 224 -> 182 us; 32768 x 1200 bf16, d_g = 4: 36 -> 23.  Four of them per step would be no faster at d_g = 16: a step is
+// f16, d_g = 8: 224 -> 157 us; 32768 x 1200 bf16, d_g = 4: 36 -> 22.  Four of them per step would be no faster at d_g = 16: a step is
 // then as long, and widens three more values of W_g (112 -> 135 us; vector instructions do not run beside fp64 products).
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
@@ -240,7 +240,7 @@ __global__ __launch_bounds__(64 * NW) void route_project_kernel(RouteLayout R, c
         const u32x4 a0 = ar[0], a1 = ar[1];
         const w_t* wr = wbuf + (lane >> 4) * WP + (lane & LC);
         const int steps = min(RC, dm - ch * RC) / 4;     // dm is a multiple of 8
-        auto step = [&](int i) {
+        auto a_of = [&](int i) -> double {
             double a;
             if constexpr (sizeof(T) == 4) {
                 a = (double)__uint_as_float(i < 4 ? a0[i % 4] : a1[i % 4]);
@@ -251,21 +251,44 @@ __global__ __launch_bounds__(64 * NW) void route_project_kernel(RouteLayout R, c
                 else
                     a = (double)__uint_as_float(i % 2 ? w2 & 0xffff0000u : w2 << 16);
             }
+            return a;
+        };
+        auto step = [&](double a, const double (&w)[CB]) {
 #pragma unroll
             for (int cb = 0; cb < CB; ++cb) {
-                const double w = (double)wr[i * 4 * WP + cb * (LC + 1)];
-                if constexpr (SMALL) acc[cb] = __builtin_amdgcn_mfma_f64_4x4x4f64(a, w, acc[cb], 0, 0, 0);
-                else acc[cb] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, w, acc[cb], 0, 0, 0);
+                if constexpr (SMALL) acc[cb] = __builtin_amdgcn_mfma_f64_4x4x4f64(a, w[cb], acc[cb], 0, 0, 0);
+                else acc[cb] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, w[cb], acc[cb], 0, 0, 0);
             }
         };
-        // a full chunk without a branch per step: all its operands can be read ahead of the products
+        // a full chunk without a branch per step, BATCH steps at a time: their operands first, then the products back to back
+        // (32768 tokens, d_g = 16: 108 us one by one, 104 with 4, 106 with 8, 105 with 16; 131072: 364 / 353 / 361 / 413, whose
+        // registers leave fewer wavefronts)
+        constexpr int BATCH = DG < 16 ? 2 : 4;
+        static_assert((RC / 4) % BATCH == 0, "whole batches");
         if (steps == RC / 4) {
 #pragma unroll
-            for (int i = 0; i < RC / 4; ++i) step(i);
+            for (int i0 = 0; i0 < RC / 4; i0 += BATCH) {
+                double w[BATCH][CB], av[BATCH];
+#pragma unroll
+                for (int i = 0; i < BATCH; ++i)
+#pragma unroll
+                    for (int cb = 0; cb < CB; ++cb) w[i][cb] = (double)wr[(i0 + i) * 4 * WP + cb * (LC + 1)];
+#pragma unroll
+                for (int i = 0; i < BATCH; ++i) av[i] = a_of(i0 + i);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int i = 0; i < BATCH; ++i) step(av[i], w[i]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
         } else {
 #pragma unroll
             for (int i = 0; i < RC / 4; ++i)
-                if (i < steps) step(i);
+                if (i < steps) {
+                    double w[CB];
+#pragma unroll
+                    for (int cb = 0; cb < CB; ++cb) w[cb] = (double)wr[i * 4 * WP + cb * (LC + 1)];
+                    step(a_of(i), w);
+                }
         }
     }
     }
