@@ -554,25 +554,31 @@ __global__ __launch_bounds__(SB) void scatter_kernel(Layout L, int which, const 
     if (!copy_k && (is_query || k == nullptr || norms_done)) return;
     s_dest[tid] = dest;
     __syncthreads();
-    const int lpr = CPR <= 8 ? 8 : CPR <= 16 ? 16 : 32;              // lanes per row, the last ones idle at d = 80 and 96
+    const int lsh = CPR <= 8 ? 3 : CPR <= 16 ? 4 : 5, lpr = 1 << lsh;    // lanes per row, the last ones idle at d = 80 and 96
     const bool f16 = L.dtype == 2;
     // source rows through the strides of k (multiples of 8 elements = one 16-byte chunk)
     const uint4* src = (const uint4*)k + ((size_t)(bh / L.Hkv) * L.ks[0] + (size_t)(bh % L.Hkv) * L.ks[1] + (size_t)blk * SB * L.ks[2]) / 8;
     const size_t pitch = (size_t)L.ks[2] / 8;
     unsigned n2max = 0u;
-    for (int id = tid; id < SB * lpr; id += SB) {
-        const int row = id / lpr, ch = id % lpr;
-        const int dd = s_dest[row];
-        uint4 val = make_uint4(0, 0, 0, 0);
-        if (dd >= 0 && ch < CPR) {
-            val = src[(size_t)row * pitch + ch];
-            if (copy_k) kc[(size_t)dd * CPR + ch] = val;
+    // four pieces in flight per lane (8 heads of 128 x 32768: 41 -> 35 us for the launch)
+    for (int id0 = tid; id0 < SB * lpr; id0 += 4 * SB) {
+        uint4 val[4];
+        int dd[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int id = id0 + i * SB, row = id >> lsh, ch = id & (lpr - 1);
+            dd[i] = ch < CPR ? s_dest[row] : -1;
+            val[i] = dd[i] >= 0 ? src[(size_t)row * pitch + ch] : make_uint4(0, 0, 0, 0);
         }
-        // the chunks of a row sit in lpr consecutive lanes (a power of two <= 32, rows do not straddle waves)
-        float n2 = chunk_norm2(val, f16);
-        for (int off = 1; off < lpr; off <<= 1) n2 += __shfl_xor(n2, off, 64);
-        const unsigned bits = __float_as_uint(n2) & 0x7fffffffu;     // a NaN may carry a sign bit
-        n2max = bits > n2max ? bits : n2max;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (copy_k && dd[i] >= 0) kc[(size_t)dd[i] * CPR + ((id0 + i * SB) & (lpr - 1))] = val[i];
+            // the chunks of a row sit in lpr consecutive lanes (a power of two <= 32, rows do not straddle waves)
+            float n2 = chunk_norm2(val[i], f16);
+            for (int off = 1; off < lpr; off <<= 1) n2 += __shfl_xor(n2, off, 64);
+            const unsigned bits = __float_as_uint(n2) & 0x7fffffffu;     // a NaN may carry a sign bit
+            n2max = bits > n2max ? bits : n2max;
+        }
     }
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) {
