@@ -531,7 +531,7 @@ __global__ __launch_bounds__(SB) void scatter_kernel(Layout L, int which, const 
     // (class NC stands for the unused end of the arrays).  qperm -1, kpos KPOS_PAD, masks and key rows zero.
     const int* cnt = (const int*)(ws + (is_query ? L.off_qcc : L.off_kcc)) + (size_t)bh * NC;
     const int plen = is_query ? L.NQP : L.NKP;
-    const bool copy_k = !is_query && k != nullptr && !(LINEAR && L.k_direct);      // else at most the norms
+    const bool copy_k = !is_query && k != nullptr && !L.k_direct;       // else at most the norms
     const int CPR = L.d / 8;                         // 16-byte chunks per row of k and of the key copy
     uint4* kc = (uint4*)(ws + L.off_kc) + (size_t)bh * L.NKP * CPR;
     for (int c = LINEAR ? L.nblk - 1 - blk : blk; c <= NC; c += L.nblk) {      // (LINEAR: NC = 1, left to the last sort blocks)
