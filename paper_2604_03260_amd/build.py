@@ -55,6 +55,31 @@ def check_no_spills(remarks):
     return seen
 
 
+# Wavefronts per SIMD without which a kernel that lives on hiding its loads is slower than what it replaced; a build that
+# falls below is refused.  (mangled-name pattern, wavefronts)
+MIN_WAVES = {"focus_assign.hip": [(r"12score_kernelI\w+Li32ELb[01]E", 2)]}
+
+
+def check_waves(remarks, rules):
+    """remarks as above, rules: (pattern of the kernel's mangled name, least wavefronts per SIMD).  Every pattern has to match
+    some kernel.  Returns the number of kernels checked."""
+    seen = 0
+    for pattern, least in rules:
+        found = 0
+        for block in remarks.split("Function Name:")[1:]:
+            name = block.split()[0]
+            if not re.search(pattern, name):
+                continue
+            found += 1
+            m = re.search(r"Occupancy \[waves/SIMD\]:\s*(\d+)", block)
+            if m is None or int(m.group(1)) < least:
+                raise RuntimeError("%s runs at %s wavefronts per SIMD, %d needed" % (name, m.group(1) if m else "no reported number of", least))
+        if found == 0:
+            raise RuntimeError("no resource report for a kernel matching %s" % pattern)
+        seen += found
+    return seen
+
+
 def build_library(verbose=False):
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     objs = []
@@ -66,24 +91,28 @@ def build_library(verbose=False):
         if s == "focus_api.hip":
             cmd.insert(1, '-DFOCUS_BUILD_ID="%s"' % source_id())
         err = None
-        if s == NO_SPILL_SOURCE:
+        if s == NO_SPILL_SOURCE or s in MIN_WAVES:
             cmd.insert(1, "-Rpass-analysis=kernel-resource-usage")
-            err = open(os.path.join(HERE, "_build", "resource_usage.txt"), "w")
+            err = open(os.path.join(HERE, "_build", "resource_usage_%s.txt" % s.replace(".hip", "")), "w")
         if verbose:
             print(" ".join(cmd), flush=True)
-        procs.append((subprocess.Popen(cmd, stderr=err), cmd, err))
+        procs.append((subprocess.Popen(cmd, stderr=err), cmd, err, s))
         objs.append(o)
-    for p, cmd, err in procs:
+    for p, cmd, err, s in procs:
         rc = p.wait()
         if err is not None:
             err.close()
             remarks = open(err.name).read()
             if rc != 0:
                 sys.stderr.write(remarks[-4000:])
-            else:
+            elif s == NO_SPILL_SOURCE:
                 n = check_no_spills(remarks)
                 if verbose:
                     print("%d instantiations of %s, none spills" % (n, NO_SPILL_KERNEL), flush=True)
+            else:
+                n = check_waves(remarks, MIN_WAVES[s])
+                if verbose:
+                    print("%s: %d kernels at their wavefronts per SIMD" % (s, n), flush=True)
         if rc != 0:
             raise RuntimeError("compile failed: " + " ".join(cmd))
     cmd = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs

@@ -37,3 +37,30 @@ def test_the_library_build_never_ablates_the_attention_loop():
     import inspect
     assert "FOCUS_ABLATE" not in inspect.getsource(build.build_library)
     assert "libfocus_ablate_%d.so" in inspect.getsource(build.build_ablation)
+
+
+WAVES = """x.hip:1:1: remark: Function Name: _ZN5focus12_GLOBAL__N_112score_kernelIfLi32ELb1EEEvNS_6LayoutE [-Rpass-analysis=kernel-resource-usage]
+x.hip:1:1: remark:     Occupancy [waves/SIMD]: 2 [-Rpass-analysis=kernel-resource-usage]
+x.hip:1:1: remark: Function Name: _ZN5focus12_GLOBAL__N_112score_kernelIfLi16ELb1EEEvNS_6LayoutE [-Rpass-analysis=kernel-resource-usage]
+x.hip:1:1: remark:     Occupancy [waves/SIMD]: 1 [-Rpass-analysis=kernel-resource-usage]
+"""
+RULES = [(r"12score_kernelI\w+Li32ELb[01]E", 2)]
+
+
+def test_accepts_kernels_at_their_wavefronts():
+    assert build.check_waves(WAVES, RULES) == 1      # only what a rule names is held to it
+
+
+@pytest.mark.parametrize("bad", [WAVES.replace("SIMD]: 2", "SIMD]: 1"), WAVES.replace("Occupancy [waves/SIMD]: 2", "VGPRs: 9"), WAVES.replace("Li32E", "Li8E")])
+def test_refuses_kernels_below_their_wavefronts(bad):
+    with pytest.raises(RuntimeError):
+        build.check_waves(bad, RULES)
+
+
+def test_the_built_kernels_run_at_their_wavefronts():
+    import os
+    for source, rules in build.MIN_WAVES.items():
+        report = os.path.join(build.HERE, "_build", "resource_usage_%s.txt" % source.replace(".hip", ""))
+        if not os.path.exists(report):
+            pytest.skip("no build here")
+        assert build.check_waves(open(report).read(), rules) >= len(rules)
