@@ -151,8 +151,13 @@ __host__ __device__ constexpr int route_wp(int dg) { return dg <= 16 ? dg : dg +
 // ... which is widened when it is staged where the space allows it, not by every wavefront at every step
 template <int DG> using route_w_t = std::conditional_t<DG <= 16, double, float>;
 
+// Wavefronts per SIMD asked for; 0: the compiler's choice.  The operands of four steps took the wide projections past the registers
+// of the wavefronts that one step at a time had left (4096 -> 64, bf16, 32768 tokens: 345 us one by one, 413 with four steps in
+// one wavefront, 333 in two; 1024 -> 64, 131072: 368 / 474 / 363; 1024 -> 32 in fp32, 131072: 193 / 205 in three, 192 in four).
+template <typename T> constexpr int route_waves(int dg) { return dg == 64 ? 2 : (dg == 32 && sizeof(T) == 4) ? 4 : 0; }
+
 template <typename T, int DG, int NW>
-__global__ __launch_bounds__(64 * NW) void route_project_kernel(RouteLayout R, const T* __restrict__ hidden,
+__global__ __launch_bounds__(64 * NW, route_waves<T>(DG)) void route_project_kernel(RouteLayout R, const T* __restrict__ hidden,
                                                                  const float* __restrict__ wg,
                                                                  const float* __restrict__ cent,
                                                                  char* __restrict__ ws,
