@@ -57,7 +57,8 @@ def check_no_spills(remarks):
 
 # Wavefronts per SIMD without which a kernel that lives on hiding its loads is slower than what it replaced; a build that
 # falls below is refused.  (mangled-name pattern, wavefronts)
-MIN_WAVES = {"focus_assign.hip": [(r"12score_kernelI\w+Li32ELb[01]E", 2)],
+MIN_WAVES = {"focus_assign.hip": [(r"12score_kernelI\w+Li32ELb[01]E", 2), (r"12score_kernelI(t|\w+f16_bitsE)Li16ELb[01]E", 4),
+                                  (r"12score_kernelI(t|\w+f16_bitsE)Li8ELb[01]E", 5), (r"12score_kernelI(t|\w+f16_bitsE)Li4ELb[01]E", 4)],
              "focus_route.hip": [(r"20route_project_kernelI\w+Li64ELi4E", 2), (r"20route_project_kernelIfLi32ELi4E", 4)]}
 
 

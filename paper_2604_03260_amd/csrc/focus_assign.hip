@@ -253,12 +253,8 @@ __global__ __launch_bounds__(SCAN_THREADS) void scan_plan_kernel(Layout L, char*
 // Memberships of one sort block on the fp64 matrix cores (focus_score.h), its group histogram and, on layouts with classes
 // (CLS), the class of every token and the class histogram.  norms: the largest squared key norm of the block goes into the
 // block's own slot (at most KN2_SLOTS blocks; layouts whose keys are not copied by the scatter launch).
-// Above 16 groups the accumulators are half of what two wavefronts per SIMD may have, and the compiler went one register past
-// the rest of it if not told: one wavefront, with nothing to run while it waits for its rows (one / two, whole bucketing:
-// 16 + 4 heads of 128 x 131072, K = 24 top-2 1018 / 693 us; 32 + 8 of 64 x 16384, K = 24 196 / 134; K = 20 top-1 in fp32 296 / 203).
-constexpr int score_waves(int km) { return km == 32 ? 2 : 0; }       // wavefronts per SIMD asked for; 0: the compiler's choice
 template <typename T, int KM, bool CLS>
-__global__ __launch_bounds__(SB, score_waves(KM)) void score_kernel(Layout L, HeadMap hm, const T* __restrict__ xq, const T* __restrict__ xk,
+__global__ __launch_bounds__(SB, score_waves<T>(KM)) void score_kernel(Layout L, HeadMap hm, const T* __restrict__ xq, const T* __restrict__ xk,
                                                    const float* __restrict__ cents, int which, int norms, char* __restrict__ ws)
 {
     __shared__ __align__(16) char s_a[4][score_lds(score_chunk<T>(KM))];

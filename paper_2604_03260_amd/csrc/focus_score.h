@@ -26,6 +26,20 @@ __host__ __device__ constexpr bool score_small(int km) { return km <= 8; }
 // 360 -> 323 us; 20000 x 48 heads of 96, K = 4 130 -> 120), above 16 groups the space in which their scores meet does (493 / 677);
 // 32-bit rows have half as many components in it (96 heads of 64 x 1024, K = 16: 23.4 / 21.9 with 128)
 template <typename T> __host__ __device__ constexpr int score_chunk(int km) { return km <= 16 && sizeof(T) == 2 ? 64 : 128; }
+// Chunks of a row asked for together.  Two are a whole cache line, which is otherwise fetched from L2 once for either half of it
+// (a work-group's rows are far more than the vector cache holds); where the registers allow them.  Bucketing, one / two: K = 4
+// top-2, 32 + 8 heads of 128 x 262144 882 / 866 us, 64 + 8 x 131072 715 / 697, 8 x 12 + 12 of 64 x 4096 39.8 / 37.1; state prefill of
+// 8 x 131072 keys of 128 105 / 91.  K = 8 then has a wavefront less: 64 + 8 x 131072 876 / 896.
+template <typename T> __host__ __device__ constexpr int score_depth(int km) { return km <= 4 && sizeof(T) == 2 ? 2 : 1; }
+// Wavefronts per SIMD the bucketing's scoring asks for, 0: the compiler's choice.  Left to it, 16-bit rows ran at one less than
+// the registers allow (its products' accumulators in a part of the register file of their own), and above 16 groups it went one
+// register past two, with nothing left to run while a wavefront waits for its rows.  Whole bucketing, its choice / asked for (us):
+// 16 + 4 heads of 64 x 131072, K = 8 top-2 209 / 202, K = 16 top-3 276 / 248; 40 + 8 of 128 x 32768, K = 16 282 / 258;
+// 16 + 4 of 128 x 131072, K = 24 top-2 1018 / 675; 32 + 8 of 64 x 16384, K = 24 196 / 131; K = 20 top-1 in fp32 296 / 196
+template <typename T> __host__ __device__ constexpr int score_waves(int km)
+{
+    return km == 32 ? 2 : sizeof(T) == 4 ? 0 : km == 16 ? 4 : km == 8 ? 5 : 4;
+}
 // LDS pitch of a staged row: four interleaved parts, padded; staging bytes per wavefront
 __host__ __device__ constexpr int score_a_row(int chunk) { return chunk + 16; }
 __host__ __device__ constexpr int score_lds(int chunk) { return 64 * score_a_row(chunk); }
@@ -40,9 +54,22 @@ template <int KM>
 __device__ inline void score_stage_centroids(const float* __restrict__ c, score_cent_t<KM>* s_c, int K, int d)
 {
     constexpr int WP = score_wp(KM);
-    for (int e = threadIdx.x; e < d * WP; e += blockDim.x) {
-        const int t = e / WP, g = e % WP;
-        s_c[e] = g < K ? (score_cent_t<KM>)c[(size_t)g * d + t] : (score_cent_t<KM>)0;
+    // a few loads in flight per thread (one at a time, the staging is a chain of up to 48 round trips: whole bucketing of
+    // 32 + 8 heads of 128 x 16384, K = 32 top-2 198 -> 192 us; two up to 16 groups: four made the
+    // state prefill of a generation 1 to 2 % longer)
+    constexpr int BT = KM <= 16 ? 2 : 4;
+    for (int e0 = threadIdx.x; e0 < d * WP; e0 += BT * blockDim.x) {
+        float v[BT];
+#pragma unroll
+        for (int i = 0; i < BT; ++i) {
+            const int e = e0 + i * blockDim.x, t = e / WP, g = e % WP;
+            v[i] = e < d * WP && g < K ? c[(size_t)g * d + t] : 0.f;
+        }
+#pragma unroll
+        for (int i = 0; i < BT; ++i) {
+            const int e = e0 + i * blockDim.x;
+            if (e < d * WP) s_c[e] = (score_cent_t<KM>)v[i];
+        }
     }
 }
 
@@ -86,14 +113,17 @@ __device__ inline uint32_t score_rows_topk(const char* __restrict__ gbase, size_
     const int lane = threadIdx.x & 63;
     const int row_bytes = d * (int)sizeof(T);
     const int nchunk = (d + RC - 1) / RC;
-    score_u32x4 stg[NP];
-    auto load_chunk = [&](int ch) {
+    constexpr int DEPTH = score_depth<T>(KM);
+    score_u32x4 stage[DEPTH][NP];
+    auto load_chunks = [&](int ch) {              // chunks ch .. ch + DEPTH - 1
 #pragma unroll
-        for (int i = 0; i < NP; ++i) {
-            const int row = i * (64 / NP) + lane / NP, byte = ch * CHUNK + lane % NP * 16;
-            const score_u32x4 z = {0u, 0u, 0u, 0u};
-            stg[i] = (row < rows && byte < row_bytes) ? *(const score_u32x4*)(gbase + (size_t)row * pitch + byte) : z;
-        }
+        for (int i = 0; i < NP; ++i)
+#pragma unroll
+            for (int p = 0; p < DEPTH; ++p) {
+                const int row = i * (64 / NP) + lane / NP, byte = (ch + p) * CHUNK + lane % NP * 16;
+                const score_u32x4 z = {0u, 0u, 0u, 0u};
+                stage[p][i] = (row < rows && byte < row_bytes) ? *(const score_u32x4*)(gbase + (size_t)row * pitch + byte) : z;
+            }
     };
     typedef std::conditional_t<SMALL, double, score_f64x4> acc_t;
     acc_t acc[4][CB];
@@ -101,7 +131,7 @@ __device__ inline uint32_t score_rows_topk(const char* __restrict__ gbase, size_
     for (int t = 0; t < 4; ++t)
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb) acc[t][cb] = acc_t{};
-    load_chunk(0);
+    load_chunks(0);
     staged();
     if (rows <= 0) {
         if (n2max) *n2max = 0u;
@@ -110,72 +140,78 @@ __device__ inline uint32_t score_rows_topk(const char* __restrict__ gbase, size_
     float n2[NP];
 #pragma unroll
     for (int i = 0; i < NP; ++i) n2[i] = 0.f;
-    for (int ch = 0; ch < nchunk; ++ch) {
-        // a wavefront's LDS accesses run in order: no barrier, only the compiler must keep the order
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
+    for (int ch0 = 0; ch0 < nchunk; ch0 += DEPTH) {
 #pragma unroll
-        for (int i = 0; i < NP; ++i) {
-            uint32_t* dst = (uint32_t*)(abuf + (i * (64 / NP) + lane / NP) * A_ROW) + lane % NP;
-            const score_u32x4 v = stg[i];
-            if constexpr (sizeof(T) == 4) {
-                dst[0] = v[0]; dst[NP] = v[1]; dst[2 * NP] = v[2]; dst[3 * NP] = v[3];
-            } else {
-                dst[0] = (v[0] & 0xffffu) | (v[2] << 16);
-                dst[NP] = (v[0] >> 16) | (v[2] & 0xffff0000u);
-                dst[2 * NP] = (v[1] & 0xffffu) | (v[3] << 16);
-                dst[3 * NP] = (v[1] >> 16) | (v[3] & 0xffff0000u);
+        for (int p = 0; p < DEPTH; ++p) {
+            const int ch = ch0 + p;
+            if (p > 0 && ch >= nchunk) break;
+            const score_u32x4 (&stg)[NP] = stage[p];
+            // a wavefront's LDS accesses run in order: no barrier, only the compiler must keep the order
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int i = 0; i < NP; ++i) {
+                uint32_t* dst = (uint32_t*)(abuf + (i * (64 / NP) + lane / NP) * A_ROW) + lane % NP;
+                const score_u32x4 v = stg[i];
+                if constexpr (sizeof(T) == 4) {
+                    dst[0] = v[0]; dst[NP] = v[1]; dst[2 * NP] = v[2]; dst[3 * NP] = v[3];
+                } else {
+                    dst[0] = (v[0] & 0xffffu) | (v[2] << 16);
+                    dst[NP] = (v[0] >> 16) | (v[2] & 0xffff0000u);
+                    dst[2 * NP] = (v[1] & 0xffffu) | (v[3] << 16);
+                    dst[3 * NP] = (v[1] >> 16) | (v[3] & 0xffff0000u);
+                }
             }
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        if constexpr (sizeof(T) == 2) {
-            if (n2max) {
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            if constexpr (sizeof(T) == 2) {
+                if (n2max) {
 #pragma unroll
-                for (int i = 0; i < NP; ++i) n2[i] = score_piece_norm2<T>(stg[i], n2[i]);
+                    for (int i = 0; i < NP; ++i) n2[i] = score_piece_norm2<T>(stg[i], n2[i]);
+                }
             }
-        }
-        if (ch + 1 < nchunk) load_chunk(ch + 1);
-        constexpr int AR = NP / 4;                // 16-byte reads of a part
-        score_u32x4 ar[4][AR];
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            const score_u32x4* p = (const score_u32x4*)(abuf + (t * 16 + (lane & 15)) * A_ROW + (lane >> 4) * (4 * NP));
-#pragma unroll
-            for (int i = 0; i < AR; ++i) ar[t][i] = p[i];
-        }
-        const score_cent_t<KM>* wr = s_c + (ch * RC + (lane >> 4)) * WP + (lane & LC);
-        const int steps = min(RC, d - ch * RC) / 4;
-        auto step = [&](int i) {
-            double bv[CB];
-#pragma unroll
-            for (int cb = 0; cb < CB; ++cb) bv[cb] = (double)wr[i * 4 * WP + cb * (LC + 1)];
+            if (p == DEPTH - 1 && ch + 1 < nchunk) load_chunks(ch + 1);
+            constexpr int AR = NP / 4;                // 16-byte reads of a part
+            score_u32x4 ar[4][AR];
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
-                double a;
-                if constexpr (sizeof(T) == 4) {
-                    a = (double)__uint_as_float(ar[t][(i / 4) % AR][i % 4]);
-                } else {
-                    const uint32_t w2 = ar[t][(i / 8) % AR][(i / 2) % 4];
-                    if constexpr (std::is_same<T, f16_bits>::value)
-                        a = (double)f16_bits_to_f32((uint16_t)(i % 2 ? w2 >> 16 : w2 & 0xffffu));
-                    else
-                        a = (double)__uint_as_float(i % 2 ? w2 & 0xffff0000u : w2 << 16);
-                }
+                const score_u32x4* src = (const score_u32x4*)(abuf + (t * 16 + (lane & 15)) * A_ROW + (lane >> 4) * (4 * NP));
 #pragma unroll
-                for (int cb = 0; cb < CB; ++cb) {
-                    if constexpr (SMALL) acc[t][cb] = __builtin_amdgcn_mfma_f64_4x4x4f64(a, bv[cb], acc[t][cb], 0, 0, 0);
-                    else acc[t][cb] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, bv[cb], acc[t][cb], 0, 0, 0);
-                }
+                for (int i = 0; i < AR; ++i) ar[t][i] = src[i];
             }
-        };
-        if (steps == RC / 4) {
+            const score_cent_t<KM>* wr = s_c + (ch * RC + (lane >> 4)) * WP + (lane & LC);
+            const int steps = min(RC, d - ch * RC) / 4;
+            auto step = [&](int i) {
+                double bv[CB];
 #pragma unroll
-            for (int i = 0; i < RC / 4; ++i) step(i);
-        } else {                                  // the last chunk of 80 or 96 components
+                for (int cb = 0; cb < CB; ++cb) bv[cb] = (double)wr[i * 4 * WP + cb * (LC + 1)];
 #pragma unroll
-            for (int i = 0; i < RC / 4; ++i)
-                if (i < steps) step(i);
+                for (int t = 0; t < 4; ++t) {
+                    double a;
+                    if constexpr (sizeof(T) == 4) {
+                        a = (double)__uint_as_float(ar[t][(i / 4) % AR][i % 4]);
+                    } else {
+                        const uint32_t w2 = ar[t][(i / 8) % AR][(i / 2) % 4];
+                        if constexpr (std::is_same<T, f16_bits>::value)
+                            a = (double)f16_bits_to_f32((uint16_t)(i % 2 ? w2 >> 16 : w2 & 0xffffu));
+                        else
+                            a = (double)__uint_as_float(i % 2 ? w2 & 0xffff0000u : w2 << 16);
+                    }
+#pragma unroll
+                    for (int cb = 0; cb < CB; ++cb) {
+                        if constexpr (SMALL) acc[t][cb] = __builtin_amdgcn_mfma_f64_4x4x4f64(a, bv[cb], acc[t][cb], 0, 0, 0);
+                        else acc[t][cb] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, bv[cb], acc[t][cb], 0, 0, 0);
+                    }
+                }
+            };
+            if (steps == RC / 4) {
+#pragma unroll
+                for (int i = 0; i < RC / 4; ++i) step(i);
+            } else {                                  // the last chunk of 80 or 96 components
+#pragma unroll
+                for (int i = 0; i < RC / 4; ++i)
+                    if (i < steps) step(i);
+            }
         }
     }
     if constexpr (sizeof(T) == 2) {
