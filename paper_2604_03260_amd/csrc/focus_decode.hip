@@ -969,7 +969,7 @@ template <> struct DecHalf<true> {
 
 constexpr float DEC_RESCALE_THRESHOLD = 8.f;
 
-// The walk is cut into as many even shares as the launch has work-groups for it, in units of the 32 keys of a wavefront's
+// The walk is cut into even shares, at most as many as the launch has work-groups for it (decode_shares), in units of the 32 keys of a wavefront's
 // round, and a share is resolved up to DEC_RESOLVE entries at a time.  The launch is memory latency and bandwidth: what
 // counts is that all work-groups are resident at once and end together.  Chunks of 512 entries left a nearly empty
 // last one (32768 cached keys, 8 KV heads: 512 work-groups and 8 more, the third on their compute units), and in list
@@ -1044,8 +1044,8 @@ __global__ __launch_bounds__(256) void decode_attn_gqa_mfma_kernel(DecodeLayout 
     __syncthreads();
     const int nseg = s_walk.nseg;
     const int vtotal = s_walk.beg[nseg];
-    const int units = (vtotal + 31) / 32;
-    const int u_beg = (int)((long)units * chunk / gridDim.x), u_end = (int)((long)units * (chunk + 1) / gridDim.x);
+    const int units = (vtotal + 31) / 32, shares = decode_shares(units, gridDim.x, gridDim.y, pos_dev != nullptr);
+    const int u_beg = (int)((long)units * min(chunk, shares) / shares), u_end = (int)((long)units * min(chunk + 1, shares) / shares);
     if (u_beg == u_end) {
         for (int i = 0; i < G; ++i) {
             float* mypart = part + ((bhq0 + i) * L.max_parts + chunk) * PW;
@@ -1340,16 +1340,19 @@ static hipError_t decode_step_d(const DecodeLayout& L, const HeadMap& hm, int po
         if constexpr (sizeof(T) == 2) {
             if ((size_t)L.n * D * 2 <= 0xffffffffull) {
                 grid.y = L.B * L.Hkv * ((G + 15) / 16);
-                // Work-groups per head.  Up to 128 heads: as many as are resident at once and no more, three per compute unit
-                // (two at 512-byte rows: LDS) where that leaves every wavefront four rounds, else two, none with less
-                // than a round per wavefront.  A step in us with two / three per unit and with 512-entry chunks: 8 heads x 32768
-                // 37.2 / 38.8 / 43.2; 8 x 131072 98 / 93 / 104; 96 x 4096 29.6 / 26.5 / 27.4; 4 x 2 heads of 256 x 30000 60 / 67 / 60.
-                // More heads: whole heads per slot no longer come out even (300 heads x 4000: 97 / 71 / 66; 256 x 9000: 217 /
-                // 215 / 206), chunks of 512 entries that the dispatcher hands out do better.
+                // Work-groups per row, for the longest walk the host knows of (decode_shares cuts the real one).  Up to 128 rows:
+                // as many as are resident at once and no more, three per compute unit (two at 512-byte rows: LDS) where
+                // that leaves every wavefront four rounds, else two, none with less than a round per wavefront, and at
+                // most DEC_MAX_PARTS (a single row then leaves some of the chip idle).  A step in us with two / three
+                // per unit and with 512-entry chunks: 8 heads x 32768 37.2 / 38.8 / 43.2; 8 x 131072 98 / 93 / 104; 96 x 4096
+                // 29.6 / 26.5 / 27.4; 4 x 2 heads of 256 x 30000 60 / 67 / 60.  More rows: whole heads per slot no longer come
+                // out even (300 heads x 4000: 97 / 71 / 66; 256 x 9000: 217 / 215 / 206), shares of 512 entries (more where
+                // that would be over DEC_MAX_PARTS of them) that the dispatcher hands out do better.
                 const long rows = grid.y, units = (pos + 32) / 32, all = rows * units;
                 const long slots = (D < 256 && all >= 3 * 256 * 16) ? 3 * 256 : 2 * 256;
-                long parts = rows <= 128 ? slots / rows : (units + 15) / 16;
-                nparts = (int)std::max<long>(1, std::min(std::min(parts, (units + 3) / 4), (long)L.max_parts));
+                constexpr long LEAST = DEC_CHUNK_SHORT / 32, MANY = DEC_CHUNK / 32;
+                long parts = rows <= DEC_MANY_ROWS ? slots / rows : (units + MANY - 1) / MANY;
+                nparts = (int)std::max<long>(1, std::min(std::min(parts, (units + LEAST - 1) / LEAST), (long)L.max_parts));
                 grid.x = nparts;
                 constexpr bool f16 = std::is_same<T, f16_bits>::value;
                 hipLaunchKernelGGL((decode_attn_gqa_mfma_kernel<f16, D>), grid, dim3(256), 0, s, L, G, pos, pos_dev,

@@ -189,8 +189,27 @@ struct RouteLayout {
 
 // Shapes and state offsets of the incremental (one token per step) path.
 constexpr int DEC_CHUNK = 512;               // keys of the key sequence a work-group of the vector decode attention resolves at a time
-constexpr int DEC_CHUNK_SHORT = 128;         // keys of the smallest share of a work-group: one round for each wavefront
+constexpr int DEC_CHUNK_SHORT = 128;         // one round of 32 keys for each wavefront of a work-group: what a share of the matrix-core decode
+                                             // attention is launched for at least (decode_shares: what it gets); sizes max_parts
 constexpr int DEC_MAX_PARTS = 384;           // partial results per head the merge reads at most
+// Shares of a walk of `units` rounds (32 keys each) in a launch of the matrix-core decode attention with `parts` work-groups for
+// each of `rows` (batch, KV head, 16 query heads).  The walk may be far shorter than the launch was made for.  With the position
+// in device memory (at) the launch is made for the whole caches, its work-groups are paid for anyway, and the walk is spread over
+// all of them; so it is up to 128 rows, where the chip is not full.  Otherwise only a walk over lists is shorter, and above 128 rows
+// a share of less than a round for each of the four wavefronts costs more work-groups than it saves time; the first eight
+// shares do not.  A step (us), spread / four rounds / as here, and with the chunks of 512 entries of before: 256 rows of 64,
+// K = 16 top-1, 9000 keys 39.0 / 33.5 / 33.4 / 34.4, 20000 70.1 / 56.2 / 55.8 / 63.6; 300 rows of 80 x 4000, K = 32 top-1 38.4 / 42.7 / 38.5 /
+// 63.7.  In device memory, 256 rows, capacity 32768, position 1000, K = 4 top-2: four rounds 79, as here 70.5, before 125.
+constexpr int DEC_MANY_ROWS = 128;
+__host__ __device__ inline int decode_shares(int units, int parts, int rows, bool at)
+{
+    if (!at && rows > DEC_MANY_ROWS) {
+        constexpr int ROUNDS = DEC_CHUNK_SHORT / 32;
+        const int most = units <= 8 * ROUNDS ? 8 : (units + ROUNDS - 1) / ROUNDS;
+        parts = most < parts ? most : parts;
+    }
+    return units < parts ? units : parts;
+}
 struct DecodeLayout {
     int B, Hq, Hkv, n, d;      // n = capacity of the caches
     int K, topk, window;
