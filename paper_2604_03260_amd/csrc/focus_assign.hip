@@ -700,11 +700,17 @@ hipError_t launch_score_k(const Layout& L, const HeadMap& hm, const void* q, con
 // One launch where a row is little enough work for one compute unit (scores are n * d products of 4 or 8 groups; above 8
 // groups 16 columns are computed).  Bucketing, one launch / two (us): 12 + 12 heads of 64, K = 4: 512 tokens 7.9 / 10.7, 1024 10.5 / 11.6;
 // 8 + 2 of 128: K = 4 512 tokens 10.0 / 12.3, 700 12.1 / 11.9, 1024 14.4 / 12.1; K = 8 512 13.0 / 15.2, 1024 19.2 / 15.1; K = 16 512
-// 21.7 / 22.7; 16 + 4 of 256 in fp32, 512, K = 16 34 / 32; 768 rows of 64 in fp32, K = 4: 512 28 / 32, 1024 58 / 55.
+// 21.7 / 22.7; 16 + 4 of 256 in fp32, 512, K = 16 34 / 32.
+// Many rows, where the chip is full in any case (fp32; a 16-bit layout of the short kernel has few): two launches share a row in
+// sort blocks of 256 tokens, and lose where the last one is mostly empty.  Rows of 64, K = 4: 480 x 512 tokens 17.4 / 19.1, 768
+// 29.6 / 25.6, 1536 52.0 / 42.7; 3072 x 400 64.3 / 78.2, x 256 42.4 / 43.0; K = 8: 3072 x 512 99.9 / 109, x 256 52.8 / 52.2; K = 16: 1536 x 256
+// 47.5 / 48.9, 3072 87.5 / 85.7, x 100 81.0 / 76.5, x 512 130 / 164.
 bool short_rows(const Layout& L)
 {
+    const int rows = L.B * (L.Hq + L.Hkv);
+    const int most = L.n > 512 || (L.n > 448 && L.K <= 4) ? 512 : L.n <= 256 && L.K > 8 ? 2048 : 0x7fffffff;
     return L.masked && (L.dtype == 0 || short_attention(L)) && (long long)L.n * L.d <= 65536 && L.n <= (L.K <= 8 ? 1024 : L.K <= 16 ? 512 : 0) &&
-           (L.n <= 512 || L.B * (L.Hq + L.Hkv) <= 512);
+           rows <= most;
 }
 
 template <typename T, int KM, int NW>

@@ -26,6 +26,16 @@ def test_short_rows_are_exact(n, K, topk, dtype, d):
     harness.check_pair_totals(wl, res, mq, mk)
 
 
+@pytest.mark.parametrize("B,n,K,topk,d", [(43, 448, 4, 2, 64), (43, 449, 4, 2, 64), (43, 512, 8, 1, 64), (171, 130, 16, 2, 64), (170, 256, 9, 2, 80)])
+def test_many_short_rows_are_exact(B, n, K, topk, d):
+    """Where a launch of many rows changes from one work-group per row to sort blocks (512 and 2048 rows; 32 bits)."""
+    wl = workloads.Workload("mr", 900 + n, B, 8, 4, n, d, "f32", K, topk, 33, mixture=3)
+    inp = workloads.make_inputs(wl, "cuda")
+    res = harness.run_gpu(wl, inp)
+    mq, mk = harness.check_assign(wl, inp, res)
+    harness.check_pair_totals(wl, res, mq, mk)
+
+
 def test_short_rows_through_strides():
     B, Hq, Hkv, n, d = 2, 4, 2, 200, 64
     x = torch.randn((B, n, Hq + 2 * Hkv, d), device="cuda").to(torch.bfloat16)
