@@ -217,7 +217,7 @@ focus_status make_layout(const focus_params* p, focus::Layout* L, focus::HeadMap
     // for the last rows; 2.8 % where rows lie 4000 bytes apart), so only while the walk is short.  Whole pass, copied / in
     // place (us): 8 x 12 heads of 64 x 4096 327 / 315; 32/8 of 128 x 4096 183 / 175; 14/2 of 64 x 8192, K = 8 top-3 183 / 180;
     // 3 x 15/5 of 80 x 5003 out of one projection 313 / 308.
-    L->k_direct = (L->masked || soft) && p->dtype != FOCUS_F32 && p->n <= 8192 && L->ks[2] < (1 << 23);
+    L->k_direct = (L->masked || soft) && p->dtype != FOCUS_F32 && p->n <= focus::KEYS_IN_PLACE && L->ks[2] < (1 << 23);
     L->nblk = (p->n + SB - 1) / SB;
     // class-major launch order only where the heads' K and V are far beyond the caches (see plan_heads_kernel)
     L->class_major = (L->BQ == 256 && p->n >= LONG_N) ? 1 : 0;

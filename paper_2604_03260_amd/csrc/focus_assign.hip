@@ -252,7 +252,7 @@ __global__ __launch_bounds__(SCAN_THREADS) void scan_plan_kernel(Layout L, char*
 // ---------------------------------------------------------------- score + top-k
 // Memberships of one sort block on the fp64 matrix cores (focus_score.h), its group histogram and, on layouts with classes
 // (CLS), the class of every token and the class histogram.  norms: the largest squared key norm of the block goes into the
-// block's own slot (at most KN2_SLOTS blocks; layouts whose keys are not copied by the scatter launch).
+// block's own slot (layouts whose keys are read in place by the tiled kernel).
 template <typename T, int KM, bool CLS>
 __global__ __launch_bounds__(SB, score_waves<T>(KM)) void score_kernel(Layout L, HeadMap hm, const T* __restrict__ xq, const T* __restrict__ xk,
                                                    const float* __restrict__ cents, int which, int norms, char* __restrict__ ws)
@@ -282,7 +282,7 @@ __global__ __launch_bounds__(SB, score_waves<T>(KM)) void score_kernel(Layout L,
         if constexpr (CLS)
             for (int e = tid; e < L.NC; e += SB) s_hist_c[e] = 0;
         __syncthreads();
-    }, want_norms ? &n2 : nullptr);
+    }, want_norms, n2);
     if (want_norms && lane == 0) s_n2[wave] = n2;
     if (lane < rows) {
         ((uint32_t*)(ws + (is_query ? L.off_mq : L.off_mk)))[(size_t)bh * n + j0 + lane] = m;
@@ -389,21 +389,6 @@ __global__ void fill_i32_kernel(int* __restrict__ p, size_t count, int value)
 }
 
 // ---------------------------------------------------------------- scatter
-// sum of the squares of the eight 16-bit values of a chunk (bf16 or IEEE half bit patterns)
-__device__ inline float chunk_norm2(const uint4& val, bool f16)
-{
-    const uint32_t w[4] = {val.x, val.y, val.z, val.w};
-    float acc = 0.f;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const float a = f16 ? f16_bits_to_f32((uint16_t)(w[e] & 0xffffu)) : __uint_as_float(w[e] << 16);
-        const float b = f16 ? f16_bits_to_f32((uint16_t)(w[e] >> 16)) : __uint_as_float(w[e] & 0xffff0000u);
-        acc = fmaf(a, a, acc);
-        acc = fmaf(b, b, acc);
-    }
-    return acc;
-}
-
 // k: the key rows (16-bit types) for the class-ordered copy the matrix-core attention kernel reads, or NULL.
 // The copy also leaves the largest squared key norm of the (batch, KV head) in the workspace (off_kn2: KN2_SLOTS
 // partial maxima per head, cleared by the kernel before it): a non-negative float orders like its bit pattern, so one
@@ -574,7 +559,7 @@ __global__ __launch_bounds__(SB) void scatter_kernel(Layout L, int which, const 
         for (int i = 0; i < 4; ++i) {
             if (copy_k && dd[i] >= 0) kc[(size_t)dd[i] * CPR + ((id0 + i * SB) & (lpr - 1))] = val[i];
             // the chunks of a row sit in lpr consecutive lanes (a power of two <= 32, rows do not straddle waves)
-            float n2 = chunk_norm2(val[i], f16);
+            float n2 = piece_norm2(val[i].x, val[i].y, val[i].z, val[i].w, f16, 0.f);
             for (int off = 1; off < lpr; off <<= 1) n2 += __shfl_xor(n2, off, 64);
             const unsigned bits = __float_as_uint(n2) & 0x7fffffffu;     // a NaN may carry a sign bit
             n2max = bits > n2max ? bits : n2max;
@@ -761,8 +746,9 @@ hipError_t launch_assign(const Layout& L, const HeadMap& hm, const void* q, cons
         return L.dtype == 0 ? launch_bucket_rows_k<float>(L, hm, q, k, centroids, ws, st)
                : L.dtype == 2 ? launch_bucket_rows_k<f16_bits>(L, hm, q, k, centroids, ws, st)
                               : launch_bucket_rows_k<uint16_t>(L, hm, q, k, centroids, ws, st);
-    // keys that stay where they are: their norms come with the scores where every sort block has a slot of its own
-    const int norms = L.k_direct && L.nblk <= KN2_SLOTS ? 1 : 0;
+    // keys that the tiled kernel reads where they are: their norms come with the scores, a slot for every sort block
+    static_assert(KEYS_IN_PLACE / SB <= KN2_SLOTS, "a slot for every sort block of keys read in place");
+    const int norms = L.k_direct && !short_attention(L) ? 1 : 0;
     const hipError_t e = L.dtype == 0 ? launch_score_k<float>(L, hm, q, k, centroids, norms, ws, st)
                          : L.dtype == 2 ? launch_score_k<f16_bits>(L, hm, q, k, centroids, norms, ws, st)
                                         : launch_score_k<uint16_t>(L, hm, q, k, centroids, norms, ws, st);

@@ -14,6 +14,7 @@ constexpr int LONG_N_TWO_PASS = 1 << 17; // ... and from this length on where th
 constexpr int KT = 64;         // keys per attention tile; class segments of the permuted keys are padded to this
 constexpr int MAX_CLASSES = 256;
 constexpr int MAX_HQ = 256;
+constexpr int KEYS_IN_PLACE = 8192;    // longest sequence whose keys the tiled kernel reads in place (Layout::k_direct)
 constexpr int KN2_SLOTS = 64;  // partial maxima of the squared key norms per (batch, KV head), one per lane of a wavefront
 constexpr int KPOS_PAD = 0x7fffffff;  // position stored in padded key slots: never <= a query position
 

@@ -73,32 +73,28 @@ __device__ inline void score_stage_centroids(const float* __restrict__ c, score_
     }
 }
 
-// acc + the sum of the squares of the eight 16-bit values of a piece
-template <typename T>
-__device__ inline float score_piece_norm2(const score_u32x4& v, float acc)
+// acc + the sum of the squares of the eight 16-bit values of a piece (bf16 or IEEE half bit patterns), products in fp32
+__device__ inline float piece_norm2(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3, bool f16, float acc)
 {
+    const uint32_t w[4] = {w0, w1, w2, w3};
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-        if constexpr (std::is_same<T, f16_bits>::value) {
-            typedef __attribute__((__vector_size__(2 * sizeof(_Float16)))) _Float16 h2;
-            const h2 x = __builtin_bit_cast(h2, (uint32_t)v[e]);
-            acc = __builtin_amdgcn_fdot2(x, x, acc, false);
-        } else {
-            typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 b2;
-            const b2 x = __builtin_bit_cast(b2, (uint32_t)v[e]);
-            acc = __builtin_amdgcn_fdot2_f32_bf16(x, x, acc, false);
-        }
+        const float a = f16 ? f16_bits_to_f32((uint16_t)(w[e] & 0xffffu)) : __uint_as_float(w[e] << 16);
+        const float b = f16 ? f16_bits_to_f32((uint16_t)(w[e] >> 16)) : __uint_as_float(w[e] & 0xffff0000u);
+        acc = fmaf(a, a, acc);
+        acc = fmaf(b, b, acc);
     }
     return acc;
 }
 
 // gbase: first row, pitch: bytes between rows, rows: at most 64 of them; abuf: score_lds(CHUNK) bytes of the wavefront's own.
 // staged: called once by all wavefronts of the work-group, after their first loads are on their way: stages the centroids
-// and waits for them.  n2max: NULL, or takes the bit pattern of the largest squared norm of the rows (16-bit types; a
-// non-negative float orders like its bit pattern, a NaN or infinite norm ends up above every finite one).  Returns the mask of row `lane` (0 past the rows).  KM = K rounded up to 4, 8, 16 or 32.
+// and waits for them.  want_norm (16-bit types): n2max takes the bit pattern of the largest squared norm of the rows (a
+// non-negative float orders like its bit pattern, a NaN or infinite norm ends up above every finite one), else it is left as
+// it is.  Returns the mask of row `lane` (0 past the rows).  KM = K rounded up to 4, 8, 16 or 32.
 template <typename T, int KM, int CHUNK, typename F>
 __device__ inline uint32_t score_rows_topk(const char* __restrict__ gbase, size_t pitch, int rows, int d, const score_cent_t<KM>* s_c,
-                                           char* abuf, int K, int topk, F&& staged, unsigned* n2max = nullptr)
+                                           char* abuf, int K, int topk, F&& staged, bool want_norm, unsigned& n2max)
 {
     constexpr int A_ROW = score_a_row(CHUNK);
     constexpr int RC = CHUNK / (int)sizeof(T);    // components per staged chunk
@@ -133,10 +129,7 @@ __device__ inline uint32_t score_rows_topk(const char* __restrict__ gbase, size_
         for (int cb = 0; cb < CB; ++cb) acc[t][cb] = acc_t{};
     load_chunks(0);
     staged();
-    if (rows <= 0) {
-        if (n2max) *n2max = 0u;
-        return 0;
-    }
+    if (rows <= 0) return 0;
     float n2[NP];
 #pragma unroll
     for (int i = 0; i < NP; ++i) n2[i] = 0.f;
@@ -165,9 +158,10 @@ __device__ inline uint32_t score_rows_topk(const char* __restrict__ gbase, size_
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             if constexpr (sizeof(T) == 2) {
-                if (n2max) {
+                if (want_norm) {
 #pragma unroll
-                    for (int i = 0; i < NP; ++i) n2[i] = score_piece_norm2<T>(stg[i], n2[i]);
+                    for (int i = 0; i < NP; ++i)
+                        n2[i] = piece_norm2(stg[i][0], stg[i][1], stg[i][2], stg[i][3], std::is_same<T, f16_bits>::value, n2[i]);
                 }
             }
             if (p == DEPTH - 1 && ch + 1 < nchunk) load_chunks(ch + 1);
@@ -215,7 +209,7 @@ __device__ inline uint32_t score_rows_topk(const char* __restrict__ gbase, size_
         }
     }
     if constexpr (sizeof(T) == 2) {
-        if (n2max) {
+        if (want_norm) {
             unsigned top = 0u;
 #pragma unroll
             for (int i = 0; i < NP; ++i) {
@@ -229,7 +223,7 @@ __device__ inline uint32_t score_rows_topk(const char* __restrict__ gbase, size_
                 const unsigned o = (unsigned)__shfl_xor((int)top, off, 64);
                 top = o > top ? o : top;
             }
-            *n2max = top;
+            n2max = top;
         }
     }
     // accumulator of lane l: row 4*(l%16/4) + l/16 of the tile, group l%4 of the block; register r of the 16-column
@@ -281,6 +275,14 @@ __device__ inline uint32_t score_rows_topk(const char* __restrict__ gbase, size_
         }
     }
     return mask;
+}
+
+template <typename T, int KM, int CHUNK, typename F>
+__device__ inline uint32_t score_rows_topk(const char* __restrict__ gbase, size_t pitch, int rows, int d, const score_cent_t<KM>* s_c,
+                                           char* abuf, int K, int topk, F&& staged)
+{
+    unsigned unused = 0u;
+    return score_rows_topk<T, KM, CHUNK>(gbase, pitch, rows, d, s_c, abuf, K, topk, staged, false, unused);
 }
 
 }  // namespace focus
