@@ -44,7 +44,9 @@
 //    either, because the query rows are pre-multiplied by scale*log2(e) when they are loaded (one more 16-bit
 //    rounding of q, a relative 2^-9 per component: about 1e-3 absolute in a logit, below the rounding of the
 //    16-bit probabilities).  The sums stay far inside fp32 (2^60 * 2^24 keys * |v|), and out = O / l is the same
-//    exact softmax.  Any other work-group (large norms, non-finite keys) runs the second copy of the loop:
+//    exact softmax.  IEEE halves do not hold that range; there a work-group looks at its row sums before it stores, and
+//    leaves a tile whose probabilities were too large or too small.  Any other work-group (large norms, non-finite keys)
+//    runs the second copy of the loop:
 //  * there the reference max of a row only moves when the true max has drifted
 //    by more than RESCALE_THRESHOLD (log2 units), so O is rarely rescaled.
 //  * The row sum adds the bf16-rounded probabilities (v_dot2), the numbers PV uses.
@@ -99,6 +101,11 @@ constexpr float LOG2E = 1.4426950408889634f;
 constexpr float RESCALE_THRESHOLD = 8.f;    // log2 units the row max may drift before O is rescaled
 constexpr float NOREF_BOUND = 60.f;         // largest |logit| bound (log2 units) up to which exp2 needs no reference
 constexpr float NOREF_SLACK = 1.01f;        // the bound is taken this much larger than computed (fp32 rounding of the norms)
+// IEEE halves end at 2^16 and lose bits below 2^-14: where a bound is above F16_SAFE, the finished row sums tell whether a
+// probability overflowed (the sum is infinite) or too many were small (F16_LEAST per visited key: each is at most 2^-25 off,
+// all together then at most 2^-11 of the sum, half an ulp of one of them); such a tile is left to the other form.  Up to F16_NONZERO
+// no probability rounds to zero, and a sum of zero is a row without pairs.
+constexpr float F16_SAFE = 15.f, F16_NONZERO = 24.f, F16_LEAST = 1.f / 16384.f;
 constexpr float CAP_POLY_Z = 0.3f;          // |score*scale/softcap| up to which tanh is taken as its Taylor polynomial to z^5
 constexpr float CAP_CUBIC_Z = 0.15f;        // ... and to z^3 (the z^5 term is then below 7.3e-4 log2 units at cap 50)
 
@@ -257,6 +264,7 @@ struct Smem {
     __attribute__((aligned(16))) char vt[2][TileGeom<D>::V_LDS];   // [stage][d][VROW] 16-bit elements
     __attribute__((aligned(16))) unsigned kmsk[PM == PM_COARSE ? 3 * KT : 4];      // membership masks of the keys (coarse classes)
     __attribute__((aligned(16))) unsigned kbits[PM == PM_MASKED ? 3 * KBITS_MAX : 4];   // membership bits of the keys (masked)
+    int f16_level;                                                 // IEEE halves without a reference: 0 every bound up to F16_SAFE, 1 up to F16_NONZERO, 2 above
     unsigned upto[PM == PM_MASKED ? 30 : 1];                       // scores at or below a key offset (masked, see the loop)
     __attribute__((aligned(16))) char gk[SOFT ? 2 * KT * grow_bytes(SOFT) : 16];   // [stage][key][grow_bytes] soft assignments of the keys
 };
@@ -385,7 +393,8 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT == 2) ? 1 : (D =
     const int n32 = lane & 31, hh = lane >> 5;
     int* nrflag = (int*)(ws_rw + L.off_nrflag) + blockIdx.x;
     if constexpr (NOREF) {
-        if (tid == 0) *nrflag = 1;                 // unless the bound check below says otherwise
+        if (tid == 0) *nrflag = 1;                 // unless the bound check below (or the row sums) say otherwise
+        if (F16 && tid == 0) S.f16_level = 0;      // (barriers follow)
     } else if constexpr (SOFT == 0) {
         if (*(volatile int*)nrflag != 0) return;   // the no-reference launch before this one did the tile
     }
@@ -476,6 +485,12 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT == 2) ? 1 : (D =
         if (__syncthreads_and((bnd <= NOREF_BOUND) ? 1 : 0) == 0) {  // a NaN bound compares false
             if (tid == 0) *nrflag = 0;
             return;
+        }
+        if constexpr (F16) {
+            if (__any(bnd > F16_SAFE)) {
+                const int level = __any(bnd > F16_NONZERO) ? 2 : 1;
+                if (lane == 0) atomicMax(&S.f16_level, level);
+            }
         }
         if constexpr (!SOFTCAP) {    // logits come off the matrix cores in log2 units
             const float sl2q = L.scale * LOG2E;
@@ -1046,6 +1061,21 @@ __global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT == 2) ? 1 : (D =
 
     // ---- epilogue
     const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
+    if constexpr (NOREF && F16) {
+        const int level = S.f16_level;
+        if (level != 0) {
+            const bool good = !rvalid || (l_tot < INFINITY && (l_tot >= F16_LEAST * (float)(total * KT) || (level == 1 && l_tot == 0.f)));
+            if (PM == PM_EXACT && L.merge_prev) {    // what the first pass left must not change unless all of the tile is done here
+                if (__syncthreads_and(good ? 1 : 0) == 0) {
+                    *nrflag = 0;
+                    return;
+                }
+            } else if (__any(!good)) {       // the other form does the whole tile, and stores the other wavefronts' rows again
+                *nrflag = 0;
+                return;
+            }
+        }
+    }
     if constexpr (PAIRS) npairs += __shfl_xor(npairs, 32, 64);
     if constexpr (MASKED) vbad |= (unsigned)__shfl_xor((int)vbad, 32, 64);
     if (!rvalid) return;
