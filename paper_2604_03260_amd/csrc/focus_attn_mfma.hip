@@ -356,8 +356,16 @@ __device__ inline void pin_operands(V8 (&a)[N])
 // instantiation first, whose work-groups check their bound, leave a flag (1 = done here, 0 = not mine) and do
 // the tile or return; then the other instantiation, whose work-groups return at once where the flag says done.
 // (v: the values as the caller holds them; the masked form alone reads them, and only where some are not finite.)
+// Wavefronts per SIMD asked for: two, one where the operands need the whole register file; the masked form with a softcap at 64
+// components takes 172 registers if it may, and is 6 % faster in the 168 of three (2 x 12 heads x 8192, K = 16 top-3, softcap: 340 us at two, 321
+// at three; the other forms at 64 components stay below 168 by themselves: 0.99 to 1.005 of the time either way).
+template <int D, int PM, int SOFT, int MFMA_WAVES, bool SOFTCAP, bool NOREF>
+constexpr int attn_waves()
+{
+    return (D == 256 || SOFT == 2) ? 1 : (D == 64 && PM == PM_MASKED && SOFTCAP && NOREF) ? 3 : 8 / MFMA_WAVES;
+}
 template <int D, int KS, int DB, int MFMA_WAVES, bool SOFTCAP, bool PAIRS, bool F16, int PM, int SOFT, bool NOREF>
-__global__ __launch_bounds__(64 * MFMA_WAVES, (D == 256 || SOFT == 2) ? 1 : (D == 64 && MFMA_WAVES == 4 && NOREF) ? 3 : 8 / MFMA_WAVES) void attn_mfma_kernel(
+__global__ __launch_bounds__(64 * MFMA_WAVES, (attn_waves<D, PM, SOFT, MFMA_WAVES, SOFTCAP, NOREF>())) void attn_mfma_kernel(
     Layout L, HeadMap hm, int default_map, const uint16_t* __restrict__ q, const uint16_t* __restrict__ v,
     const float* __restrict__ g, char* ws_rw, uint16_t* __restrict__ out, float* __restrict__ lse,
     int32_t* __restrict__ row_pairs, const uint16_t* __restrict__ k)
