@@ -25,12 +25,16 @@
  *   - The caller owns all buffers.  The library allocates no device memory and
  *     keeps no state between calls.  The workspace is caller-allocated,
  *     256-byte aligned, at least focus_workspace_size() bytes, and carries the
- *     result of focus_assign to focus_attn_fwd (same params, same k).  Both
- *     calls WRITE it: focus_assign fills the membership, the lists, the schedule
- *     and the class-ordered copy of the keys; focus_attn_fwd (and its variants)
- *     adds the class-ordered, transposed copy of the values before its attention
- *     launch, so v may change between two attention calls on one workspace, while
- *     k may not.  Two attention calls that share a workspace must not overlap.
+ *     result of focus_assign to focus_attn_fwd (same params, strides included, and
+ *     the same k).  Both calls WRITE it: focus_assign fills the membership, the lists
+ *     and whatever the attention kernel of these params needs beside them (the
+ *     schedule, a copy of the keys in the order in which it visits them, their largest
+ *     norms: a short sequence needs none of these); focus_attn_fwd (and its variants)
+ *     adds the copy of the values where its kernel reads one, so v may change
+ *     between two attention calls on one workspace, while k may not: it is read
+ *     again by the attention call, and its memory must stay as it is until the last
+ *     attention call on the workspace has ended.  Two attention calls that share a
+ *     workspace must not overlap.
  *   - focus_assign and focus_attn_fwd only enqueue work on `stream`
  *     (a hipStream_t passed as void*, NULL = default stream) and return; the
  *     caller synchronises.  Inputs are never modified; out must not alias them.
@@ -133,7 +137,7 @@ focus_status focus_attn_fwd_vector(const focus_params *p, const void *q, const v
  * focus_route's `soft` output rounded to fp32, or any other); lambda finite.  p->K is the width of g,
  * p->topk is not used (give 1), p->causal must be 1 and p->softcap 0 (else FOCUS_EUNSUPPORTED).
  * One call does everything (no focus_assign): the workspace of focus_soft_workspace_size(p) bytes is
- * scratch (position-ordered copies of K, V and g).  out [B,Hq,n,d] in p->dtype, lse (nullable)
+ * scratch (position-ordered copies of V and g, of K too above 8192 tokens).  out [B,Hq,n,d] in p->dtype, lse (nullable)
  * [B,Hq,n] fp32.  Forward only.  d = 256 runs on the vector ALUs in every dtype (slow). */
 focus_status focus_soft_workspace_size(const focus_params *p, size_t *bytes);
 focus_status focus_attn_soft_fwd(const focus_params *p, float lambda, const float *g,
@@ -193,8 +197,8 @@ focus_status focus_route_noalloc(const focus_route_params *rp, const void *hidde
 
 /* focus_assign for memberships given per token (the router's output): token_masks [B,n]
  * uint32 DEVICE, each a topk-subset of the K groups, shared by all query and KV heads of
- * the token.  Fills the workspace exactly as focus_assign does (masks, counts, lists,
- * schedule), so focus_attn_fwd follows unchanged.  A mask with another popcount or with
+ * the token.  Fills the workspace for the same views and attention calls as focus_assign
+ * (masks, counts, lists, schedule), so focus_attn_fwd follows unchanged.  A mask with another popcount or with
  * bits at or above K is replaced by the first topk groups; invalid_count (nullable, DEVICE
  * int32) receives how many were replaced. */
 focus_status focus_assign_tokens(const focus_params *p, const uint32_t *token_masks, const void *k,
@@ -277,8 +281,8 @@ focus_status focus_decode_step_tokens(const focus_params *p, int32_t pos, const 
  * advances pos_dev on the device between replays), and the sequences of a batch may stand at different
  * positions.  A sequence whose position is outside [0, n) is skipped: its caches, state and outputs stay
  * untouched (a finished or not yet started sequence of a continuous batch; the host cannot check device
- * values).  The launch shapes are those of the last position the caches can hold; work-groups past a
- * sequence's real length exit at once. */
+ * values).  The launch shapes are those of the last position the caches can hold; work-groups that a
+ * sequence's real length leaves without keys exit at once. */
 focus_status focus_decode_step_at(const focus_params *p, const int32_t *pos_dev, const void *q_new,
                                   const void *k_new, const void *v_new, const float *centroids,
                                   void *k_cache, void *v_cache, void *state, size_t state_bytes,

@@ -214,12 +214,14 @@ focus_status make_layout(const focus_params* p, focus::Layout* L, focus::HeadMap
         }
     }
     // Keys read in place: the copy and its launch time are saved, a tile visit is up to 1 % longer (runtime pitch, the check
-    // for the last rows; 2.8 % where rows lie 4000 bytes apart), so only while the walk is short.  Whole pass, copied / in
-    // place (us): 8 x 12 heads of 64 x 4096 327 / 315; 32/8 of 128 x 4096 183 / 175; 14/2 of 64 x 8192, K = 8 top-3 183 / 180;
-    // 3 x 15/5 of 80 x 5003 out of one projection 313 / 308.
+    // for the last rows; 2.8 % where rows lie 4000 bytes apart), so while the walk is short.  Whole pass, copied / in place
+    // (us): 8 x 12 heads of 64 x 4096 327 / 315; 32/8 of 128 x 4096 183 / 175; 14/2 of 64 x 8192, K = 8 top-3 183 / 180; 3 x 15/5
+    // of 80 x 5003 out of one projection 313 / 308.  Past 8192 tokens, where the line was drawn,
+    // reading in place would still win 1 to 2 % of contiguous keys (16/4 of 128 x 12000 605 / 595, x 16384 1032 / 1022), and of
+    // rows of one projection between -2 % (16/4 of 256 x 12000 1333 / 1293) and +0.7 % (40/8 of 96 x 16384 2083 / 2098).
     L->k_direct = (L->masked || soft) && p->dtype != FOCUS_F32 && p->n <= focus::KEYS_IN_PLACE && L->ks[2] < (1 << 23);
     L->nblk = (p->n + SB - 1) / SB;
-    // class-major launch order only where the heads' K and V are far beyond the caches (see plan_heads_kernel)
+    // class-major launch order only where the heads' K and V are far beyond the caches (see scan_and_plan_row)
     L->class_major = (L->BQ == 256 && p->n >= LONG_N) ? 1 : 0;
     L->NT = (p->n + L->BQ - 1) / L->BQ + L->NC;
     L->NQP = L->NT * L->BQ;

@@ -3,8 +3,8 @@
 // "Efficiency at inference"; the stable sort by group of App. D done as a
 // counting sort).
 //
-// Three launches per focus_assign call, the work item everywhere a (sort block of
-// SB positions, batch*head) pair:
+// Three launches per focus_assign call on class layouts, one or two on masked ones (end of this comment), the work item a
+// (sort block of SB positions, batch*head) pair:
 //   score        streams q (or k) once, scores every token against the K centroids of its KV
 //                head in fp64 (products are exact in fp64, added in index order,
 //                so the result is reproducible bit for bit), keeps the top-k
@@ -21,7 +21,7 @@
 //                with the largest squared key norm of the head.
 // Memberships given per token (focus_assign_tokens) take token_classes in place
 // of score.  Layouts without classes (masked) leave the scan out where the scatter launch can add up
-// the histograms itself.
+// the histograms itself, and short rows of theirs are bucketed in one launch, a work-group per row.
 #include "focus_internal.h"
 #include "focus_score.h"
 #include <hip/hip_bf16.h>

@@ -98,8 +98,11 @@ struct Layout {
     size_t off_qcc, off_kcc;           // class counts [.,NC]
     size_t off_qco, off_kco;           // padded class offsets [.,NC+1]
     size_t off_clsmask;                // group bit mask of each class [NC]
-    size_t unused;                     // keeps the offsets below where kernel-argument loads take them in whole groups: 8 bytes
-                                       // lower, the attention kernel at 262144 tokens was 0.7 % slower (408 -> 405 ms)
+    size_t unused;                     // 8 bytes without a meaning.  Without them the attention kernel at 262144 tokens took 0.4 to 0.9 %
+                                       // longer (three boxes, in turn: 400.2 / 402.2, 408.5 / 411.2, 411.2 / 414.9 ms; 32768 tokens +0.1 %,
+                                       // 131072 with a softcap +0.3 %), also with the structure padded back to its size: the offsets below
+                                       // are then loaded in other groups, and the kernel's registers fall otherwise.  Results are the same
+                                       // bits.  To be measured again when a field is added or leaves.
     size_t off_qperm;                  // [B,Hq,NQP] positions in class order, -1 in pads (the scatter kernel writes both)
     size_t off_kpos;                   // [B,Hkv,NKP] positions in class order, KPOS_PAD in pads
     size_t off_kmsk;                   // [B,Hkv,NKP] membership masks in class order, 0 in pads (coarse classes only)
