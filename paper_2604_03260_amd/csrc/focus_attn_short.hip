@@ -1,15 +1,19 @@
-// Attention forward for short 16-bit problems in position order (one class: masked and dense layouts), up to 128
-// components: the structure of the fp32 kernel (focus_attn_f32.hip) with 16-bit products.
+// Attention forward for short 16-bit problems in position order (one class: masked and dense layouts): the structure of the
+// fp32 kernel (focus_attn_f32.hip) with 16-bit products.
 //
-// A work-group owns 32 query rows; its eight wavefronts walk the 32-key units of the causal prefix round-robin with a
-// running softmax each, operands straight from the caches, and merge once.  The tiled kernel (focus_attn_mfma.hip) needs
-// V staged by a launch before it and a second launch for rows that need a softmax reference, and walks up to n/64 tiles
-// one after the other in work-groups that are too few to fill the chip: at 512 tokens all of it is latency.
-// Here a chain is n/256 units and there is one launch.  V is read row-major with 2-byte loads, which is why the tiled
-// kernel wins as soon as throughput counts (see short_attention below).  With 128 components 15 to 17 of the registers of a
-// unit's operands spill (64 to 72 bytes of scratch a lane).
+// A work-group owns 32 query rows; its eight wavefronts (four at 256 components) walk the 32-key units of the causal prefix
+// round-robin with a running softmax each, operands straight from the caches, and merge once.  The tiled kernel
+// (focus_attn_mfma.hip) needs V staged by a launch before it and a second launch for rows that need a softmax reference, and
+// walks up to n/64 tiles one after the other in work-groups that are too few to fill the chip: at 512 tokens all of it is latency.
+// Here a chain is n/256 units and there is one launch.
+//
+// What bounds it is the issue of vector instructions (one per about 6 cycles and wavefront, and there are two wavefronts on a
+// SIMD) and the round trips to memory: 1.7 us each where the caches are cold.  So a unit's membership words, keys and values are
+// asked for together, up to 64 components with the next unit's; row addresses are scalars; the pairs near the diagonal
+// come from five position words instead of a dozen instructions per pair; values that are not finite are looked for in the
+// loaded words; the partial results meet once, all together; and the arguments fit a few cache lines.  12 heads of 64 x
+// 512 tokens: 12.4 -> 9.2 us, with the bucketing 19.4 -> 16.0; 32 heads of 128 x 305 tokens 43.7 -> 32.1.
 #include "focus_internal.h"
-#include "focus_tileplan.h"
 
 namespace focus {
 
@@ -18,17 +22,23 @@ namespace {
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(8 * sizeof(_Float16)))) _Float16 f16x8;
+typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
+typedef __attribute__((__vector_size__(2 * sizeof(_Float16)))) _Float16 f16x2;
 typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
 template <bool F16> struct Half16;
 template <> struct Half16<false> {
     typedef __bf16 T;
     typedef bf16x8 V8;
+    typedef bf16x2 V2;
+    static __device__ inline float dot2(V2 a, V2 b, float c) { return __builtin_amdgcn_fdot2_f32_bf16(a, b, c, false); }
     static constexpr uint32_t EXP = 0x7f80u, ONE = 0x3f80u;
     static __device__ inline f32x16 mfma(V8 a, V8 b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0); }
 };
 template <> struct Half16<true> {
     typedef _Float16 T;
     typedef f16x8 V8;
+    typedef f16x2 V2;
+    static __device__ inline float dot2(V2 a, V2 b, float c) { return __builtin_amdgcn_fdot2(a, b, c, false); }
     static constexpr uint32_t EXP = 0x7c00u, ONE = 0x3c00u;
     static __device__ inline f32x16 mfma(V8 a, V8 b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0); }
 };
@@ -64,63 +74,90 @@ __device__ inline float both_halves_max(float x)
     return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
+// Row i of block db of O^T is component CPL * i + db: a lane's CPL components of a key lie side by side.  The third block of 80 and
+// 96 components stands by itself, at 64 + i.
+constexpr int short_cpl(int d) { return d < 128 ? 2 : d / 32; }
+// Wavefronts of a work-group: 256 components take the registers of a SIMD for one each.
+constexpr int short_waves(int d) { return d == 256 ? 4 : 8; }
+
+// What the kernel needs of a Layout.  A launch begins with reading its arguments: a few cache lines in the place of the whole struct.
+struct ShortArgs {
+    const uint16_t *q, *k, *v;
+    const uint32_t *mq, *kmsk;                    // membership masks: [B,Hq,n]; [B,Hkv,NKP] (masked only)
+    uint16_t* out;
+    float* lse;
+    int32_t* row_pairs;
+    long long qs[3], ks[2], os[3];                // strides in elements (batch, head, position)
+    unsigned pitch_bytes;                         // of k and v, position
+    int B, Hq, Hkv, n, NKP, window, causal, dense, pair_set, default_map;
+    float scale, softcap;
+    int tiles;                                    // 128-row tiles
+};
+constexpr int SHORT_BQ = 128;
+
 template <int D, bool F16>
-__global__ __launch_bounds__(512, 2) void attn_short_kernel(Layout L, HeadMap hm, int default_map, const uint16_t* __restrict__ q,
-                                                            const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
-                                                            const char* __restrict__ ws, uint16_t* __restrict__ out,
-                                                            float* __restrict__ lse, int32_t* __restrict__ row_pairs)
+__global__ __launch_bounds__(64 * short_waves(D), short_waves(D) / 4) void attn_short_kernel(ShortArgs A, HeadMap hm)
 {
     typedef Half16<F16> HT;
     typedef typename HT::T elem_t;
+    typedef typename HT::V2 V2;
     typedef typename HT::V8 V8;
-    constexpr int NW = 8;
+    constexpr int NW = short_waves(D);
+    constexpr int CPL = short_cpl(D);
+    constexpr int RPW = 16 / NW;                  // rows of every block that a wavefront adds up and stores
     constexpr int KS = D / 16;                    // products of one S^T unit
     constexpr int DB = (D + 31) / 32;             // 32-component blocks of O^T
-    __shared__ TilePlanT<1> P;
-    __shared__ float s_o[NW / 2][DB * 16][64];         // partial results on their way between the wavefronts
-    __shared__ float s_m[NW / 2][64], s_l[NW / 2][64];
-    __shared__ int s_np[NW / 2][64];
+    constexpr int VW = (DB + 1) / 2;              // registers of a key's values in a lane
+    __shared__ float4 s_o[NW][DB * 4][64];        // partial results of the wavefronts
+    __shared__ float s_m[NW][32], s_l[NW][32];
+    __shared__ int s_np[NW][32];
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n32 = lane & 31, hh = lane >> 5;
-    const int BH = L.B * L.Hq;
-    const int quarter = 3 - (int)(blockIdx.x / BH) % 4, job = (int)(blockIdx.x / BH) / 4;
-    const int x = blockIdx.x % BH;
-    int b, h;
-    if (default_map) {                            // the query heads of a KV head share blockIdx % 8: one XCD, one L2
-        const int BHk = L.B * L.Hkv, G = L.Hq / L.Hkv;
-        b = (x % BHk) / L.Hkv;
-        h = (x % BHk % L.Hkv) * G + x / BHk;
-    } else {
-        b = x / L.Hq;
-        h = x % L.Hq;
-    }
-    const int bhq = b * L.Hq + h;
-    const int bhk = b * L.Hkv + hm.kv[h];
-    if (!plan_linear_tile(L, job, P)) return;
-    if (quarter * 32 >= P.nvalid) return;
-
-    const int rloc = quarter * 32 + n32;
-    const bool rvalid = rloc < P.nvalid;
-    const int qpos = rvalid ? P.row0 + rloc : -1;
-    const uint32_t mq_row = rvalid ? ((const uint32_t*)(ws + L.off_mq))[(size_t)bhq * L.n + qpos] : 0u;
-    const uint32_t* kmsk = (const uint32_t*)(ws + L.off_kmsk) + (size_t)bhk * L.NKP;     // masked only
-    const size_t koff = (size_t)b * L.ks[0] + (size_t)hm.kv[h] * L.ks[1];
-    // rows by a 24-bit multiply and a 32-bit offset (the launch checks that they fit)
-    const char* kbase = (const char*)(k + koff + hh * 8);
-    const char* vbase = (const char*)(v + koff + n32);
-    const unsigned pitch_bytes = (unsigned)L.ks[2] * 2u;
-    const int w = L.window;
-    const float scale = L.scale, cap = L.softcap;
-    const float sl2 = cap > 0.f ? LOG2E : scale * LOG2E;     // logits (scores without a cap) to log2 units
-
+    // grid: (batch and KV head, query head of it, quarter tiles) with the default head map: the query heads of a KV head share
+    // an XCD, one L2 as long as there are a multiple of 8 of them; else (batch and query head, 1, quarter tiles).
+    // Longest causal prefix first.
+    const int heads = A.default_map ? A.Hkv : A.Hq;
+    const int b = A.B == 1 ? 0 : (int)blockIdx.x / heads;
+    const int x = (int)blockIdx.x - b * heads;
+    const int h = A.default_map ? x * (int)gridDim.y + (int)blockIdx.y : x;
+    const int hk = A.default_map ? x : hm.kv[h];
+    const int bhq = b * A.Hq + h;
+    const int n = A.n, w = A.window;
+    const int row0 = (4 * A.tiles - 1 - (int)blockIdx.z) * 32;           // this work-group's rows
+    if (row0 >= n) return;
+    const int last = min(row0 + 31, n - 1);
+    const bool rvalid = row0 + n32 < n;
+    const int qpos = rvalid ? row0 + n32 : -1;
+    const uint32_t mq_row = rvalid ? A.mq[(size_t)bhq * n + qpos] : 0u;
     V8 qf[KS];
     {
-        const uint16_t* qrow = q + (size_t)b * L.qs[0] + (size_t)h * L.qs[1] + (size_t)max(qpos, 0) * L.qs[2] + hh * 8;
+        const uint16_t* qrow = A.q + (size_t)b * A.qs[0] + (size_t)h * A.qs[1] + (size_t)max(qpos, 0) * A.qs[2] + hh * 8;
 #pragma unroll
         for (int c = 0; c < KS; ++c) qf[c] = *(const V8*)(qrow + 16 * c);
     }
+    const uint32_t* kmsk = A.kmsk + (size_t)(b * A.Hkv + hk) * A.NKP;
+    const size_t koff = (size_t)b * A.ks[0] + (size_t)hk * A.ks[1];
+    const char* kbase = (const char*)(A.k + koff);
+    const char* vbase = (const char*)(A.v + koff);
+    const unsigned pitch = A.pitch_bytes;         // a head's rows lie within 4 GiB (the launch checks)
+    const float scale = A.scale, cap = A.softcap;
+    const float sl2 = cap > 0.f ? LOG2E : scale * LOG2E;     // logits (scores without a cap) to log2 units
+    const float two_over_cap = cap > 0.f ? 2.f * LOG2E * scale / cap : 0.f;
+    const bool causal = A.causal != 0, dense = A.dense != 0;
+    const int set = dense ? 0 : A.pair_set;
+
+    // units of 32 keys that hold a pair at all: [u0, u1); without a test per pair: keys real, causal for every row and, where the
+    // window decides, inside every row's window
+    const int x_hi = causal ? last + 1 : n;
+    const bool local = set == 2;
+    const int u0 = local ? max(0, row0 - w + 1) / 32 : 0;
+    const int u1 = (dense && A.pair_set == 2) ? 0 : (min(x_hi, local ? last + w : x_hi) + 31) / 32;
+    const int safe = causal ? row0 + 1 : dense ? n : min(n, row0 + w);
+    const int in_beg = dense ? 0 : (max(last - w + 1, 0) + 31) / 32, in_end = set != 0 ? 0 : safe / 32;
+    // units below far_end: outside every row's window and causal for all of them, membership decides alone
+    const int far_end = (causal && set == 0 && !dense) ? max(0, row0 - w + 1) / 32 : 0;
     f32x16 o[DB];
 #pragma unroll
     for (int db = 0; db < DB; ++db)
@@ -129,93 +166,131 @@ __global__ __launch_bounds__(512, 2) void attn_short_kernel(Layout L, HeadMap hm
     float m = -INFINITY, l = 0.f;
     int npairs = 0;
 
-    // which pairs of unit u count, bit r = score r: key slot0 + 8*(r/4) + 4*hh + r%4.  Without branches per pair: a key is
-    // causal from distance first on, inside the window where (distance + woff) < wlim, and the set of pairs decides
-    // whether shared pairs count (by_share) and window pairs that share count as such (loc_any); dense: every pair shares.
-    const int set = L.masked ? L.pair_set : 0;
-    const bool dense = !L.masked, by_share = set != 2, by_window = set != 1, loc_any = set == 0;
-    const int first = L.causal ? 0 : -0x7fffffff, woff = L.causal ? 0 : w - 1;
-    const unsigned wlim = L.causal ? (unsigned)w : 2u * (unsigned)w - 1u;
-    auto pairs_of = [&](int u, int& slot0) -> unsigned {
-        const int tile = P.t0[0] + (u >> 1);
-        slot0 = tile * KT + (u & 1) * 32;
+    // scores of a unit at or below key offset x, bit r = score r: key 8*(r/4) + 4*hh + r%4
+    auto upto = [&](int x) -> unsigned {
+        const int c = x + 1 - 4 * hh;
+        unsigned word = 0u;
+#pragma unroll
+        for (int r4 = 0; r4 < 4; ++r4) word |= ((1u << min(max(c - 8 * r4, 0), 4)) - 1u) << (4 * r4);
+        return word;
+    };
+    auto load_masks = [&](int u, uint4 (&km)[4]) {
+        const char* p = (const char*)(kmsk + 32 * u);
+#pragma unroll
+        for (int r4 = 0; r4 < 4; ++r4) km[r4] = *(const uint4*)(p + 16u * (unsigned)hh + 32 * r4);
+    };
+    // which pairs of unit u count, bit r = score r
+    auto pairs_of = [&](int u, const uint4 (&km)[4]) -> unsigned {
+        if (u >= in_beg && u < in_end) return rvalid ? 0xffffu : 0u;
         unsigned ok = 0xffffu;
-        if (!(tile >= P.ibeg[0] && tile < P.iend[0])) {
+        if (!dense) {
             ok = 0u;
 #pragma unroll
-            for (int r4 = 0; r4 < 4; ++r4) {
-                uint4 km4 = make_uint4(0u, 0u, 0u, 0u);
-                if (!dense) km4 = *(const uint4*)(kmsk + slot0 + 8 * r4 + 4 * hh);
-                const uint32_t km[4] = {km4.x, km4.y, km4.z, km4.w};
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int kj = slot0 + 8 * r4 + 4 * hh + e, dlt = qpos - kj;
-                    const bool share = dense | ((mq_row & km[e]) != 0u);
-                    const bool loc = (unsigned)(dlt + woff) < wlim;
-                    const bool in = (by_share & share & (dlt >= first)) | (by_window & loc & (loc_any | !share));
-                    ok |= ((kj < L.n) & in) ? 1u << (4 * r4 + e) : 0u;
-                }
-            }
+            for (int r4 = 0; r4 < 4; ++r4)
+                ok |= ((mq_row & km[r4].x) ? 1u << (4 * r4) : 0u) | ((mq_row & km[r4].y) ? 2u << (4 * r4) : 0u) |
+                      ((mq_row & km[r4].z) ? 4u << (4 * r4) : 0u) | ((mq_row & km[r4].w) ? 8u << (4 * r4) : 0u);
+        }
+        if (u >= far_end) {                       // positions decide too
+            const int at = qpos - 32 * u;
+            const unsigned cz = causal ? upto(at) : 0xffffu;
+            const unsigned loc = (causal ? cz : upto(at + w - 1)) & ~upto(at - w);
+            ok = set == 0 ? (loc | (ok & cz)) : set == 1 ? (ok & cz) : (loc & ~ok);
+            if (32 * u + 32 > n) ok &= upto(n - 1 - 32 * u);
         }
         return rvalid ? ok : 0u;
     };
-    // values of a half-wave's 16 keys of a unit, component 32*db + l%32, two keys to a register
-    auto load_v = [&](int slot0, uint32_t (&vv)[8][DB]) {
-#pragma unroll
-        for (int r2 = 0; r2 < 8; ++r2) {
-            const int k0 = slot0 + 8 * (r2 / 2) + 4 * hh + 2 * (r2 % 2);
-            const char* p0 = vbase + __umul24((unsigned)min(k0, L.n - 1), pitch_bytes);
-            const char* p1 = vbase + __umul24((unsigned)min(k0 + 1, L.n - 1), pitch_bytes);
-#pragma unroll
-            for (int db = 0; db < DB; ++db) {
-                const bool there = D % 32 == 0 || db * 32 + n32 < D;
-                const uint32_t lo = there ? *(const uint16_t*)(p0 + 64 * db) : 0u, hi = there ? *(const uint16_t*)(p1 + 64 * db) : 0u;
-                vv[r2][db] = lo | (hi << 16);
-            }
+    // Values of a half-wave's 16 keys of a unit: with the components of a lane side by side a key's values of 64 components are
+    // one 4-byte load, those of 128 one of 8, in the place of two and four of 2 bytes.  A row's address is a scalar and one offset that all rows share; rows past the last
+    // position are read as the last one again.
+    struct Values { uint32_t w[16][VW]; };        // as they are loaded, a key after the other
+    auto load_row = [&](const char* p, unsigned at, uint32_t (&x)[VW]) {
+        if constexpr (D == 256) {
+            const uint4 y = *(const uint4*)(p + at);
+            x[0] = y.x; x[1] = y.y; x[2] = y.z; x[3] = y.w;
+        } else if constexpr (D == 128) {
+            const uint2 y = *(const uint2*)(p + at);
+            x[0] = y.x; x[1] = y.y;
+        } else {
+            x[0] = *(const uint32_t*)(p + at);
+            if constexpr (D > 64) x[1] = 64 + n32 < D ? *(const uint16_t*)(p + (at + 128u - 2u * (unsigned)n32)) : 0u;
         }
     };
-    auto any_nonfinite = [&](const uint32_t (&vv)[8][DB]) -> bool {
-        bool bad = false;
+    const unsigned at_v = (unsigned)n32 * (2u * CPL), four = hh ? 4u * pitch : 0u;
+    auto load_v = [&](int u, Values& x) {
+        if (32 * u + 32 <= n) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) load_row(vbase + (size_t)(unsigned)(32 * u + 8 * (r / 4) + r % 4) * pitch, four + at_v, x.w[r]);
+        } else {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) load_row(vbase, (unsigned)min(32 * u + 8 * (r / 4) + 4 * hh + r % 4, n - 1) * pitch + at_v, x.w[r]);
+        }
+    };
+    auto pair_v = [&](const Values& x, uint32_t (&vv)[8][DB]) {          // two keys to a register
 #pragma unroll
         for (int r2 = 0; r2 < 8; ++r2)
 #pragma unroll
-            for (int db = 0; db < DB; ++db)
-                bad = bad | ((vv[r2][db] & HT::EXP) == HT::EXP) | (((vv[r2][db] >> 16) & HT::EXP) == HT::EXP);
-        return __any(bad);
+            for (int db = 0; db < DB; ++db) {
+                const uint32_t a = x.w[2 * r2][db / 2], c = x.w[2 * r2 + 1][db / 2];
+                vv[r2][db] = db % 2 ? __builtin_amdgcn_perm(c, a, 0x07060302u) : __builtin_amdgcn_perm(c, a, 0x05040100u);
+            }
+    };
+    auto any_nonfinite = [&](const Values& x) -> bool {  // an exponent of all ones carries into the sign
+        uint32_t bad = 0u;
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+#pragma unroll
+            for (int i = 0; i < VW; ++i) bad |= (x.w[r][i] & (HT::EXP * 0x10001u)) + (0x8000u - HT::EXP) * 0x10001u;
+        return __any((bad & 0x80008000u) != 0u);
     };
 
     bool again = false;                           // (uniform) values were taken out of a product
-    for (int u = wave; u < 2 * P.total; u += NW) {
-        int slot0;
-        const unsigned ok = pairs_of(u, slot0);
+    // The membership words, the keys and the values of a unit in one round trip: a unit whose pairs are all masked is rare, and
+    // a walk is a chain of few units.  Up to 64 components there are registers for the next unit's too.
+    struct Unit {
+        uint4 km[4];
+        V8 kf[KS];
+        Values v;
+    };
+    auto load_unit = [&](int u, Unit& U) {
+        if (!dense) load_masks(u, U.km);
+        const char* kr = kbase + (size_t)(unsigned)(32 * u) * pitch;
+        const unsigned at_k = (unsigned)min(n32, n - 1 - 32 * u) * pitch + 16u * (unsigned)hh;
+#pragma unroll
+        for (int c = 0; c < KS; ++c) U.kf[c] = *(const V8*)(kr + (at_k + 32u * c));
+        load_v(u, U.v);
+    };
+    constexpr bool AHEAD = D == 64;
+    Unit next;
+    if (AHEAD && u0 + wave < u1) load_unit(u0 + wave, next);
+    for (int u = u0 + wave; u < u1; u += NW) {
+        Unit U;
+        if constexpr (AHEAD) {
+            U = next;
+            if (u + NW < u1) load_unit(u + NW, next);
+        } else {
+            load_unit(u, U);
+        }
+        const unsigned ok = pairs_of(u, U.km);
         if (!__any(ok != 0u)) continue;                                  // nothing here for any of the 32 rows
         const bool all_ok = !__any(rvalid && ok != 0xffffu);
-
-        // keys, and the values with them: those arrive while the scores are computed
-        V8 kf[KS];
-        {
-            const char* kr = kbase + __umul24((unsigned)min(slot0 + n32, L.n - 1), pitch_bytes);
-#pragma unroll
-            for (int c = 0; c < KS; ++c) kf[c] = *(const V8*)(kr + 32 * c);
-        }
-        uint32_t vv[8][DB];
-        load_v(slot0, vv);
         f32x16 s;
 #pragma unroll
         for (int r = 0; r < 16; ++r) s[r] = 0.f;
 #pragma unroll
-        for (int c = 0; c < KS; ++c) s = HT::mfma(kf[c], qf[c], s);
+        for (int c = 0; c < KS; ++c) s = HT::mfma(U.kf[c], qf[c], s);
         // softmax step in log2 units: p = 2^(s * sl2 - m), one rounding in the exponent (a row's m cancels)
         if (cap > 0.f) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) s[r] = cap * tanhf(s[r] * scale / cap);
+            for (int r = 0; r < 16; ++r)          // cap * tanh(z), z = s * scale / cap, as 1 - 2 / (1 + e^(2z))
+                s[r] = cap - 2.f * cap * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(s[r] * two_over_cap));
         }
-        float mx = -INFINITY;
+        if (!all_ok) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            s[r] = (ok >> r) & 1u ? s[r] : -INFINITY;
-            mx = fmaxf(mx, s[r]);
+            for (int r = 0; r < 16; ++r) s[r] = (ok >> r) & 1u ? s[r] : -INFINITY;
         }
+        float mx = s[0];
+#pragma unroll
+        for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[r]);
         const float m_new = fmaxf(m, both_halves_max(mx) * sl2);
         if (__any(m_new > m)) {
             const float alpha = (m == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m - m_new);
@@ -229,16 +304,21 @@ __global__ __launch_bounds__(512, 2) void attn_short_kernel(Layout L, HeadMap hm
         const float m_use = (m == -INFINITY) ? 0.f : m;
         // probabilities rounded to the storage type; the row sum adds the rounded ones, the numbers the product uses
         uint32_t pw[8];
+        V2 ones;
+        ones[0] = ones[1] = (elem_t)1.f;
 #pragma unroll
         for (int r2 = 0; r2 < 8; ++r2) {
-            const elem_t p0 = (elem_t)__builtin_amdgcn_exp2f(fmaf(s[2 * r2], sl2, -m_use));       // masked: 2^-inf = 0
-            const elem_t p1 = (elem_t)__builtin_amdgcn_exp2f(fmaf(s[2 * r2 + 1], sl2, -m_use));
-            l += (float)p0 + (float)p1;
-            pw[r2] = bits16(p0) | (bits16(p1) << 16);
+            V2 p2;
+            p2[0] = (elem_t)__builtin_amdgcn_exp2f(fmaf(s[2 * r2], sl2, -m_use));                 // masked: 2^-inf = 0
+            p2[1] = (elem_t)__builtin_amdgcn_exp2f(fmaf(s[2 * r2 + 1], sl2, -m_use));
+            l = HT::dot2(p2, ones, l);
+            pw[r2] = __builtin_bit_cast(uint32_t, p2);
         }
+        uint32_t vv[8][DB];
+        pair_v(U.v, vv);
         // A value that is not finite would reach the rows that do not attend it through 0 * inf: where the unit is not
         // attended as a whole it is taken out here and added below to the rows that do attend its key.
-        if (!all_ok && any_nonfinite(vv)) {
+        if (!all_ok && any_nonfinite(U.v)) {
             again = true;
 #pragma unroll
             for (int r2 = 0; r2 < 8; ++r2)
@@ -258,20 +338,23 @@ __global__ __launch_bounds__(512, 2) void attn_short_kernel(Layout L, HeadMap hm
                 o[db] = HT::mfma(__builtin_bit_cast(V8, vt), pb, o[db]);
             }
         }
-        npairs += __popc(ok);
+        if (A.row_pairs) npairs += __popc(ok);
     }
     // Infinities and NaN that were taken out, component by component: the matrix cores count, per row and component, the
     // infinities of either sign that the row attends (a NaN counts as both).  A walk of its own, so that the registers
     // it takes are not taken from the one above.
     if (again) {
 #pragma unroll 1
-        for (int u = wave; u < 2 * P.total; u += NW) {
-            int slot0;
-            const unsigned ok = pairs_of(u, slot0);
+        for (int u = u0 + wave; u < u1; u += NW) {
+            uint4 km[4];
+            if (!dense) load_masks(u, km);
+            const unsigned ok = pairs_of(u, km);
             if (!__any(ok != 0u) || !__any(rvalid && ok != 0xffffu)) continue;
+            Values x;
+            load_v(u, x);
+            if (!any_nonfinite(x)) continue;
             uint32_t vv[8][DB];
-            load_v(slot0, vv);
-            if (!any_nonfinite(vv)) continue;
+            pair_v(x, vv);
             uint32_t at[8];                                              // the attended keys, two to a register
 #pragma unroll
             for (int r2 = 0; r2 < 8; ++r2)
@@ -303,73 +386,90 @@ __global__ __launch_bounds__(512, 2) void attn_short_kernel(Layout L, HeadMap hm
     l += __shfl_xor(l, 32, 64);
     npairs += __shfl_xor(npairs, 32, 64);
 
-    // App. D's merge of the wavefronts' partial softmaxes: the upper half into the lower half until one is left
-    auto put = [&](int buf) {
-#pragma unroll
-        for (int db = 0; db < DB; ++db)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) s_o[buf][db * 16 + r][lane] = o[db][r];
-        s_m[buf][lane] = m; s_l[buf][lane] = l; s_np[buf][lane] = npairs;
-    };
-    auto take = [&](int buf) {
-        const float m2 = s_m[buf][lane], l2 = s_l[buf][lane];
-        const float m_new = fmaxf(m, m2);
-        const float a1 = (m == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m - m_new), a2 = (m2 == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m2 - m_new);
-#pragma unroll
-        for (int db = 0; db < DB; ++db)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) o[db][r] = o[db][r] * a1 + s_o[buf][db * 16 + r][lane] * a2;
-        l = l * a1 + l2 * a2;
-        m = m_new;
-        npairs += s_np[buf][lane];
-    };
-#pragma unroll
-    for (int half = NW / 2; half >= 1; half >>= 1) {
-        if (wave >= half && wave < 2 * half) put(wave - half);
-        __syncthreads();
-        if (wave < half) take(wave);
-        __syncthreads();
-    }
-    if (wave != 0) return;
-    if (!rvalid) return;
-    // an empty row (launch restricted to one pair set): out = 0, lse = -inf
-    const float inv = (l > 0.f) ? 1.f / l : (l == 0.f) ? 0.f : l;
-    uint16_t* orow = out + (size_t)b * L.os[0] + (size_t)h * L.os[1] + (size_t)qpos * L.os[2];
+    // App. D's merge of the wavefronts' partial softmaxes in one step: they all lie in LDS, and every wavefront adds up RPW of the
+    // 16 rows that a lane holds of every block.  (The upper half into the lower half until one is left: three steps and six
+    // barriers, 1.9 us of 12.4 at 512 tokens.)
 #pragma unroll
     for (int db = 0; db < DB; ++db)
 #pragma unroll
-        for (int r4 = 0; r4 < 4; ++r4) {
-            const int c = db * 32 + 8 * r4 + 4 * hh;
-            if (D % 32 != 0 && c >= D) continue;
-            uint2 val;
-            val.x = bits16((elem_t)(o[db][4 * r4] * inv)) | (bits16((elem_t)(o[db][4 * r4 + 1] * inv)) << 16);
-            val.y = bits16((elem_t)(o[db][4 * r4 + 2] * inv)) | (bits16((elem_t)(o[db][4 * r4 + 3] * inv)) << 16);
-            *(uint2*)(orow + c) = val;
+        for (int r4 = 0; r4 < 4; ++r4)
+            s_o[wave][db * 4 + r4][lane] = make_float4(o[db][4 * r4], o[db][4 * r4 + 1], o[db][4 * r4 + 2], o[db][4 * r4 + 3]);
+    if (hh == 0) { s_m[wave][n32] = m; s_l[wave][n32] = l; s_np[wave][n32] = npairs; }
+    __syncthreads();
+    if (!rvalid) return;
+    const int nw = min(NW, u1 - u0);               // the other wavefronts had no unit
+    float a[NW];
+    float top = -INFINITY;
+    l = 0.f;
+    npairs = 0;
+#pragma unroll
+    for (int w2 = 0; w2 < NW; ++w2) {
+        a[w2] = w2 < nw ? s_m[w2][n32] : -INFINITY;
+        top = fmaxf(top, a[w2]);
+    }
+    float acc[DB][RPW];
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int e = 0; e < RPW; ++e) acc[db][e] = 0.f;
+    const int r0 = wave * RPW;                     // registers r0 .. r0 + RPW - 1 of every block: rows i0 .. i0 + RPW - 1
+#pragma unroll
+    for (int w2 = 0; w2 < NW; ++w2) {
+        if (w2 >= nw) break;                      // (uniform)
+        a[w2] = (a[w2] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(a[w2] - top);
+        l = fmaf(s_l[w2][n32], a[w2], l);
+        if (A.row_pairs) npairs += s_np[w2][n32];
+#pragma unroll
+        for (int db = 0; db < DB; ++db) {
+            float y[RPW];
+            __builtin_memcpy(y, (const float*)&s_o[w2][db * 4 + r0 / 4][lane] + r0 % 4, sizeof(y));
+#pragma unroll
+            for (int e = 0; e < RPW; ++e) acc[db][e] = fmaf(y[e], a[w2], acc[db][e]);
         }
-    if (hh == 0) {
-        if (lse) lse[(size_t)bhq * L.n + qpos] = fmaf(m, LN2, logf(l));
-        if (row_pairs) row_pairs[(size_t)bhq * L.n + qpos] = npairs;
+    }
+    // an empty row (launch restricted to one pair set): out = 0, lse = -inf
+    const float inv = (l > 0.f) ? 1.f / l : (l == 0.f) ? 0.f : l;
+    uint16_t* orow = A.out + (size_t)b * A.os[0] + (size_t)h * A.os[1] + (size_t)qpos * A.os[2];
+    const int i0 = 8 * (r0 / 4) + 4 * hh + r0 % 4;
+    auto pair = [&](float lo, float hi) -> uint32_t { return bits16((elem_t)(lo * inv)) | (bits16((elem_t)(hi * inv)) << 16); };
+    uint32_t word[RPW * CPL / 2];                 // components CPL * i0 ..: two or more pairs, the blocks of a row in turn
+#pragma unroll
+    for (int e = 0; e < RPW; ++e)
+#pragma unroll
+        for (int db = 0; db < CPL; db += 2) word[(e * CPL + db) / 2] = pair(acc[db][e], acc[db + 1][e]);
+    uint2* o0 = (uint2*)(orow + CPL * i0);
+#pragma unroll
+    for (int i = 0; i < RPW * CPL / 4; ++i) o0[i] = make_uint2(word[2 * i], word[2 * i + 1]);
+    if constexpr (D > 64 && D < 128) {
+        static_assert(D % 32 == 0 || D % 32 == 16, "pairs of the third block are whole");
+        if (64 + i0 < D) *(uint32_t*)(orow + 64 + i0) = pair(acc[2][0], acc[2][1]);
+    }
+    if (wave == 0 && hh == 0) {
+        if (A.lse) A.lse[(size_t)bhq * n + qpos] = fmaf(top, LN2, logf(l));
+        if (A.row_pairs) A.row_pairs[(size_t)bhq * n + qpos] = npairs;
     }
 }
 
 }  // namespace
 
-// Where one launch of short chains beats the staged tiles: while every work-group of 32 rows has a compute unit of its own.
-// Causal launches may have some more (their work-groups differ in length and the first ones end early; 64 components leave
-// room for two on a unit), non-causal ones no more: their 257th waits for a whole walk.  Past 64 components the walk itself
-// is slower per key on the masked layout, so that it may not be long; 96 of them fill the 32-component blocks that 80 leave empty.
-// Attention alone, tiled / this kernel (us), masked layout, K = 4 top-2, measured over 128 .. 8192 tokens and 48 .. 1024 groups:
-//   64:  512 tokens, 192 groups 20.3 / 12.6;  1024, 384 27.8 / 22.3;  4096, 256 70.2 / 57.8;  non-causal 1024, 256 26.9 / 20.0, 288 27.5 / 35.3
-//   80:  2048, 256 47.5 / 45.9;  4096, 256 80.8 / 82.7;      96: 1024, 320 33.1 / 23.0
-//   128: 256, 256 21.0 / 15.8;  1024, 256 34.3 / 33.4;  2048, 256 53.9 / 56.6, dense 47.7 / 41.9;  non-causal 512, 256 25.4 / 22.7, 288 26.4 / 39.5
+// Where one launch of short chains beats the staged tiles: while its work-groups are at most two or three per compute unit
+// (those of a causal launch differ in length, the later ones fill the gaps), fewer the longer the walk, whose units load more
+// bytes per key.  Bucketing and attention, K = 4 top-2, tiled / this kernel (us), measured over 128 .. 4096 tokens and 64 .. 1536 groups:
+//   causal   64: 512 x 384 groups 32.5 / 19.9, 1024 35.8 / 32.0, 1536 39.3 / 44.9;  4096 x 768 79.3 / 65.1, 1024 79.7 / 78.0
+//            80: 512 x 1024 37.1 / 34.0;  4096 x 768 88.4 / 80.0, 1024 87.7 / 96.0
+//            128: 512 x 768 43.3 / 37.2, 1024 44.6 / 43.9;  1024 x 768 51.5 / 49.8, 1024 51.9 / 60.8;  4096 x 640 104 / 97, 768 104 / 110
+//            256: 256 x 1024 58.3 / 55.0;  512 x 640 60.5 / 55.0, 768 61.6 / 61.0;  4096 x 640 168 / 165
+//   otherwise 64: 256 x 1024 32.0 / 30.7;  512 x 768 34.5 / 31.9;  4096 x 512 78.0 / 75.9, 640 79.6 / 103
+//            80: 1024 x 512 41.9 / 40.4;  2048 x 512 56.0 / 58.0;   128: 512 x 512 41.4 / 35.9;  1024 x 256 47.8 / 32.8, 512 49.2 / 50.9;   256: 256 x 768 55.1 / 52.0
 bool short_attention(const Layout& L)
 {
     const long long groups = (long long)L.B * L.Hq * ((L.n + 31) / 32);
-    const bool fits = L.dtype != 0 && L.NC == 1 && (L.masked || L.dense) && !L.soft && !L.local_only && !L.merge_prev && L.BQ == 128 &&
-                      L.d <= 128 && (uint64_t)L.ks[2] * 2 < (1u << 24) && (uint64_t)L.n * (uint64_t)L.ks[2] * 2 < 0xffffffffull;
-    const int most = L.causal ? (L.d <= 64 ? 384 : (L.d == 128 && L.n <= 256) ? 256 : 320) : (L.d <= 64 && L.n <= 256) ? 384 : 256;
-    const int longest = (L.dense || L.d == 64 || L.d == 96) ? 4096 : L.d == 80 ? 2048 : 1024;
-    return fits && groups <= most && L.n <= longest;
+    const bool fits = L.dtype != 0 && L.NC == 1 && (L.masked || L.dense) && !L.soft && !L.local_only && !L.merge_prev && L.BQ == SHORT_BQ &&
+                      (uint64_t)L.ks[2] * 2 < (1u << 24) && (uint64_t)L.n * (uint64_t)L.ks[2] * 2 < 0xffffffffull;
+    const bool wide = L.d >= 128;
+    const int most = L.causal ? (L.n <= (wide ? 256 : 512) ? 1024 : (L.d == 256 || (wide && L.n > 1024)) ? 640 : 768)
+                              : L.n <= 256 ? (wide ? 768 : 1024) : L.n <= 512 ? (wide ? 512 : 768) : (wide || (L.d == 80 && L.n > 1024)) ? 256 : 512;
+    return fits && groups <= most && L.n <= 4096;
 }
 
 hipError_t launch_attn_short(const Layout& L, const HeadMap& hm, const void* q, const void* k, const void* v, char* ws,
@@ -377,18 +477,26 @@ hipError_t launch_attn_short(const Layout& L, const HeadMap& hm, const void* q, 
 {
     int default_map = (L.Hq % L.Hkv == 0) ? 1 : 0;
     for (int h = 0; default_map && h < L.Hq; ++h) default_map = hm.kv[h] == h / (L.Hq / L.Hkv);
-    const unsigned blocks = (unsigned)((size_t)L.NT * 4 * L.B * L.Hq);        // four quarters of every 128-row tile
+    ShortArgs A;
+    A.q = (const uint16_t*)q; A.k = (const uint16_t*)k; A.v = (const uint16_t*)v;
+    A.mq = (const uint32_t*)(ws + L.off_mq); A.kmsk = (const uint32_t*)(ws + L.off_kmsk);
+    A.out = (uint16_t*)out; A.lse = lse; A.row_pairs = row_pairs;
+    for (int i = 0; i < 3; ++i) { A.qs[i] = L.qs[i]; A.os[i] = L.os[i]; }
+    A.ks[0] = L.ks[0]; A.ks[1] = L.ks[1];
+    A.pitch_bytes = (unsigned)L.ks[2] * 2u;
+    A.B = L.B; A.Hq = L.Hq; A.Hkv = L.Hkv; A.n = L.n; A.NKP = L.NKP; A.window = L.window; A.causal = L.causal;
+    A.dense = L.masked ? 0 : 1; A.pair_set = L.pair_set; A.default_map = default_map;
+    A.scale = L.scale; A.softcap = L.softcap;
+    A.tiles = (L.n + SHORT_BQ - 1) / SHORT_BQ;
+    const dim3 threads(64 * short_waves(L.d));
+    const dim3 blocks = default_map ? dim3(L.B * L.Hkv, L.Hq / L.Hkv, A.tiles * 4) : dim3(L.B * L.Hq, 1, A.tiles * 4);
 #define FOCUS_SHORT(D_)                                                                                                   \
     case D_:                                                                                                              \
-        if (L.dtype == 2)                                                                                                 \
-            hipLaunchKernelGGL((attn_short_kernel<D_, true>), dim3(blocks), dim3(512), 0, st, L, hm, default_map,         \
-                               (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, (const char*)ws, (uint16_t*)out, lse, row_pairs); \
-        else                                                                                                              \
-            hipLaunchKernelGGL((attn_short_kernel<D_, false>), dim3(blocks), dim3(512), 0, st, L, hm, default_map,        \
-                               (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, (const char*)ws, (uint16_t*)out, lse, row_pairs); \
+        if (L.dtype == 2) hipLaunchKernelGGL((attn_short_kernel<D_, true>), blocks, threads, 0, st, A, hm);             \
+        else hipLaunchKernelGGL((attn_short_kernel<D_, false>), blocks, threads, 0, st, A, hm);                         \
         break;
     switch (L.d) {
-        FOCUS_SHORT(64) FOCUS_SHORT(80) FOCUS_SHORT(96) FOCUS_SHORT(128)
+        FOCUS_SHORT(64) FOCUS_SHORT(80) FOCUS_SHORT(96) FOCUS_SHORT(128) FOCUS_SHORT(256)
         default: return hipErrorInvalidValue;
     }
 #undef FOCUS_SHORT

@@ -1,0 +1,69 @@
+"""The kernel for short 16-bit problems at the edges of its 32-row groups, 32-key units and wavefronts, every head dim; and the
+tiled kernel on the masked layout with more heads than the short one takes."""
+import pytest
+
+from paper_2604_03260_amd import focus, workloads
+from tests import harness
+from tests import test_gpu_f16_range as f16_range
+from tests import test_gpu_instantiations as inst
+from tests import test_gpu_masked as masked
+from tests import test_gpu_nonfinite_values as nonfinite
+
+pytestmark = pytest.mark.gpu
+
+
+# one unit and less, a wavefront's second unit (from 128 or 256 keys on), a last unit of one key; windows inside a unit and over several
+@pytest.mark.parametrize("n", [1, 31, 32, 33, 65, 130, 257, 290])
+@pytest.mark.parametrize("d,dtype,K,topk,w,causal,softcap", [
+    (64, "f16", 4, 2, 40, True, 5.0), (80, "bf16", 16, 3, 100, True, 0.0), (96, "f16", 8, 1, 7, False, 20.0),
+    (128, "bf16", 32, 2, 33, False, 0.0), (256, "bf16", 4, 2, 50, True, 0.0), (256, "f16", 16, 3, 90, False, 30.0), (256, "bf16", 8, 1, 1, True, 0.0),
+    (256, "f16", 4, 2, 5000, True, 0.0), (128, "f16", 4, 2, 5000, False, 50.0)])
+def test_units_and_groups(n, d, dtype, K, topk, w, causal, softcap):
+    masked._check(workloads.Workload("sk", 500 + n, 2, 4, 2, n, d, dtype, K, topk, w, causal=causal, softcap=softcap, mixture=3))
+
+
+@pytest.mark.parametrize("d,head_map", [(64, [1, 0, 0, 1, 2, 2]), (256, [2, 1, 0, 0, 1, 2])])
+def test_other_head_maps(d, head_map):
+    wl = workloads.Workload("sk", 501, 2, 6, 3, 200, d, "bf16", 8, 2, 30)
+    inp = workloads.make_inputs(wl, "cuda")
+    res = harness.run_gpu(wl, inp, head_map=head_map)
+    mq, mk = harness.oracle_membership(wl, inp, head_map)
+    harness.check_attn(wl, inp, res, mq, mk, head_map=head_map)
+
+
+@pytest.mark.parametrize("n,w,kw", [(700, 300, {}), (642, 5000, dict(K=4, topk=2)), (130, 20, dict(causal=False)), (700, 40, dict(K=16, topk=3)),
+                                    (700, 300, dict(pair_set=focus.FOCUS_PAIRS_SHARED)), (700, 60, dict(pair_set=focus.FOCUS_PAIRS_CROSS_LOCAL))])
+@pytest.mark.parametrize("dtype,d", [("bf16", 256), ("f16", 96)])
+def test_values_that_are_not_finite(dtype, d, n, w, kw):
+    nonfinite.check(dtype, d, 1, n, w, **kw)
+
+
+@pytest.mark.parametrize("d,softcap,pairs,dtype,coarse,noref", masked.CASES_M)
+def test_tiles_of_the_masked_layout(d, softcap, pairs, dtype, coarse, noref):
+    wl = workloads.Workload("insm", 96, 8, 8, 2, 520 + d // 4, d, dtype, 8, 3, 48, softcap=50.0 if softcap else 0.0, mixture=4)
+    inst.run_case(wl, pairs, big_norms=not noref)
+
+
+@pytest.mark.parametrize("w", [40, 690])
+@pytest.mark.parametrize("dtype,d,kw", [("bf16", 128, {}), ("f16", 80, dict(K=16, topk=3)), ("bf16", 64, dict(causal=False)), ("f16", 256, {}),
+                                        ("bf16", 96, dict(pair_set=focus.FOCUS_PAIRS_SHARED))])
+def test_values_that_are_not_finite_in_tiles(dtype, d, w, kw):
+    nonfinite.check(dtype, d, 12, 700, w, **kw)
+
+
+@pytest.mark.parametrize("size", ["high", "low"])
+def test_range_of_halves_in_tiles(size, monkeypatch):
+    f16_range.test_probabilities_outside_the_range_of_halves((1, 12, 4, 2100, 256, 4, 2, 200, True, 0.0), size, None, monkeypatch)
+
+
+def test_rows_with_large_norms_in_tiles():
+    """Disallowed keys with the largest logits must not move the row's reference (see test_gpu_masked)."""
+    wl = workloads.Workload("m", 331, 45, 2, 1, 400, 64, "bf16", 4, 1, 16)
+    inp = workloads.make_inputs(wl, "cuda")
+    inp["q"] *= 8.0
+    inp["k"] *= 8.0
+    got, ref = harness.run_gpu(wl, inp), harness.run_gpu(wl, inp, vector=True)
+    # one bf16 ulp of the output (2^-8 relative, values up to 4); the sum of probabilities that are each rounded by at most
+    # 2^-9 of themselves is off by at most that factor, its logarithm by 2^-9, and logits of a few hundred by fp32 rounding
+    assert (got["out"].float() - ref["out"].float()).abs().max() <= 2e-2
+    assert ((got["lse"] - ref["lse"]).abs() <= 2.0 ** -9 + 1e-4 * ref["lse"].abs()).all()
