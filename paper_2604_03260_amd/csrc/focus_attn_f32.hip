@@ -14,7 +14,7 @@
 // Measured (d = 64, K = 4 top-2, attention launch) against the vector kernel: 12 heads x 1024 tokens 671 -> 41 us;
 // 40 heads x 4096 tokens 967 us, 89 of the 152 TFLOP/s a library product of 8192 x 8192 matrices reaches: the rest is
 // vector work (masks, 16 exponentials and 24 row addresses per unit) that two wavefronts per SIMD cover in part.
-#include "focus_internal.h"
+#include "focus_short.h"
 #include "focus_tileplan.h"
 
 namespace focus {
@@ -32,9 +32,9 @@ __device__ inline float both_halves_max(float x)
     return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
-// LINEAR: one class in position order.  WIDE: some row of k or v lies 4 GiB or more past its head's first, or rows are 16 MiB or more apart: 64-bit products
+// WIDE: some row of k or v lies 4 GiB or more past its head's first, or rows are 16 MiB or more apart: 64-bit products
 // for every row address, a fifth of the vector work of a unit.  Otherwise one 24-bit multiply and a 32-bit offset.
-template <int D, int NW, bool WIDE, bool LINEAR>
+template <int D, int NW, bool WIDE>
 __global__ __launch_bounds__(64 * NW, D <= 128 ? 2 : 1) void attn_f32_kernel(Layout L, HeadMap hm, int default_map,
                                                                         const float* __restrict__ q, const float* __restrict__ k,
                                                                         const float* __restrict__ v, const char* __restrict__ ws,
@@ -113,28 +113,25 @@ __global__ __launch_bounds__(64 * NW, D <= 128 ? 2 : 1) void attn_f32_kernel(Lay
         int slot0, krow;
         bool inter, interior;
         uint4 km[4];                              // membership masks of the 16 keys (coarse classes and masked)
-        int4 kp[LINEAR ? 1 : 4];                  // their positions; LINEAR: slot = position
+        int4 kp[4];                               // their positions
     };
     auto fetch = [&](Unit& U, int u) {
         const int it = u >> 1;
         while (it >= P.cum[cur + 1]) ++cur;
         const int tile = __builtin_amdgcn_readfirstlane(P.t0[cur] + (it - P.cum[cur]));
-        U.inter = LINEAR || P.inter[cur] != 0;
+        U.inter = P.inter[cur] != 0;
         U.interior = tile >= P.ibeg[cur] && tile < P.iend[cur];
         U.slot0 = tile * KT + (u & 1) * 32;
-        U.krow = LINEAR ? U.slot0 + n32 : kpos[U.slot0 + n32];
+        U.krow = kpos[U.slot0 + n32];
         if (L.coarse && U.inter) {
 #pragma unroll
             for (int r4 = 0; r4 < 4; ++r4) U.km[r4] = *(const uint4*)(kmsk + U.slot0 + 8 * r4 + 4 * hh);
         }
-        if constexpr (!LINEAR) {
 #pragma unroll
-            for (int r4 = 0; r4 < 4; ++r4) U.kp[r4] = *(const int4*)(kpos + U.slot0 + 8 * r4 + 4 * hh);
-        }
+        for (int r4 = 0; r4 < 4; ++r4) U.kp[r4] = *(const int4*)(kpos + U.slot0 + 8 * r4 + 4 * hh);
     };
     auto key_pos = [&](const Unit& U, int r) -> int {
-        if constexpr (LINEAR) return U.slot0 + 8 * (r / 4) + 4 * hh + r % 4;
-        const int4 p4 = U.kp[LINEAR ? 0 : r / 4];
+        const int4 p4 = U.kp[r / 4];
         return r % 4 == 0 ? p4.x : r % 4 == 1 ? p4.y : r % 4 == 2 ? p4.z : p4.w;
     };
     auto pairs_of = [&](const Unit& U) -> unsigned {              // which pairs of the unit count, bit r = score r
@@ -335,6 +332,221 @@ __global__ __launch_bounds__(64 * NW, D <= 128 ? 2 : 1) void attn_f32_kernel(Lay
     }
 }
 
+// Rows in position order (one class), a head's rows within 4 GiB: the same walk with the work around the products cut down, as in
+// focus_attn_short.hip: scalar row addresses, pairs near the diagonal from position words, a key's values in one load or two
+// (DB 4-byte loads before), keys and membership words of the next unit asked for when the scores have used this one's, its values
+// after the last product, one merge.  12 heads of 64 x 1024 tokens, with the bucketing: 44.8 -> 41.4 us; 8 x 15/5 of 80 x 627
+// 170 -> 135; 32 of 128 x 2028 451 -> 428; 4 x 40/8 of 64 x 2048 1065 -> 985.
+template <int D, int NW>
+__global__ __launch_bounds__(64 * NW, D <= 128 ? 2 : 1) void attn_f32_linear_kernel(ShortArgs A, HeadMap hm)
+{
+    constexpr int H = D / 2;                      // components per half-wave = products of one S^T unit
+    constexpr int DB = (D + 31) / 32;             // 32-component blocks of O^T
+    constexpr int CPL = short_cpl(D);
+    constexpr int RPW = 16 / NW;
+    constexpr int VG = D <= 96 ? 16 : 4;          // keys whose V rows are in flight (the registers hold no more of longer rows)
+    constexpr bool K_AHEAD = D == 64, V_AHEAD = D <= 96;     // ... nor the next unit's rows of all of them
+    __shared__ typename ShortMerge<NW, DB>::Space s_merge;
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n32 = lane & 31, hh = lane >> 5;
+    const ShortWalk W(A, hm, lane);
+    const int n = W.n;
+    const bool rvalid = W.rvalid;
+    float4 qf[H / 4];
+    {
+        const float* qrow = (const float*)A.q + (size_t)W.b * A.qs[0] + (size_t)W.h * A.qs[1] + (size_t)max(W.qpos, 0) * A.qs[2] + hh * H;
+#pragma unroll
+        for (int c = 0; c < H / 4; ++c) qf[c] = *(const float4*)(qrow + 4 * c);
+    }
+    const size_t koff = (size_t)W.b * A.ks[0] + (size_t)W.hk * A.ks[1];
+    const char* kbase = (const char*)((const float*)A.k + koff);
+    const char* vbase = (const char*)((const float*)A.v + koff);
+    const unsigned pitch = A.pitch_bytes;
+    const float scale = A.scale, cap = A.softcap;
+    const float sl2 = cap > 0.f ? LOG2E : scale * LOG2E;     // logits (scores without a cap) to log2 units
+    f32x16 o[DB];
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[db][r] = 0.f;
+    float m = -INFINITY, l = 0.f;
+    int npairs = 0;
+
+    struct Keys { uint4 km[4]; float4 kf[H / 4]; };
+    auto load_keys = [&](int u, Keys& K) {
+        if constexpr (D < 256) W.load_masks(u, K.km);
+        const char* kr = kbase + (size_t)(unsigned)(32 * u) * pitch;
+        const unsigned at = (unsigned)min(n32, n - 1 - 32 * u) * pitch + (unsigned)(hh * H) * 4u;
+#pragma unroll
+        for (int c = 0; c < H / 4; ++c) K.kf[c] = *(const float4*)(kr + (at + 16u * c));
+    };
+    // a half-wave's keys r0 .. r0 + VG - 1 of a unit, the lane's components of every block
+    auto load_row = [&](const char* p, unsigned at, float (&x)[DB]) {
+        __builtin_memcpy(&x[0], __builtin_assume_aligned(p + at, CPL * 4 < 16 ? CPL * 4 : 16), CPL * 4);
+        if constexpr (D > 64 && D < 128) x[2] = 64 + n32 < D ? *(const float*)(p + (at + 256u - 4u * (unsigned)n32)) : 0.f;
+    };
+    const unsigned at_v = (unsigned)n32 * (4u * CPL), four = hh ? 4u * pitch : 0u;
+    auto load_v = [&](int u, int r0, float (&vv)[VG][DB]) {
+        if (32 * u + 32 <= n) {
+#pragma unroll
+            for (int r = 0; r < VG; ++r) load_row(vbase + (size_t)(unsigned)(32 * u + 8 * ((r0 + r) / 4) + r % 4) * pitch, four + at_v, vv[r]);
+        } else {
+#pragma unroll
+            for (int r = 0; r < VG; ++r) load_row(vbase, (unsigned)min(32 * u + 8 * ((r0 + r) / 4) + 4 * hh + r % 4, n - 1) * pitch + at_v, vv[r]);
+        }
+    };
+    auto any_nonfinite = [&](const float (&vv)[VG][DB]) -> bool {
+        uint32_t top = 0u;
+#pragma unroll
+        for (int r = 0; r < VG; ++r)
+#pragma unroll
+            for (int db = 0; db < DB; ++db) top = max(top, __float_as_uint(vv[r][db]) & 0x7fffffffu);
+        return __any(top >= 0x7f800000u);
+    };
+    bool again = false;                           // (uniform) values were taken out of a product
+    Keys K;
+    float vv[VG][DB];
+    if (W.u0 + wave < W.u1) {
+        if constexpr (K_AHEAD) load_keys(W.u0 + wave, K);
+        if constexpr (V_AHEAD) load_v(W.u0 + wave, 0, vv);
+    }
+    for (int u = W.u0 + wave; u < W.u1; u += NW) {
+        const bool more = u + NW < W.u1;
+        if constexpr (D == 256) W.load_masks(u, K.km);                   // (its registers hold the words or the rows)
+        else if constexpr (!K_AHEAD) load_keys(u, K);
+        const unsigned ok = W.pairs(u, K.km);
+        if constexpr (D == 256) {
+            if (!__any(ok != 0u)) continue;
+            load_keys(u, K);
+        }
+        const bool some = __any(ok != 0u);                               // else nothing here for any of the 32 rows
+        const bool all_ok = !__any(rvalid && ok != 0xffffu);
+        f32x16 s;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) s[r] = 0.f;
+        if (some) {
+#pragma unroll
+            for (int c = 0; c < H / 4; ++c) {
+                s = __builtin_amdgcn_mfma_f32_32x32x2f32(K.kf[c].x, qf[c].x, s, 0, 0, 0);
+                s = __builtin_amdgcn_mfma_f32_32x32x2f32(K.kf[c].y, qf[c].y, s, 0, 0, 0);
+                s = __builtin_amdgcn_mfma_f32_32x32x2f32(K.kf[c].z, qf[c].z, s, 0, 0, 0);
+                s = __builtin_amdgcn_mfma_f32_32x32x2f32(K.kf[c].w, qf[c].w, s, 0, 0, 0);
+            }
+        }
+        if (K_AHEAD && more) load_keys(u + NW, K);
+        if (some) {
+            // softmax step in log2 units: p = 2^(s * sl2 - m), one rounding in the exponent (a row's m cancels)
+            if (cap > 0.f) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) s[r] = cap * tanhf(s[r] * scale / cap);
+            }
+            if (!all_ok) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) s[r] = (ok >> r) & 1u ? s[r] : -INFINITY;
+            }
+            float mx = s[0];
+#pragma unroll
+            for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[r]);
+            const float m_new = fmaxf(m, both_halves_max(mx) * sl2);
+            if (__any(m_new > m)) {
+                const float alpha = (m == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m - m_new);
+                m = m_new;
+                l *= alpha;
+#pragma unroll
+                for (int db = 0; db < DB; ++db)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
+            }
+            const float m_use = (m == -INFINITY) ? 0.f : m;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                s[r] = __builtin_amdgcn_exp2f(fmaf(s[r], sl2, -m_use));      // masked: 2^-inf = 0
+                l += s[r];
+            }
+#pragma unroll
+            for (int r0 = 0; r0 < 16; r0 += VG) {
+                if constexpr (VG < 16) load_v(u, r0, vv);
+                // A value that is not finite would reach the rows that do not attend it through 0 * inf: where the unit is
+                // not attended as a whole it is taken out here and added below to the rows that do attend its key.
+                if (!all_ok && any_nonfinite(vv)) {
+                    again = true;
+#pragma unroll
+                    for (int r = 0; r < VG; ++r)
+#pragma unroll
+                        for (int db = 0; db < DB; ++db) vv[r][db] = __builtin_isfinite(vv[r][db]) ? vv[r][db] : 0.f;
+                }
+#pragma unroll
+                for (int r = 0; r < VG; ++r)
+#pragma unroll
+                    for (int db = 0; db < DB; ++db)
+                        o[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(vv[r][db], s[r0 + r], o[db], 0, 0, 0);
+            }
+            if (A.row_pairs) npairs += __popc(ok);
+        }
+        if constexpr (V_AHEAD) if (more) load_v(u + NW, 0, vv);
+    }
+    // Infinities and NaN that were taken out (see the kernel above)
+    if (again) {
+#pragma unroll 1
+        for (int u = W.u0 + wave; u < W.u1; u += NW) {
+            uint4 km[4];
+            W.load_masks(u, km);
+            const unsigned ok = W.pairs(u, km);
+            if (!__any(ok != 0u) || !__any(rvalid && ok != 0xffffu)) continue;
+#pragma unroll
+            for (int r0 = 0; r0 < 16; r0 += VG) {
+                load_v(u, r0, vv);
+                if (!any_nonfinite(vv)) continue;
+#pragma unroll 1
+                for (int neg = 0; neg < 2; ++neg) {
+                    const unsigned flip = neg ? 0x80000000u : 0u;
+#pragma unroll
+                    for (int db = 0; db < DB; ++db) {
+                        f32x16 cnt;
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) cnt[r] = 0.f;
+#pragma unroll
+                        for (int r = 0; r < VG; ++r)
+                            cnt = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(__float_as_uint(vv[r][db]) ^ flip) < INFINITY ? 0.f : 1.f,
+                                                                       (ok >> (r0 + r)) & 1u ? 1.f : 0.f, cnt, 0, 0, 0);
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) o[db][r] = cnt[r] > 0.f ? o[db][r] + (neg ? -INFINITY : INFINITY) : o[db][r];
+                    }
+                }
+            }
+        }
+    }
+    l += __shfl_xor(l, 32, 64);
+    npairs += __shfl_xor(npairs, 32, 64);
+    const ShortMerge<NW, DB> M(s_merge, o, m, l, npairs, wave, lane, min(NW, W.u1 - W.u0), A.row_pairs != nullptr);
+    if (!rvalid) return;
+    // an empty row (launch restricted to one pair set): out = 0, lse = -inf
+    const float inv = (M.l > 0.f) ? 1.f / M.l : (M.l == 0.f) ? 0.f : M.l;
+    float* orow = (float*)A.out + (size_t)W.b * A.os[0] + (size_t)W.h * A.os[1] + (size_t)W.qpos * A.os[2];
+    const int i0 = M.first_row(wave, hh);
+    float x[RPW * CPL];                           // components CPL * i0 ..: the blocks of a row in turn
+#pragma unroll
+    for (int e = 0; e < RPW; ++e)
+#pragma unroll
+        for (int db = 0; db < CPL; ++db) x[e * CPL + db] = M.acc[db][e] * inv;
+    float4* o0 = (float4*)(orow + CPL * i0);
+#pragma unroll
+    for (int i = 0; i < RPW * CPL / 4; ++i) o0[i] = make_float4(x[4 * i], x[4 * i + 1], x[4 * i + 2], x[4 * i + 3]);
+    if constexpr (D > 64 && D < 128) {
+        if (64 + i0 < D) {
+#pragma unroll
+            for (int e = 0; e < RPW; e += 2) *(float2*)(orow + 64 + i0 + e) = make_float2(M.acc[2][e] * inv, M.acc[2][e + 1] * inv);
+        }
+    }
+    if (wave == 0 && hh == 0) {
+        const size_t row = (size_t)(W.b * A.Hq + W.h) * n + W.qpos;
+        if (A.lse) A.lse[row] = fmaf(M.top, LN2, logf(M.l));
+        if (A.row_pairs) A.row_pairs[row] = M.npairs;
+    }
+}
+
 }  // namespace
 
 hipError_t launch_attn_f32(const Layout& L, const HeadMap& hm, const void* q, const void* k, const void* v, char* ws,
@@ -350,9 +562,16 @@ hipError_t launch_attn_f32(const Layout& L, const HeadMap& hm, const void* q, co
     // meet in one merge less (12 heads x 2048 tokens: 110 -> 96 us).  128 components are faster with eight at every
     // size (8 heads x 4096: 470 -> 400 us), 256 fill the registers of one wavefront per SIMD.
     const bool eight = L.d == 128 || (L.d < 128 && blocks <= 512);
-#define FOCUS_F32N(D_, N_, W_, L_) hipLaunchKernelGGL((attn_f32_kernel<D_, N_, W_, L_>), dim3((unsigned)blocks), dim3(64 * N_), 0, st, L, hm, default_map, \
+    const ShortArgs A = short_args(L, hm, q, k, v, ws, out, lse, row_pairs);
+    const bool linear = L.NC == 1 && !wide && !L.local_only && A.groups <= 65535;
+#define FOCUS_F32N(D_, N_, W_) hipLaunchKernelGGL((attn_f32_kernel<D_, N_, W_>), dim3((unsigned)blocks), dim3(64 * N_), 0, st, L, hm, default_map, \
                                                   (const float*)q, (const float*)k, (const float*)v, (const char*)ws, (float*)out, lse, row_pairs)
-#define FOCUS_F32W(D_, N_) { if (wide) FOCUS_F32N(D_, N_, true, false); else if (L.NC == 1) FOCUS_F32N(D_, N_, false, true); else FOCUS_F32N(D_, N_, false, false); }
+#define FOCUS_F32W(D_, N_)                                                                                                \
+    {                                                                                                                     \
+        if (linear) hipLaunchKernelGGL((attn_f32_linear_kernel<D_, N_>), short_grid(A), dim3(64 * N_), 0, st, A, hm);    \
+        else if (wide) FOCUS_F32N(D_, N_, true);                                                                          \
+        else FOCUS_F32N(D_, N_, false);                                                                                   \
+    }
 #define FOCUS_F32(D_) case D_: if (eight) FOCUS_F32W(D_, 8) else FOCUS_F32W(D_, 4) break;
     switch (L.d) {
         FOCUS_F32(64) FOCUS_F32(80) FOCUS_F32(96)

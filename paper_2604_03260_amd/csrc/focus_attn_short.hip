@@ -12,8 +12,8 @@
 // asked for together, up to 64 components with the next unit's; row addresses are scalars; the pairs near the diagonal
 // come from five position words instead of a dozen instructions per pair; values that are not finite are looked for in the
 // loaded words; the partial results meet once, all together; and the arguments fit a few cache lines.  12 heads of 64 x
-// 512 tokens: 12.4 -> 9.2 us, with the bucketing 19.4 -> 16.0; 32 heads of 128 x 305 tokens 43.7 -> 32.1.
-#include "focus_internal.h"
+// 512 tokens: 12.4 -> 9.2 us, with the bucketing 19.4 -> 16.0; 32 heads of 128 x 305 tokens 43.7 -> 34.2.
+#include "focus_short.h"
 
 namespace focus {
 
@@ -74,26 +74,9 @@ __device__ inline float both_halves_max(float x)
     return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
-// Row i of block db of O^T is component CPL * i + db: a lane's CPL components of a key lie side by side.  The third block of 80 and
-// 96 components stands by itself, at 64 + i.
-constexpr int short_cpl(int d) { return d < 128 ? 2 : d / 32; }
 // Wavefronts of a work-group: 256 components take the registers of a SIMD for one each.
 constexpr int short_waves(int d) { return d == 256 ? 4 : 8; }
 
-// What the kernel needs of a Layout.  A launch begins with reading its arguments: a few cache lines in the place of the whole struct.
-struct ShortArgs {
-    const uint16_t *q, *k, *v;
-    const uint32_t *mq, *kmsk;                    // membership masks: [B,Hq,n]; [B,Hkv,NKP] (masked only)
-    uint16_t* out;
-    float* lse;
-    int32_t* row_pairs;
-    long long qs[3], ks[2], os[3];                // strides in elements (batch, head, position)
-    unsigned pitch_bytes;                         // of k and v, position
-    int B, Hq, Hkv, n, NKP, window, causal, dense, pair_set, default_map;
-    float scale, softcap;
-    int tiles;                                    // 128-row tiles
-};
-constexpr int SHORT_BQ = 128;
 
 template <int D, bool F16>
 __global__ __launch_bounds__(64 * short_waves(D), short_waves(D) / 4) void attn_short_kernel(ShortArgs A, HeadMap hm)
@@ -108,56 +91,27 @@ __global__ __launch_bounds__(64 * short_waves(D), short_waves(D) / 4) void attn_
     constexpr int KS = D / 16;                    // products of one S^T unit
     constexpr int DB = (D + 31) / 32;             // 32-component blocks of O^T
     constexpr int VW = (DB + 1) / 2;              // registers of a key's values in a lane
-    __shared__ float4 s_o[NW][DB * 4][64];        // partial results of the wavefronts
-    __shared__ float s_m[NW][32], s_l[NW][32];
-    __shared__ int s_np[NW][32];
+    __shared__ typename ShortMerge<NW, DB>::Space s_merge;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n32 = lane & 31, hh = lane >> 5;
-    // grid: (batch and KV head, query head of it, quarter tiles) with the default head map: the query heads of a KV head share
-    // an XCD, one L2 as long as there are a multiple of 8 of them; else (batch and query head, 1, quarter tiles).
-    // Longest causal prefix first.
-    const int heads = A.default_map ? A.Hkv : A.Hq;
-    const int b = A.B == 1 ? 0 : (int)blockIdx.x / heads;
-    const int x = (int)blockIdx.x - b * heads;
-    const int h = A.default_map ? x * (int)gridDim.y + (int)blockIdx.y : x;
-    const int hk = A.default_map ? x : hm.kv[h];
-    const int bhq = b * A.Hq + h;
-    const int n = A.n, w = A.window;
-    const int row0 = (4 * A.tiles - 1 - (int)blockIdx.z) * 32;           // this work-group's rows
-    if (row0 >= n) return;
-    const int last = min(row0 + 31, n - 1);
-    const bool rvalid = row0 + n32 < n;
-    const int qpos = rvalid ? row0 + n32 : -1;
-    const uint32_t mq_row = rvalid ? A.mq[(size_t)bhq * n + qpos] : 0u;
+    const ShortWalk W(A, hm, lane);
+    const int n = W.n;
+    const bool rvalid = W.rvalid;
     V8 qf[KS];
     {
-        const uint16_t* qrow = A.q + (size_t)b * A.qs[0] + (size_t)h * A.qs[1] + (size_t)max(qpos, 0) * A.qs[2] + hh * 8;
+        const uint16_t* qrow = (const uint16_t*)A.q + (size_t)W.b * A.qs[0] + (size_t)W.h * A.qs[1] + (size_t)max(W.qpos, 0) * A.qs[2] + hh * 8;
 #pragma unroll
         for (int c = 0; c < KS; ++c) qf[c] = *(const V8*)(qrow + 16 * c);
     }
-    const uint32_t* kmsk = A.kmsk + (size_t)(b * A.Hkv + hk) * A.NKP;
-    const size_t koff = (size_t)b * A.ks[0] + (size_t)hk * A.ks[1];
-    const char* kbase = (const char*)(A.k + koff);
-    const char* vbase = (const char*)(A.v + koff);
-    const unsigned pitch = A.pitch_bytes;         // a head's rows lie within 4 GiB (the launch checks)
+    const size_t koff = (size_t)W.b * A.ks[0] + (size_t)W.hk * A.ks[1];
+    const char* kbase = (const char*)((const uint16_t*)A.k + koff);
+    const char* vbase = (const char*)((const uint16_t*)A.v + koff);
+    const unsigned pitch = A.pitch_bytes;
     const float scale = A.scale, cap = A.softcap;
     const float sl2 = cap > 0.f ? LOG2E : scale * LOG2E;     // logits (scores without a cap) to log2 units
     const float two_over_cap = cap > 0.f ? 2.f * LOG2E * scale / cap : 0.f;
-    const bool causal = A.causal != 0, dense = A.dense != 0;
-    const int set = dense ? 0 : A.pair_set;
-
-    // units of 32 keys that hold a pair at all: [u0, u1); without a test per pair: keys real, causal for every row and, where the
-    // window decides, inside every row's window
-    const int x_hi = causal ? last + 1 : n;
-    const bool local = set == 2;
-    const int u0 = local ? max(0, row0 - w + 1) / 32 : 0;
-    const int u1 = (dense && A.pair_set == 2) ? 0 : (min(x_hi, local ? last + w : x_hi) + 31) / 32;
-    const int safe = causal ? row0 + 1 : dense ? n : min(n, row0 + w);
-    const int in_beg = dense ? 0 : (max(last - w + 1, 0) + 31) / 32, in_end = set != 0 ? 0 : safe / 32;
-    // units below far_end: outside every row's window and causal for all of them, membership decides alone
-    const int far_end = (causal && set == 0 && !dense) ? max(0, row0 - w + 1) / 32 : 0;
     f32x16 o[DB];
 #pragma unroll
     for (int db = 0; db < DB; ++db)
@@ -166,42 +120,9 @@ __global__ __launch_bounds__(64 * short_waves(D), short_waves(D) / 4) void attn_
     float m = -INFINITY, l = 0.f;
     int npairs = 0;
 
-    // scores of a unit at or below key offset x, bit r = score r: key 8*(r/4) + 4*hh + r%4
-    auto upto = [&](int x) -> unsigned {
-        const int c = x + 1 - 4 * hh;
-        unsigned word = 0u;
-#pragma unroll
-        for (int r4 = 0; r4 < 4; ++r4) word |= ((1u << min(max(c - 8 * r4, 0), 4)) - 1u) << (4 * r4);
-        return word;
-    };
-    auto load_masks = [&](int u, uint4 (&km)[4]) {
-        const char* p = (const char*)(kmsk + 32 * u);
-#pragma unroll
-        for (int r4 = 0; r4 < 4; ++r4) km[r4] = *(const uint4*)(p + 16u * (unsigned)hh + 32 * r4);
-    };
-    // which pairs of unit u count, bit r = score r
-    auto pairs_of = [&](int u, const uint4 (&km)[4]) -> unsigned {
-        if (u >= in_beg && u < in_end) return rvalid ? 0xffffu : 0u;
-        unsigned ok = 0xffffu;
-        if (!dense) {
-            ok = 0u;
-#pragma unroll
-            for (int r4 = 0; r4 < 4; ++r4)
-                ok |= ((mq_row & km[r4].x) ? 1u << (4 * r4) : 0u) | ((mq_row & km[r4].y) ? 2u << (4 * r4) : 0u) |
-                      ((mq_row & km[r4].z) ? 4u << (4 * r4) : 0u) | ((mq_row & km[r4].w) ? 8u << (4 * r4) : 0u);
-        }
-        if (u >= far_end) {                       // positions decide too
-            const int at = qpos - 32 * u;
-            const unsigned cz = causal ? upto(at) : 0xffffu;
-            const unsigned loc = (causal ? cz : upto(at + w - 1)) & ~upto(at - w);
-            ok = set == 0 ? (loc | (ok & cz)) : set == 1 ? (ok & cz) : (loc & ~ok);
-            if (32 * u + 32 > n) ok &= upto(n - 1 - 32 * u);
-        }
-        return rvalid ? ok : 0u;
-    };
     // Values of a half-wave's 16 keys of a unit: with the components of a lane side by side a key's values of 64 components are
-    // one 4-byte load, those of 128 one of 8, in the place of two and four of 2 bytes.  A row's address is a scalar and one offset that all rows share; rows past the last
-    // position are read as the last one again.
+    // one 4-byte load, those of 128 one of 8, in the place of two and four of 2 bytes.  A row's address is a scalar and one
+    // offset that all rows share; rows past the last position are read as the last one again.
     struct Values { uint32_t w[16][VW]; };        // as they are loaded, a key after the other
     auto load_row = [&](const char* p, unsigned at, uint32_t (&x)[VW]) {
         if constexpr (D == 256) {
@@ -245,14 +166,15 @@ __global__ __launch_bounds__(64 * short_waves(D), short_waves(D) / 4) void attn_
 
     bool again = false;                           // (uniform) values were taken out of a product
     // The membership words, the keys and the values of a unit in one round trip: a unit whose pairs are all masked is rare, and
-    // a walk is a chain of few units.  Up to 64 components there are registers for the next unit's too.
+    // a walk is a chain of few units.  Up to 64 components there are registers for the next unit's too; asked for as this one's
+    // are used up, without a second set of registers, those of 128 components made a pass longer (34.8 against 34.2 us, 32 heads x 305).
     struct Unit {
         uint4 km[4];
         V8 kf[KS];
         Values v;
     };
     auto load_unit = [&](int u, Unit& U) {
-        if (!dense) load_masks(u, U.km);
+        W.load_masks(u, U.km);
         const char* kr = kbase + (size_t)(unsigned)(32 * u) * pitch;
         const unsigned at_k = (unsigned)min(n32, n - 1 - 32 * u) * pitch + 16u * (unsigned)hh;
 #pragma unroll
@@ -261,16 +183,16 @@ __global__ __launch_bounds__(64 * short_waves(D), short_waves(D) / 4) void attn_
     };
     constexpr bool AHEAD = D == 64;
     Unit next;
-    if (AHEAD && u0 + wave < u1) load_unit(u0 + wave, next);
-    for (int u = u0 + wave; u < u1; u += NW) {
+    if (AHEAD && W.u0 + wave < W.u1) load_unit(W.u0 + wave, next);
+    for (int u = W.u0 + wave; u < W.u1; u += NW) {
         Unit U;
         if constexpr (AHEAD) {
             U = next;
-            if (u + NW < u1) load_unit(u + NW, next);
+            if (u + NW < W.u1) load_unit(u + NW, next);
         } else {
             load_unit(u, U);
         }
-        const unsigned ok = pairs_of(u, U.km);
+        const unsigned ok = W.pairs(u, U.km);
         if (!__any(ok != 0u)) continue;                                  // nothing here for any of the 32 rows
         const bool all_ok = !__any(rvalid && ok != 0xffffu);
         f32x16 s;
@@ -345,10 +267,10 @@ __global__ __launch_bounds__(64 * short_waves(D), short_waves(D) / 4) void attn_
     // it takes are not taken from the one above.
     if (again) {
 #pragma unroll 1
-        for (int u = u0 + wave; u < u1; u += NW) {
+        for (int u = W.u0 + wave; u < W.u1; u += NW) {
             uint4 km[4];
-            if (!dense) load_masks(u, km);
-            const unsigned ok = pairs_of(u, km);
+            W.load_masks(u, km);
+            const unsigned ok = W.pairs(u, km);
             if (!__any(ok != 0u) || !__any(rvalid && ok != 0xffffu)) continue;
             Values x;
             load_v(u, x);
@@ -386,67 +308,30 @@ __global__ __launch_bounds__(64 * short_waves(D), short_waves(D) / 4) void attn_
     l += __shfl_xor(l, 32, 64);
     npairs += __shfl_xor(npairs, 32, 64);
 
-    // App. D's merge of the wavefronts' partial softmaxes in one step: they all lie in LDS, and every wavefront adds up RPW of the
-    // 16 rows that a lane holds of every block.  (The upper half into the lower half until one is left: three steps and six
-    // barriers, 1.9 us of 12.4 at 512 tokens.)
-#pragma unroll
-    for (int db = 0; db < DB; ++db)
-#pragma unroll
-        for (int r4 = 0; r4 < 4; ++r4)
-            s_o[wave][db * 4 + r4][lane] = make_float4(o[db][4 * r4], o[db][4 * r4 + 1], o[db][4 * r4 + 2], o[db][4 * r4 + 3]);
-    if (hh == 0) { s_m[wave][n32] = m; s_l[wave][n32] = l; s_np[wave][n32] = npairs; }
-    __syncthreads();
+    const ShortMerge<NW, DB> M(s_merge, o, m, l, npairs, wave, lane, min(NW, W.u1 - W.u0), A.row_pairs != nullptr);
     if (!rvalid) return;
-    const int nw = min(NW, u1 - u0);               // the other wavefronts had no unit
-    float a[NW];
-    float top = -INFINITY;
-    l = 0.f;
-    npairs = 0;
-#pragma unroll
-    for (int w2 = 0; w2 < NW; ++w2) {
-        a[w2] = w2 < nw ? s_m[w2][n32] : -INFINITY;
-        top = fmaxf(top, a[w2]);
-    }
-    float acc[DB][RPW];
-#pragma unroll
-    for (int db = 0; db < DB; ++db)
-#pragma unroll
-        for (int e = 0; e < RPW; ++e) acc[db][e] = 0.f;
-    const int r0 = wave * RPW;                     // registers r0 .. r0 + RPW - 1 of every block: rows i0 .. i0 + RPW - 1
-#pragma unroll
-    for (int w2 = 0; w2 < NW; ++w2) {
-        if (w2 >= nw) break;                      // (uniform)
-        a[w2] = (a[w2] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(a[w2] - top);
-        l = fmaf(s_l[w2][n32], a[w2], l);
-        if (A.row_pairs) npairs += s_np[w2][n32];
-#pragma unroll
-        for (int db = 0; db < DB; ++db) {
-            float y[RPW];
-            __builtin_memcpy(y, (const float*)&s_o[w2][db * 4 + r0 / 4][lane] + r0 % 4, sizeof(y));
-#pragma unroll
-            for (int e = 0; e < RPW; ++e) acc[db][e] = fmaf(y[e], a[w2], acc[db][e]);
-        }
-    }
+    l = M.l;
     // an empty row (launch restricted to one pair set): out = 0, lse = -inf
     const float inv = (l > 0.f) ? 1.f / l : (l == 0.f) ? 0.f : l;
-    uint16_t* orow = A.out + (size_t)b * A.os[0] + (size_t)h * A.os[1] + (size_t)qpos * A.os[2];
-    const int i0 = 8 * (r0 / 4) + 4 * hh + r0 % 4;
+    uint16_t* orow = (uint16_t*)A.out + (size_t)W.b * A.os[0] + (size_t)W.h * A.os[1] + (size_t)W.qpos * A.os[2];
+    const int i0 = M.first_row(wave, hh);
     auto pair = [&](float lo, float hi) -> uint32_t { return bits16((elem_t)(lo * inv)) | (bits16((elem_t)(hi * inv)) << 16); };
     uint32_t word[RPW * CPL / 2];                 // components CPL * i0 ..: two or more pairs, the blocks of a row in turn
 #pragma unroll
     for (int e = 0; e < RPW; ++e)
 #pragma unroll
-        for (int db = 0; db < CPL; db += 2) word[(e * CPL + db) / 2] = pair(acc[db][e], acc[db + 1][e]);
+        for (int db = 0; db < CPL; db += 2) word[(e * CPL + db) / 2] = pair(M.acc[db][e], M.acc[db + 1][e]);
     uint2* o0 = (uint2*)(orow + CPL * i0);
 #pragma unroll
     for (int i = 0; i < RPW * CPL / 4; ++i) o0[i] = make_uint2(word[2 * i], word[2 * i + 1]);
     if constexpr (D > 64 && D < 128) {
         static_assert(D % 32 == 0 || D % 32 == 16, "pairs of the third block are whole");
-        if (64 + i0 < D) *(uint32_t*)(orow + 64 + i0) = pair(acc[2][0], acc[2][1]);
+        if (64 + i0 < D) *(uint32_t*)(orow + 64 + i0) = pair(M.acc[2][0], M.acc[2][1]);
     }
     if (wave == 0 && hh == 0) {
-        if (A.lse) A.lse[(size_t)bhq * n + qpos] = fmaf(top, LN2, logf(l));
-        if (A.row_pairs) A.row_pairs[(size_t)bhq * n + qpos] = npairs;
+        const size_t row = (size_t)(W.b * A.Hq + W.h) * n + W.qpos;
+        if (A.lse) A.lse[row] = fmaf(M.top, LN2, logf(l));
+        if (A.row_pairs) A.row_pairs[row] = M.npairs;
     }
 }
 
@@ -464,7 +349,7 @@ __global__ __launch_bounds__(64 * short_waves(D), short_waves(D) / 4) void attn_
 bool short_attention(const Layout& L)
 {
     const long long groups = (long long)L.B * L.Hq * ((L.n + 31) / 32);
-    const bool fits = L.dtype != 0 && L.NC == 1 && (L.masked || L.dense) && !L.soft && !L.local_only && !L.merge_prev && L.BQ == SHORT_BQ &&
+    const bool fits = L.dtype != 0 && L.NC == 1 && (L.masked || L.dense) && !L.soft && !L.local_only && !L.merge_prev && L.BQ == 128 &&
                       (uint64_t)L.ks[2] * 2 < (1u << 24) && (uint64_t)L.n * (uint64_t)L.ks[2] * 2 < 0xffffffffull;
     const bool wide = L.d >= 128;
     const int most = L.causal ? (L.n <= (wide ? 256 : 512) ? 1024 : (L.d == 256 || (wide && L.n > 1024)) ? 640 : 768)
@@ -475,21 +360,9 @@ bool short_attention(const Layout& L)
 hipError_t launch_attn_short(const Layout& L, const HeadMap& hm, const void* q, const void* k, const void* v, char* ws,
                              void* out, float* lse, int32_t* row_pairs, hipStream_t st)
 {
-    int default_map = (L.Hq % L.Hkv == 0) ? 1 : 0;
-    for (int h = 0; default_map && h < L.Hq; ++h) default_map = hm.kv[h] == h / (L.Hq / L.Hkv);
-    ShortArgs A;
-    A.q = (const uint16_t*)q; A.k = (const uint16_t*)k; A.v = (const uint16_t*)v;
-    A.mq = (const uint32_t*)(ws + L.off_mq); A.kmsk = (const uint32_t*)(ws + L.off_kmsk);
-    A.out = (uint16_t*)out; A.lse = lse; A.row_pairs = row_pairs;
-    for (int i = 0; i < 3; ++i) { A.qs[i] = L.qs[i]; A.os[i] = L.os[i]; }
-    A.ks[0] = L.ks[0]; A.ks[1] = L.ks[1];
-    A.pitch_bytes = (unsigned)L.ks[2] * 2u;
-    A.B = L.B; A.Hq = L.Hq; A.Hkv = L.Hkv; A.n = L.n; A.NKP = L.NKP; A.window = L.window; A.causal = L.causal;
-    A.dense = L.masked ? 0 : 1; A.pair_set = L.pair_set; A.default_map = default_map;
-    A.scale = L.scale; A.softcap = L.softcap;
-    A.tiles = (L.n + SHORT_BQ - 1) / SHORT_BQ;
+    const ShortArgs A = short_args(L, hm, q, k, v, ws, out, lse, row_pairs);
     const dim3 threads(64 * short_waves(L.d));
-    const dim3 blocks = default_map ? dim3(L.B * L.Hkv, L.Hq / L.Hkv, A.tiles * 4) : dim3(L.B * L.Hq, 1, A.tiles * 4);
+    const dim3 blocks = short_grid(A);
 #define FOCUS_SHORT(D_)                                                                                                   \
     case D_:                                                                                                              \
         if (L.dtype == 2) hipLaunchKernelGGL((attn_short_kernel<D_, true>), blocks, threads, 0, st, A, hm);             \

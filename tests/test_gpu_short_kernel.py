@@ -1,4 +1,4 @@
-"""The kernel for short 16-bit problems at the edges of its 32-row groups, 32-key units and wavefronts, every head dim; and the
+"""The kernel for short 16-bit problems and the fp32 kernel for rows in position order at the edges of its 32-row groups, 32-key units and wavefronts, every head dim; and the
 tiled kernel on the masked layout with more heads than the short one takes."""
 import pytest
 
@@ -17,14 +17,15 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("d,dtype,K,topk,w,causal,softcap", [
     (64, "f16", 4, 2, 40, True, 5.0), (80, "bf16", 16, 3, 100, True, 0.0), (96, "f16", 8, 1, 7, False, 20.0),
     (128, "bf16", 32, 2, 33, False, 0.0), (256, "bf16", 4, 2, 50, True, 0.0), (256, "f16", 16, 3, 90, False, 30.0), (256, "bf16", 8, 1, 1, True, 0.0),
-    (256, "f16", 4, 2, 5000, True, 0.0), (128, "f16", 4, 2, 5000, False, 50.0)])
+    (256, "f16", 4, 2, 5000, True, 0.0), (128, "f16", 4, 2, 5000, False, 50.0), (64, "f32", 4, 2, 40, False, 0.0), (80, "f32", 16, 3, 7, True, 20.0),
+    (96, "f32", 8, 2, 60, True, 0.0), (128, "f32", 4, 1, 100, True, 0.0), (256, "f32", 32, 2, 33, True, 0.0)])
 def test_units_and_groups(n, d, dtype, K, topk, w, causal, softcap):
     masked._check(workloads.Workload("sk", 500 + n, 2, 4, 2, n, d, dtype, K, topk, w, causal=causal, softcap=softcap, mixture=3))
 
 
-@pytest.mark.parametrize("d,head_map", [(64, [1, 0, 0, 1, 2, 2]), (256, [2, 1, 0, 0, 1, 2])])
-def test_other_head_maps(d, head_map):
-    wl = workloads.Workload("sk", 501, 2, 6, 3, 200, d, "bf16", 8, 2, 30)
+@pytest.mark.parametrize("d,dtype,head_map", [(64, "bf16", [1, 0, 0, 1, 2, 2]), (256, "f16", [2, 1, 0, 0, 1, 2]), (80, "f32", [2, 1, 0, 0, 1, 2])])
+def test_other_head_maps(d, dtype, head_map):
+    wl = workloads.Workload("sk", 501, 2, 6, 3, 200, d, dtype, 8, 2, 30)
     inp = workloads.make_inputs(wl, "cuda")
     res = harness.run_gpu(wl, inp, head_map=head_map)
     mq, mk = harness.oracle_membership(wl, inp, head_map)
