@@ -76,9 +76,11 @@ __device__ inline void dec_load8(const f16_bits* p, float (&x)[8])
 // top-k mask of the scores held by lanes 0..K-1 of a wavefront (ties to the smaller group index)
 __device__ inline uint32_t wave_topk_mask(double s, int lane, int K, int topk)
 {
+    const uint64_t bits = __builtin_bit_cast(uint64_t, s);
     int beaten = 0;
-    for (int o = 0; o < K; ++o) {
-        const double so = __shfl(s, o, 64);
+    for (int o = 0; o < K; ++o) {                 // (through scalar registers: an exchange in LDS per group was the longer chain)
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)bits, o), hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(bits >> 32), o);
+        const double so = __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
         beaten += (o != lane && (so > s || (so == s && o < lane))) ? 1 : 0;
     }
     uint32_t member = (uint32_t)__ballot(lane < K && beaten < topk);
@@ -224,14 +226,19 @@ __global__ __launch_bounds__(DEC_LIST_THREADS) void decode_prefill_lists_kernel(
 }
 
 // ---------------------------------------------------------------- step 1: route and append
-// One wavefront per (batch, head): heads [0, Hq) are the new queries, [Hq, Hq + Hkv) the new keys.
+// One work-group per (batch, head): heads [0, Hq) are the new queries, [Hq, Hq + Hkv) the new keys.
 // The vector and the K centroid rows are staged in LDS first, so the fp64 chain of lane g (group g,
 // components in index order) runs from LDS instead of waiting for a global load per component.  A launch of latency:
 // every load that does not depend on another one is issued before the first wait (the position among them: nothing but
 // the exit and the last stores depends on it), and the components of the next 16 products are read while 16 are added.
+// The centroid rows come in one round trip, 16 loads a lane: one wavefront does everything else, the others (from 17 loads on)
+// only bring rows.  (One wavefront with K * NI / 16 batches, one round trip after the other: a step of 16/4 heads of 256, K = 16,
+// 826 cached tokens 18.0 us, now 17.0; 32 heads of 128 x 27861, K = 16 41.4, 40.6.  Scores
+// on v_mfma_f64_4x4x4_4b, whose four products are one step of the same sum: a longer chain, 1.6 us more at 128 components.)
 // NI = d / 64, rounded up: components of a row per lane.
-template <typename T, int NI>
-__global__ __launch_bounds__(64) void decode_route_kernel(DecodeLayout L, HeadMap hm, int pos_arg, const int* __restrict__ pos_dev,
+__host__ __device__ constexpr int route_wavefronts(int K, int ni) { return (K * ni + 15) / 16; }
+template <typename T, int NI, bool ONE>
+__global__ __launch_bounds__(ONE ? 64 : 64 * route_wavefronts(32, NI)) void decode_route_kernel(DecodeLayout L, HeadMap hm, int pos_arg, const int* __restrict__ pos_dev,
                                                           const T* __restrict__ q_new,
                                                           const T* __restrict__ k_new, const T* __restrict__ v_new,
                                                           const float* __restrict__ cents,
@@ -241,7 +248,8 @@ __global__ __launch_bounds__(64) void decode_route_kernel(DecodeLayout L, HeadMa
     constexpr int CPITCH = 64 * NI + 4;           // the K lanes read 16 bytes each of K different rows: banks 4 apart
     __shared__ __attribute__((aligned(16))) float s_x[64 * NI];
     __shared__ __attribute__((aligned(16))) float s_c[32 * CPITCH];
-    const int lane = threadIdx.x;
+    const int lane = threadIdx.x & 63;
+    const int wave = ONE ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     // the position comes from the launch (one for all sequences), or from device memory, one per sequence,
     // when a captured graph serves every step or the sequences of a batch stand at different positions;
     // a position outside the caches makes the step skip that sequence (the host could not check it)
@@ -260,12 +268,12 @@ __global__ __launch_bounds__(64) void decode_route_kernel(DecodeLayout L, HeadMa
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
         const int t = lane + 64 * i;
-        if (t < d) xr[i] = x[t];
-        if (!is_q && t < d) vr[i] = v_new[bhk * d + t];
+        if (wave == 0 && t < d) xr[i] = x[t];
+        if (wave == 0 && !is_q && t < d) vr[i] = v_new[bhk * d + t];
     }
     int cn = 0, w = 0, l0 = 0, l1 = 0;
     const int* list = (const int*)(st + L.off_lists) + (bhk * L.K + lane) * L.n;   // of group `lane`
-    if (!is_q && lane < L.K) {
+    if (wave == 0 && !is_q && lane < L.K) {
         cn = ((const int*)(st + L.off_counts))[bhk * L.K + lane];
         w = ((const int*)(st + L.off_wp))[bhk * L.K + lane];
     }
@@ -278,29 +286,29 @@ __global__ __launch_bounds__(64) void decode_route_kernel(DecodeLayout L, HeadMa
         if (w + 1 < cn) l1 = list[w + 1];
     } else {
         const float* c = cents + (size_t)hk * L.K * d;
-        constexpr int RB = 16 / NI;               // centroid rows per batch: 16 loads in flight per lane
-        for (int g0 = 0; g0 < L.K; g0 += RB) {
-            float cv[RB][NI];
+        constexpr int RB = 16 / NI;               // centroid rows of a wavefront
+        const int g0 = wave * RB;
+        float cv[RB][NI];
 #pragma unroll
-            for (int g = 0; g < RB; ++g)
+        for (int g = 0; g < RB; ++g)
 #pragma unroll
-                for (int i = 0; i < NI; ++i)
-                    cv[g][i] = (g0 + g < L.K && lane + 64 * i < d) ? c[(g0 + g) * d + lane + 64 * i] : 0.f;
-            if (g0 == 0) {
-                if (pos < 0 || pos >= L.n) return;
-                if (w < cn) l0 = list[w];
-                if (w + 1 < cn) l1 = list[w + 1];
+            for (int i = 0; i < NI; ++i)
+                cv[g][i] = (g0 + g < L.K && lane + 64 * i < d) ? c[(g0 + g) * d + lane + 64 * i] : 0.f;
+        if (pos < 0 || pos >= L.n) return;
+        if (w < cn) l0 = list[w];
+        if (w + 1 < cn) l1 = list[w + 1];
+        if (wave == 0) {
 #pragma unroll
-                for (int i = 0; i < NI; ++i)
-                    if (lane + 64 * i < d) s_x[lane + 64 * i] = dec_to_f32<T>(xr[i]);
-            }
-#pragma unroll
-            for (int g = 0; g < RB; ++g)
-#pragma unroll
-                for (int i = 0; i < NI; ++i)
-                    if (g0 + g < L.K) s_c[(g0 + g) * CPITCH + lane + 64 * i] = cv[g][i];
+            for (int i = 0; i < NI; ++i)
+                if (lane + 64 * i < d) s_x[lane + 64 * i] = dec_to_f32<T>(xr[i]);
         }
+#pragma unroll
+        for (int g = 0; g < RB; ++g)
+#pragma unroll
+            for (int i = 0; i < NI; ++i)
+                if (g0 + g < L.K) s_c[(g0 + g) * CPITCH + lane + 64 * i] = cv[g][i];
         __syncthreads();
+        if (wave != 0) return;
         double s = 0.0;
         if (lane < L.K) {
             // index order, 16 components at a time (d is a multiple of 16)
@@ -1379,10 +1387,16 @@ static hipError_t decode_step_t(const DecodeLayout& L, const HeadMap& hm, int po
                                 const void* v_new, const float* cents, const uint32_t* token_mask, void* kc, void* vc, char* st, void* out,
                                 float* lse, int32_t* row_pairs, hipStream_t s)
 {
-#define FOCUS_DEC_ROUTE(NI_) hipLaunchKernelGGL((decode_route_kernel<T, NI_>), dim3(L.Hq + L.Hkv, L.B), dim3(64), 0, s, L, hm, pos, pos_dev, (const T*)q_new, \
-                       (const T*)k_new, (const T*)v_new, cents, token_mask, (T*)kc, (T*)vc, st)
-    if (L.d <= 64) FOCUS_DEC_ROUTE(1); else if (L.d <= 128) FOCUS_DEC_ROUTE(2); else FOCUS_DEC_ROUTE(4);
+#define FOCUS_DEC_ROUTE_N(NI_, ONE_, WAVES_) hipLaunchKernelGGL((decode_route_kernel<T, NI_, ONE_>), dim3(L.Hq + L.Hkv, L.B), dim3(64 * (WAVES_)), 0, s, L, hm, pos, \
+                       pos_dev, (const T*)q_new, (const T*)k_new, (const T*)v_new, cents, token_mask, (T*)kc, (T*)vc, st)
+#define FOCUS_DEC_ROUTE(NI_)                                                                                              \
+    {                                                                                                                     \
+        const int waves = token_mask ? 1 : route_wavefronts(L.K, NI_);                                                   \
+        if (waves == 1) FOCUS_DEC_ROUTE_N(NI_, true, 1); else FOCUS_DEC_ROUTE_N(NI_, false, waves);                       \
+    }
+    if (L.d <= 64) FOCUS_DEC_ROUTE(1) else if (L.d <= 128) FOCUS_DEC_ROUTE(2) else FOCUS_DEC_ROUTE(4)
 #undef FOCUS_DEC_ROUTE
+#undef FOCUS_DEC_ROUTE_N
 #define FOCUS_DEC_D(D_) decode_step_d<T, D_>(L, hm, pos, pos_dev, (const T*)q_new, (const T*)kc, (const T*)vc, st, (T*)out, lse, row_pairs, s)
     switch (L.d) {
         case 64: return FOCUS_DEC_D(64);
