@@ -12,7 +12,9 @@
 // Kernels:
 //   route_project     a wavefront = 16 tokens x all router outputs on the fp64 matrix cores (see the kernel); writes S,
 //                     the work-group's largest score, and the masks directly when no Sinkhorn is asked;
-//   sinkhorn_pass     Sinkhorn as diagonal scaling: Q = diag(u) E diag(v) with E = exp((S - max)/tau).
+//   sinkhorn_rounds   Sinkhorn in one launch wherever its rows fit the registers of work-groups that are resident at once
+//                     (sink_groups); the same sums as
+//   sinkhorn_pass     a launch per round: Sinkhorn as diagonal scaling: Q = diag(u) E diag(v) with E = exp((S - max)/tau).
 //                     A round is  v_g = 1 / sum_i u_i E[i,g],  u_i = 1 / sum_g E[i,g] v_g,  so one pass
 //                     over E per round: every work-group first folds the previous pass's per-block
 //                     column partial sums (fixed order, no atomics: deterministic), then updates its
@@ -124,6 +126,30 @@ __device__ inline uint32_t topk_mask(const double (&s)[KP], int K, int topk)
     return m;
 }
 
+// ---------------------------------------------------------------- how the Sinkhorn rounds are launched
+// Groups padded to a power of two, as the kernels hold them.
+__host__ __device__ constexpr int sink_kp(int K) { return K <= 4 ? 4 : K <= 8 ? 8 : K <= 16 ? 16 : 32; }
+// All rounds in one launch: work-groups per sequence, or 0 where the rows do not fit the registers (64 doubles a thread) or
+// there are too many sequences for the work-groups to be resident at once, which they have to be as soon as they wait for each
+// other (at most 128 of 256 threads on 256 compute units; other launches on the device end without waiting for these).
+// One work-group as long as its rows take less time than an exchange.  Routing of a sequence, a launch per round / one work-group /
+// several (us): 2 x 500 tokens, K = 8 (d_model 3840) 126 / 104;  4493, K = 8 76.5 / - / 66.3;  32768, K = 4 199 / - / 187 (the rounds alone 51 / 30).
+__host__ __device__ inline int sink_groups(const RouteLayout& R)
+{
+    const int most = 256 * 64 / sink_kp(R.K);     // tokens of a work-group
+    if ((long long)R.n * sink_kp(R.K) <= 8192) return 1;
+    int g = R.nsink / 2 < 64 ? R.nsink / 2 : 64;
+    if (g * R.B > 128) g = 128 / R.B;
+    return g >= 2 && (R.n + g - 1) / g <= most ? g : 0;
+}
+// Column sums on their way between the work-groups: [3][work-groups][K] per sequence, in the place of the partial sums of the
+// launches.  A slot is EMPTY until its sum is there.
+constexpr unsigned long long SINK_EMPTY = ~0ull;
+__device__ inline unsigned long long* sink_slots(const RouteLayout& R, char* ws, int b)
+{
+    return (unsigned long long*)(ws + R.off_colpart) + (size_t)b * R.nsink * 64;
+}
+
 // ---------------------------------------------------------------- projection + scores
 // z = W_g^T h on the fp64 matrix cores.  v_mfma_f64_16x16x4 adds its four products to the accumulator one by one in
 // index order, each with one rounding (a fused multiply-add; checked on 512000 results against the scalar chain, and
@@ -183,6 +209,10 @@ __global__ __launch_bounds__(64 * NW, route_waves<T>(DG)) void route_project_ker
     const int tok0 = blockIdx.x * TB;
     const int n = R.n, dm = R.dm, K = R.K;
     const int rows = min(TB, n - tok0);
+    if (R.iters > 0) {
+        unsigned long long* slots = sink_slots(R, ws, b);
+        for (int i = blockIdx.x * NTHR + tid; i < 3 * sink_groups(R) * K; i += gridDim.x * NTHR) slots[i] = SINK_EMPTY;
+    }
     const int row_bytes = dm * (int)sizeof(T);
     const char* gbase = (const char*)hidden + ((size_t)b * n + tok0) * row_bytes;
     const int nchunk = (dm + RC - 1) / RC;
@@ -460,6 +490,130 @@ __global__ __launch_bounds__(256) void sinkhorn_pass_kernel(RouteLayout R, int p
     if (tid < K) mine[tid] = __dadd_rn(__dadd_rn(s_part[0][tid], s_part[1][tid]), __dadd_rn(s_part[2][tid], s_part[3][tid]));
 }
 
+// All rounds in one launch: the rows of E stay in registers (R per thread), a round is their scaling, the work-group's column sums and
+// one exchange of them.  Work-group w leaves its sums of round p in slot p % 3 and takes those of the others as they come (8 bytes
+// a sum, whole: no flag beside it); they are added in the order of the work-groups, so the result does not depend on who came first.
+// Once it has everybody's sums of round p, everybody is done with those of round p - 1, and it empties its slot of that round,
+// before it leaves its sums of round p + 1: whoever sees those sees the empty slot.  A wait ends after some seconds whatever happens.
+template <int KP, int R>
+__global__ __launch_bounds__(256) void sinkhorn_rounds_kernel(RouteLayout L, int tokens, char* __restrict__ ws, uint32_t* __restrict__ masks,
+                                                              double* __restrict__ soft)
+{
+    constexpr int EX = 64 * 32;                   // sums of a round at most
+    __shared__ double s_part[4][KP], s_v[KP], s_m[4];
+    __shared__ double s_ex[EX];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int blk = blockIdx.x, nwg = gridDim.x, b = blockIdx.y;
+    const int n = L.n, K = L.K;
+    const double* S = (const double*)(ws + L.off_S) + (size_t)b * n * K;
+    unsigned long long* slots = sink_slots(L, ws, b);
+    const int t0 = blk * tokens, t1 = min(n, t0 + tokens);
+    double r[R][KP];
+#pragma unroll
+    for (int t = 0; t < R; ++t) {
+        const int i = t0 + t * 256 + tid;
+        if (K == KP) {
+            const double* src = S + (size_t)min(i, n - 1) * KP;
+            __builtin_memcpy(r[t], __builtin_assume_aligned(src, 16), sizeof(r[t]));
+        } else {
+#pragma unroll
+            for (int g = 0; g < KP; ++g) r[t][g] = g < K ? S[(size_t)min(i, n - 1) * K + g] : 0.0;
+        }
+    }
+    double smax;
+    {
+        const double* mp = (const double*)(ws + L.off_maxpart) + (size_t)b * L.nproj;
+        double m = -INFINITY;
+        for (int i = tid; i < L.nproj; i += 256) m = fmax(m, mp[i]);
+        m = wave_max(m);
+        if (lane == 0) s_m[wave] = m;
+        __syncthreads();
+        smax = fmax(fmax(s_m[0], s_m[1]), fmax(s_m[2], s_m[3]));
+    }
+    double cs[KP];
+#pragma unroll
+    for (int g = 0; g < KP; ++g) cs[g] = 0.0;
+#pragma unroll
+    for (int t = 0; t < R; ++t) {
+        const bool there = t0 + t * 256 + tid < t1;
+#pragma unroll
+        for (int g = 0; g < KP; ++g) {
+            r[t][g] = there && g < K ? exp((r[t][g] - smax) / L.tau) : 0.0;
+            cs[g] = __dadd_rn(cs[g], r[t][g]);
+        }
+    }
+    for (int p = 0; p < L.iters; ++p) {
+        // column sums of the work-group, then of the sequence: s_v = 1 / sum
+        const double ws_sum = wave_sum_columns<KP>(cs, lane);
+        if ((lane & (64 / KP - 1)) == 0) s_part[wave][wave_column<KP>(lane)] = ws_sum;
+        __syncthreads();
+        double mine = 0.0;
+        if (tid < K) mine = __dadd_rn(__dadd_rn(s_part[0][tid], s_part[1][tid]), __dadd_rn(s_part[2][tid], s_part[3][tid]));
+        if (nwg == 1) {
+            if (tid < K) s_v[tid] = 1.0 / mine;
+        } else {
+            unsigned long long* at = slots + (size_t)(p % 3) * nwg * K;
+            if (tid < K) {
+                unsigned long long bits = __builtin_bit_cast(unsigned long long, mine);
+                if (bits == SINK_EMPTY) bits = 0x7ff8000000000000ull;    // another NaN
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // the slot of two rounds ago is empty
+                __hip_atomic_store(at + blk * K + tid, bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            for (int i = tid; i < nwg * K; i += 256) {
+                unsigned long long x = SINK_EMPTY;
+                for (int spin = 0; spin < (1 << 22); ++spin) {
+                    x = __hip_atomic_load(at + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if (x != SINK_EMPTY) break;
+                }
+                s_ex[i] = __builtin_bit_cast(double, x);                 // (never there: a NaN)
+            }
+            __syncthreads();
+            if (p > 0 && tid < K)
+                __hip_atomic_store(slots + (size_t)((p + 2) % 3) * nwg * K + blk * K + tid, SINK_EMPTY, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            for (int g = wave; g < K; g += 4) {
+                const double sum = wave_sum(lane < nwg ? s_ex[lane * K + g] : 0.0);
+                if (lane == 0) s_v[g] = 1.0 / sum;
+            }
+        }
+        __syncthreads();
+        double v[KP];
+#pragma unroll
+        for (int g = 0; g < KP; ++g) {
+            v[g] = g < K ? s_v[g] : 1.0;
+            cs[g] = 0.0;
+        }
+        const bool last = p + 1 == L.iters;
+#pragma unroll
+        for (int t = 0; t < R; ++t) {
+            const int i = t0 + t * 256 + tid;
+            if (i >= t1) continue;
+            double e[KP], rs = 0.0;
+#pragma unroll
+            for (int g = 0; g < KP; ++g) {
+                e[g] = g < K ? __dmul_rn(r[t][g], v[g]) : 0.0;
+                rs = __dadd_rn(rs, e[g]);
+            }
+            const double u = 1.0 / rs;
+            if (!last) {
+#pragma unroll
+                for (int g = 0; g < KP; ++g)
+                    if (g < K) cs[g] = __dadd_rn(cs[g], __dmul_rn(u, r[t][g]));
+            } else {
+                const size_t tok = (size_t)b * n + i;
+#pragma unroll
+                for (int g = 0; g < KP; ++g) e[g] = __dmul_rn(e[g], u);
+                masks[tok] = topk_mask<KP>(e, K, L.topk);
+                if (soft) {
+#pragma unroll
+                    for (int g = 0; g < KP; ++g)
+                        if (g < K) soft[tok * K + g] = e[g];
+                }
+            }
+        }
+        __syncthreads();                          // s_part, s_ex and s_v are written again
+    }
+}
+
 template <typename T>
 hipError_t launch_project(const RouteLayout& R, const void* hidden, const float* wg, const float* cent, char* ws,
                           uint32_t* masks, double* soft, hipStream_t st)
@@ -495,6 +649,18 @@ hipError_t launch_route(const RouteLayout& R, const void* hidden, const float* w
     else e = launch_project<uint16_t>(R, hidden, wg, cent, ws, masks, soft, st);
     if (e != hipSuccess) return e;
     if (R.iters == 0) return hipSuccess;
+    const int groups = sink_groups(R);
+    if (groups > 0) {
+        const int tokens = (R.n + groups - 1) / groups, rows = (tokens + 255) / 256;
+        dim3 grid(groups, R.B);
+#define FOCUS_ROUNDS(KP_, R_) hipLaunchKernelGGL((sinkhorn_rounds_kernel<KP_, R_>), grid, dim3(256), 0, st, R, tokens, ws, masks, soft)
+        if (R.K <= 4) { if (rows <= 2) FOCUS_ROUNDS(4, 2); else if (rows <= 4) FOCUS_ROUNDS(4, 4); else if (rows <= 8) FOCUS_ROUNDS(4, 8); else FOCUS_ROUNDS(4, 16); }
+        else if (R.K <= 8) { if (rows <= 2) FOCUS_ROUNDS(8, 2); else if (rows <= 4) FOCUS_ROUNDS(8, 4); else FOCUS_ROUNDS(8, 8); }
+        else if (R.K <= 16) { if (rows <= 2) FOCUS_ROUNDS(16, 2); else FOCUS_ROUNDS(16, 4); }
+        else FOCUS_ROUNDS(32, 2);
+#undef FOCUS_ROUNDS
+        return hipGetLastError();
+    }
     dim3 grid(R.nsink, R.B);
     for (int pass = 0; pass <= R.iters; ++pass) {
 #define FOCUS_SINK(KP_)                                                                                                   \

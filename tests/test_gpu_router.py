@@ -192,3 +192,26 @@ def test_route_full_size(name):
     rin = workloads.make_router_inputs(wl, "cuda")
     check_route(wl, rin, 10)
     check_route(wl, rin, 0)
+
+
+@pytest.mark.parametrize("B,n,K,topk,iters", [
+    (2, 1024, 8, 3, 7), (2, 1025, 8, 3, 7), (1, 256, 32, 2, 10), (3, 257, 32, 5, 10), (2, 2048, 4, 1, 1), (2, 2049, 3, 1, 2), (1, 1500, 11, 2, 4), (1, 5000, 1, 1, 3),
+    (1, 131072, 4, 2, 5), (1, 66000, 8, 2, 3), (4, 9000, 16, 3, 10), (1, 40000, 16, 1, 3), (1, 16000, 32, 2, 3), (1, 17000, 32, 2, 3), (70, 700, 16, 2, 3), (9, 1300, 5, 2, 12)])
+def test_sinkhorn_rounds(B, n, K, topk, iters):
+    """One work-group per sequence, several that exchange their sums (two rows per thread and more), and a launch per round (too many
+    tokens or sequences), at the edges between them."""
+    wl = workloads.Workload("r", 63, B, 1, 1, n, 64, "bf16", K, topk, 16, mixture=3 if K > 4 else 0)
+    rin = workloads.make_router_inputs(wl, "cuda", d_model=64, d_g=16)
+    got = check_route(wl, rin, iters)
+    for _ in range(2):              # the sums of the call before are still in the workspace
+        assert np.array_equal(check_route(wl, rin, iters), got)
+
+
+def test_sinkhorn_rounds_of_scores_that_are_not_finite():
+    """Every wait ends and the memberships are topk-subsets, whatever the sums are."""
+    wl = workloads.Workload("r", 64, 1, 1, 1, 5000, 64, "f32", 8, 2, 16)
+    rin = workloads.make_router_inputs(wl, "cuda", d_model=64, d_g=16)
+    rin["hidden"][0, 77, 3] = float("nan")
+    masks, _ = run_route(wl, rin, 3)
+    m = masks.cpu().numpy().view(np.uint32)
+    assert all(bin(int(x)).count("1") == 2 for x in m.ravel())
