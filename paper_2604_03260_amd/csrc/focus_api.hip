@@ -584,6 +584,11 @@ focus_status soft_launch(const focus_params* p, float lambda, const float* g, co
     hipStream_t s = (hipStream_t)stream;
     // one class holding every token, in position order (the vector kernel reads it through the tables of the bucketing)
     const bool tiled = L.dtype != FOCUS_F32 && !vector;
+    if (tiled && focus::short_soft_attention(L)) {
+        const hipError_t es = focus::launch_attn_short_soft(L, hm, g, q, k, v, (char*)workspace, out, lse, s);
+        if (es != hipSuccess) return fail(FOCUS_EHIP, "focus_attn_soft_fwd: %s", hipGetErrorString(es));
+        return FOCUS_OK;
+    }
     hipError_t e = tiled ? focus::launch_position_layout(L, k, nullptr, (char*)workspace, s)
                          : focus::launch_assign_tokens(L, nullptr, k, (char*)workspace, nullptr, s);
     if (e == hipSuccess && tiled) e = focus::launch_soft_gather_g(L, g, (char*)workspace, s);

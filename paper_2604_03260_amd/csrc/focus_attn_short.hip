@@ -78,7 +78,10 @@ __device__ inline float both_halves_max(float x)
 constexpr int short_waves(int d) { return d == 256 ? 4 : 8; }
 
 
-template <int D, bool F16>
+// SOFT: Sec. 2 Eq. 2, every causal pair, the score of a pair outside the window times 1 / (1 + 2^G), G = -lambda * log2(e) * g_i . g_j from
+// the bf16 high and low parts of the assignments as in the tiled kernel (focus_attn_mfma.hip), taken apart here; SOFT k-steps of
+// 16 groups.
+template <int D, bool F16, int SOFT>
 __global__ __launch_bounds__(64 * short_waves(D), short_waves(D) / 4) void attn_short_kernel(ShortArgs A, HeadMap hm)
 {
     typedef Half16<F16> HT;
@@ -112,6 +115,32 @@ __global__ __launch_bounds__(64 * short_waves(D), short_waves(D) / 4) void attn_
     const float scale = A.scale, cap = A.softcap;
     const float sl2 = cap > 0.f ? LOG2E : scale * LOG2E;     // logits (scores without a cap) to log2 units
     const float two_over_cap = cap > 0.f ? 2.f * LOG2E * scale / cap : 0.f;
+    bf16x8 gqh[SOFT + 1], gql[SOFT + 1];          // the row's assignment times the slope
+    const float* gbase = SOFT ? A.g + (size_t)W.b * n * A.K : nullptr;
+    // components 16 * ks + 8 * hh .. + 7 of the assignment of position pos
+    auto load_g = [&](int pos, int ks, float (&x)[8]) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int c = 16 * ks + 8 * hh + e;
+            x[e] = c < A.K ? gbase[(size_t)pos * A.K + c] : 0.f;
+        }
+    };
+    auto split_g = [&](const float (&x)[8], float slope, bf16x8& hi, bf16x8& lo) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float y = x[e] * slope;
+            hi[e] = (__bf16)y;
+            lo[e] = (__bf16)(y - (float)hi[e]);
+        }
+    };
+    if constexpr (SOFT > 0) {
+#pragma unroll
+        for (int ks = 0; ks < SOFT; ++ks) {
+            float x[8];
+            load_g(max(W.qpos, 0), ks, x);
+            split_g(x, A.gate_slope, gqh[ks], gql[ks]);
+        }
+    }
     f32x16 o[DB];
 #pragma unroll
     for (int db = 0; db < DB; ++db)
@@ -172,16 +201,21 @@ __global__ __launch_bounds__(64 * short_waves(D), short_waves(D) / 4) void attn_
         uint4 km[4];
         V8 kf[KS];
         Values v;
+        float g[SOFT + 1][8];
     };
     auto load_unit = [&](int u, Unit& U) {
         W.load_masks(u, U.km);
+        if constexpr (SOFT > 0) {
+#pragma unroll
+            for (int ks = 0; ks < SOFT; ++ks) load_g(min(32 * u + n32, n - 1), ks, U.g[ks]);
+        }
         const char* kr = kbase + (size_t)(unsigned)(32 * u) * pitch;
         const unsigned at_k = (unsigned)min(n32, n - 1 - 32 * u) * pitch + 16u * (unsigned)hh;
 #pragma unroll
         for (int c = 0; c < KS; ++c) U.kf[c] = *(const V8*)(kr + (at_k + 32u * c));
         load_v(u, U.v);
     };
-    constexpr bool AHEAD = D == 64;
+    constexpr bool AHEAD = D == 64 && SOFT < 2;
     Unit next;
     if (AHEAD && W.u0 + wave < W.u1) load_unit(W.u0 + wave, next);
     for (int u = W.u0 + wave; u < W.u1; u += NW) {
@@ -200,6 +234,28 @@ __global__ __launch_bounds__(64 * short_waves(D), short_waves(D) / 4) void attn_
         for (int r = 0; r < 16; ++r) s[r] = 0.f;
 #pragma unroll
         for (int c = 0; c < KS; ++c) s = HT::mfma(U.kf[c], qf[c], s);
+        if constexpr (SOFT > 0) {
+            const int at = W.qpos - 32 * u;       // of the row, from the unit's first key on
+            if (__any(at >= W.w)) {               // some pair outside the window
+                f32x16 gate;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) gate[r] = 0.f;
+#pragma unroll
+                for (int ks = 0; ks < SOFT; ++ks) {
+                    bf16x8 hi, lo;
+                    split_g(U.g[ks], 1.f, hi, lo);
+                    gate = Half16<false>::mfma(hi, gqh[ks], gate);
+                    gate = Half16<false>::mfma(hi, gql[ks], gate);
+                    gate = Half16<false>::mfma(lo, gqh[ks], gate);
+                }
+                const unsigned far = W.upto(at - W.w);                   // pairs outside the window
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const float x = __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(gate[r]));
+                    s[r] *= (far >> r) & 1u ? x : 1.f;
+                }
+            }
+        }
         // softmax step in log2 units: p = 2^(s * sl2 - m), one rounding in the exponent (a row's m cancels)
         if (cap > 0.f) {
 #pragma unroll
@@ -365,14 +421,52 @@ hipError_t launch_attn_short(const Layout& L, const HeadMap& hm, const void* q, 
     const dim3 blocks = short_grid(A);
 #define FOCUS_SHORT(D_)                                                                                                   \
     case D_:                                                                                                              \
-        if (L.dtype == 2) hipLaunchKernelGGL((attn_short_kernel<D_, true>), blocks, threads, 0, st, A, hm);             \
-        else hipLaunchKernelGGL((attn_short_kernel<D_, false>), blocks, threads, 0, st, A, hm);                         \
+        if (L.dtype == 2) hipLaunchKernelGGL((attn_short_kernel<D_, true, 0>), blocks, threads, 0, st, A, hm);             \
+        else hipLaunchKernelGGL((attn_short_kernel<D_, false, 0>), blocks, threads, 0, st, A, hm);                         \
         break;
     switch (L.d) {
         FOCUS_SHORT(64) FOCUS_SHORT(80) FOCUS_SHORT(96) FOCUS_SHORT(128) FOCUS_SHORT(256)
         default: return hipErrorInvalidValue;
     }
 #undef FOCUS_SHORT
+    return hipGetLastError();
+}
+
+// The soft gate in the place of four launches (positions, assignments, V, tiles).  What a unit costs grows with the groups, which every
+// wavefront takes apart for itself.  Pass, tiled / this kernel (us), 256 .. 4096 tokens, by work-groups of 32 rows:
+//   K = 4, 96 components:  512 x 512 groups 30.8 / 14.7;  4096 x 768 122 / 71, 1024 120 / 86, 1536 124 / 129
+//   K = 8, 64:  512 x 768 29.7 / 25.3, 1024 30.9 / 32.2;  4096 x 768 108 / 72;   128: 512 x 768 36.2 / 33.2, 1024 38.3 / 42.1;  4096 x 768 132 / 117
+//   K = 16, 80:  512 x 768 32.0 / 27.9, 1024 33.2 / 36.4;  4096 x 768 119 / 95
+//   K = 32, 64:  512 x 512 32.2 / 26.9, 768 33.1 / 39.9;  4096 x 512 128 / 95;   128: 512 x 512 39.1 / 33.1;  4096 x 512 158 / 123, 768 158 / 193
+bool short_soft_attention(const Layout& L)
+{
+    const long long groups = (long long)L.B * L.Hq * ((L.n + 31) / 32);
+    return L.dtype != 0 && L.soft && L.d <= 128 && L.n <= 4096 && groups <= (L.K > 16 ? 512 : (L.K <= 4 && L.d < 128) ? 1024 : 768) &&
+           (uint64_t)L.ks[2] * 2 < (1u << 24) && (uint64_t)L.n * (uint64_t)L.ks[2] * 2 < 0xffffffffull;
+}
+
+hipError_t launch_attn_short_soft(const Layout& L, const HeadMap& hm, const float* g, const void* q, const void* k, const void* v, char* ws,
+                                  void* out, float* lse, hipStream_t st)
+{
+    ShortArgs A = short_args(L, hm, q, k, v, ws, out, lse, nullptr);
+    A.g = g;
+    A.dense = 1;
+    const dim3 threads(64 * short_waves(L.d)), blocks = short_grid(A);
+#define FOCUS_SHORT_SOFT(D_)                                                                                              \
+    case D_:                                                                                                              \
+        if (L.dtype == 2) {                                                                                               \
+            if (L.K <= 16) hipLaunchKernelGGL((attn_short_kernel<D_, true, 1>), blocks, threads, 0, st, A, hm);           \
+            else hipLaunchKernelGGL((attn_short_kernel<D_, true, 2>), blocks, threads, 0, st, A, hm);                     \
+        } else {                                                                                                          \
+            if (L.K <= 16) hipLaunchKernelGGL((attn_short_kernel<D_, false, 1>), blocks, threads, 0, st, A, hm);          \
+            else hipLaunchKernelGGL((attn_short_kernel<D_, false, 2>), blocks, threads, 0, st, A, hm);                    \
+        }                                                                                                                 \
+        break;
+    switch (L.d) {
+        FOCUS_SHORT_SOFT(64) FOCUS_SHORT_SOFT(80) FOCUS_SHORT_SOFT(96) FOCUS_SHORT_SOFT(128)
+        default: return hipErrorInvalidValue;
+    }
+#undef FOCUS_SHORT_SOFT
     return hipGetLastError();
 }
 

@@ -254,6 +254,9 @@ hipError_t launch_attn_simple(const Layout& L, const HeadMap& hm, const void* q,
 bool short_attention(const Layout& L);
 hipError_t launch_attn_short(const Layout& L, const HeadMap& hm, const void* q, const void* k, const void* v, char* ws,
                              void* out, float* lse, int32_t* row_pairs, hipStream_t st);
+bool short_soft_attention(const Layout& L);
+hipError_t launch_attn_short_soft(const Layout& L, const HeadMap& hm, const float* g, const void* q, const void* k, const void* v, char* ws,
+                                  void* out, float* lse, hipStream_t st);
 hipError_t launch_attn_f32(const Layout& L, const HeadMap& hm, const void* q, const void* k, const void* v, char* ws,
                            void* out, float* lse, int32_t* row_pairs, hipStream_t st);
 hipError_t launch_soft_gather_g(const Layout& L, const float* g, char* ws, hipStream_t st);

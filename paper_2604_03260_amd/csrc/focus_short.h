@@ -17,6 +17,9 @@ struct ShortArgs {
     int B, Hq, Hkv, n, NKP, window, causal, dense, pair_set, default_map;
     float scale, softcap;
     int groups;                                   // of 32 rows
+    const float* g;                               // soft gate: assignments [B,n,K] and -lambda * log2(e)
+    float gate_slope;
+    int K;
 };
 
 inline ShortArgs short_args(const Layout& L, const HeadMap& hm, const void* q, const void* k, const void* v, const char* ws, void* out,
@@ -35,6 +38,7 @@ inline ShortArgs short_args(const Layout& L, const HeadMap& hm, const void* q, c
     for (int h = 0; A.default_map && h < L.Hq; ++h) A.default_map = hm.kv[h] == h / (L.Hq / L.Hkv);
     A.scale = L.scale; A.softcap = L.softcap;
     A.groups = (L.n + 31) / 32;
+    A.g = nullptr; A.gate_slope = L.gate_slope; A.K = L.K;
     return A;
 }
 // Grid: (batch and KV head, query head of it, groups of rows) with the default head map: the query heads of a KV head share an
@@ -72,9 +76,10 @@ struct ShortWalk {
         const int last = min(row0 + 31, n - 1);
         rvalid = row0 + (lane & 31) < n;
         qpos = rvalid ? row0 + (lane & 31) : -1;
-        mq_row = rvalid ? A.mq[(size_t)(b * A.Hq + h) * n + qpos] : 0u;
+        dense = A.dense != 0;
+        mq_row = rvalid && !dense ? A.mq[(size_t)(b * A.Hq + h) * n + qpos] : 0u;
         kmsk = A.kmsk + (size_t)(b * A.Hkv + hk) * A.NKP;
-        causal = A.causal != 0; dense = A.dense != 0;
+        causal = A.causal != 0;
         set = dense ? 0 : A.pair_set;
         const int x_hi = causal ? last + 1 : n;
         const bool local = set == 2;
