@@ -133,21 +133,22 @@ __host__ __device__ constexpr int sink_kp(int K) { return K <= 4 ? 4 : K <= 8 ? 
 // there are too many sequences for the work-groups to be resident at once, which they have to be as soon as they wait for each
 // other (at most 128 of 256 threads on 256 compute units; other launches on the device end without waiting for these).
 // One work-group as long as its rows take less time than an exchange.  Routing of a sequence, a launch per round / one work-group /
-// several (us): 2 x 500 tokens, K = 8 (d_model 3840) 126 / 104;  4493, K = 8 76.5 / - / 66.3;  32768, K = 4 199 / - / 187 (the rounds alone 51 / 30).
+// several (us): 2 x 500 tokens, K = 8 (d_model 3840) 126 / 104;  4493, K = 8 76.5 / - / 66.3;  32768, K = 4 199 / - / 187 (the rounds alone 51 / 30).  K = 4, d_model 768: 2000
+// tokens 40 in one, 4000 37 in several.
 __host__ __device__ inline int sink_groups(const RouteLayout& R)
 {
     const int most = 256 * 64 / sink_kp(R.K);     // tokens of a work-group
-    if ((long long)R.n * sink_kp(R.K) <= 8192) return 1;
+    if ((long long)R.n * sink_kp(R.K) <= 6144) return 1;
     int g = R.nsink / 2 < 64 ? R.nsink / 2 : 64;
     if (g * R.B > 128) g = 128 / R.B;
-    return g >= 2 && (R.n + g - 1) / g <= most ? g : 0;
+    return g >= 2 && (R.n + g - 1) / g <= most ? g : R.n <= most ? 1 : 0;
 }
 // Column sums on their way between the work-groups: [3][work-groups][K] per sequence, in the place of the partial sums of the
 // launches.  A slot is EMPTY until its sum is there.
 constexpr unsigned long long SINK_EMPTY = ~0ull;
 __device__ inline unsigned long long* sink_slots(const RouteLayout& R, char* ws, int b)
 {
-    return (unsigned long long*)(ws + R.off_colpart) + (size_t)b * R.nsink * 64;
+    return (unsigned long long*)(ws + R.off_colpart) + (size_t)b * (3 * sink_groups(R) * R.K);     // at most 48 of the 64 * nsink words
 }
 
 // ---------------------------------------------------------------- projection + scores
@@ -182,7 +183,11 @@ template <int DG> using route_w_t = std::conditional_t<DG <= 16, double, float>;
 // one wavefront, 333 in two; 1024 -> 64, 131072: 368 / 474 / 363; 1024 -> 32 in fp32, 131072: 193 / 205 in three, 192 in four).
 template <typename T> constexpr int route_waves(int dg) { return dg == 64 ? 2 : (dg == 32 && sizeof(T) == 4) ? 4 : 0; }
 
-template <typename T, int DG, int NW>
+// SPLIT (d_g = 16): few tokens leave the chip idle behind a chain of one 64-cycle product per four components.  A work-group then is 16
+// tokens, its four wavefronts take four outputs each, one product of 16 cycles a step; all wavefronts read the same rows.
+// Routing, whole / split (us), ten rounds, K = 4, bf16: d_model 4096: 500 tokens 83 / 60, 2000 99 / 75, 8000 98 / 84, 12000 104 / 101, 16000 103 / 116;
+// 768: 500 30 / 25, 8000 44 / 42, 12000 50 / 50; fp32, 4096: 500 98 / 71, 8000 113 / 97, 12000 118 / 112, 16000 120 / 132.
+template <typename T, int DG, int NW, bool SPLIT>
 __global__ __launch_bounds__(64 * NW, route_waves<T>(DG)) void route_project_kernel(RouteLayout R, const T* __restrict__ hidden,
                                                                  const float* __restrict__ wg,
                                                                  const float* __restrict__ cent,
@@ -190,10 +195,12 @@ __global__ __launch_bounds__(64 * NW, route_waves<T>(DG)) void route_project_ker
                                                                  uint32_t* __restrict__ masks,
                                                                  double* __restrict__ soft)
 {
-    constexpr int NTHR = 64 * NW, TB = 16 * NW;
+    static_assert(!SPLIT || (DG == 16 && NW == 4), "four outputs for each of four wavefronts");
+    constexpr int NTHR = 64 * NW, TB = SPLIT ? 16 : 16 * NW;
     constexpr int RC = 128 / (int)sizeof(T);             // components per chunk
-    constexpr bool SMALL = route_small(DG);
-    constexpr int LC = SMALL ? 3 : 15, CB = (DG + LC) / (LC + 1);    // column of a block, blocks of 4 or of 16 outputs
+    constexpr bool SMALL = route_small(DG) || SPLIT;
+    constexpr int LC = SMALL ? 3 : 15, CB = SPLIT ? 1 : (DG + LC) / (LC + 1);    // column of a block, blocks of 4 or of 16 outputs
+    constexpr int NP = SPLIT ? 1 : 2;                    // 16-byte pieces of the rows per thread and chunk (SPLIT: of the first 128 threads)
     constexpr int WP = route_wp(DG);
     typedef route_w_t<DG> w_t;
     typedef std::conditional_t<SMALL, double, f64x4> acc_t;
@@ -209,22 +216,19 @@ __global__ __launch_bounds__(64 * NW, route_waves<T>(DG)) void route_project_ker
     const int tok0 = blockIdx.x * TB;
     const int n = R.n, dm = R.dm, K = R.K;
     const int rows = min(TB, n - tok0);
-    if (R.iters > 0) {
-        unsigned long long* slots = sink_slots(R, ws, b);
-        for (int i = blockIdx.x * NTHR + tid; i < 3 * sink_groups(R) * K; i += gridDim.x * NTHR) slots[i] = SINK_EMPTY;
-    }
+    const int row0 = SPLIT ? 0 : wave * 16, col0 = SPLIT ? wave * 4 : 0;         // of this wavefront
     const int row_bytes = dm * (int)sizeof(T);
     const char* gbase = (const char*)hidden + ((size_t)b * n + tok0) * row_bytes;
     const int nchunk = (dm + RC - 1) / RC;
     char* s_a = s_dyn;
     w_t* s_w = (w_t*)(s_dyn + 2 * TB * A_ROW);
 
-    u32x4 sta[PF][2];
+    u32x4 sta[PF][NP];
     float swa[PF][WPT];
-    auto load_chunk = [&](int ch, u32x4 (&st)[2], float (&sw)[WPT]) {
+    auto load_chunk = [&](int ch, u32x4 (&st)[NP], float (&sw)[WPT]) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {                    // this wavefront's 16 rows, 8 pieces of 16 bytes each
-            const int pid = i * 64 + lane, row = wave * 16 + pid / 8, byte = ch * 128 + pid % 8 * 16;
+        for (int i = 0; i < NP; ++i) {                   // this wavefront's 16 rows (SPLIT: the work-group's), 8 pieces of 16 bytes each
+            const int pid = SPLIT ? tid : i * 64 + lane, row = row0 + pid / 8, byte = ch * 128 + pid % 8 * 16;
             const u32x4 z = {0u, 0u, 0u, 0u};
             st[i] = (row < rows && byte < row_bytes) ? *(const u32x4*)(gbase + (size_t)row * row_bytes + byte) : z;
         }
@@ -246,14 +250,15 @@ __global__ __launch_bounds__(64 * NW, route_waves<T>(DG)) void route_project_ker
     for (int p = 0; p < PF; ++p) {
         const int ch = ch0 + p;
         if (ch >= nchunk) break;                         // uniform over the work-group
-        u32x4 (&st)[2] = sta[p];
+        u32x4 (&st)[NP] = sta[p];
         float (&sw)[WPT] = swa[p];
         char* abuf = s_a + (ch & 1) * (TB * A_ROW);
         w_t* wbuf = s_w + (ch & 1) * (RC * WP);
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int pid = i * 64 + lane;
-            uint32_t* dst = (uint32_t*)(abuf + (wave * 16 + pid / 8) * A_ROW) + pid % 8;
+        for (int i = 0; i < NP; ++i) {
+            const int pid = SPLIT ? tid : i * 64 + lane;
+            if (SPLIT && tid >= 128) break;              // (uniform over a wavefront)
+            uint32_t* dst = (uint32_t*)(abuf + (row0 + pid / 8) * A_ROW) + pid % 8;
             const u32x4 v = st[i];
             if constexpr (sizeof(T) == 4) {              // components 4c .. 4c+3: step c of the four parts
                 dst[0] = v[0]; dst[8] = v[1]; dst[16] = v[2]; dst[24] = v[3];
@@ -271,9 +276,9 @@ __global__ __launch_bounds__(64 * NW, route_waves<T>(DG)) void route_project_ker
         }
         __syncthreads();               // also orders these writes after every wave's reads two chunks ago
         if (ch + PF < nchunk) load_chunk(ch + PF, st, sw);
-        const u32x4* ar = (const u32x4*)(abuf + (wave * 16 + (lane & 15)) * A_ROW + (lane >> 4) * 32);
+        const u32x4* ar = (const u32x4*)(abuf + (row0 + (lane & 15)) * A_ROW + (lane >> 4) * 32);
         const u32x4 a0 = ar[0], a1 = ar[1];
-        const w_t* wr = wbuf + (lane >> 4) * WP + (lane & LC);
+        const w_t* wr = wbuf + (lane >> 4) * WP + col0 + (lane & LC);
         const int steps = min(RC, dm - ch * RC) / 4;     // dm is a multiple of 8
         auto a_of = [&](int i) -> double {
             double a;
@@ -336,7 +341,7 @@ __global__ __launch_bounds__(64 * NW, route_waves<T>(DG)) void route_project_ker
 #pragma unroll
     for (int cb = 0; cb < CB; ++cb) {
         if constexpr (SMALL) {
-            s_z[(wave * 16 + (lane & 12) + (lane >> 4)) * (DG + 1) + cb * 4 + (lane & 3)] = acc[cb];
+            s_z[(row0 + (lane & 12) + (lane >> 4)) * (DG + 1) + col0 + cb * 4 + (lane & 3)] = acc[cb];
         } else {
 #pragma unroll
             for (int r = 0; r < 4; ++r) s_z[(wave * 16 + 4 * r + (lane >> 4)) * (DG + 1) + cb * 16 + (lane & 15)] = acc[cb][r];
@@ -359,6 +364,10 @@ __global__ __launch_bounds__(64 * NW, route_waves<T>(DG)) void route_project_ker
         double m = s_wmax[0];
         for (int w = 1; w < NW; ++w) m = fmax(m, s_wmax[w]);
         ((double*)(ws + R.off_maxpart))[(size_t)b * R.nproj + blockIdx.x] = m;
+    }
+    if (R.iters > 0) {
+        unsigned long long* slots = sink_slots(R, ws, b);
+        for (int i = blockIdx.x * NTHR + tid; i < 3 * sink_groups(R) * K; i += gridDim.x * NTHR) slots[i] = SINK_EMPTY;
     }
     if (tid < rows) {
         const size_t tg = (size_t)b * n + tok0 + tid;
@@ -616,23 +625,23 @@ __global__ __launch_bounds__(256) void sinkhorn_rounds_kernel(RouteLayout L, int
 
 template <typename T>
 hipError_t launch_project(const RouteLayout& R, const void* hidden, const float* wg, const float* cent, char* ws,
-                          uint32_t* masks, double* soft, hipStream_t st)
+                          uint32_t* masks, double* soft, bool split, hipStream_t st)
 {
-    const int nw = route_tokens_per_group(R.B, R.n, R.dg) / 16;
+    const int tb = split ? 16 : route_tokens_per_group(R.B, R.n, R.dg), nw = tb == 128 ? 8 : 4;
     dim3 grid(R.nproj, R.B);
     const int rc = 128 / (int)sizeof(T);
-    const size_t stage = 2 * ((size_t)nw * 16 * A_ROW + (size_t)rc * route_wp(R.dg) * (R.dg <= 16 ? 8 : 4));
-    const size_t tail = (size_t)nw * 16 * (R.dg + 1 + (R.K | 1)) * sizeof(double);
+    const size_t stage = 2 * ((size_t)tb * A_ROW + (size_t)rc * route_wp(R.dg) * (R.dg <= 16 ? 8 : 4));
+    const size_t tail = (size_t)tb * (R.dg + 1 + (R.K | 1)) * sizeof(double);
     const size_t lds = stage > tail ? stage : tail;      // at most 53 KB (8 wavefronts, d_g <= 16) or 59 KB (4, d_g = 64, 16-bit rows)
-#define FOCUS_PROJ(DG, NW)                                                                                   \
-    hipLaunchKernelGGL((route_project_kernel<T, DG, NW>), grid, dim3(64 * NW), lds, st, R, (const T*)hidden, wg, \
+#define FOCUS_PROJ(DG, NW, SPLIT)                                                                            \
+    hipLaunchKernelGGL((route_project_kernel<T, DG, NW, SPLIT>), grid, dim3(64 * NW), lds, st, R, (const T*)hidden, wg, \
                        cent, ws, masks, soft)
     switch (R.dg) {
-        case 4: if (nw == 8) FOCUS_PROJ(4, 8); else FOCUS_PROJ(4, 4); break;
-        case 8: if (nw == 8) FOCUS_PROJ(8, 8); else FOCUS_PROJ(8, 4); break;
-        case 16: if (nw == 8) FOCUS_PROJ(16, 8); else FOCUS_PROJ(16, 4); break;
-        case 32: FOCUS_PROJ(32, 4); break;
-        default: FOCUS_PROJ(64, 4); break;
+        case 4: if (nw == 8) FOCUS_PROJ(4, 8, false); else FOCUS_PROJ(4, 4, false); break;
+        case 8: if (nw == 8) FOCUS_PROJ(8, 8, false); else FOCUS_PROJ(8, 4, false); break;
+        case 16: if (split) FOCUS_PROJ(16, 4, true); else if (nw == 8) FOCUS_PROJ(16, 8, false); else FOCUS_PROJ(16, 4, false); break;
+        case 32: FOCUS_PROJ(32, 4, false); break;
+        default: FOCUS_PROJ(64, 4, false); break;
     }
 #undef FOCUS_PROJ
     return hipGetLastError();
@@ -640,13 +649,19 @@ hipError_t launch_project(const RouteLayout& R, const void* hidden, const float*
 
 }  // namespace
 
-hipError_t launch_route(const RouteLayout& R, const void* hidden, const float* wg, const float* cent, char* ws,
+hipError_t launch_route(const RouteLayout& layout, const void* hidden, const float* wg, const float* cent, char* ws,
                         uint32_t* masks, double* soft, hipStream_t st)
 {
     hipError_t e;
-    if (R.dtype == 0) e = launch_project<float>(R, hidden, wg, cent, ws, masks, soft, st);
-    else if (R.dtype == 2) e = launch_project<f16_bits>(R, hidden, wg, cent, ws, masks, soft, st);
-    else e = launch_project<uint16_t>(R, hidden, wg, cent, ws, masks, soft, st);
+    RouteLayout R = layout;
+    const bool split = R.dg == 16 && (long long)R.B * R.n <= 8192 && (R.iters == 0 || sink_groups(R) > 0);
+    if (split) {       // a largest score for every 16 tokens: behind the sums of the rounds, which take at most 48 of 64 words a sort block
+        R.nproj = (R.n + 15) / 16;
+        R.off_maxpart = R.off_colpart + (size_t)48 * R.B * R.nsink * 8;
+    }
+    if (R.dtype == 0) e = launch_project<float>(R, hidden, wg, cent, ws, masks, soft, split, st);
+    else if (R.dtype == 2) e = launch_project<f16_bits>(R, hidden, wg, cent, ws, masks, soft, split, st);
+    else e = launch_project<uint16_t>(R, hidden, wg, cent, ws, masks, soft, split, st);
     if (e != hipSuccess) return e;
     if (R.iters == 0) return hipSuccess;
     const int groups = sink_groups(R);

@@ -195,7 +195,7 @@ def test_route_full_size(name):
 
 
 @pytest.mark.parametrize("B,n,K,topk,iters", [
-    (2, 1024, 8, 3, 7), (2, 1025, 8, 3, 7), (1, 256, 32, 2, 10), (3, 257, 32, 5, 10), (2, 2048, 4, 1, 1), (2, 2049, 3, 1, 2), (1, 1500, 11, 2, 4), (1, 5000, 1, 1, 3),
+    (2, 768, 8, 3, 7), (2, 769, 8, 3, 7), (1, 192, 32, 2, 10), (3, 600, 32, 5, 10), (2, 1536, 4, 1, 1), (2, 1537, 3, 1, 2), (1, 1500, 11, 2, 4), (1, 5000, 1, 1, 3),
     (1, 131072, 4, 2, 5), (1, 66000, 8, 2, 3), (4, 9000, 16, 3, 10), (1, 40000, 16, 1, 3), (1, 16000, 32, 2, 3), (1, 17000, 32, 2, 3), (70, 700, 16, 2, 3), (9, 1300, 5, 2, 12)])
 def test_sinkhorn_rounds(B, n, K, topk, iters):
     """One work-group per sequence, several that exchange their sums (two rows per thread and more), and a launch per round (too many
@@ -215,3 +215,11 @@ def test_sinkhorn_rounds_of_scores_that_are_not_finite():
     masks, _ = run_route(wl, rin, 3)
     m = masks.cpu().numpy().view(np.uint32)
     assert all(bin(int(x)).count("1") == 2 for x in m.ravel())
+
+
+@pytest.mark.parametrize("n,dm,dtype,iters", [(1, 64, "bf16", 0), (15, 72, "f32", 4), (17, 8, "f16", 0), (4096, 136, "bf16", 10), (4097, 136, "bf16", 10), (2731, 200, "f32", 0)])
+@pytest.mark.parametrize("B", [1, 2])
+def test_projection_of_few_tokens(B, n, dm, dtype, iters):
+    """Sixteen tokens per work-group up to 8192 tokens in all, the last one partly filled; the same sums as with more."""
+    wl = workloads.Workload("r", 65, B, 1, 1, n, 64, dtype, 7, 2, 16, mixture=3)
+    check_route(wl, workloads.make_router_inputs(wl, "cuda", d_model=dm, d_g=16), iters)
