@@ -366,8 +366,10 @@ __global__ __launch_bounds__(64 * NW, route_waves<T>(DG)) void route_project_ker
         ((double*)(ws + R.off_maxpart))[(size_t)b * R.nproj + blockIdx.x] = m;
     }
     if (R.iters > 0) {
+        const int groups = sink_groups(R);
         unsigned long long* slots = sink_slots(R, ws, b);
-        for (int i = blockIdx.x * NTHR + tid; i < 3 * sink_groups(R) * K; i += gridDim.x * NTHR) slots[i] = SINK_EMPTY;
+        if (groups > 1)                                  // (one work-group exchanges nothing, and a short sequence has no space for it)
+            for (int i = blockIdx.x * NTHR + tid; i < 3 * groups * K; i += gridDim.x * NTHR) slots[i] = SINK_EMPTY;
     }
     if (tid < rows) {
         const size_t tg = (size_t)b * n + tok0 + tid;

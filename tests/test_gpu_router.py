@@ -223,3 +223,19 @@ def test_projection_of_few_tokens(B, n, dm, dtype, iters):
     """Sixteen tokens per work-group up to 8192 tokens in all, the last one partly filled; the same sums as with more."""
     wl = workloads.Workload("r", 65, B, 1, 1, n, 64, dtype, 7, 2, 16, mixture=3)
     check_route(wl, workloads.make_router_inputs(wl, "cuda", d_model=dm, d_g=16), iters)
+
+
+@pytest.mark.parametrize("B,n,K,iters", [(1, 100, 32, 3), (2, 256, 32, 2), (1, 40, 24, 0), (3, 1024, 32, 2), (1, 8000, 32, 2), (2, 4000, 20, 3), (1, 30000, 4, 2)])
+def test_route_stays_in_its_workspace(B, n, K, iters):
+    wl = workloads.Workload("r", 66, B, 1, 1, n, 64, "bf16", K, 2, 16, mixture=3)
+    rin = workloads.make_router_inputs(wl, "cuda", d_model=64, d_g=16)
+    rp = focus.make_route_params(B, n, 64, 16, K, 2, dtype="bf16", sinkhorn_iters=iters, tau=0.1)
+    size = focus.alloc_route_workspace(rp).numel()
+    buf = torch.full((size + 4096,), 0x5a, dtype=torch.uint8, device="cuda")
+    masks = torch.empty((B, n), dtype=torch.int32, device="cuda")
+    soft = torch.empty((B, n, K), dtype=torch.float64, device="cuda")
+    focus.focus_route(rp, rin["hidden"], rin["w_g"], rin["router_centroids"], buf[:size], masks, soft)
+    torch.cuda.synchronize()
+    assert (buf[size:] == 0x5a).all()
+    m_ref, _, g_ref = oracle_route(wl, rin, iters)
+    assert (np.abs(soft.cpu().numpy() - g_ref) <= SOFT_RTOL * np.abs(g_ref)).all()
