@@ -114,7 +114,6 @@ __global__ __launch_bounds__(64 * short_waves(D), short_waves(D) / 4) void attn_
     const unsigned pitch = A.pitch_bytes;
     const float scale = A.scale, cap = A.softcap;
     const float sl2 = cap > 0.f ? LOG2E : scale * LOG2E;     // logits (scores without a cap) to log2 units
-    const float two_over_cap = cap > 0.f ? 2.f * LOG2E * scale / cap : 0.f;
     bf16x8 gqh[SOFT + 1], gql[SOFT + 1];          // the row's assignment times the slope
     const float* gbase = SOFT ? A.g + (size_t)W.b * n * A.K : nullptr;
     // components 16 * ks + 8 * hh .. + 7 of the assignment of position pos
@@ -257,10 +256,11 @@ __global__ __launch_bounds__(64 * short_waves(D), short_waves(D) / 4) void attn_
             }
         }
         // softmax step in log2 units: p = 2^(s * sl2 - m), one rounding in the exponent (a row's m cancels)
+        // cap * tanh(s * scale / cap), the quotient rounded once, in place of a division per score.  (As 1 - 2 / (1 + e^(2z)) the
+        // difference cancels where z is small: logits of unit variance at cap 50 off by up to 9e-6, here by 6e-7.)
         if (cap > 0.f) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r)          // cap * tanh(z), z = s * scale / cap, as 1 - 2 / (1 + e^(2z))
-                s[r] = cap - 2.f * cap * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(s[r] * two_over_cap));
+            for (int r = 0; r < 16; ++r) s[r] = cap * tanhf(fmaf(s[r], A.cap_ratio, s[r] * A.cap_rest));
         }
         if (!all_ok) {
 #pragma unroll
@@ -402,14 +402,21 @@ __global__ __launch_bounds__(64 * short_waves(D), short_waves(D) / 4) void attn_
 //            256: 256 x 1024 58.3 / 55.0;  512 x 640 60.5 / 55.0, 768 61.6 / 61.0;  4096 x 640 168 / 165
 //   otherwise 64: 256 x 1024 32.0 / 30.7;  512 x 768 34.5 / 31.9;  4096 x 512 78.0 / 75.9, 640 79.6 / 103
 //            80: 1024 x 512 41.9 / 40.4;  2048 x 512 56.0 / 58.0;   128: 512 x 512 41.4 / 35.9;  1024 x 256 47.8 / 32.8, 512 49.2 / 50.9;   256: 256 x 768 55.1 / 52.0
+// A softcap costs a score more here (tanh) than in the tiles (a polynomial), so that some lines lie lower with one: causal ones, whose
+// work-groups differ in length, by an eighth; others by a work-group per compute unit.  With cap 50, causal 64: 512 x 896 35.4 / 34.5,
+// 1024 35.9 / 36.2;  256: 512 x 560 61.4 / 60.5;  1024 x 544 78.9 / 76.6, 640 78.6 / 86.0;  4096 x 512 184 / 162, 640 185 / 207;
+// otherwise 64: 256 x 768 30.2 / 26.3, 896 30.6 / 32.3;  512 x 512 34.5 / 27.2, 672 35.0 / 36.1;  96: 1024 x 512 48.1 / 43.4;  128: 512 x 512
+// 42.4 / 36.1;  256: 256 x 512 51.7 / 42.5, 672 53.8 / 57.8;  512 x 384 58.7 / 63.2.
 bool short_attention(const Layout& L)
 {
     const long long groups = (long long)L.B * L.Hq * ((L.n + 31) / 32);
     const bool fits = L.dtype != 0 && L.NC == 1 && (L.masked || L.dense) && !L.soft && !L.local_only && !L.merge_prev && L.BQ == 128 &&
                       (uint64_t)L.ks[2] * 2 < (1u << 24) && (uint64_t)L.n * (uint64_t)L.ks[2] * 2 < 0xffffffffull;
     const bool wide = L.d >= 128;
-    const int most = L.causal ? (L.n <= (wide ? 256 : 512) ? 1024 : (L.d == 256 || (wide && L.n > 1024)) ? 640 : 768)
+    int most = L.causal ? (L.n <= (wide ? 256 : 512) ? 1024 : (L.d == 256 || (wide && L.n > 1024)) ? 640 : 768)
                               : L.n <= 256 ? (wide ? 768 : 1024) : L.n <= 512 ? (wide ? 512 : 768) : (wide || (L.d == 80 && L.n > 1024)) ? 256 : 512;
+    if (L.softcap > 0.f && L.causal && (L.d == 64 ? L.n <= 512 : L.d == 256)) most -= most / 8;
+    if (L.softcap > 0.f && !L.causal && L.n <= 512 && L.d != 128) most -= 256;
     return fits && groups <= most && L.n <= 4096;
 }
 

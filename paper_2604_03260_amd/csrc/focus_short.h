@@ -16,6 +16,7 @@ struct ShortArgs {
     unsigned pitch_bytes;                         // of k and v, position; a head's rows lie within 4 GiB (the launch checks)
     int B, Hq, Hkv, n, NKP, window, causal, dense, pair_set, default_map;
     float scale, softcap;
+    float cap_ratio, cap_rest;                    // scale / softcap and what its rounding left off
     int groups;                                   // of 32 rows
     const float* g;                               // soft gate: assignments [B,n,K] and -lambda * log2(e)
     float gate_slope;
@@ -37,6 +38,8 @@ inline ShortArgs short_args(const Layout& L, const HeadMap& hm, const void* q, c
     A.default_map = (L.Hq % L.Hkv == 0) ? 1 : 0;
     for (int h = 0; A.default_map && h < L.Hq; ++h) A.default_map = hm.kv[h] == h / (L.Hq / L.Hkv);
     A.scale = L.scale; A.softcap = L.softcap;
+    const double ratio = L.softcap > 0.f ? (double)L.scale / (double)L.softcap : 0.0;
+    A.cap_ratio = (float)ratio; A.cap_rest = (float)(ratio - (double)A.cap_ratio);
     A.groups = (L.n + 31) / 32;
     A.g = nullptr; A.gate_slope = L.gate_slope; A.K = L.K;
     return A;

@@ -1,6 +1,7 @@
 """The kernel for short 16-bit problems and the fp32 kernel for rows in position order at the edges of its 32-row groups, 32-key units and wavefronts, every head dim; and the
 tiled kernel on the masked layout with more heads than the short one takes."""
 import pytest
+import torch
 
 from paper_2604_03260_amd import focus, workloads
 from tests import harness
@@ -68,3 +69,20 @@ def test_rows_with_large_norms_in_tiles():
     # 2^-9 of themselves is off by at most that factor, its logarithm by 2^-9, and logits of a few hundred by fp32 rounding
     assert (got["out"].float() - ref["out"].float()).abs().max() <= 2e-2
     assert ((got["lse"] - ref["lse"]).abs() <= 2.0 ** -9 + 1e-4 * ref["lse"].abs()).all()
+
+
+@pytest.mark.parametrize("d,dtype,cap", [(64, "bf16", 50.0), (80, "f16", 30.0), (128, "f16", 50.0), (256, "bf16", 5.0)])
+def test_softcap_of_single_pairs_keeps_32_bits(d, dtype, cap):
+    """Rows that attend only their own key: lse is the capped logit, from a product whose sum is exact (halves of small whole numbers).
+    The quotient, tanh (5 units in the last place at most), the product with the cap and the way to log2 units and back, two
+    roundings each, are 12 roundings of 2^-24 relative; the one probability is 1."""
+    wl = workloads.Workload("sc", 503, 2, 8, 4, 90, d, dtype, 32, 1, 1, softcap=cap)
+    inp = workloads.make_inputs(wl, "cuda")
+    for x in ("q", "k"):
+        inp[x] = (inp[x].float() * 2.0).round().clamp(-4, 4).mul(0.5).to(inp[x].dtype)
+    res = harness.run_gpu(wl, inp, scale=0.125)
+    alone = (res["row_pairs"] == 1).cpu()
+    logit = (inp["q"].double() * inp["k"].double().repeat_interleave(2, dim=1)).sum(-1).cpu() * 0.125
+    want = cap * torch.tanh(logit / cap)
+    assert alone.sum() > 100 and want[alone].abs().max() > 1.0
+    assert ((res["lse"].cpu().double() - want)[alone].abs() <= 12 * 2.0 ** -24 * want[alone].abs()).all()
