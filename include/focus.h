@@ -177,7 +177,12 @@ focus_status focus_route_workspace_size(const focus_route_params *rp, size_t *by
  * hidden, w_g [d_model,d_g] fp32, centroids [K,d_g] fp32, route_workspace (256-byte aligned),
  * token_masks and soft are DEVICE pointers; rp is a HOST pointer.  Only enqueues on `stream`.
  * Scores so far apart that a whole row or column of Q underflows give NaN rows, as the
- * recipe itself does. */
+ * recipe itself does.
+ * The rounds run in one launch where the sequences are few and short enough.  Its work-groups wait for each other's column sums
+ * when they are resident together; one that has waited some milliseconds computes them itself, so the call needs no share of the
+ * device for itself, gives the same bits whatever runs beside it, and is only slower then.  The environment variable
+ * FOCUS_SINKHORN_LOOKS (tests and measurements), read by the call, is the number of looks for a sum before that, 4096 if unset;
+ * negative: a launch per round. */
 focus_status focus_route(const focus_route_params *rp, const void *hidden, const float *w_g,
                          const float *centroids, void *route_workspace, size_t workspace_bytes,
                          uint32_t *token_masks, double *soft, void *stream);

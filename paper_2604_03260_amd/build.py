@@ -59,7 +59,9 @@ def check_no_spills(remarks):
 # falls below is refused.  (mangled-name pattern, wavefronts)
 MIN_WAVES = {"focus_assign.hip": [(r"12score_kernelI\w+Li32ELb[01]E", 2), (r"12score_kernelI(t|\w+f16_bitsE)Li16ELb[01]E", 4),
                                   (r"12score_kernelI(t|\w+f16_bitsE)Li8ELb[01]E", 5), (r"12score_kernelI(t|\w+f16_bitsE)Li4ELb[01]E", 4)],
-             "focus_route.hip": [(r"20route_project_kernelI\w+Li64ELi4E", 2), (r"20route_project_kernelIfLi32ELi4E", 4)]}
+             "focus_route.hip": [(r"20route_project_kernelI\w+Li64ELi4E", 2), (r"20route_project_kernelIfLi32ELi4E", 4),
+                                 # (two work-groups per compute unit is what sink_groups counts on)
+                                 (r"22sinkhorn_rounds_kernelILi[48]ELi\d+E", 2), (r"22sinkhorn_rounds_kernelILi16ELi2E", 2)]}
 
 
 def check_waves(remarks, rules):

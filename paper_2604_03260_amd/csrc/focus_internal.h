@@ -185,6 +185,7 @@ struct RouteLayout {
     int nproj;                 // work-groups of the projection per sequence = ceil(n / route_tokens_per_group)
     int nsink;                 // work-groups of a Sinkhorn pass per sequence (<= 256)
     int sink_tokens;           // tokens per Sinkhorn work-group
+    int nround;                // work-groups per sequence of the launch that does all rounds, 0 = a launch per round (launch_route sets it)
     size_t off_S;              // [B][n][K] fp64: scores, then exp((S - max)/tau) in place
     size_t off_maxpart;        // [B][nproj] fp64
     size_t off_colpart;        // [2][B][nsink][KP] fp64 column partial sums, ping-pong between passes

@@ -12,8 +12,8 @@
 // Kernels:
 //   route_project     a wavefront = 16 tokens x all router outputs on the fp64 matrix cores (see the kernel); writes S,
 //                     the work-group's largest score, and the masks directly when no Sinkhorn is asked;
-//   sinkhorn_rounds   Sinkhorn in one launch wherever its rows fit the registers of work-groups that are resident at once
-//                     (sink_groups); the same sums as
+//   sinkhorn_rounds   Sinkhorn in one launch wherever its rows fit the registers of few enough work-groups (sink_groups); the
+//                     same sums as
 //   sinkhorn_pass     a launch per round: Sinkhorn as diagonal scaling: Q = diag(u) E diag(v) with E = exp((S - max)/tau).
 //                     A round is  v_g = 1 / sum_i u_i E[i,g],  u_i = 1 / sum_g E[i,g] v_g,  so one pass
 //                     over E per round: every work-group first folds the previous pass's per-block
@@ -21,6 +21,8 @@
 //                     rows and leaves its own partial sums for the next pass.  The last pass writes
 //                     the masks (ties to the smaller group index) and, if asked, the soft assignment.
 #include "focus_internal.h"
+#include <algorithm>
+#include <cstdlib>
 #include <mutex>
 #include <type_traits>
 
@@ -128,27 +130,42 @@ __device__ inline uint32_t topk_mask(const double (&s)[KP], int K, int topk)
 
 // ---------------------------------------------------------------- how the Sinkhorn rounds are launched
 // Groups padded to a power of two, as the kernels hold them.
-__host__ __device__ constexpr int sink_kp(int K) { return K <= 4 ? 4 : K <= 8 ? 8 : K <= 16 ? 16 : 32; }
-// All rounds in one launch: work-groups per sequence, or 0 where the rows do not fit the registers (64 doubles a thread) or
-// there are too many sequences for the work-groups to be resident at once, which they have to be as soon as they wait for each
-// other (at most 128 of 256 threads on 256 compute units; other launches on the device end without waiting for these).
+constexpr int sink_kp(int K) { return K <= 4 ? 4 : K <= 8 ? 8 : K <= 16 ? 16 : 32; }
+// Rows per thread of an instantiation for `tokens` tokens of a work-group (0: more than pays, or than the registers hold, 64 doubles a
+// thread.  Of up to 4 groups 14, below the 16 that they would hold: 200000 tokens, a launch per round / one 127 / 123 us, 262144 136.5 / 139).
+constexpr int sink_rows(int kp, int tokens)
+{
+    const int rows = (tokens + 255) / 256, most = kp == 4 ? 14 : 64 / kp;
+    return rows > most ? 0 : rows <= 2 ? 2 : rows <= 4 ? 4 : rows <= 8 ? 8 : 16;
+}
+// Work-groups of an instantiation that a compute unit holds (its launch bounds): 16 and 32 padded groups with 64 doubles a thread take all
+// registers of a SIMD.
+constexpr int sink_resident(int kp, int rows) { return kp >= 16 && kp * rows >= 64 ? 1 : 2; }
+// All rounds in one launch: work-groups per sequence, or 0 where the rows do not fit the registers or there are too many sequences.
+// Work-groups that exchange their sums should be resident together; one that is left waiting computes the others' sums itself
+// (sinkhorn_rounds_kernel), which is right but slow.  So a launch takes at most a quarter of the work-groups that the device holds: four
+// launches at once, one on each hardware queue, still fit.
 // One work-group as long as its rows take less time than an exchange.  Routing of a sequence, a launch per round / one work-group /
 // several (us): 2 x 500 tokens, K = 8 (d_model 3840) 126 / 104;  4493, K = 8 76.5 / - / 66.3;  32768, K = 4 199 / - / 187 (the rounds alone 51 / 30).  K = 4, d_model 768: 2000
 // tokens 40 in one, 4000 37 in several.
-__host__ __device__ inline int sink_groups(const RouteLayout& R)
+inline int sink_groups(const RouteLayout& R, int compute_units)
 {
-    const int most = 256 * 64 / sink_kp(R.K);     // tokens of a work-group
-    if ((long long)R.n * sink_kp(R.K) <= 6144) return 1;
-    int g = R.nsink / 2 < 64 ? R.nsink / 2 : 64;
-    if (g * R.B > 128) g = 128 / R.B;
-    return g >= 2 && (R.n + g - 1) / g <= most ? g : R.n <= most ? 1 : 0;
+    const int kp = sink_kp(R.K);
+    if ((long long)R.n * kp <= 6144) return 1;
+    for (int per_unit = 2; per_unit >= 1; --per_unit) {
+        const int g = std::min({R.nsink / 2, 64, compute_units / 4 * per_unit / R.B});
+        const int rows = g >= 2 ? sink_rows(kp, (R.n + g - 1) / g) : 0;
+        if (rows > 0 && sink_resident(kp, rows) >= per_unit) return g;
+    }
+    return sink_rows(kp, R.n) > 0 ? 1 : 0;
 }
 // Column sums on their way between the work-groups: [3][work-groups][K] per sequence, in the place of the partial sums of the
 // launches.  A slot is EMPTY until its sum is there.
 constexpr unsigned long long SINK_EMPTY = ~0ull;
+constexpr int SINK_LOOKS = 4096;                  // for a sum that is not there yet, about a microsecond each
 __device__ inline unsigned long long* sink_slots(const RouteLayout& R, char* ws, int b)
 {
-    return (unsigned long long*)(ws + R.off_colpart) + (size_t)b * (3 * sink_groups(R) * R.K);     // at most 48 of the 64 * nsink words
+    return (unsigned long long*)(ws + R.off_colpart) + (size_t)b * (3 * R.nround * R.K);     // at most 48 of the 64 * nsink words
 }
 
 // ---------------------------------------------------------------- projection + scores
@@ -366,10 +383,9 @@ __global__ __launch_bounds__(64 * NW, route_waves<T>(DG)) void route_project_ker
         ((double*)(ws + R.off_maxpart))[(size_t)b * R.nproj + blockIdx.x] = m;
     }
     if (R.iters > 0) {
-        const int groups = sink_groups(R);
         unsigned long long* slots = sink_slots(R, ws, b);
-        if (groups > 1)                                  // (one work-group exchanges nothing, and a short sequence has no space for it)
-            for (int i = blockIdx.x * NTHR + tid; i < 3 * groups * K; i += gridDim.x * NTHR) slots[i] = SINK_EMPTY;
+        if (R.nround > 1)                                // (one work-group exchanges nothing, and a short sequence has no space for it)
+            for (int i = blockIdx.x * NTHR + tid; i < 3 * R.nround * K; i += gridDim.x * NTHR) slots[i] = SINK_EMPTY;
     }
     if (tid < rows) {
         const size_t tg = (size_t)b * n + tok0 + tid;
@@ -505,32 +521,43 @@ __global__ __launch_bounds__(256) void sinkhorn_pass_kernel(RouteLayout R, int p
 // one exchange of them.  Work-group w leaves its sums of round p in slot p % 3 and takes those of the others as they come (8 bytes
 // a sum, whole: no flag beside it); they are added in the order of the work-groups, so the result does not depend on who came first.
 // Once it has everybody's sums of round p, everybody is done with those of round p - 1, and it empties its slot of that round,
-// before it leaves its sums of round p + 1: whoever sees those sees the empty slot.  A wait ends after some seconds whatever happens.
+// before it leaves its sums of round p + 1: whoever sees those sees the empty slot.
+// Nothing makes the work-groups of a launch resident together (a device of fewer units, a stream that is kept to some of them, other
+// launches that wait), so none relies on it: one that has looked `looks` times for a sum goes on alone.  It takes the rows of every
+// work-group in turn and adds up their sums itself, in the same order, and leaves no more of its own, so that the others do the same a
+// round later at the latest; only its own rows are its to write.  Nobody leaves sums of round p + 1 without having seen all of round
+// p, so a slot never holds those of a later round than the one that is looked for.  The result is the same bits either way, and
+// every wait ends: with the sum, or as the last wait of its work-group.  Alone, a round takes 0.02 ms for 4096 tokens of 4 groups, 0.13
+// for 32768, 0.7 for 131072 of 8, 1.0 for 32768 of 32.
 template <int KP, int R>
-__global__ __launch_bounds__(256) void sinkhorn_rounds_kernel(RouteLayout L, int tokens, char* __restrict__ ws, uint32_t* __restrict__ masks,
-                                                              double* __restrict__ soft)
+__global__ __launch_bounds__(256, sink_resident(KP, R)) void sinkhorn_rounds_kernel(RouteLayout L, int tokens, int looks, char* __restrict__ ws,
+                                                                                    uint32_t* __restrict__ masks, double* __restrict__ soft)
 {
     constexpr int EX = 64 * 32;                   // sums of a round at most
     __shared__ double s_part[4][KP], s_v[KP], s_m[4];
     __shared__ double s_ex[EX];
+    __shared__ int s_late;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int blk = blockIdx.x, nwg = gridDim.x, b = blockIdx.y;
     const int n = L.n, K = L.K;
     const double* S = (const double*)(ws + L.off_S) + (size_t)b * n * K;
     unsigned long long* slots = sink_slots(L, ws, b);
-    const int t0 = blk * tokens, t1 = min(n, t0 + tokens);
     double r[R][KP];
+    auto load = [&](int of) {                     // the scores of work-group `of`
 #pragma unroll
-    for (int t = 0; t < R; ++t) {
-        const int i = t0 + t * 256 + tid;
-        if (K == KP) {
-            const double* src = S + (size_t)min(i, n - 1) * KP;
-            __builtin_memcpy(r[t], __builtin_assume_aligned(src, 16), sizeof(r[t]));
-        } else {
+        for (int t = 0; t < R; ++t) {
+            const int i = min(of * tokens + t * 256 + tid, n - 1);
+            if (K == KP) {
+                const double* src = S + (size_t)i * KP;
+                __builtin_memcpy(r[t], __builtin_assume_aligned(src, 16), sizeof(r[t]));
+            } else {
 #pragma unroll
-            for (int g = 0; g < KP; ++g) r[t][g] = g < K ? S[(size_t)min(i, n - 1) * K + g] : 0.0;
+                for (int g = 0; g < KP; ++g) r[t][g] = g < K ? S[(size_t)i * K + g] : 0.0;
+            }
         }
-    }
+    };
+    auto there = [&](int of, int t) { return of * tokens + t * 256 + tid < min(n, (of + 1) * tokens); };
+    load(blk);
     double smax;
     {
         const double* mp = (const double*)(ws + L.off_maxpart) + (size_t)b * L.nproj;
@@ -538,32 +565,62 @@ __global__ __launch_bounds__(256) void sinkhorn_rounds_kernel(RouteLayout L, int
         for (int i = tid; i < L.nproj; i += 256) m = fmax(m, mp[i]);
         m = wave_max(m);
         if (lane == 0) s_m[wave] = m;
+        if (tid == 0) s_late = 0;
         __syncthreads();
         smax = fmax(fmax(s_m[0], s_m[1]), fmax(s_m[2], s_m[3]));
     }
-    double cs[KP];
+    auto expand = [&](int of) {                   // to rows of E
 #pragma unroll
-    for (int g = 0; g < KP; ++g) cs[g] = 0.0;
+        for (int t = 0; t < R; ++t)
 #pragma unroll
-    for (int t = 0; t < R; ++t) {
-        const bool there = t0 + t * 256 + tid < t1;
+            for (int g = 0; g < KP; ++g) r[t][g] = there(of, t) && g < K ? exp((r[t][g] - smax) / L.tau) : 0.0;
+    };
+    expand(blk);
+    double v[KP];
 #pragma unroll
-        for (int g = 0; g < KP; ++g) {
-            r[t][g] = there && g < K ? exp((r[t][g] - smax) / L.tau) : 0.0;
-            cs[g] = __dadd_rn(cs[g], r[t][g]);
-        }
-    }
+    for (int g = 0; g < KP; ++g) v[g] = 1.0;
+    bool alone = false;                           // (uniform over the work-group)
     for (int p = 0; p < L.iters; ++p) {
-        // column sums of the work-group, then of the sequence: s_v = 1 / sum
-        const double ws_sum = wave_sum_columns<KP>(cs, lane);
-        if ((lane & (64 / KP - 1)) == 0) s_part[wave][wave_column<KP>(lane)] = ws_sum;
-        __syncthreads();
-        double mine = 0.0;
-        if (tid < K) mine = __dadd_rn(__dadd_rn(s_part[0][tid], s_part[1][tid]), __dadd_rn(s_part[2][tid], s_part[3][tid]));
-        if (nwg == 1) {
-            if (tid < K) s_v[tid] = 1.0 / mine;
-        } else {
-            unsigned long long* at = slots + (size_t)(p % 3) * nwg * K;
+        unsigned long long* at = slots + (size_t)(p % 3) * nwg * K;
+        int of = alone ? 0 : blk;
+        for (;;) {
+            if (alone) {
+                load(of);
+                expand(of);
+            }
+            // column sums of the work-group
+            double cs[KP];
+#pragma unroll
+            for (int g = 0; g < KP; ++g) cs[g] = 0.0;
+#pragma unroll
+            for (int t = 0; t < R; ++t) {
+                if (!there(of, t)) continue;
+                double u = 1.0;
+                if (p > 0) {
+                    double rs = 0.0;
+#pragma unroll
+                    for (int g = 0; g < KP; ++g) rs = __dadd_rn(rs, g < K ? __dmul_rn(r[t][g], v[g]) : 0.0);
+                    u = 1.0 / rs;
+                }
+#pragma unroll
+                for (int g = 0; g < KP; ++g)
+                    if (g < K) cs[g] = __dadd_rn(cs[g], __dmul_rn(u, r[t][g]));
+            }
+            const double ws_sum = wave_sum_columns<KP>(cs, lane);
+            if ((lane & (64 / KP - 1)) == 0) s_part[wave][wave_column<KP>(lane)] = ws_sum;
+            __syncthreads();
+            double mine = 0.0;
+            if (tid < K) mine = __dadd_rn(__dadd_rn(s_part[0][tid], s_part[1][tid]), __dadd_rn(s_part[2][tid], s_part[3][tid]));
+            if (nwg == 1) {
+                if (tid < K) s_v[tid] = 1.0 / mine;
+                break;
+            }
+            if (alone) {
+                if (tid < K) s_ex[of * K + tid] = mine;
+                __syncthreads();                  // (s_part is written again)
+                if (++of < nwg) continue;
+                break;
+            }
             if (tid < K) {
                 unsigned long long bits = __builtin_bit_cast(unsigned long long, mine);
                 if (bits == SINK_EMPTY) bits = 0x7ff8000000000000ull;    // another NaN
@@ -572,56 +629,58 @@ __global__ __launch_bounds__(256) void sinkhorn_rounds_kernel(RouteLayout L, int
             }
             for (int i = tid; i < nwg * K; i += 256) {
                 unsigned long long x = SINK_EMPTY;
-                for (int spin = 0; spin < (1 << 22); ++spin) {
+                for (int look = 0; look < looks; ++look) {
                     x = __hip_atomic_load(at + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     if (x != SINK_EMPTY) break;
                 }
-                s_ex[i] = __builtin_bit_cast(double, x);                 // (never there: a NaN)
+                if (x == SINK_EMPTY) {
+                    s_late = 1;
+                    break;
+                }
+                s_ex[i] = __builtin_bit_cast(double, x);
             }
             __syncthreads();
-            if (p > 0 && tid < K)
-                __hip_atomic_store(slots + (size_t)((p + 2) % 3) * nwg * K + blk * K + tid, SINK_EMPTY, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (__builtin_amdgcn_readfirstlane(s_late) == 0) {
+                if (p > 0 && tid < K)
+                    __hip_atomic_store(slots + (size_t)((p + 2) % 3) * nwg * K + blk * K + tid, SINK_EMPTY, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                break;
+            }
+            alone = true;
+            of = 0;
+        }
+        if (nwg > 1) {
             for (int g = wave; g < K; g += 4) {
                 const double sum = wave_sum(lane < nwg ? s_ex[lane * K + g] : 0.0);
                 if (lane == 0) s_v[g] = 1.0 / sum;
             }
         }
         __syncthreads();
-        double v[KP];
+#pragma unroll
+        for (int g = 0; g < KP; ++g) v[g] = g < K ? s_v[g] : 1.0;
+    }
+    if (alone) {
+        load(blk);
+        expand(blk);
+    }
+#pragma unroll
+    for (int t = 0; t < R; ++t) {
+        if (!there(blk, t)) continue;
+        double e[KP], rs = 0.0;
 #pragma unroll
         for (int g = 0; g < KP; ++g) {
-            v[g] = g < K ? s_v[g] : 1.0;
-            cs[g] = 0.0;
+            e[g] = g < K ? __dmul_rn(r[t][g], v[g]) : 0.0;
+            rs = __dadd_rn(rs, e[g]);
         }
-        const bool last = p + 1 == L.iters;
+        const double u = 1.0 / rs;
+        const size_t tok = (size_t)b * n + blk * tokens + t * 256 + tid;
 #pragma unroll
-        for (int t = 0; t < R; ++t) {
-            const int i = t0 + t * 256 + tid;
-            if (i >= t1) continue;
-            double e[KP], rs = 0.0;
+        for (int g = 0; g < KP; ++g) e[g] = __dmul_rn(e[g], u);
+        masks[tok] = topk_mask<KP>(e, K, L.topk);
+        if (soft) {
 #pragma unroll
-            for (int g = 0; g < KP; ++g) {
-                e[g] = g < K ? __dmul_rn(r[t][g], v[g]) : 0.0;
-                rs = __dadd_rn(rs, e[g]);
-            }
-            const double u = 1.0 / rs;
-            if (!last) {
-#pragma unroll
-                for (int g = 0; g < KP; ++g)
-                    if (g < K) cs[g] = __dadd_rn(cs[g], __dmul_rn(u, r[t][g]));
-            } else {
-                const size_t tok = (size_t)b * n + i;
-#pragma unroll
-                for (int g = 0; g < KP; ++g) e[g] = __dmul_rn(e[g], u);
-                masks[tok] = topk_mask<KP>(e, K, L.topk);
-                if (soft) {
-#pragma unroll
-                    for (int g = 0; g < KP; ++g)
-                        if (g < K) soft[tok * K + g] = e[g];
-                }
-            }
+            for (int g = 0; g < KP; ++g)
+                if (g < K) soft[tok * K + g] = e[g];
         }
-        __syncthreads();                          // s_part, s_ex and s_v are written again
     }
 }
 
@@ -656,7 +715,15 @@ hipError_t launch_route(const RouteLayout& layout, const void* hidden, const flo
 {
     hipError_t e;
     RouteLayout R = layout;
-    const bool split = R.dg == 16 && (long long)R.B * R.n <= 8192 && (R.iters == 0 || sink_groups(R) > 0);
+    const char* env = getenv("FOCUS_SINKHORN_LOOKS");        // (tests, measurements; negative: a launch per round)
+    const int looks = env ? atoi(env) : SINK_LOOKS;
+    if (R.iters > 0 && looks >= 0) {
+        int dev = 0, units = 0;
+        if ((e = hipGetDevice(&dev)) != hipSuccess) return e;
+        if ((e = hipDeviceGetAttribute(&units, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess) return e;
+        R.nround = sink_groups(R, units);
+    }
+    const bool split = R.dg == 16 && (long long)R.B * R.n <= 8192 && (R.iters == 0 || R.nround > 0);
     if (split) {       // a largest score for every 16 tokens: behind the sums of the rounds, which take at most 48 of 64 words a sort block
         R.nproj = (R.n + 15) / 16;
         R.off_maxpart = R.off_colpart + (size_t)48 * R.B * R.nsink * 8;
@@ -666,14 +733,13 @@ hipError_t launch_route(const RouteLayout& layout, const void* hidden, const flo
     else e = launch_project<uint16_t>(R, hidden, wg, cent, ws, masks, soft, split, st);
     if (e != hipSuccess) return e;
     if (R.iters == 0) return hipSuccess;
-    const int groups = sink_groups(R);
-    if (groups > 0) {
-        const int tokens = (R.n + groups - 1) / groups, rows = (tokens + 255) / 256;
-        dim3 grid(groups, R.B);
-#define FOCUS_ROUNDS(KP_, R_) hipLaunchKernelGGL((sinkhorn_rounds_kernel<KP_, R_>), grid, dim3(256), 0, st, R, tokens, ws, masks, soft)
-        if (R.K <= 4) { if (rows <= 2) FOCUS_ROUNDS(4, 2); else if (rows <= 4) FOCUS_ROUNDS(4, 4); else if (rows <= 8) FOCUS_ROUNDS(4, 8); else FOCUS_ROUNDS(4, 16); }
-        else if (R.K <= 8) { if (rows <= 2) FOCUS_ROUNDS(8, 2); else if (rows <= 4) FOCUS_ROUNDS(8, 4); else FOCUS_ROUNDS(8, 8); }
-        else if (R.K <= 16) { if (rows <= 2) FOCUS_ROUNDS(16, 2); else FOCUS_ROUNDS(16, 4); }
+    if (R.nround > 0) {
+        const int tokens = (R.n + R.nround - 1) / R.nround, rows = sink_rows(sink_kp(R.K), tokens);
+        dim3 grid(R.nround, R.B);
+#define FOCUS_ROUNDS(KP_, R_) hipLaunchKernelGGL((sinkhorn_rounds_kernel<KP_, R_>), grid, dim3(256), 0, st, R, tokens, looks, ws, masks, soft)
+        if (R.K <= 4) { if (rows == 2) FOCUS_ROUNDS(4, 2); else if (rows == 4) FOCUS_ROUNDS(4, 4); else if (rows == 8) FOCUS_ROUNDS(4, 8); else FOCUS_ROUNDS(4, 16); }
+        else if (R.K <= 8) { if (rows == 2) FOCUS_ROUNDS(8, 2); else if (rows == 4) FOCUS_ROUNDS(8, 4); else FOCUS_ROUNDS(8, 8); }
+        else if (R.K <= 16) { if (rows == 2) FOCUS_ROUNDS(16, 2); else FOCUS_ROUNDS(16, 4); }
         else FOCUS_ROUNDS(32, 2);
 #undef FOCUS_ROUNDS
         return hipGetLastError();

@@ -217,6 +217,38 @@ def test_sinkhorn_rounds_of_scores_that_are_not_finite():
     assert all(bin(int(x)).count("1") == 2 for x in m.ravel())
 
 
+@pytest.mark.parametrize("B,n,K,topk,iters", [(1, 2000, 4, 2, 4), (2, 5000, 8, 2, 5), (1, 9000, 16, 3, 3), (1, 3001, 32, 2, 3), (3, 2500, 5, 2, 12),
+                                              (1, 40000, 16, 1, 3), (1, 131073, 4, 2, 2), (1, 60000, 7, 2, 1)])
+def test_work_groups_that_go_on_alone(B, n, K, topk, iters, monkeypatch):
+    """A work-group that has waited in vain computes the others' sums itself: none of them waits at all, some see a sum in time and
+    some do not.  The same bits as when all see each other's."""
+    wl = workloads.Workload("r", 67, B, 1, 1, n, 64, "bf16", K, topk, 16, mixture=3 if K > 4 else 0)
+    rin = workloads.make_router_inputs(wl, "cuda", d_model=64, d_g=16)
+    check_route(wl, rin, iters)
+    masks, soft = run_route(wl, rin, iters)
+    for looks in ("0", "1", "2", "5", "20"):
+        monkeypatch.setenv("FOCUS_SINKHORN_LOOKS", looks)
+        m, s = run_route(wl, rin, iters)
+        assert torch.equal(m, masks) and torch.equal(s, soft), looks
+
+
+def test_rounds_on_several_streams():
+    """Four calls at once, each with its own workspace, whose work-groups wait for each other's sums within a call."""
+    wl = workloads.Workload("r", 68, 2, 1, 1, 30000, 64, "bf16", 16, 2, 16, mixture=3)
+    rin = workloads.make_router_inputs(wl, "cuda", d_model=64, d_g=16)
+    want, want_soft = run_route(wl, rin, 10)
+    rp = focus.make_route_params(wl.B, wl.n, 64, 16, wl.K, wl.topk, dtype=wl.dtype, sinkhorn_iters=10, tau=0.1)
+    calls = [(torch.cuda.Stream(), focus.alloc_route_workspace(rp), torch.zeros_like(want), torch.zeros_like(want_soft)) for _ in range(4)]
+    torch.cuda.synchronize()
+    for _ in range(3):
+        for stream, ws, masks, soft in calls:
+            with torch.cuda.stream(stream):
+                focus.focus_route(rp, rin["hidden"], rin["w_g"], rin["router_centroids"], ws, masks, soft)
+    torch.cuda.synchronize()
+    for _, _, masks, soft in calls:
+        assert torch.equal(masks, want) and torch.equal(soft, want_soft)
+
+
 @pytest.mark.parametrize("n,dm,dtype,iters", [(1, 64, "bf16", 0), (15, 72, "f32", 4), (17, 8, "f16", 0), (4096, 136, "bf16", 10), (4097, 136, "bf16", 10), (2731, 200, "f32", 0)])
 @pytest.mark.parametrize("B", [1, 2])
 def test_projection_of_few_tokens(B, n, dm, dtype, iters):
