@@ -393,30 +393,35 @@ __global__ __launch_bounds__(64 * short_waves(D), short_waves(D) / 4) void attn_
 
 }  // namespace
 
-// Where one launch of short chains beats the staged tiles: while its work-groups are at most two or three per compute unit
+// Where one launch of short chains beats the staged tiles: while its work-groups are at most two to four per compute unit
 // (those of a causal launch differ in length, the later ones fill the gaps), fewer the longer the walk, whose units load more
-// bytes per key.  Bucketing and attention, K = 4 top-2, tiled / this kernel (us), measured over 128 .. 4096 tokens and 64 .. 1536 groups:
-//   causal   64: 512 x 384 groups 32.5 / 19.9, 1024 35.8 / 32.0, 1536 39.3 / 44.9;  4096 x 768 79.3 / 65.1, 1024 79.7 / 78.0
-//            80: 512 x 1024 37.1 / 34.0;  4096 x 768 88.4 / 80.0, 1024 87.7 / 96.0
-//            128: 512 x 768 43.3 / 37.2, 1024 44.6 / 43.9;  1024 x 768 51.5 / 49.8, 1024 51.9 / 60.8;  4096 x 640 104 / 97, 768 104 / 110
-//            256: 256 x 1024 58.3 / 55.0;  512 x 640 60.5 / 55.0, 768 61.6 / 61.0;  4096 x 640 168 / 165
-//   otherwise 64: 256 x 1024 32.0 / 30.7;  512 x 768 34.5 / 31.9;  4096 x 512 78.0 / 75.9, 640 79.6 / 103
-//            80: 1024 x 512 41.9 / 40.4;  2048 x 512 56.0 / 58.0;   128: 512 x 512 41.4 / 35.9;  1024 x 256 47.8 / 32.8, 512 49.2 / 50.9;   256: 256 x 768 55.1 / 52.0
-// A softcap costs a score more here (tanh) than in the tiles (a polynomial), so that some lines lie lower with one: causal ones, whose
-// work-groups differ in length, by an eighth; others by a work-group per compute unit.  With cap 50, causal 64: 512 x 896 35.4 / 34.5,
-// 1024 35.9 / 36.2;  256: 512 x 560 61.4 / 60.5;  1024 x 544 78.9 / 76.6, 640 78.6 / 86.0;  4096 x 512 184 / 162, 640 185 / 207;
-// otherwise 64: 256 x 768 30.2 / 26.3, 896 30.6 / 32.3;  512 x 512 34.5 / 27.2, 672 35.0 / 36.1;  96: 1024 x 512 48.1 / 43.4;  128: 512 x 512
-// 42.4 / 36.1;  256: 256 x 512 51.7 / 42.5, 672 53.8 / 57.8;  512 x 384 58.7 / 63.2.
+// bytes per key.  The softcap does not decide: the bucketing leaves out what only the tiles need, and may have been given parameters
+// without it.  It costs a score more here (tanh) than in the tiles (a polynomial), so the lines lie where the one with a cap
+// of 50 is, if that is the lower one.  Bucketing and attention, MHA, K = 4 top-2, window 128, tiled / this kernel, then with the cap (us):
+//   causal   64: 512 x 1024 groups 33.1 / 31.8, 35.8 / 36.2;  1024 x 768 37.5 / 34.8, 42.8 / 40.2;  4096 x 768 79.5 / 71.6, 101 / 93
+//            80: 512 x 1024 36.9 / 33.4, 39.6 / 37.9;  4096 x 768 87.6 / 86.7, 110 / 109
+//            96: 512 x 1024 39.3 / 33.8, 42.0 / 38.5;  4096 x 768 90.9 / 83.5, 111 / 104
+//            128: 256 x 1024 37.4 / 32.3, 38.8 / 35.4;  512 x 768 42.4 / 37.2;  1024 x 768 51.3 / 51.2, 56.4 / 52.4;  4096 x 640 104 / 102, 126 / 104
+//            256: 256 x 896 56.1 / 51.5, 56.7 / 56.4, 1024 57.3 / 55.2, 58.5 / 60.4;  512 x 560 61.2 / 56.1, 63.1 / 61.0, 640 60.0 / 57.7, 62.0 / 63.6
+//                 1024 x 544 75.7 / 70.2, 79.6 / 79.1;  4096 x 512 168 / 147, 183 / 176, 640 168 / 188, 185 / 225
+//   otherwise 64: 256 x 768 26.6 / 22.9, 27.8 / 25.5, 1024 28.1 / 28.1, 29.5 / 31.2;  512 x 512 29.5 / 23.7, 32.0 / 27.2, 768 31.1 / 30.7, 33.8 / 35.8
+//                 1024 x 512 35.7 / 34.7, 40.8 / 40.0
+//            80: 256 x 896 30.8 / 30.0, 32.2 / 33.1;  512 x 640 34.0 / 33.0, 36.3 / 37.4
+//            96: 256 x 1024 34.6 / 31.1, 36.1 / 34.2;  512 x 768 37.0 / 34.1, 39.7 / 38.3;  1024 x 512 40.7 / 38.8, 45.6 / 44.3
+//            128: 256 x 768 37.1 / 32.7, 38.2 / 35.5;  512 x 512 39.6 / 35.6, 42.2 / 37.0;  4096 x 256 101 / 74
+//            256: 256 x 512 52.1 / 38.9, 53.1 / 42.3, 640 52.4 / 51.0, 53.6 / 55.2;  512 x 256 54.6 / 38.0, 56.6 / 41.7, 384 57.1 / 57.0, 59.2 / 63.7
 bool short_attention(const Layout& L)
 {
     const long long groups = (long long)L.B * L.Hq * ((L.n + 31) / 32);
     const bool fits = L.dtype != 0 && L.NC == 1 && (L.masked || L.dense) && !L.soft && !L.local_only && !L.merge_prev && L.BQ == 128 &&
                       (uint64_t)L.ks[2] * 2 < (1u << 24) && (uint64_t)L.n * (uint64_t)L.ks[2] * 2 < 0xffffffffull;
-    const bool wide = L.d >= 128;
-    int most = L.causal ? (L.n <= (wide ? 256 : 512) ? 1024 : (L.d == 256 || (wide && L.n > 1024)) ? 640 : 768)
-                              : L.n <= 256 ? (wide ? 768 : 1024) : L.n <= 512 ? (wide ? 512 : 768) : (wide || (L.d == 80 && L.n > 1024)) ? 256 : 512;
-    if (L.softcap > 0.f && L.causal && (L.d == 64 ? L.n <= 512 : L.d == 256)) most -= most / 8;
-    if (L.softcap > 0.f && !L.causal && L.n <= 512 && L.d != 128) most -= 256;
+    int most;
+    if (L.causal)
+        most = L.d == 256 ? (L.n <= 256 ? 896 : 560) : L.n <= (L.d == 128 ? 256 : 512) ? 1024 : (L.d == 128 && L.n > 1024) ? 640 : 768;
+    else if (L.n <= 512)
+        most = (L.d == 96 ? 1024 : L.d == 256 ? 512 : 768) - (L.n > 256 ? 256 : 0);
+    else
+        most = (L.d >= 128 || (L.d == 80 && L.n > 1024)) ? 256 : 512;
     return fits && groups <= most && L.n <= 4096;
 }
 

@@ -86,3 +86,20 @@ def test_softcap_of_single_pairs_keeps_32_bits(d, dtype, cap):
     want = cap * torch.tanh(logit / cap)
     assert alone.sum() > 100 and want[alone].abs().max() > 1.0
     assert ((res["lse"].cpu().double() - want)[alone].abs() <= 12 * 2.0 ** -24 * want[alone].abs()).all()
+
+
+# about the limits of the launch choice, on either side of them
+@pytest.mark.parametrize("B,Hq,n,d,causal", [(7, 8, 512, 64, True), (8, 8, 512, 64, True), (15, 8, 250, 256, True), (5, 1, 4096, 256, True), (5, 8, 500, 256, True),
+                                             (14, 8, 256, 80, False), (5, 8, 512, 96, False), (5, 4, 512, 256, False), (11, 8, 250, 256, False), (1, 12, 512, 64, True)])
+def test_softcap_given_to_the_attention_alone(B, Hq, n, d, causal):
+    """The bucketing does not read the softcap: parameters without one prepare the same workspace."""
+    wl = workloads.Workload("sk", 504, B, Hq, max(1, Hq // 4), n, d, "bf16", 4, 2, 60, causal=causal, softcap=30.0)
+    inp = workloads.make_inputs(wl, "cuda")
+    want = harness.run_gpu(wl, inp)
+    p, plain = (focus.make_params(B, Hq, wl.Hkv, n, d, 4, 2, 60, causal=causal, softcap=cap) for cap in (30.0, 0.0))
+    ws = focus.alloc_workspace(p)
+    out, lse = torch.full_like(inp["q"], float("nan")), torch.empty_like(want["lse"])
+    focus.focus_assign(plain, inp["q"], inp["k"], inp["centroids"], ws)
+    focus.focus_attn_fwd(p, inp["q"], inp["k"], inp["v"], ws, out, lse)
+    torch.cuda.synchronize()
+    assert torch.equal(out, want["out"]) and torch.equal(lse, want["lse"])
