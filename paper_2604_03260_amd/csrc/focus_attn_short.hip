@@ -405,9 +405,10 @@ __global__ __launch_bounds__(64 * short_waves(D), short_waves(D) / 4) void attn_
 //            256: 256 x 896 56.1 / 51.5, 56.7 / 56.4, 1024 57.3 / 55.2, 58.5 / 60.4;  512 x 560 61.2 / 56.1, 63.1 / 61.0, 640 60.0 / 57.7, 62.0 / 63.6
 //                 1024 x 544 75.7 / 70.2, 79.6 / 79.1;  4096 x 512 168 / 147, 183 / 176, 640 168 / 188, 185 / 225
 //   otherwise 64: 256 x 768 26.6 / 22.9, 27.8 / 25.5, 1024 28.1 / 28.1, 29.5 / 31.2;  512 x 512 29.5 / 23.7, 32.0 / 27.2, 768 31.1 / 30.7, 33.8 / 35.8
-//                 1024 x 512 35.7 / 34.7, 40.8 / 40.0
+//                 1024 x 512 35.7 / 34.7, 40.8 / 40.0;  2048 x 512 48.9 / 49.4, 59.6 / 61.5;  4096 x 512 75.6 / 79.6, 97.3 / 105
+//                 dense (no memberships to test): 4096 x 512 83.3 / 69.1, 102 / 95
 //            80: 256 x 896 30.8 / 30.0, 32.2 / 33.1;  512 x 640 34.0 / 33.0, 36.3 / 37.4
-//            96: 256 x 1024 34.6 / 31.1, 36.1 / 34.2;  512 x 768 37.0 / 34.1, 39.7 / 38.3;  1024 x 512 40.7 / 38.8, 45.6 / 44.3
+//            96: 4096 x 384 90.8 / 96.4, 110 / 120;  256 x 1024 34.6 / 31.1, 36.1 / 34.2;  512 x 768 37.0 / 34.1, 39.7 / 38.3;  1024 x 512 40.7 / 38.8, 45.6 / 44.3
 //            128: 256 x 768 37.1 / 32.7, 38.2 / 35.5;  512 x 512 39.6 / 35.6, 42.2 / 37.0;  4096 x 256 101 / 74
 //            256: 256 x 512 52.1 / 38.9, 53.1 / 42.3, 640 52.4 / 51.0, 53.6 / 55.2;  512 x 256 54.6 / 38.0, 56.6 / 41.7, 384 57.1 / 57.0, 59.2 / 63.7
 bool short_attention(const Layout& L)
@@ -421,7 +422,7 @@ bool short_attention(const Layout& L)
     else if (L.n <= 512)
         most = (L.d == 96 ? 1024 : L.d == 256 ? 512 : 768) - (L.n > 256 ? 256 : 0);
     else
-        most = (L.d >= 128 || (L.d == 80 && L.n > 1024)) ? 256 : 512;
+        most = (L.d >= 128 || (L.masked && L.n > 1024)) ? 256 : 512;
     return fits && groups <= most && L.n <= 4096;
 }
 

@@ -3,6 +3,8 @@ kernel needs (key copy, key norms, membership words), so whatever the bucketing 
 import os
 import subprocess
 
+import pytest
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 SOURCE = os.path.join(ROOT, "paper_2604_03260_amd", "csrc", "focus_attn_short.hip")
 
@@ -12,8 +14,15 @@ PROGRAM = """
 #include <initializer_list>
 struct Layout { int B, Hq, n, d, dtype, NC, masked, dense, soft, local_only, merge_prev, BQ, causal; long long ks[3]; float softcap; };
 %s
-int main()
+int main(int argc, char**)
 {
+    int d, n, groups, causal, dense;
+    while (argc > 1 && scanf("%%d %%d %%d %%d %%d", &d, &n, &groups, &causal, &dense) == 5) {
+        const int per = (n + 31) / 32;
+        Layout L{groups / per, 1, n, d, 1, 1, !dense, dense, 0, 0, 0, 128, causal, {1LL * n * d, 1LL * n * d, d}, 0.f};
+        printf("%%d\\n", (int)short_attention(L));
+    }
+    if (argc > 1) return 0;
     long long taken = 0, left = 0;
     for (int d : {64, 80, 96, 128, 256})
         for (int causal : {0, 1})
@@ -32,12 +41,39 @@ int main()
 """
 
 
-def test_the_softcap_does_not_decide(tmp_path):
+# d, tokens, work-groups of 32 rows, causal, dense; microseconds of bucketing and attention: tiled, short, tiled with a cap of 50, short with it
+MEASURED = [
+    (64, 512, 1024, 1, 0, 33.1, 31.8, 35.8, 36.2), (64, 4096, 768, 1, 0, 79.5, 71.6, 101, 93.2), (80, 4096, 768, 1, 0, 87.6, 86.7, 110, 109),
+    (96, 4096, 768, 1, 0, 90.9, 83.5, 111, 104), (128, 256, 1024, 1, 0, 37.4, 32.3, 38.8, 35.4), (128, 1024, 768, 1, 0, 51.3, 51.2, 56.4, 52.4),
+    (128, 4096, 640, 1, 0, 104, 102, 126, 104), (256, 256, 1024, 1, 0, 57.3, 55.2, 58.5, 60.4), (256, 1024, 640, 1, 0, 75.2, 78.5, 79.3, 89.2),
+    (256, 4096, 640, 1, 0, 168, 188, 185, 225), (256, 4096, 512, 1, 0, 168, 147, 183, 176),
+    (64, 256, 768, 0, 0, 26.6, 22.9, 27.8, 25.5), (64, 256, 896, 0, 0, 27.3, 27.8, 28.7, 31.1), (64, 512, 640, 0, 0, 30.2, 30.3, 32.9, 35.0),
+    (96, 512, 768, 0, 0, 37.0, 34.1, 39.7, 38.3), (64, 1024, 512, 0, 0, 35.7, 34.7, 40.8, 40.0), (64, 4096, 512, 0, 0, 75.6, 79.6, 97.3, 105),
+    (96, 4096, 384, 0, 0, 90.8, 96.4, 110, 120), (64, 2048, 512, 0, 0, 48.9, 49.4, 59.6, 61.5), (64, 4096, 256, 0, 0, 74.6, 46.8, 96.5, 60.2),
+    (64, 4096, 512, 0, 1, 83.3, 69.1, 102, 94.8), (80, 4096, 512, 0, 1, 98.5, 86.8, 116, 111), (128, 4096, 256, 0, 1, 114, 77.8, 133, 80.7),
+    (256, 256, 640, 0, 0, 52.4, 51.0, 53.6, 55.2), (256, 512, 512, 0, 0, 59.6, 59.5, 61.3, 66.0), (256, 4096, 256, 0, 0, 169, 146, 185, 171),
+]
+
+
+@pytest.fixture(scope="module")
+def rule(tmp_path_factory):
+    tmp = tmp_path_factory.mktemp("rule")
     text = open(SOURCE).read()
     begin, end = text.index("bool short_attention("), text.index("hipError_t launch_attn_short(")
-    (tmp_path / "rule.cpp").write_text(PROGRAM % text[begin:end])
-    subprocess.check_call(["g++", "-std=c++17", "-O1", "-o", str(tmp_path / "rule"), str(tmp_path / "rule.cpp")])
-    r = subprocess.run([str(tmp_path / "rule")], capture_output=True, text=True)
+    (tmp / "rule.cpp").write_text(PROGRAM % text[begin:end])
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-o", str(tmp / "rule"), str(tmp / "rule.cpp")])
+    return str(tmp / "rule")
+
+
+def test_the_softcap_does_not_decide(rule):
+    r = subprocess.run([rule], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout
     taken, left = map(int, r.stdout.split())
     assert taken > 1000 and left > 1000
+
+
+def test_the_faster_kernel_is_taken(rule):
+    """... or one within 5 %, with and without a softcap."""
+    r = subprocess.run([rule, "shapes"], input="".join("%d %d %d %d %d\n" % m[:5] for m in MEASURED), capture_output=True, text=True, check=True)
+    for short, m in zip(map(int, r.stdout.split()), MEASURED):
+        assert m[5 + short] <= 1.05 * min(m[5:7]) and m[7 + short] <= 1.05 * min(m[7:9]), m
