@@ -17,7 +17,8 @@ def fresh_inputs(wl, seed):
 
 
 @pytest.mark.parametrize("kw", [dict(dtype="bf16", d=128), dict(dtype="f16", d=96, K=8, topk=2),
-                                dict(dtype="f32", d=64), dict(dtype="bf16", d=128, K=32, topk=2)])
+                                dict(dtype="f32", d=64), dict(dtype="bf16", d=128, K=32, topk=2),
+                                dict(dtype="bf16", d=128, B=3), dict(dtype="f16", d=96, K=8, topk=2, B=3)])
 def test_assign_and_attention_replay_from_a_graph(kw):
     base = dict(name="graph", config_id=60, B=1, Hq=4, Hkv=2, n=3000, d=128, dtype="bf16", K=4, topk=2, window=100)
     base.update(kw)
@@ -58,8 +59,9 @@ def test_assign_and_attention_replay_from_a_graph(kw):
         out.zero_(); lse.zero_(); rp.zero_()          # a replay must write everything again
 
 
-def test_router_and_soft_gate_replay_from_a_graph():
-    wl = workloads.Workload("graph_soft", 62, 1, 4, 2, 2000, 128, "bf16", 4, 2, 64)
+@pytest.mark.parametrize("B", [1, 4])             # the kernels for short problems, tiles
+def test_router_and_soft_gate_replay_from_a_graph(B):
+    wl = workloads.Workload("graph_soft", 62, B, 4, 2, 2000, 128, "bf16", 4, 2, 64)
     inp = fresh_inputs(wl, 62)
     rin = workloads.make_router_inputs(wl, "cuda", d_model=256)
     rp = focus.make_route_params(wl.B, wl.n, 256, workloads.ROUTER_DG, wl.K, wl.topk, dtype=wl.dtype, sinkhorn_iters=10, tau=0.1)

@@ -194,27 +194,47 @@ def test_route_full_size(name):
     check_route(wl, rin, 0)
 
 
-@pytest.mark.parametrize("B,n,K,topk,iters", [
-    (2, 768, 8, 3, 7), (2, 769, 8, 3, 7), (1, 192, 32, 2, 10), (3, 600, 32, 5, 10), (2, 1536, 4, 1, 1), (2, 1537, 3, 1, 2), (1, 1500, 11, 2, 4), (1, 5000, 1, 1, 3),
-    (1, 131072, 4, 2, 5), (1, 66000, 8, 2, 3), (4, 9000, 16, 3, 10), (1, 40000, 16, 1, 3), (1, 16000, 32, 2, 3), (1, 17000, 32, 2, 3), (70, 700, 16, 2, 3), (9, 1300, 5, 2, 12)])
+# B, n, K, topk, rounds: one work-group per sequence; several that exchange their sums; a launch per round (too many tokens or sequences);
+# at the edges between them on a device of 256 compute units, every instantiation (tests/test_route_rule.py)
+ROUNDS_IN_ONE_LAUNCH = [
+    (2, 768, 8, 3, 7), (2, 769, 8, 3, 7), (1, 192, 32, 2, 10), (2, 1536, 4, 1, 1), (2, 1537, 3, 1, 2), (1, 1500, 11, 2, 4), (1, 5000, 1, 1, 3),
+    (1, 131072, 4, 2, 5), (1, 66000, 8, 2, 3), (4, 9000, 16, 3, 10), (1, 40000, 16, 1, 3), (1, 16384, 32, 2, 3), (70, 700, 16, 2, 3),
+    (9, 1300, 5, 2, 12), (8, 40000, 4, 2, 2), (1, 131073, 3, 2, 2), (1, 229376, 4, 2, 1), (70, 3584, 4, 1, 2), (70, 512, 20, 3, 2)]
+A_LAUNCH_PER_ROUND = [
+    (3, 600, 32, 5, 10), (1, 16000, 32, 2, 3), (1, 17000, 32, 2, 3), (1, 229377, 4, 2, 2), (70, 3585, 4, 1, 3), (70, 3585, 3, 1, 1), (70, 2049, 8, 3, 2), (70, 2049, 7, 2, 10), (70, 1025, 16, 3, 3),
+    (70, 1025, 12, 2, 4), (70, 513, 20, 3, 5)]
+
+
+@pytest.mark.parametrize("B,n,K,topk,iters", ROUNDS_IN_ONE_LAUNCH + A_LAUNCH_PER_ROUND)
 def test_sinkhorn_rounds(B, n, K, topk, iters):
-    """One work-group per sequence, several that exchange their sums (two rows per thread and more), and a launch per round (too many
-    tokens or sequences), at the edges between them."""
     wl = workloads.Workload("r", 63, B, 1, 1, n, 64, "bf16", K, topk, 16, mixture=3 if K > 4 else 0)
     rin = workloads.make_router_inputs(wl, "cuda", d_model=64, d_g=16)
     got = check_route(wl, rin, iters)
     for _ in range(2):              # the sums of the call before are still in the workspace
-        assert np.array_equal(check_route(wl, rin, iters), got)
+        assert np.array_equal(run_route(wl, rin, iters)[0].cpu().numpy().view(np.uint32), got)
 
 
-def test_sinkhorn_rounds_of_scores_that_are_not_finite():
-    """Every wait ends and the memberships are topk-subsets, whatever the sums are."""
-    wl = workloads.Workload("r", 64, 1, 1, 1, 5000, 64, "f32", 8, 2, 16)
+@pytest.mark.parametrize("K,topk", [(1, 1), (3, 1), (4, 2), (7, 2), (8, 3), (12, 1), (16, 3), (17, 2), (31, 4), (32, 2)])
+def test_a_launch_per_round_for_every_number_of_groups(K, topk, monkeypatch):
+    """Asked for by the environment: the same sums at sizes that otherwise take one launch."""
+    monkeypatch.setenv("FOCUS_SINKHORN_LOOKS", "-1")
+    wl = workloads.Workload("r", 69, 2, 1, 1, 1300, 64, "bf16", K, topk, 16, mixture=3 if K > 4 else 0)
+    check_route(wl, workloads.make_router_inputs(wl, "cuda", d_model=64, d_g=16), 6)
+
+
+@pytest.mark.parametrize("n,K", [(5000, 8), (2000, 3), (300, 4), (9000, 32)])
+@pytest.mark.parametrize("value", [float("nan"), float("inf"), float("-inf")])
+def test_sinkhorn_rounds_of_scores_that_are_not_finite(n, K, value, monkeypatch):
+    """The same memberships and the same assignments, NaN among them, as a launch per round leaves."""
+    wl = workloads.Workload("r", 64, 1, 1, 1, n, 64, "f32", K, 2, 16)
     rin = workloads.make_router_inputs(wl, "cuda", d_model=64, d_g=16)
-    rin["hidden"][0, 77, 3] = float("nan")
-    masks, _ = run_route(wl, rin, 3)
-    m = masks.cpu().numpy().view(np.uint32)
-    assert all(bin(int(x)).count("1") == 2 for x in m.ravel())
+    rin["hidden"][0, 77, 3] = value
+    masks, soft = run_route(wl, rin, 3)
+    monkeypatch.setenv("FOCUS_SINKHORN_LOOKS", "-1")
+    m, s = run_route(wl, rin, 3)
+    assert torch.equal(masks, m)
+    assert torch.allclose(soft, s, rtol=SOFT_RTOL, atol=0.0, equal_nan=True)
+    assert all(bin(int(x)).count("1") == 2 for x in masks.cpu().numpy().view(np.uint32).ravel())
 
 
 @pytest.mark.parametrize("B,n,K,topk,iters", [(1, 2000, 4, 2, 4), (2, 5000, 8, 2, 5), (1, 9000, 16, 3, 3), (1, 3001, 32, 2, 3), (3, 2500, 5, 2, 12),

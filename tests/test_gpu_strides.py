@@ -7,6 +7,7 @@ import torch
 
 from paper_2604_03260_amd import focus, workloads
 from tests import harness
+from tests import test_gpu_soft_gate as soft
 
 pytestmark = pytest.mark.gpu
 
@@ -32,6 +33,11 @@ CASES = [
     dict(dtype="f16", d=80, Hq=6, Hkv=2, n=900, K=4, topk=2, window=33),
     dict(dtype="bf16", d=256, Hq=2, Hkv=1, n=640, K=4, topk=1, window=16, B=2),
     dict(dtype="bf16", d=64, Hq=4, Hkv=2, n=1100, K=32, topk=2, window=25, causal=False),
+    # more work-groups of 32 rows than the kernel for short problems takes: tiles
+    dict(dtype="bf16", d=128, Hq=8, Hkv=2, n=1500, K=4, topk=2, window=64, B=3),
+    dict(dtype="f16", d=80, Hq=6, Hkv=2, n=900, K=4, topk=2, window=33, B=6),
+    dict(dtype="bf16", d=256, Hq=2, Hkv=1, n=640, K=4, topk=1, window=16, B=26),
+    dict(dtype="bf16", d=64, Hq=4, Hkv=2, n=1100, K=32, topk=2, window=25, causal=False, B=4),
 ]
 
 
@@ -72,8 +78,9 @@ def test_strided_tensors_give_the_contiguous_result(kw):
     assert torch.equal(out_buf.permute(0, 2, 1, 3), vec["out"])
 
 
-def test_strided_soft_gate_and_token_membership():
-    wl = workloads.Workload("strided_soft", 53, 1, 4, 2, 800, 128, "bf16", 4, 2, 40)
+@pytest.mark.parametrize("B", [1, 10])            # the kernel for short problems, tiles
+def test_strided_soft_gate_and_token_membership(B):
+    wl = workloads.Workload("strided_soft", 53, B, 4, 2, 800, 128, "bf16", 4, 2, 40)
     inp = workloads.make_inputs(wl, "cuda")
     buf, q, k, v, out_buf, out = packed_views(wl, inp)
     kw = dict(q_strides=focus.strides_of(q), kv_strides=focus.strides_of(k), o_strides=focus.strides_of(out))
@@ -87,6 +94,9 @@ def test_strided_soft_gate_and_token_membership():
     focus.focus_attn_soft_fwd(ps, 5.0, g, q, k, v, focus.alloc_soft_workspace(ps), out)
     torch.cuda.synchronize()
     assert torch.equal(out_buf.permute(0, 2, 1, 3), o_ref)
+    lse = torch.empty((wl.B, wl.Hq, wl.n), dtype=torch.float32, device="cuda")
+    focus.focus_attn_soft_fwd(ps, 5.0, g, q, k, v, focus.alloc_soft_workspace(ps), out, lse)
+    soft.check_soft(wl, inp, g, 5.0, out.contiguous(), lse)
     # membership given per token: only k is read by the bucketing
     masks = torch.randint(0, 2, (wl.B, wl.n), generator=gen, device="cuda", dtype=torch.int32) * 2 + 5   # {0,2} or {0,1,2}->invalid
     masks = torch.where(masks == 7, torch.full_like(masks, 6), masks)                                      # {1,2} or {0,2}
