@@ -11,8 +11,9 @@
 //                    of the inner index is free: half-wave h takes components [h*d/2, (h+1)*d/2), contiguous loads.
 //   O^T += V^T P^T   the accumulator lane of S^T (row l%32) holds keys 8*(r/4) + 4*h + r%4, which is the B operand of
 //                    step r; A = V[that key][component], 32 consecutive components per half-wave.
-// Measured (d = 64, K = 4 top-2, attention launch) against the vector kernel: 12 heads x 1024 tokens 671 -> 41 us;
-// 40 heads x 4096 tokens 967 us, 89 of the 152 TFLOP/s a library product of 8192 x 8192 matrices reaches: the rest is
+// Two kernels: attn_f32_linear_kernel for most problems in position order, attn_f32_kernel for class tiles, for rows too far apart and
+// where it is the faster one (by_tiles).  The latter, measured when it served both (d = 64, K = 4 top-2, attention launch), against the vector kernel: 12 heads x 1024 tokens
+// 671 -> 41 us; 40 heads x 4096 tokens 967 us, 89 of the 152 TFLOP/s a library product of 8192 x 8192 matrices reaches: the rest is
 // vector work (masks, 16 exponentials and 24 row addresses per unit) that two wavefronts per SIMD cover in part.
 #include "focus_short.h"
 #include "focus_tileplan.h"
@@ -32,9 +33,9 @@ __device__ inline float both_halves_max(float x)
     return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
-// WIDE: some row of k or v lies 4 GiB or more past its head's first, or rows are 16 MiB or more apart: 64-bit products
+// LINEAR: one class in position order.  WIDE: some row of k or v lies 4 GiB or more past its head's first, or rows are 16 MiB or more apart: 64-bit products
 // for every row address, a fifth of the vector work of a unit.  Otherwise one 24-bit multiply and a 32-bit offset.
-template <int D, int NW, bool WIDE>
+template <int D, int NW, bool WIDE, bool LINEAR>
 __global__ __launch_bounds__(64 * NW, D <= 128 ? 2 : 1) void attn_f32_kernel(Layout L, HeadMap hm, int default_map,
                                                                         const float* __restrict__ q, const float* __restrict__ k,
                                                                         const float* __restrict__ v, const char* __restrict__ ws,
@@ -107,31 +108,35 @@ __global__ __launch_bounds__(64 * NW, D <= 128 ? 2 : 1) void attn_f32_kernel(Lay
     const int first_pos = P.row0 + quarter * 32;
     const int far_end = (L.masked && L.causal && L.pair_set == 0) ? first_pos - w + 1 : 0;
     // (Fetching the next unit's masks before this one's products and its key rows right after them takes 65 registers
-    // more and was slower at every size: 45 -> 48 us at 12 heads x 1024 tokens, 325 -> 338 at 4096.)
+    // more in this kernel, and was slower at every size while it walked rows in position order too: 45 -> 48 us at 12 heads x
+    // 1024 tokens, 325 -> 338 at 4096.  attn_f32_linear_kernel has the registers at 64 components, and does it.)
     int cur = 0;
     struct Unit {
         int slot0, krow;
         bool inter, interior;
         uint4 km[4];                              // membership masks of the 16 keys (coarse classes and masked)
-        int4 kp[4];                               // their positions
+        int4 kp[LINEAR ? 1 : 4];                  // their positions; LINEAR: slot = position
     };
     auto fetch = [&](Unit& U, int u) {
         const int it = u >> 1;
         while (it >= P.cum[cur + 1]) ++cur;
         const int tile = __builtin_amdgcn_readfirstlane(P.t0[cur] + (it - P.cum[cur]));
-        U.inter = P.inter[cur] != 0;
+        U.inter = LINEAR || P.inter[cur] != 0;
         U.interior = tile >= P.ibeg[cur] && tile < P.iend[cur];
         U.slot0 = tile * KT + (u & 1) * 32;
-        U.krow = kpos[U.slot0 + n32];
+        U.krow = LINEAR ? U.slot0 + n32 : kpos[U.slot0 + n32];
         if (L.coarse && U.inter) {
 #pragma unroll
             for (int r4 = 0; r4 < 4; ++r4) U.km[r4] = *(const uint4*)(kmsk + U.slot0 + 8 * r4 + 4 * hh);
         }
+        if constexpr (!LINEAR) {
 #pragma unroll
-        for (int r4 = 0; r4 < 4; ++r4) U.kp[r4] = *(const int4*)(kpos + U.slot0 + 8 * r4 + 4 * hh);
+            for (int r4 = 0; r4 < 4; ++r4) U.kp[r4] = *(const int4*)(kpos + U.slot0 + 8 * r4 + 4 * hh);
+        }
     };
     auto key_pos = [&](const Unit& U, int r) -> int {
-        const int4 p4 = U.kp[r / 4];
+        if constexpr (LINEAR) return U.slot0 + 8 * (r / 4) + 4 * hh + r % 4;
+        const int4 p4 = U.kp[LINEAR ? 0 : r / 4];
         return r % 4 == 0 ? p4.x : r % 4 == 1 ? p4.y : r % 4 == 2 ? p4.z : p4.w;
     };
     auto pairs_of = [&](const Unit& U) -> unsigned {              // which pairs of the unit count, bit r = score r
@@ -549,6 +554,21 @@ __global__ __launch_bounds__(64 * NW, D <= 128 ? 2 : 1) void attn_f32_linear_ker
 
 }  // namespace
 
+// Rows in position order that attn_f32_kernel walks faster than attn_f32_linear_kernel: with 256 components the latter has no registers
+// to ask for a unit's keys and values together, with 96 the loads of a value come in two sizes, and with 64 the former fits three work-groups
+// of four wavefronts on a compute unit where there are no memberships.  Bucketing and attention, MHA, linear / by tiles (us), work-groups of 32 rows:
+//   256: causal 1024 tokens x 384 groups 126 / 122, dense 138 / 132, x 800 241 / 246;  2048 x 768 375 / 350;  otherwise 1024 x 384 231 / 218, dense
+//        239 / 220;  masked 700 x 400 187 / 183, x 88 92.5 / 97.4, dense 512 x 800 259 / 248, causal x 192 89.7 / 88.4, x 800 160 / 173
+//   96:  causal 2048 x 768 150 / 138, dense 143 / 138 (x 640), 1024 x 1024 equal, x 1600 linear by 11 %;  otherwise dense 2048 x 768 231 / 226, masked 1.26 times linear
+//   64:  otherwise dense 1024 x 768 111 / 99, 2048 x 768 186 / 162, x 640 155 / 161, x 896 192 / 203
+bool by_tiles(const Layout& L)
+{
+    const long long groups = (long long)L.B * L.Hq * ((L.n + 31) / 32);
+    if (L.d == 256) return L.n > 1024 || (L.n >= (!L.masked ? 512 : L.causal || groups <= 256 ? 768 : 640) && !(L.causal && groups > 384));
+    if (L.d == 96) return L.n >= 1024 && groups <= 1024 && (L.causal ? groups > 512 : !L.masked);
+    return L.d == 64 && !L.causal && !L.masked && L.n >= 1024 && groups > 704 && groups <= 768;
+}
+
 hipError_t launch_attn_f32(const Layout& L, const HeadMap& hm, const void* q, const void* k, const void* v, char* ws,
                            void* out, float* lse, int32_t* row_pairs, hipStream_t st)
 {
@@ -564,15 +584,22 @@ hipError_t launch_attn_f32(const Layout& L, const HeadMap& hm, const void* q, co
     const bool eight = L.d == 128 || (L.d < 128 && blocks <= 512);
     const ShortArgs A = short_args(L, hm, q, k, v, ws, out, lse, row_pairs);
     const bool linear = L.NC == 1 && !wide && !L.local_only && A.groups <= 65535;
-#define FOCUS_F32N(D_, N_, W_) hipLaunchKernelGGL((attn_f32_kernel<D_, N_, W_>), dim3((unsigned)blocks), dim3(64 * N_), 0, st, L, hm, default_map, \
+#define FOCUS_F32N(D_, N_, W_, L_) hipLaunchKernelGGL((attn_f32_kernel<D_, N_, W_, L_>), dim3((unsigned)blocks), dim3(64 * N_), 0, st, L, hm, default_map, \
                                                   (const float*)q, (const float*)k, (const float*)v, (const char*)ws, (float*)out, lse, row_pairs)
 #define FOCUS_F32W(D_, N_)                                                                                                \
     {                                                                                                                     \
         if (linear) hipLaunchKernelGGL((attn_f32_linear_kernel<D_, N_>), short_grid(A), dim3(64 * N_), 0, st, A, hm);    \
-        else if (wide) FOCUS_F32N(D_, N_, true);                                                                          \
-        else FOCUS_F32N(D_, N_, false);                                                                                   \
+        else if (wide) FOCUS_F32N(D_, N_, true, false);                                                                   \
+        else FOCUS_F32N(D_, N_, false, false);                                                                            \
     }
 #define FOCUS_F32(D_) case D_: if (eight) FOCUS_F32W(D_, 8) else FOCUS_F32W(D_, 4) break;
+    if (linear && by_tiles(L)) {
+        if (L.d == 64) FOCUS_F32N(64, 4, false, true);
+        else if (L.d == 96 && eight) FOCUS_F32N(96, 8, false, true);
+        else if (L.d == 96) FOCUS_F32N(96, 4, false, true);
+        else FOCUS_F32N(256, 4, false, true);
+        return hipGetLastError();
+    }
     switch (L.d) {
         FOCUS_F32(64) FOCUS_F32(80) FOCUS_F32(96)
         case 128: FOCUS_F32W(128, 8) break;

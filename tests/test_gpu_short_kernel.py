@@ -24,6 +24,14 @@ def test_units_and_groups(n, d, dtype, K, topk, w, causal, softcap):
     masked._check(workloads.Workload("sk", 500 + n, 2, 4, 2, n, d, dtype, K, topk, w, causal=causal, softcap=softcap, mixture=3))
 
 
+# rows in position order that the fp32 kernel for class tiles walks (by_tiles), at the edges of units
+@pytest.mark.parametrize("B,Hq,n,d,w,causal,softcap", [
+    (1, 4, 513, 256, 5000, True, 0.0), (1, 3, 545, 256, 5000, False, 20.0), (1, 4, 770, 256, 100, True, 0.0), (1, 12, 650, 256, 90, False, 0.0), (1, 2, 1057, 256, 33, True, 30.0),
+    (2, 8, 1030, 96, 60, True, 0.0), (1, 4, 1030, 96, 5000, False, 0.0), (11, 2, 1030, 64, 5000, False, 10.0)])
+def test_rows_in_position_order_by_tiles(B, Hq, n, d, w, causal, softcap):
+    masked._check(workloads.Workload("sk", 505, B, Hq, Hq // 2 if Hq % 2 == 0 else 1, n, d, "f32", 8, 2, w, causal=causal, softcap=softcap, mixture=3))
+
+
 @pytest.mark.parametrize("d,dtype,head_map", [(64, "bf16", [1, 0, 0, 1, 2, 2]), (256, "f16", [2, 1, 0, 0, 1, 2]), (80, "f32", [2, 1, 0, 0, 1, 2])])
 def test_other_head_maps(d, dtype, head_map):
     wl = workloads.Workload("sk", 501, 2, 6, 3, 200, d, dtype, 8, 2, 30)

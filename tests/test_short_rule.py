@@ -1,26 +1,29 @@
-"""Which problems the kernel for short 16-bit problems takes, from its source for the host.  The bucketing skips for it what the tiled
-kernel needs (key copy, key norms, membership words), so whatever the bucketing does not read must not decide: the softcap."""
+"""Which problems the kernels for rows in position order take, from their sources for the host.  The bucketing skips for the 16-bit one
+what the tiled kernel needs (key copy, key norms, membership words), so whatever the bucketing does not read must not decide: the
+softcap."""
 import os
 import subprocess
 
 import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-SOURCE = os.path.join(ROOT, "paper_2604_03260_amd", "csrc", "focus_attn_short.hip")
+CSRC = os.path.join(ROOT, "paper_2604_03260_amd", "csrc")
 
 PROGRAM = """
 #include <cstdint>
 #include <cstdio>
 #include <initializer_list>
-struct Layout { int B, Hq, n, d, dtype, NC, masked, dense, soft, local_only, merge_prev, BQ, causal; long long ks[3]; float softcap; };
+struct Layout { int B, Hq, n, d, dtype, NC, masked, dense, soft, local_only, merge_prev, BQ, causal; long long ks[3]; float softcap; int K; };
 %s
-int main(int argc, char**)
+int main(int argc, char** argv)
 {
-    int d, n, groups, causal, dense;
+    int d, n, groups, causal, dense;                  // dense of the soft gate: its groups
     while (argc > 1 && scanf("%%d %%d %%d %%d %%d", &d, &n, &groups, &causal, &dense) == 5) {
         const int per = (n + 31) / 32;
-        Layout L{groups / per, 1, n, d, 1, 1, !dense, dense, 0, 0, 0, 128, causal, {1LL * n * d, 1LL * n * d, d}, 0.f};
-        printf("%%d\\n", (int)short_attention(L));
+        Layout L{groups / per, 1, n, d, 1, 1, !dense, dense, 0, 0, 0, 128, causal, {1LL * n * d, 1LL * n * d, d}, 0.f, dense};
+        const char rule = argv[1][0];
+        L.soft = rule == 's';
+        printf("%%d\\n", (int)(rule == 'h' ? short_attention(L) : rule == 's' ? short_soft_attention(L) : by_tiles(L)));
     }
     if (argc > 1) return 0;
     long long taken = 0, left = 0;
@@ -55,14 +58,32 @@ MEASURED = [
 ]
 
 
+# d, tokens, work-groups of 32 rows, causal, dense; microseconds in 32 bits: attn_f32_linear_kernel, attn_f32_kernel
+MEASURED_F32 = [
+    (256, 256, 400, 1, 0, 70.1, 78.5), (256, 512, 800, 0, 1, 259, 248), (256, 512, 800, 1, 0, 153, 168), (256, 700, 198, 1, 1, 114, 109),
+    (256, 700, 396, 0, 0, 187, 183), (256, 700, 88, 0, 0, 92.5, 97.4), (256, 1024, 384, 1, 0, 126, 122), (256, 1024, 384, 0, 1, 239, 220),
+    (256, 1024, 800, 1, 0, 241, 246), (256, 2048, 768, 1, 0, 375, 350), (256, 2048, 768, 0, 1, 634, 556), (96, 2048, 768, 1, 0, 150, 138),
+    (96, 2048, 1600, 1, 0, 1.0, 1.07), (96, 2048, 768, 0, 0, 1.0, 1.26), (96, 1024, 640, 0, 1, 134, 130), (64, 1024, 768, 0, 1, 111, 99.2),
+    (64, 2048, 768, 0, 1, 186, 162), (64, 2048, 640, 0, 1, 155, 161), (64, 2048, 768, 0, 0, 189, 210), (64, 700, 748, 0, 1, 91.8, 97.9),
+]
+
+
 @pytest.fixture(scope="module")
 def rule(tmp_path_factory):
     tmp = tmp_path_factory.mktemp("rule")
-    text = open(SOURCE).read()
-    begin, end = text.index("bool short_attention("), text.index("hipError_t launch_attn_short(")
-    (tmp / "rule.cpp").write_text(PROGRAM % text[begin:end])
+    text = open(os.path.join(CSRC, "focus_attn_short.hip")).read()
+    source = text[text.index("bool short_attention("):text.index("hipError_t launch_attn_short(")]
+    source += text[text.index("bool short_soft_attention("):text.index("hipError_t launch_attn_short_soft(")]
+    text = open(os.path.join(CSRC, "focus_attn_f32.hip")).read()
+    source += text[text.index("bool by_tiles("):text.index("hipError_t launch_attn_f32(")]
+    (tmp / "rule.cpp").write_text(PROGRAM % source)
     subprocess.check_call(["g++", "-std=c++17", "-O1", "-o", str(tmp / "rule"), str(tmp / "rule.cpp")])
     return str(tmp / "rule")
+
+
+def chosen(rule, which, table):
+    r = subprocess.run([rule, which], input="".join("%d %d %d %d %d\n" % m[:5] for m in table), capture_output=True, text=True, check=True)
+    return list(zip(map(int, r.stdout.split()), table))
 
 
 def test_the_softcap_does_not_decide(rule):
@@ -73,7 +94,8 @@ def test_the_softcap_does_not_decide(rule):
 
 
 def test_the_faster_kernel_is_taken(rule):
-    """... or one within 5 %, with and without a softcap."""
-    r = subprocess.run([rule, "shapes"], input="".join("%d %d %d %d %d\n" % m[:5] for m in MEASURED), capture_output=True, text=True, check=True)
-    for short, m in zip(map(int, r.stdout.split()), MEASURED):
+    """... or one within 5 %, with and without a softcap; 32 bits: within 2.5 %."""
+    for short, m in chosen(rule, "hard", MEASURED):
         assert m[5 + short] <= 1.05 * min(m[5:7]) and m[7 + short] <= 1.05 * min(m[7:9]), m
+    for tiles, m in chosen(rule, "f32", MEASURED_F32):
+        assert m[5 + tiles] <= 1.025 * min(m[5:7]), m
