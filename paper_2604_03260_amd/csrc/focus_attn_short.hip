@@ -408,7 +408,7 @@ __global__ __launch_bounds__(64 * short_waves(D), short_waves(D) / 4) void attn_
 //                 1024 x 512 35.7 / 34.7, 40.8 / 40.0;  2048 x 512 48.9 / 49.4, 59.6 / 61.5;  4096 x 512 75.6 / 79.6, 97.3 / 105
 //                 dense (no memberships to test): 4096 x 512 83.3 / 69.1, 102 / 95
 //            80: 256 x 896 30.8 / 30.0, 32.2 / 33.1;  512 x 640 34.0 / 33.0, 36.3 / 37.4
-//            96: 4096 x 384 90.8 / 96.4, 110 / 120;  256 x 1024 34.6 / 31.1, 36.1 / 34.2;  512 x 768 37.0 / 34.1, 39.7 / 38.3;  1024 x 512 40.7 / 38.8, 45.6 / 44.3
+//            96: 4096 x 384 90.8 / 96.4, 110 / 120;  256 x 1024 34.6 / 31.1, 36.1 / 34.2;  512 x 768 37.0 / 34.1, 39.7 / 38.3, 47 heads (752) 39.2 / 41.5;  1024 x 512 40.7 / 38.8, 45.6 / 44.3
 //            128: 256 x 768 37.1 / 32.7, 38.2 / 35.5;  512 x 512 39.6 / 35.6, 42.2 / 37.0;  4096 x 256 101 / 74
 //            256: 256 x 512 52.1 / 38.9, 53.1 / 42.3, 640 52.4 / 51.0, 53.6 / 55.2;  512 x 256 54.6 / 38.0, 56.6 / 41.7, 384 57.1 / 57.0, 59.2 / 63.7
 bool short_attention(const Layout& L)
@@ -419,8 +419,10 @@ bool short_attention(const Layout& L)
     int most;
     if (L.causal)
         most = L.d == 256 ? (L.n <= 256 ? 896 : 560) : L.n <= (L.d == 128 ? 256 : 512) ? 1024 : (L.d == 128 && L.n > 1024) ? 640 : 768;
+    else if (L.n <= 256)
+        most = L.d == 96 ? 1024 : L.d == 256 ? 512 : 768;
     else if (L.n <= 512)
-        most = (L.d == 96 ? 1024 : L.d == 256 ? 512 : 768) - (L.n > 256 ? 256 : 0);
+        most = L.d == 256 ? 256 : 512;
     else
         most = (L.d >= 128 || (L.masked && L.n > 1024)) ? 256 : 512;
     return fits && groups <= most && L.n <= 4096;
@@ -446,15 +448,22 @@ hipError_t launch_attn_short(const Layout& L, const HeadMap& hm, const void* q, 
 }
 
 // The soft gate in the place of four launches (positions, assignments, V, tiles).  What a unit costs grows with the groups, which every
-// wavefront takes apart for itself.  Pass, tiled / this kernel (us), 256 .. 4096 tokens, by work-groups of 32 rows:
-//   K = 4, 96 components:  512 x 512 groups 30.8 / 14.7;  4096 x 768 122 / 71, 1024 120 / 86, 1536 124 / 129
-//   K = 8, 64:  512 x 768 29.7 / 25.3, 1024 30.9 / 32.2;  4096 x 768 108 / 72;   128: 512 x 768 36.2 / 33.2, 1024 38.3 / 42.1;  4096 x 768 132 / 117
-//   K = 16, 80:  512 x 768 32.0 / 27.9, 1024 33.2 / 36.4;  4096 x 768 119 / 95
-//   K = 32, 64:  512 x 512 32.2 / 26.9, 768 33.1 / 39.9;  4096 x 512 128 / 95;   128: 512 x 512 39.1 / 33.1;  4096 x 512 158 / 123, 768 158 / 193
+// wavefront takes apart for itself.  Pass, tiled / this kernel (us), 40 .. 4096 tokens, by work-groups of 32 rows, one KV head:
+//   K = 4   64: 512 x 752 27.7 / 21.1, 300 x 1000 22.3 / 23.1, 512 x 992 1.03 times, 1000 x 992 1.13, 4096 x 896 1.52;  80, 96: 40 x 1000 0.93 times, 512 x 992 1.07
+//           128: 300 x 760 1.05 times, 512 x 752 1.09, 4096 x 640 1.53
+//   K = 8   64: 40 x 760 1.04 times, 512 x 752 1.12;  80: 1.15, 1.26;  96: 1.10, 1.24;   128: 300 x 760 25.4 / 27.1, 512 x 752 31.3 / 32.5, 1000 x 736 1.03 times
+//   K = 16  64: 300 x 760 22.5 / 24.5, 512 x 752 27.4 / 29.3, 1000 x 736 1.01 times;  80: 300 x 760 1.03;  96: 40 x 760 0.98, 512 x 752 1.02
+//           128: 300 x 500 1.15 times, 760 25.5 / 30.8, 2048 x 704 74.2 / 77.0
+//   K = 32  64: 300 x 500 1.10 times;  80: 1.17;  96: 1.12;   128: 300 x 250 1.46 times, 500 28.5 / 29.8, 512 x 496 1.05, 1000 x 480 1.13
 bool short_soft_attention(const Layout& L)
 {
     const long long groups = (long long)L.B * L.Hq * ((L.n + 31) / 32);
-    return L.dtype != 0 && L.soft && L.d <= 128 && L.n <= 4096 && groups <= (L.K > 16 ? 512 : (L.K <= 4 && L.d < 128) ? 1024 : 768) &&
+    int most;
+    if (L.K > 16) most = L.d == 128 && L.n <= 512 ? 384 : 512;
+    else if (L.K <= 4) most = L.d < 128 && L.n >= 512 ? 1024 : 768;
+    else if (L.K <= 8) most = L.d == 128 && L.n < 1000 ? 512 : 768;
+    else most = L.d == 128 || (L.d == 64 && L.n < 1000) ? 512 : 768;
+    return L.dtype != 0 && L.soft && L.d <= 128 && L.n <= 4096 && groups <= most &&
            (uint64_t)L.ks[2] * 2 < (1u << 24) && (uint64_t)L.n * (uint64_t)L.ks[2] * 2 < 0xffffffffull;
 }
 
