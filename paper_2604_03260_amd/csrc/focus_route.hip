@@ -10,8 +10,9 @@
 // and, without Sinkhorn, the membership are reproducible bit for bit.
 //
 // Kernels:
-//   route_project     a wavefront = 16 tokens x all router outputs on the fp64 matrix cores (see the kernel); writes S,
-//                     the work-group's largest score, and the masks directly when no Sinkhorn is asked;
+//   route_project     a wavefront = 16 tokens x all router outputs on the fp64 matrix cores, or, of few tokens, four of the
+//                     outputs (see the kernel); writes S, the work-group's largest score, and the masks directly when no
+//                     Sinkhorn is asked;
 //   sinkhorn_rounds   Sinkhorn in one launch wherever its rows fit the registers of few enough work-groups (sink_groups); the
 //                     same sums as
 //   sinkhorn_pass     a launch per round: Sinkhorn as diagonal scaling: Q = diag(u) E diag(v) with E = exp((S - max)/tau).
@@ -145,15 +146,17 @@ constexpr int sink_resident(int kp, int rows) { return kp >= 16 && kp * rows >= 
 // Work-groups that exchange their sums should be resident together; one that is left waiting computes the others' sums itself
 // (sinkhorn_rounds_kernel), which is right but slow.  So a launch takes at most a quarter of the work-groups that the device holds: four
 // launches at once, one on each hardware queue, still fit.
-// One work-group as long as its rows take less time than an exchange.  Routing of a sequence, a launch per round / one work-group /
-// several (us): 2 x 500 tokens, K = 8 (d_model 3840) 126 / 104;  4493, K = 8 76.5 / - / 66.3;  32768, K = 4 199 / - / 187 (the rounds alone 51 / 30).  K = 4, d_model 768: 2000
-// tokens 40 in one, 4000 37 in several.
+// One work-group as long as its rows take less time than an exchange (K = 4, d_model 768: 2000 tokens 40 us in one, 4000 37 in several),
+// else one for every 512 tokens, the most that fit two rows a thread, as far as the slots do.  Routing with ten rounds, a launch per
+// round / one (us; up to 8192 tokens the projection in work-groups of 16 tokens comes with the latter): 2 x 500 tokens, K = 8, d_model
+// 3840 106 / 62;  2000, K = 4, 768 51 / 38;  4493, K = 8, 4096 115 / 93;  16000, K = 16, 768 84 / 77 (in 31 work-groups of 517 tokens and
+// four rows 86);  32768, K = 4, 4096 142 / 133;  4 x 9000, K = 16, 768 108 / 98;  200000, K = 4, 256 109 / 108.
 inline int sink_groups(const RouteLayout& R, int compute_units)
 {
     const int kp = sink_kp(R.K);
     if ((long long)R.n * kp <= 6144) return 1;
     for (int per_unit = 2; per_unit >= 1; --per_unit) {
-        const int g = std::min({R.nsink / 2, 64, compute_units / 4 * per_unit / R.B});
+        const int g = std::min({(R.nsink + 1) / 2, 16 * R.nsink / R.K, 64, compute_units / 4 * per_unit / R.B});
         const int rows = g >= 2 ? sink_rows(kp, (R.n + g - 1) / g) : 0;
         if (rows > 0 && sink_resident(kp, rows) >= per_unit) return g;
     }
@@ -203,7 +206,8 @@ template <typename T> constexpr int route_waves(int dg) { return dg == 64 ? 2 : 
 // SPLIT (d_g = 16): few tokens leave the chip idle behind a chain of one 64-cycle product per four components.  A work-group then is 16
 // tokens, its four wavefronts take four outputs each, one product of 16 cycles a step; all wavefronts read the same rows.
 // Routing, whole / split (us), ten rounds, K = 4, bf16: d_model 4096: 500 tokens 83 / 60, 2000 99 / 75, 8000 98 / 84, 12000 104 / 101, 16000 103 / 116;
-// 768: 500 30 / 25, 8000 44 / 42, 12000 50 / 50; fp32, 4096: 500 98 / 71, 8000 113 / 97, 12000 118 / 112, 16000 120 / 132.
+// 768: 500 30 / 25, 8000 44 / 42, 12000 50 / 50; fp32, 4096: 500 98 / 71, 8000 113 / 97, 12000 118 / 112, 16000 120 / 132.  Without rounds and
+// above 16 groups, whose masks take K * K steps a token here, only up to 4096 tokens: K = 32, d_model 768: 2000 85 / 82, 8000 85 / 94.
 template <typename T, int DG, int NW, bool SPLIT>
 __global__ __launch_bounds__(64 * NW, route_waves<T>(DG)) void route_project_kernel(RouteLayout R, const T* __restrict__ hidden,
                                                                  const float* __restrict__ wg,
@@ -723,7 +727,7 @@ hipError_t launch_route(const RouteLayout& layout, const void* hidden, const flo
         if ((e = hipDeviceGetAttribute(&units, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess) return e;
         R.nround = sink_groups(R, units);
     }
-    const bool split = R.dg == 16 && (long long)R.B * R.n <= 8192 && (R.iters == 0 || R.nround > 0);
+    const bool split = R.dg == 16 && (long long)R.B * R.n <= ((R.iters == 0 && R.K > 16) ? 4096 : 8192) && (R.iters == 0 || R.nround > 0);
     if (split) {       // a largest score for every 16 tokens: behind the sums of the rounds, which take at most 48 of 64 words a sort block
         R.nproj = (R.n + 15) / 16;
         R.off_maxpart = R.off_colpart + (size_t)48 * R.B * R.nsink * 8;

@@ -197,7 +197,7 @@ def test_route_full_size(name):
 # B, n, K, topk, rounds: one work-group per sequence; several that exchange their sums; a launch per round (too many tokens or sequences);
 # at the edges between them on a device of 256 compute units, every instantiation (tests/test_route_rule.py)
 ROUNDS_IN_ONE_LAUNCH = [
-    (2, 768, 8, 3, 7), (2, 769, 8, 3, 7), (1, 192, 32, 2, 10), (2, 1536, 4, 1, 1), (2, 1537, 3, 1, 2), (1, 1500, 11, 2, 4), (1, 5000, 1, 1, 3),
+    (2, 768, 8, 3, 7), (2, 769, 8, 3, 7), (1, 192, 32, 2, 10), (2, 1536, 4, 1, 1), (2, 1537, 3, 1, 2), (3, 1000, 4, 2, 3), (1, 1500, 11, 2, 4), (1, 5000, 1, 1, 3),
     (1, 131072, 4, 2, 5), (1, 66000, 8, 2, 3), (4, 9000, 16, 3, 10), (1, 40000, 16, 1, 3), (1, 16384, 32, 2, 3), (70, 700, 16, 2, 3),
     (9, 1300, 5, 2, 12), (8, 40000, 4, 2, 2), (1, 131073, 3, 2, 2), (1, 229376, 4, 2, 1), (70, 3584, 4, 1, 2), (70, 512, 20, 3, 2)]
 A_LAUNCH_PER_ROUND = [
