@@ -208,7 +208,9 @@ template <typename T> constexpr int route_waves(int dg) { return dg == 64 ? 2 : 
 // Routing, whole / split (us), ten rounds, K = 4, bf16: d_model 4096: 500 tokens 83 / 60, 2000 99 / 75, 8000 98 / 84, 12000 104 / 101, 16000 103 / 116;
 // 768: 500 30 / 25, 8000 44 / 42, 12000 50 / 50; fp32, 4096: 500 98 / 71, 8000 113 / 97, 12000 118 / 112, 16000 120 / 132.  Without rounds and
 // above 16 groups, whose masks take K * K steps a token here, only up to 4096 tokens: K = 32, d_model 768: 2000 85 / 82, 8000 85 / 94.
-template <typename T, int DG, int NW, bool SPLIT>
+// CLEAR: the slots of the Sinkhorn sums are emptied here.  A template, since the branch alone cost projections without rounds 1 to 2.5 % (500 tokens,
+// K = 32, d_g = 8 80.3 -> 82.3 us; 130 x 600 fp32, K = 8 75.6 -> 82.5).
+template <typename T, int DG, int NW, bool SPLIT, bool CLEAR>
 __global__ __launch_bounds__(64 * NW, route_waves<T>(DG)) void route_project_kernel(RouteLayout R, const T* __restrict__ hidden,
                                                                  const float* __restrict__ wg,
                                                                  const float* __restrict__ cent,
@@ -386,10 +388,9 @@ __global__ __launch_bounds__(64 * NW, route_waves<T>(DG)) void route_project_ker
         for (int w = 1; w < NW; ++w) m = fmax(m, s_wmax[w]);
         ((double*)(ws + R.off_maxpart))[(size_t)b * R.nproj + blockIdx.x] = m;
     }
-    if (R.iters > 0) {
+    if constexpr (CLEAR) {
         unsigned long long* slots = sink_slots(R, ws, b);
-        if (R.nround > 1)                                // (one work-group exchanges nothing, and a short sequence has no space for it)
-            for (int i = blockIdx.x * NTHR + tid; i < 3 * R.nround * K; i += gridDim.x * NTHR) slots[i] = SINK_EMPTY;
+        for (int i = blockIdx.x * NTHR + tid; i < 3 * R.nround * K; i += gridDim.x * NTHR) slots[i] = SINK_EMPTY;
     }
     if (tid < rows) {
         const size_t tg = (size_t)b * n + tok0 + tid;
@@ -698,9 +699,11 @@ hipError_t launch_project(const RouteLayout& R, const void* hidden, const float*
     const size_t stage = 2 * ((size_t)tb * A_ROW + (size_t)rc * route_wp(R.dg) * (R.dg <= 16 ? 8 : 4));
     const size_t tail = (size_t)tb * (R.dg + 1 + (R.K | 1)) * sizeof(double);
     const size_t lds = stage > tail ? stage : tail;      // at most 53 KB (8 wavefronts, d_g <= 16) or 59 KB (4, d_g = 64, 16-bit rows)
-#define FOCUS_PROJ(DG, NW, SPLIT)                                                                            \
-    hipLaunchKernelGGL((route_project_kernel<T, DG, NW, SPLIT>), grid, dim3(64 * NW), lds, st, R, (const T*)hidden, wg, \
+#define FOCUS_PROJ_C(DG, NW, SPLIT, CLEAR)                                                                   \
+    hipLaunchKernelGGL((route_project_kernel<T, DG, NW, SPLIT, CLEAR>), grid, dim3(64 * NW), lds, st, R, (const T*)hidden, wg, \
                        cent, ws, masks, soft)
+    // (one work-group exchanges nothing, and a short sequence has no space for its slots)
+#define FOCUS_PROJ(DG, NW, SPLIT) do { if (R.nround > 1) FOCUS_PROJ_C(DG, NW, SPLIT, true); else FOCUS_PROJ_C(DG, NW, SPLIT, false); } while (0)
     switch (R.dg) {
         case 4: if (nw == 8) FOCUS_PROJ(4, 8, false); else FOCUS_PROJ(4, 4, false); break;
         case 8: if (nw == 8) FOCUS_PROJ(8, 8, false); else FOCUS_PROJ(8, 4, false); break;
@@ -709,6 +712,7 @@ hipError_t launch_project(const RouteLayout& R, const void* hidden, const float*
         default: FOCUS_PROJ(64, 4, false); break;
     }
 #undef FOCUS_PROJ
+#undef FOCUS_PROJ_C
     return hipGetLastError();
 }
 
