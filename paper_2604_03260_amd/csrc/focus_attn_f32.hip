@@ -340,8 +340,8 @@ __global__ __launch_bounds__(64 * NW, D <= 128 ? 2 : 1) void attn_f32_kernel(Lay
 // Rows in position order (one class), a head's rows within 4 GiB: the same walk with the work around the products cut down, as in
 // focus_attn_short.hip: scalar row addresses, pairs near the diagonal from position words, a key's values in one load or two
 // (DB 4-byte loads before), keys and membership words of the next unit asked for when the scores have used this one's, its values
-// after the last product, one merge.  12 heads of 64 x 1024 tokens, with the bucketing: 44.8 -> 41.4 us; 8 x 15/5 of 80 x 627
-// 170 -> 135; 32 of 128 x 2028 451 -> 428; 4 x 40/8 of 64 x 2048 1065 -> 985.
+// after the last product, one merge.  12 heads of 64 x 1024 tokens, with the bucketing: 44.7 -> 40.7 us; 8 x 15/5 of 80 x 627
+// 163 -> 128; 32 of 128 x 2028 462 -> 431; 4 x 40/8 of 64 x 2048 1047 -> 955.
 template <int D, int NW>
 __global__ __launch_bounds__(64 * NW, D <= 128 ? 2 : 1) void attn_f32_linear_kernel(ShortArgs A, HeadMap hm)
 {

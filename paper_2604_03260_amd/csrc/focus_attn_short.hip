@@ -12,7 +12,7 @@
 // asked for together, up to 64 components with the next unit's; row addresses are scalars; the pairs near the diagonal
 // come from five position words instead of a dozen instructions per pair; values that are not finite are looked for in the
 // loaded words; the partial results meet once, all together; and the arguments fit a few cache lines.  12 heads of 64 x
-// 512 tokens: 12.4 -> 9.2 us, with the bucketing 19.4 -> 16.0; 32 heads of 128 x 305 tokens 43.7 -> 34.2.
+// 512 tokens, with the bucketing: 19.4 -> 16.2 us; 32/8 heads of 128 x 305 tokens, K = 16 top-3 44.2 -> 32.9.
 #include "focus_short.h"
 
 namespace focus {
@@ -195,7 +195,7 @@ __global__ __launch_bounds__(64 * short_waves(D), short_waves(D) / 4) void attn_
     bool again = false;                           // (uniform) values were taken out of a product
     // The membership words, the keys and the values of a unit in one round trip: a unit whose pairs are all masked is rare, and
     // a walk is a chain of few units.  Up to 64 components there are registers for the next unit's too; asked for as this one's
-    // are used up, without a second set of registers, those of 128 components made a pass longer (34.8 against 34.2 us, 32 heads x 305).
+    // are used up, without a second set of registers, those of 128 components made a pass 2 % longer (32 heads x 305 tokens).
     struct Unit {
         uint4 km[4];
         V8 kf[KS];
