@@ -393,7 +393,7 @@ __global__ __launch_bounds__(64 * short_waves(D), short_waves(D) / 4) void attn_
 
 }  // namespace
 
-// Where one launch of short chains beats the staged tiles: while its work-groups are at most two to four per compute unit
+// Where one launch of short chains beats the staged tiles: while its work-groups are at most one to four per compute unit
 // (those of a causal launch differ in length, the later ones fill the gaps), fewer the longer the walk, whose units load more
 // bytes per key.  The softcap does not decide: the bucketing leaves out what only the tiles need, and may have been given parameters
 // without it.  It costs a score more here (tanh) than in the tiles (a polynomial), so the lines lie where the one with a cap
